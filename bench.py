@@ -161,20 +161,18 @@ def main():
                 k["hbm_traffic_GBps"] = round((mk[0] + mk[1]) * _MIB / (ms / n * 1e-3) / 1e9, 1)
                 k["valu_issue_frac"] = round(mk[2] * 64 / (ms / n * 1e-3) / 1e12 / VALU_PEAK_TINSTR, 3)
             kernels[name] = k
-    # Algorithmic lane-operations per launch of the two conversion kernels on FP64 limbs (the kernels that VALU
-    # issue binds), from operation counts and the shortest exact FP64 sequences: a modular product of two
-    # residues below 2^50 is 6 instructions (mul, fma for the low part, mul by 1/q, round, fma, add), a
-    # multiply-accumulate 7, a butterfly 8 (product, add, sub), the reduction of an accumulator 3; a 60-bit source
-    # is first brought below the target prime (4: mul by 1/q, round, fma, add of the low half) and then takes one
-    # multiply-accumulate.  Every converted word then takes (log2 N - 8) / 2 butterflies of the first forward pass.
+    # Algorithmic lane-operations per launch of the two conversion kernels on FP64 limbs: a converted word is recombined
+    # from its digit sums in 15 instructions (three joins of digit pairs, four conversions to FP64, eight FP64
+    # operations; the products themselves run on the matrix cores) and then takes (log2 N - 8) / 2 butterflies of the
+    # first forward pass, 8 instructions each (a modular product of residues below 2^50 is 6: mul, fma for the low part,
+    # mul by 1/q, round, fma, add).
     bfly = 8 * (ps.logN - 8) // 2
     n_fp_q = sum(1 for q in ps.q_primes if q < 3 << 48)
     alg_lane_ops = {
         # ModUp: per ciphertext and coefficient, every digit writes the FP64 q-limbs it does not own
-        "conv_fwd_strided_kernel<FpAr, 8, 1, 3, false>": B * N * dnum * (n_fp_q - ps.L // dnum) * (7 * (ps.L // dnum) + 3 + bfly),
-        # ModDown: both components, every FP64 q-limb, K sources of 60 bits
-        # ModDown on the matrix cores: 7 conversions + 12 FP64 operations recombine an output, then the butterflies
-        "conv_mfma_kernel<8, 2, 2, 1>": B * 2 * N * n_fp_q * (19 + bfly),
+        "conv_fwd_strided_kernel<FpAr, 8, 1, 4, false>": B * N * dnum * (n_fp_q - ps.L // dnum) * (15 + bfly),
+        # ModDown: both components, every FP64 q-limb
+        "conv_mfma_kernel<8, 2, 2, 2>": B * 2 * N * n_fp_q * (15 + bfly),
     }
     for kname_, ops in alg_lane_ops.items():
         if kname_ in kernels:

@@ -92,31 +92,19 @@ static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // constants over the whole chain), one block of conversion constants per level ell = 1..L (basis
 // q_0..q_{ell-1}, p_0..p_{K-1}) and one small block per rescale step ell -> ell-1 (ell = 2..L).
 struct SharedLayout {
-    size_t tw_int, tw_fp, pc, sc_plain, sc_dn, dn_hatinv, end;
+    size_t tw_int, tw_fp, pc, sc_plain, sc_dn, dn_hatinv, up_aop, dn_aop, end;
 };
 struct LevelLayout {
-    size_t sc_up, up_hatinv, up_chat, up_chat_fp, up_fp_ok, dn_chat, dn_chat_fp, dn_fp_ok, pinv, pmod, up_tiles, up_aop,
-        dn_tiles, dn_aop, end;
+    size_t sc_up, up_hatinv, up_chat, dn_chat, pinv, pmod, up_aop, end;
 };
 
-// Conversion on the matrix cores: targets per tile and the bound on tiles for a basis of `targets` limbs; ks = products
-// per coefficient group = ceil(sources / 4), used for 2..8 sources only
-// CKKS_MFMA_NTT: targets per lane half of a tile.  2 halves the matrix-core work per output but needs 128 registers
-// for the converted words alone and spills (1.1 KB per lane); 1 is what runs.
-// CKKS_MFMA_UP: the ModUp conversion (6 sources of 50 bits at the benchmark shape) measured the same on the matrix
-// cores as on the FP64 pipe (125 vs 124 us), so only the ModDown direction (60-bit sources: 11 FP64 instructions per
-// source and output against 19 in total) uses them by default.
-#ifndef CKKS_MFMA_NTT
-#define CKKS_MFMA_NTT 1
-#endif
-#ifndef CKKS_MFMA_UP
-#define CKKS_MFMA_UP 0
-#endif
-static inline u32 mfma_ks(u32 sources) { return (sources >= 2 && sources <= 8) ? (sources + 3) / 4 : 0; }
-static inline u32 mfma_ks_up(u32 sources) { return CKKS_MFMA_UP ? mfma_ks(sources) : 0; }
-static inline u32 mfma_tile_bound(u32 targets) { return (targets + 2 * CKKS_MFMA_NTT - 1) / (2 * CKKS_MFMA_NTT) + 1; }
+// Conversion from `sources` limbs on the matrix cores: products per coefficient group (few values, so that few kernels are
+// built; 5 = the merged rescale of a 16-prime special basis).  Two sources are enough for it to pay: a batch of 8 rotations
+// at N = 2^16, L = 12 with digits of two / three limbs takes 409 / 366 us, with direct multiply-accumulates 427 / 393 us.
+static inline u32 mfma_ks(u32 sources) { return sources < 2 ? 0 : sources <= 4 ? 1 : sources <= 8 ? 2 : sources <= 16 ? 4 : 5; }
+static inline size_t aop_words(u32 ks) { return (size_t)ks * 32; }  // constant operands of one (digit, target)
 struct RescaleLayout {
-    size_t sc_dn, dn_chat, dn_chat_fp, dn_fp_ok, pinv, end;
+    size_t sc_dn, pinv, end;
 };
 
 struct Taker {
@@ -128,7 +116,7 @@ struct Taker {
     }
 };
 
-static SharedLayout shared_layout(u32 logN, u32 L, u32 K) {
+static SharedLayout shared_layout(u32 logN, u32 L, u32 K, u32 alpha) {
     const size_t N = (size_t)1 << logN, D = L + K, K1 = K ? K : 1;
     Taker t{0};
     SharedLayout l;
@@ -138,28 +126,23 @@ static SharedLayout shared_layout(u32 logN, u32 L, u32 K) {
     l.sc_plain = t.take(D * sizeof(InvScale));
     l.sc_dn = t.take(K1 * sizeof(InvScale));
     l.dn_hatinv = t.take(K1 * 2 * sizeof(u64));
+    l.up_aop = t.take((K ? (size_t)(L / alpha) : 0) * D * aop_words(mfma_ks(alpha)) * sizeof(u64));
+    l.dn_aop = t.take(L * aop_words(mfma_ks(K)) * sizeof(u64));
     l.end = t.o;
     return l;
 }
 
 static LevelLayout level_layout(size_t base, u32 ell, u32 K, u32 alpha) {
-    const size_t D = ell + K, K1 = K ? K : 1, beta = (ell + alpha - 1) / alpha;
+    const size_t D = ell + K, K1 = K ? K : 1;
     Taker t{base};
     LevelLayout l;
     l.sc_up = t.take(ell * sizeof(InvScale));
     l.up_hatinv = t.take(ell * 2 * sizeof(u64));
     l.up_chat = t.take(ell * D * sizeof(u64));
-    l.up_chat_fp = t.take(ell * D * sizeof(double));
-    l.up_fp_ok = t.take(beta * D * sizeof(u32));
     l.dn_chat = t.take(K1 * ell * sizeof(u64));
-    l.dn_chat_fp = t.take(K1 * ell * sizeof(double));
-    l.dn_fp_ok = t.take(ell * sizeof(u32));
     l.pinv = t.take(ell * sizeof(PinvConst));
     l.pmod = t.take(ell * sizeof(u64));
-    l.up_tiles = t.take((mfma_ks_up(alpha) ? beta * mfma_tile_bound(D) : 0) * sizeof(ConvTile));
-    l.up_aop = t.take(beta * mfma_tile_bound(D) * mfma_ks_up(alpha) * 128 * sizeof(u64));
-    l.dn_tiles = t.take(mfma_tile_bound(ell) * sizeof(ConvTile));
-    l.dn_aop = t.take(mfma_tile_bound(ell) * mfma_ks(K) * 128 * sizeof(u64));
+    l.up_aop = t.take((K && ell % alpha ? D : 0) * aop_words(mfma_ks(alpha)) * sizeof(u64));  // a shorter last digit
     l.end = t.o;
     return l;
 }
@@ -170,9 +153,6 @@ static RescaleLayout rescale_layout(size_t base, u32 ell) {
     Taker t{base};
     RescaleLayout l;
     l.sc_dn = t.take(sizeof(InvScale));
-    l.dn_chat = t.take(T * sizeof(u64));
-    l.dn_chat_fp = t.take(T * sizeof(double));
-    l.dn_fp_ok = t.take(T * sizeof(u32));
     l.pinv = t.take(T * sizeof(PinvConst));
     l.end = t.o;
     return l;
@@ -180,26 +160,23 @@ static RescaleLayout rescale_layout(size_t base, u32 ell) {
 
 // ModDown merged with the rescale after it, from level ell: sources q_{ell-1}, p_0..p_{K-1}; targets q_0..q_{ell-2}
 struct MergedLayout {
-    size_t sc_dn, dn_chat, dn_chat_fp, dn_fp_ok, pinv, dn_tiles, dn_aop, end;
+    size_t sc_dn, pinv, dn_aop, end;
 };
 static MergedLayout merged_layout(size_t base, u32 ell, u32 K) {
     const size_t T = ell - 1, S = K + 1;
     Taker t{base};
     MergedLayout l;
     l.sc_dn = t.take(S * sizeof(InvScale));
-    l.dn_chat = t.take(S * T * sizeof(u64));
-    l.dn_chat_fp = t.take(S * T * sizeof(double));
-    l.dn_fp_ok = t.take(T * sizeof(u32));
     l.pinv = t.take(T * sizeof(PinvConst));
-    l.dn_tiles = t.take(mfma_tile_bound(T) * sizeof(ConvTile));
-    l.dn_aop = t.take(mfma_tile_bound(T) * mfma_ks(S) * 128 * sizeof(u64));
+    l.dn_aop = t.take(T * aop_words(mfma_ks((u32)S)) * sizeof(u64));
     l.end = t.o;
     return l;
 }
 
 static size_t table_total(u32 logN, u32 L, u32 K, u32 dnum) {
-    size_t o = shared_layout(logN, L, K).end;
-    for (u32 ell = 1; ell <= L; ell++) o = level_layout(o, ell, K, (L + dnum - 1) / dnum).end;
+    const u32 alpha = (L + dnum - 1) / dnum;
+    size_t o = shared_layout(logN, L, K, alpha).end;
+    for (u32 ell = 1; ell <= L; ell++) o = level_layout(o, ell, K, alpha).end;
     for (u32 ell = 2; ell <= L; ell++) o = rescale_layout(o, ell).end;
     if (K)
         for (u32 ell = 2; ell <= L; ell++) o = merged_layout(o, ell, K).end;
@@ -250,12 +227,21 @@ struct Shared {
     SideStream side;
 };
 
+// Constant operands of the matrix-core conversions of one direction (device pointers; ConvArgs states the layout)
+struct ConvTab {
+    const u64* aop = nullptr;
+    const u64* aop_part = nullptr;
+    u32 n_full = 0;
+    u32 ks = 0;  // products per coefficient group; 0 = few sources, converted directly
+};
+
 // One level of the context: everything a launch needs.  `primes` is the level's basis in limb order.
 struct View {
     u32 logN = 0, L = 0, K = 0, dnum = 0, alpha = 0, D = 0;
     std::vector<u64> primes;
     Tables tb;
     bool mixed_classes = false;  // both FpAr and IntAr primes present
+    ConvTab up, dn;              // conversions of ModUp and ModDown
     Shared* sh = nullptr;
 };
 
@@ -418,44 +404,27 @@ static u64 prod_except(const std::vector<u64>& src, size_t skip, u64 m) {
     return r;
 }
 
-// Tiles and constant operands of the matrix-core conversion for one digit (conv_mfma_kernel states the layout).
-// targets: limb indices of the FpAr targets, in order; mod_of(t): their primes; hat(i, t): (product of the other
-// sources) mod that prime, for source i < ns.  Returns the number of tiles written (at most `bound`).
-template <class ModFn, class HatFn>
-static u32 build_conv_tiles(ConvTile* tiles, u64* aop, u32 bound, u32 ks_n, u32 ns, const std::vector<u32>& targets,
-                            ModFn mod_of, HatFn hat) {
-    u32 n_tiles = 0;
-    for (size_t first = 0; first < targets.size() && n_tiles < bound; n_tiles++) {
-        const u32 left = (u32)(targets.size() - first);
-        ConvTile& ct = tiles[n_tiles];
-        memset(&ct, 0, sizeof(ct));
-        ct.ntt = (left > 2 && CKKS_MFMA_NTT == 2) ? 2 : 1;
-        const u32 take = left < 2 * ct.ntt ? left : 2 * ct.ntt;
-        for (u32 tl = 0; tl < 4; tl++) ct.target[tl] = tl < take ? targets[first + tl] : 0xffffffffu;
-        first += take;
-        for (u32 ks = 0; ks < ks_n; ks++) {
-            for (u32 lane = 0; lane < 64; lane++) {
-                const u32 m_row = lane % 32, hk = lane / 32, hrow = (m_row / 4) % 2, a = (m_row / 8) * 4 + m_row % 4;
-                const u32 slot = hrow * ct.ntt + a / 8, dg = a % 8;
-                for (u32 half = 0; half < 2; half++) {  // the two sources this lane half carries in product ks
-                    const u32 i = 4 * ks + 2 * hk + half;
-                    u64 word = 0;
-                    if (a / 8 < ct.ntt && slot < 4 && ct.target[slot] != 0xffffffffu && i < ns) {
-                        const u64 m = mod_of(ct.target[slot]);
-                        u64 c = hat(i, ct.target[slot]) % m;  // times 256^bb below
-                        for (u32 bb = 0; bb < 8; bb++) {
-                            const int64_t centred = c > m / 2 ? (int64_t)c - (int64_t)m : (int64_t)c;
-                            const u64 z = (u64)centred + CKKS_DIGIT_BIAS;
-                            word |= (u64)((u8_of(z, dg)) ^ 0x80u) << (8 * bb);
-                            c = h_mulmod(c, 256 % m, m);
-                        }
-                    }
-                    aop[(((size_t)n_tiles * ks_n + ks) * 64 + lane) * 2 + half] = word;
-                }
-            }
+// Constant operands of the matrix-core conversion onto one target prime m (conv_mfma_body states the layout): source
+// i < ns has the constant hat[i] mod m.  aop: aop_words(ks) zeroed words.
+static void build_aop(u64* aop, const std::vector<u64>& hat, u64 m) {
+    for (u32 i = 0; i < hat.size(); i++) {
+        u64 c = hat[i] % m;
+        // source i travels in product i / 4, lane half (i / 2) % 2, word i % 2; digit row dg: byte bb = digit dg of
+        // hat * 256^bb
+        u64* rows = aop + (size_t)(i / 4) * 32 + (i / 2) % 2 * 16 + i % 2;
+        for (u32 bb = 0; bb < 8; bb++) {
+            const int64_t centred = c > m / 2 ? (int64_t)c - (int64_t)m : (int64_t)c;
+            const u64 z = (u64)centred + CKKS_DIGIT_BIAS;
+            for (u32 dg = 0; dg < 8; dg++) rows[2 * dg] |= (u64)(u8_of(z, dg) ^ 0x80u) << (8 * bb);
+            c = h_mulmod(c, 256 % m, m);
         }
     }
-    return n_tiles;
+}
+// prod of src[k], k != i, mod m, for every i
+static std::vector<u64> hats(const std::vector<u64>& src, u64 m) {
+    std::vector<u64> h(src.size());
+    for (size_t i = 0; i < src.size(); i++) h[i] = prod_except(src, i, m);
+    return h;
 }
 
 extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32_t K, uint32_t dnum,
@@ -469,8 +438,8 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
     if (((uintptr_t)d_tables) & 255) return CKKS_EINVAL;
     const size_t total = table_total(logN, L, K, dnum);
     if (table_bytes < total) return CKKS_ENOMEM;
-    const SharedLayout lay = shared_layout(logN, L, K);
     const u32 D = L + K, alpha = (L + dnum - 1) / dnum;
+    const SharedLayout lay = shared_layout(logN, L, K, alpha);
     const size_t N = (size_t)1 << logN;
     for (u32 i = 0; i < D; i++) {
         const u64 m = h_primes[i];
@@ -524,8 +493,8 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         p.r1 = (u64)(((u128)1 << 64) % m);
         p.r1_p = h_shoup(p.r1, m);
         p.r2 = h_mulmod(p.r1, p.r1, m);
-        p.qd = fp ? (double)m : 0.0;
-        p.qinv = fp ? 1.0 / (double)m : 0.0;
+        p.qd = (double)m;  // exact for FpAr primes
+        p.qinv = 1.0 / (double)m;
         p.fp = fp ? 1 : 0;
         p.pad = 0;
         ninv[i] = h_invmod(N % m, m);
@@ -554,6 +523,17 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         return any_fp && any_int;
     };
 
+    // constant operands of the matrix-core conversions that every level shares: full digits, and ModDown by P
+    const u32 up_ks = K ? mfma_ks(alpha) : 0, dn_ks = mfma_ks(K);
+    for (u32 j = 0; up_ks && j < L / alpha; j++) {
+        const std::vector<u64> digit(c->primes.begin() + j * alpha, c->primes.begin() + (j + 1) * alpha);
+        for (u32 t = 0; t < D; t++)
+            if (t / alpha != j || t >= L)
+                build_aop((u64*)(hb + lay.up_aop) + ((size_t)j * D + t) * aop_words(up_ks), hats(digit, c->primes[t]), c->primes[t]);
+    }
+    for (u32 t = 0; dn_ks && t < L; t++)
+        build_aop((u64*)(hb + lay.dn_aop) + t * aop_words(dn_ks), hats(specials, c->primes[t]), c->primes[t]);
+
     // ---- one block per level: limb index i of the level is prime ph(i) of the chain
     size_t off = lay.end;
     c->level.resize(L + 1);
@@ -565,11 +545,7 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         InvScale* sc_up = (InvScale*)(hb + ll.sc_up);
         u64* up_hatinv = (u64*)(hb + ll.up_hatinv);
         u64* up_chat = (u64*)(hb + ll.up_chat);
-        double* up_chat_fp = (double*)(hb + ll.up_chat_fp);
-        u32* up_fp_ok = (u32*)(hb + ll.up_fp_ok);
         u64* dn_chat = (u64*)(hb + ll.dn_chat);
-        double* dn_chat_fp = (double*)(hb + ll.dn_chat_fp);
-        u32* dn_fp_ok = (u32*)(hb + ll.dn_fp_ok);
         PinvConst* pinv = (PinvConst*)(hb + ll.pinv);
         u64* pmod = (u64*)(hb + ll.pmod);
         for (u32 j = 0; j < beta; j++) {  // ModUp constants of digit j = limbs [lo, hi)
@@ -586,13 +562,7 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
                     const u64 mt = c->primes[ph(t)];
                     const u64 hatb = prod_except(digit, i - lo, mt);
                     up_chat[(size_t)i * Dl + t] = h_mont(hatb, mt);
-                    up_chat_fp[(size_t)i * Dl + t] = pc[ph(t)].fp ? (double)hatb : 0.0;
                 }
-            }
-            for (u32 t = 0; t < Dl; t++) {
-                bool ok = pc[ph(t)].fp != 0;
-                for (u32 i = lo; i < hi; i++) ok = ok && pc[i].fp && c->primes[i] <= 2 * c->primes[ph(t)];
-                up_fp_ok[(size_t)j * Dl + t] = ok ? 1 : 0;
             }
         }
         for (u32 i = 0; i < ell; i++) {  // ModDown constants of target q_i
@@ -600,38 +570,10 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
             for (u32 k = 0; k < K; k++) {
                 const u64 hatb = prod_except(specials, k, qi);
                 dn_chat[(size_t)k * ell + i] = h_mont(hatb, qi);
-                // the conversion kernel strides by ell entries, i.e. 2*ell doubles: index (k*ell + i)*2
-                dn_chat_fp[(size_t)k * ell + i] = pc[i].fp ? (double)hatb : 0.0;
             }
-            dn_fp_ok[i] = (pc[i].fp && qi >= (1ull << 28)) ? 1 : 0;
             pmod[i] = prod_except(specials, specials.size(), qi);
             const u64 pi = h_invmod(pmod[i], qi);
             pinv[i] = PinvConst{pi, h_shoup(pi, qi), (double)pi};
-        }
-        // matrix-core conversion: ModUp tiles per digit (FpAr targets outside the digit), ModDown tiles (FpAr q-limbs)
-        u32 up_nt = 0, dn_nt = 0;
-        const u32 up_ks = mfma_ks_up(alpha), dn_ks = mfma_ks(K), up_bound = mfma_tile_bound(Dl), dn_bound = mfma_tile_bound(ell);
-        if (up_ks) {
-            for (u32 j = 0; j < beta; j++) {
-                const u32 lo = j * alpha, hi = (j + 1) * alpha < ell ? (j + 1) * alpha : ell;
-                const std::vector<u64> digit(c->primes.begin() + lo, c->primes.begin() + hi);
-                std::vector<u32> tg;
-                for (u32 t = 0; t < Dl; t++)
-                    if (!(t >= lo && t < hi) && pc[ph(t)].fp) tg.push_back(t);
-                const u32 nt = build_conv_tiles((ConvTile*)(hb + ll.up_tiles) + (size_t)j * up_bound,
-                                                (u64*)(hb + ll.up_aop) + (size_t)j * up_bound * up_ks * 128, up_bound, up_ks,
-                                                hi - lo, tg, [&](u32 t) { return c->primes[ph(t)]; },
-                                                [&](u32 i, u32 t) { return prod_except(digit, i, c->primes[ph(t)]); });
-                if (nt > up_nt) up_nt = nt;
-            }
-        }
-        if (dn_ks) {
-            std::vector<u32> tg;
-            for (u32 i = 0; i < ell; i++)
-                if (pc[i].fp) tg.push_back(i);
-            dn_nt = build_conv_tiles((ConvTile*)(hb + ll.dn_tiles), (u64*)(hb + ll.dn_aop), dn_bound, dn_ks, K, tg,
-                                     [&](u32 t) { return c->primes[t]; },
-                                     [&](u32 k, u32 t) { return prod_except(specials, k, c->primes[t]); });
         }
         View& v = c->level[ell];
         v.logN = logN, v.L = ell, v.K = K, v.dnum = beta, v.alpha = alpha, v.D = Dl, v.sh = &c->sh;
@@ -643,17 +585,18 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         tb.sc_up = (const InvScale*)(dbase + ll.sc_up);
         tb.up_hatinv = (const u64*)(dbase + ll.up_hatinv);
         tb.up_chat = (const u64*)(dbase + ll.up_chat);
-        tb.up_chat_fp = (const double*)(dbase + ll.up_chat_fp);
-        tb.up_fp_ok = (const u32*)(dbase + ll.up_fp_ok);
         tb.dn_chat = (const u64*)(dbase + ll.dn_chat);
-        tb.dn_chat_fp = (const double*)(dbase + ll.dn_chat_fp);
-        tb.dn_fp_ok = (const u32*)(dbase + ll.dn_fp_ok);
         tb.pinv = (const PinvConst*)(dbase + ll.pinv);
         tb.pmod = (const u64*)(dbase + ll.pmod);
-        tb.up_tiles = (const ConvTile*)(dbase + ll.up_tiles), tb.up_aop = (const u64*)(dbase + ll.up_aop);
-        tb.dn_tiles = (const ConvTile*)(dbase + ll.dn_tiles), tb.dn_aop = (const u64*)(dbase + ll.dn_aop);
-        tb.up_ntiles = up_nt, tb.up_tstride = up_bound, tb.up_ks = up_ks, tb.dn_ntiles = dn_nt, tb.dn_ks = dn_ks;
-        tb.L = ell, tb.K = K, tb.dnum = beta, tb.alpha = alpha, tb.D = Dl, tb.Lfull = L, tb.Lq = ell;
+        tb.L = ell, tb.K = K, tb.dnum = beta, tb.alpha = alpha, tb.D = Dl, tb.Lfull = L, tb.Kfull = K, tb.Lq = ell;
+        v.up = ConvTab{(const u64*)(dbase + lay.up_aop), (const u64*)(dbase + ll.up_aop), ell / alpha, up_ks};
+        v.dn = ConvTab{(const u64*)(dbase + lay.dn_aop), nullptr, 1, dn_ks};
+        if (up_ks && ell % alpha) {  // the last digit of this level is shorter than the chain's
+            const std::vector<u64> digit(c->primes.begin() + ell / alpha * alpha, c->primes.begin() + ell);
+            for (u32 t = 0; t < Dl; t++)
+                if (t < ell / alpha * alpha || t >= ell)
+                    build_aop((u64*)(hb + ll.up_aop) + t * aop_words(up_ks), hats(digit, v.primes[t]), v.primes[t]);
+        }
     }
     // ---- one block per rescale step: a ModDown whose only "special" prime is q_{ell-1}
     c->rescale.resize(L + 1);
@@ -663,16 +606,10 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         const u32 T = ell - 1;
         const u64 ql = c->primes[T];
         InvScale* rsc = (InvScale*)(hb + rl.sc_dn);
-        u64* dn_chat = (u64*)(hb + rl.dn_chat);
-        double* dn_chat_fp = (double*)(hb + rl.dn_chat_fp);
-        u32* dn_fp_ok = (u32*)(hb + rl.dn_fp_ok);
         PinvConst* pinv = (PinvConst*)(hb + rl.pinv);
         rsc[0] = make_scale(1, ninv[T], wlast[T], ql, pc[T].fp != 0);
         for (u32 i = 0; i < T; i++) {
             const u64 qi = c->primes[i];
-            dn_chat[i] = h_mont(1, qi);
-            dn_chat_fp[i] = pc[i].fp ? 1.0 : 0.0;
-            dn_fp_ok[i] = (pc[i].fp && qi >= (1ull << 28)) ? 1 : 0;
             const u64 pi = h_invmod(ql % qi, qi);
             pinv[i] = PinvConst{pi, h_shoup(pi, qi), (double)pi};
         }
@@ -685,11 +622,8 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         shared_tables(tb);
         tb.sc_dn = (const InvScale*)(dbase + rl.sc_dn);
         tb.dn_hatinv = nullptr;
-        tb.dn_chat = (const u64*)(dbase + rl.dn_chat);
-        tb.dn_chat_fp = (const double*)(dbase + rl.dn_chat_fp);
-        tb.dn_fp_ok = (const u32*)(dbase + rl.dn_fp_ok);
         tb.pinv = (const PinvConst*)(dbase + rl.pinv);
-        tb.L = T, tb.K = 1, tb.dnum = 1, tb.alpha = T, tb.D = ell, tb.Lfull = ell, tb.Lq = ell;  // phys() is the identity
+        tb.L = T, tb.K = 1, tb.dnum = 1, tb.alpha = T, tb.D = ell, tb.Lfull = ell, tb.Kfull = 0, tb.Lq = ell;  // phys() is the identity
     }
     // ---- one block per merged ModDown + rescale: sources q_{ell-1}, p_0..p_{K-1} (limbs ell-1 .. of level ell)
     c->merged.resize(L + 1);
@@ -701,9 +635,6 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         src.insert(src.end(), specials.begin(), specials.end());
         auto sph = [&](u32 k) { return k == 0 ? T : L + (k - 1); };  // chain index of source k
         InvScale* msc = (InvScale*)(hb + ml.sc_dn);
-        u64* dn_chat = (u64*)(hb + ml.dn_chat);
-        double* dn_chat_fp = (double*)(hb + ml.dn_chat_fp);
-        u32* dn_fp_ok = (u32*)(hb + ml.dn_fp_ok);
         PinvConst* pinv = (PinvConst*)(hb + ml.pinv);
         for (u32 k = 0; k < S; k++) {
             const u64 sk = src[k];
@@ -712,24 +643,8 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         }
         for (u32 i = 0; i < T; i++) {
             const u64 qi = c->primes[i];
-            for (u32 k = 0; k < S; k++) {
-                const u64 hatb = prod_except(src, k, qi);
-                dn_chat[(size_t)k * T + i] = h_mont(hatb, qi);
-                dn_chat_fp[(size_t)k * T + i] = pc[i].fp ? (double)hatb : 0.0;
-            }
-            dn_fp_ok[i] = (pc[i].fp && qi >= (1ull << 28)) ? 1 : 0;
             const u64 pi = h_invmod(prod_except(src, src.size(), qi), qi);
             pinv[i] = PinvConst{pi, h_shoup(pi, qi), (double)pi};
-        }
-        u32 dn_nt = 0;
-        const u32 dn_ks = mfma_ks(S);
-        if (dn_ks) {
-            std::vector<u32> tg;
-            for (u32 i = 0; i < T; i++)
-                if (pc[i].fp) tg.push_back(i);
-            dn_nt = build_conv_tiles((ConvTile*)(hb + ml.dn_tiles), (u64*)(hb + ml.dn_aop), mfma_tile_bound(T), dn_ks, S, tg,
-                                     [&](u32 t) { return c->primes[t]; },
-                                     [&](u32 k, u32 t) { return prod_except(src, k, c->primes[t]); });
         }
         View& v = c->merged[ell];
         v.logN = logN, v.L = T, v.K = S, v.dnum = 1, v.alpha = T, v.D = ell + K, v.sh = &c->sh;
@@ -740,13 +655,11 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         shared_tables(tb);
         tb.sc_dn = (const InvScale*)(dbase + ml.sc_dn);
         tb.dn_hatinv = nullptr;
-        tb.dn_chat = (const u64*)(dbase + ml.dn_chat);
-        tb.dn_chat_fp = (const double*)(dbase + ml.dn_chat_fp);
-        tb.dn_fp_ok = (const u32*)(dbase + ml.dn_fp_ok);
         tb.pinv = (const PinvConst*)(dbase + ml.pinv);
-        tb.dn_tiles = (const ConvTile*)(dbase + ml.dn_tiles), tb.dn_aop = (const u64*)(dbase + ml.dn_aop);
-        tb.dn_ntiles = dn_nt, tb.dn_ks = dn_ks;
-        tb.L = T, tb.K = S, tb.dnum = 1, tb.alpha = T, tb.D = ell + K, tb.Lfull = L, tb.Lq = ell;
+        tb.L = T, tb.K = S, tb.dnum = 1, tb.alpha = T, tb.D = ell + K, tb.Lfull = L, tb.Kfull = K, tb.Lq = ell;
+        v.dn = ConvTab{(const u64*)(dbase + ml.dn_aop), nullptr, 1, mfma_ks(S)};
+        for (u32 t = 0; t < T; t++)
+            build_aop((u64*)(hb + ml.dn_aop) + t * aop_words(v.dn.ks), hats(src, c->primes[t]), c->primes[t]);
     }
 
     hipStream_t s = (hipStream_t)stream;
@@ -863,26 +776,18 @@ static std::string kname(const char* base, const char* ar, int A, const char* ta
     return std::string(base) + "<" + ar + ", " + std::to_string(A) + tail + ">";
 }
 
-// One launch per arithmetic run of the primes [lo, hi).  limb_base converts a prime index into the
-// kernel's limb index.  by_limb: groups = run limbs x groups_n, instances = inst_n; otherwise
-// (conversion targets): groups = groups_n, instances = the run's limbs in blocks of inst_n.  alg(first, count) gives
-// the algorithmic limbs (read + written once) of the launch covering primes [first, first+count).
-// only: -1 = every run, 0 = IntAr runs only, 1 = FpAr runs only.
+// One launch per arithmetic run of the primes [lo, hi).  limb_base converts a prime index into the kernel's limb index;
+// groups = run limbs x groups_n, instances = inst_n.  alg(first, count) gives the algorithmic limbs (read + written once)
+// of the launch covering primes [first, first+count).
 template <class L, class ArgT, class AlgFn>
-static void launch_runs(const View* c, u32 lo, u32 hi, u32 limb_base, bool by_limb, u32 groups_n, u32 inst_n,
-                        const ArgT& a, hipStream_t s, AlgFn alg, int only = -1) {
+static void launch_runs(const View* c, u32 lo, u32 hi, u32 limb_base, u32 groups_n, u32 inst_n, const ArgT& a, hipStream_t s,
+                        AlgFn alg) {
     for (const ClassRun& cr : class_runs(c, lo, hi)) {
-        if (only >= 0 && (int)cr.fp != only) continue;
         const LimbRun run = {cr.first - limb_base, cr.count};
-        // conversion launches: inst_n holds the targets per workgroup of FpAr runs in its low half and of
-        // IntAr runs in its high half
-        const u32 tbn = cr.fp ? (inst_n & 0xffff) : (inst_n >> 16);
-        const dim3 grid(by_limb ? xcd_grid(cr.count * groups_n, inst_n)
-                                : xcd_grid(groups_n, (cr.count + tbn - 1) / tbn));
         hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
         ProfScope ps(c, c->sh->prof.on ? L::name(cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(),
                      c->sh->prof.on ? alg(cr.first, cr.count) : 0, rs);
-        dispatch_kernel<L>(c, cr.fp, grid, rs, a, run);
+        dispatch_kernel<L>(c, cr.fp, dim3(xcd_grid(cr.count * groups_n, inst_n)), rs, a, run);
     }
 }
 
@@ -910,35 +815,27 @@ struct FwdStridedL {
     }
     static std::string name(const char* ar, int A) { return kname("fwd_strided_kernel", ar, A, ""); }
 };
-// target limbs converted per workgroup, per direction and arithmetic (measured optimum: more targets save L2
-// reads and conversions of the sources but cost registers; 4 FP64 or 3 integer targets are slower again)
-#ifndef CKKS_CONV_TB_UP_FP
-#define CKKS_CONV_TB_UP_FP 3
-#endif
-#ifndef CKKS_CONV_TB_DN_FP
-#define CKKS_CONV_TB_DN_FP 3
-#endif
-#ifndef CKKS_CONV_TB_INT
-#define CKKS_CONV_TB_INT 2
-#endif
-template <int DIR, bool FP>
-struct ConvTB {
-    static constexpr int value = FP ? (DIR == CONV_UP ? CKKS_CONV_TB_UP_FP : CKKS_CONV_TB_DN_FP) : CKKS_CONV_TB_INT;
-};
-// DG: the sources are digit-format words (only where the FpAr targets of the view go to the matrix-core kernel, so
-// only integer-arithmetic runs are launched with it)
-template <int DIR, bool DG>
+// Conversions: KS products per coefficient group on the matrix cores, or (KS = 0) a single source and TB targets per
+// workgroup
+template <int DIR, int KS, int TB = 0>
 struct ConvL {
+    static constexpr bool packed = KS > 0;  // blocks are numbered over the targets alone, without a digit's own limbs
+    template <class AR>
+    static constexpr int per_block() { return KS ? 2 * conv_mfma_ntt<AR>() : TB; }
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const ConvArgs& a, const Tables& tb, LimbRun run) {
-        if constexpr (!(AR::is_fp && DG))
-            hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, ConvTB<DIR, AR::is_fp>::value, DG>), g, dim3(256), 0, s, a, tb,
-                               run);
+        constexpr int NTT = conv_mfma_ntt<AR>();
+        if constexpr (KS == 0) hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, TB, true>), g, dim3(256), 0, s, a, tb, run);
+        else if constexpr (AR::is_fp && DIR == CONV_DN)
+            hipLaunchKernelGGL((conv_mfma_kernel<A, KS, DIR, NTT>), g, dim3(256 * NTT), 0, s, a, tb, run);
+        else hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, KS + NTT, false>), g, dim3(256 * NTT), 0, s, a, tb, run);
     }
     static std::string name(const char* ar, int A) {
-        const int tbv = ar[0] == 'F' ? ConvTB<DIR, true>::value : ConvTB<DIR, false>::value;
-        return kname("conv_fwd_strided_kernel", ar, A,
-                     (std::string(", ") + std::to_string(DIR) + ", " + std::to_string(tbv) + (DG ? ", true" : ", false")).c_str());
+        const bool fp = ar[0] == 'F';
+        const int ntt = fp ? conv_mfma_ntt<FpAr>() : conv_mfma_ntt<IntAr>();
+        const std::string dir = std::to_string(DIR);
+        if (KS && fp && DIR == CONV_DN) return "conv_mfma_kernel<" + std::to_string(A) + ", " + std::to_string(KS) + ", " + dir + ", " + std::to_string(ntt) + ">";
+        return kname("conv_fwd_strided_kernel", ar, A, (", " + dir + ", " + std::to_string(KS ? KS + ntt : TB) + (KS ? ", false" : ", true")).c_str());
     }
 };
 struct FwdContigL {
@@ -975,99 +872,83 @@ template <int LOAD>
 static void launch_inv_contig(const View* c, const InvContigArgs& a, hipStream_t s) {
     const u32 pb = a.sel.prime_base;
     const u64 per = (u64)a.sel.n_inst * (LOAD == INV_TENSOR ? 3 : 2);
-    launch_runs<InvContigL<LOAD>>(c, pb, pb + a.sel.n_l, pb, true, tiles_of(c), a.sel.n_inst, a, s,
+    launch_runs<InvContigL<LOAD>>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s,
                                   [per](u32, u32 n) { return per * n; });
 }
 
 static void launch_inv_strided(const View* c, const InvStridedArgs& a, hipStream_t s) {
     const u32 pb = a.sel.prime_base;
     const u64 per = (u64)a.sel.n_inst * 2;
-    launch_runs<InvStridedL>(c, pb, pb + a.sel.n_l, pb, true, tiles_of(c), a.sel.n_inst, a, s,
+    launch_runs<InvStridedL>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s,
                              [per](u32, u32 n) { return per * n; });
 }
 
 static void launch_fwd_strided(const View* c, const FwdStridedArgs& a, hipStream_t s) {
     const u32 pb = a.sel.prime_base;
     const u64 per = (u64)a.sel.n_inst * 2;
-    launch_runs<FwdStridedL>(c, pb, pb + a.sel.n_l, pb, true, tiles_of(c), a.sel.n_inst, a, s,
+    launch_runs<FwdStridedL>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s,
                              [per](u32, u32 n) { return per * n; });
 }
 
-template <int A, int DIR>
-static void launch_conv_mfma_ks(const View* c, u32 ks, dim3 grid, hipStream_t s, const MfmaConvArgs& a) {
-    switch (ks) {
-        case 1: hipLaunchKernelGGL((conv_mfma_kernel<A, 1, DIR, CKKS_MFMA_NTT>), grid, dim3(256), 0, s, a, c->tb); break;
-        case 2: hipLaunchKernelGGL((conv_mfma_kernel<A, 2, DIR, CKKS_MFMA_NTT>), grid, dim3(256), 0, s, a, c->tb); break;
+// one launch per arithmetic run of the targets
+// only: -1 = every run, 0 = IntAr runs only, 1 = FpAr runs only
+template <class L, int DIR>
+static void launch_conv_runs(const View* c, ConvArgs a, hipStream_t s, int only) {
+    for (const ClassRun& cr : class_runs(c, 0, DIR == CONV_UP ? c->D : c->L)) {
+        if (only >= 0 && (int)cr.fp != only) continue;
+        const u32 blk = cr.fp ? L::template per_block<FpAr>() : L::template per_block<IntAr>();
+        // targets of the run: a digit's own limbs are none of its targets
+        u32 most = cr.count, written = cr.count;
+        if (DIR == CONV_UP) {
+            most = written = 0;
+            for (u32 j = 0; j < c->dnum; j++) {
+                const u32 own_hi = (j + 1) * c->alpha < c->L ? (j + 1) * c->alpha : c->L;
+                const u32 lo = j * c->alpha > cr.first ? j * c->alpha : cr.first, hi = own_hi < cr.first + cr.count ? own_hi : cr.first + cr.count;
+                const u32 n = cr.count - (hi > lo ? hi - lo : 0);
+                written += n;
+                if (n > most) most = n;
+            }
+        }
+        if (!most) continue;
+        a.blocks = ((L::packed ? most : cr.count) + blk - 1) / blk;
+        const dim3 grid(xcd_grid(a.groups_outer * (DIR == CONV_UP ? c->dnum : 1) * tiles_of(c), a.blocks));
+        hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
+        // every target written, plus the source coefficients, read once
+        ProfScope ps(c, c->sh->prof.on ? L::name(cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(),
+                     (u64)a.groups_outer * (written + (DIR == CONV_UP ? c->L : c->K)), rs);
+        dispatch_kernel<L>(c, cr.fp, grid, rs, a, LimbRun{cr.first, cr.count});
     }
 }
 
-// conversion of every FpAr target on the matrix cores (the view's tile tables say which targets those are)
-template <int DIR>
-static void launch_conv_mfma(const View* c, const ConvArgs& a, hipStream_t s) {
-    const Tables& tb = c->tb;
-    MfmaConvArgs m;
-    m.src = a.src, m.dst = a.dst, m.groups_outer = a.groups_outer;
-    m.tiles = DIR == CONV_UP ? tb.up_tiles : tb.dn_tiles;
-    m.aop = DIR == CONV_UP ? tb.up_aop : tb.dn_aop;
-    m.n_tiles = DIR == CONV_UP ? tb.up_ntiles : tb.dn_ntiles;
-    m.tile_stride = DIR == CONV_UP ? tb.up_tstride : tb.dn_ntiles;
-    const u32 ks = DIR == CONV_UP ? tb.up_ks : tb.dn_ks;
-    const u32 groups = a.groups_outer * (DIR == CONV_UP ? c->dnum : 1) * tiles_of(c);
-    const dim3 grid(xcd_grid(groups, m.n_tiles));
-    u64 limbs = 0;  // FpAr targets written (per digit that does not own them) plus the sources, read once
-    if (c->sh->prof.on) {
-        const u32 hi = DIR == CONV_UP ? c->D : c->L;
-        for (u32 t = 0; t < hi; t++)
-            if (c->primes[t] < CKKS_FP_PRIME_LIMIT) limbs += DIR == CONV_UP ? c->dnum - (t < c->L ? 1 : 0) : 1;
-        limbs = (u64)a.groups_outer * (limbs + (DIR == CONV_UP ? c->L : c->K));
-    }
-    ProfScope ps(c, c->sh->prof.on ? std::string("conv_mfma_kernel<") + std::to_string((int)c->logN - 8) + ", " + std::to_string(ks) +
-                                         ", " + std::to_string(DIR) + ", " + std::to_string(CKKS_MFMA_NTT) + ">"
-                                   : std::string(),
-                 limbs, s);
-    switch (c->logN - 8) {
-        case 4: launch_conv_mfma_ks<4, DIR>(c, ks, grid, s, m); break;
-        case 5: launch_conv_mfma_ks<5, DIR>(c, ks, grid, s, m); break;
-        case 6: launch_conv_mfma_ks<6, DIR>(c, ks, grid, s, m); break;
-        case 7: launch_conv_mfma_ks<7, DIR>(c, ks, grid, s, m); break;
-        case 8: launch_conv_mfma_ks<8, DIR>(c, ks, grid, s, m); break;
-    }
-}
-
-static inline bool conv_on_matrix_cores(const View* c, int dir) {
-    return dir == CONV_UP ? c->tb.up_ntiles != 0 : c->tb.dn_ntiles != 0;
-}
+// word format in which the last inverse stage leaves the sources of a conversion
+static inline u32 conv_src_fmt(const ConvTab& t, int dir) { return t.ks ? SRC_DIGITS : dir == CONV_UP ? SRC_F64 : SRC_CANON; }
 
 // cls: -1 = every target, 0 = IntAr targets only, 1 = FpAr targets only
 template <int DIR>
-static void launch_conv(const View* c, const ConvArgs& a, hipStream_t s, int cls = -1) {
-    const u64 outer = a.groups_outer;
-    const bool mfma = conv_on_matrix_cores(c, DIR);  // FpAr targets go to the matrix-core kernel when the view has tiles
-    if (mfma && cls != 0) launch_conv_mfma<DIR>(c, a, s);
-    if (mfma && cls == 1) return;
-    const int only = mfma ? 0 : cls;
-    const u32 tbs = ConvTB<DIR, true>::value | (ConvTB<DIR, false>::value << 16);
-    if (DIR == CONV_UP) {  // groups = (batch, digit, tile); instances = blocks of the run's target primes
-        auto alg = [c, outer](u32 first, u32 n) {
-            u64 w = 0;  // every target limb is written for each digit that does not own it
-            for (u32 t = first; t < first + n; t++) w += c->dnum - (t < c->L ? 1 : 0);
-            return outer * (w + c->L);  // plus the source coefficients, read once
-        };
-        const u32 groups = a.groups_outer * c->dnum * tiles_of(c);
-        if (a.src_fmt == SRC_DIGITS) launch_runs<ConvL<DIR, true>>(c, 0, c->D, 0, false, groups, tbs, a, s, alg, only);
-        else launch_runs<ConvL<DIR, false>>(c, 0, c->D, 0, false, groups, tbs, a, s, alg, only);
-    } else {  // groups = (g, tile); instances = blocks of the run's target q-limbs
-        auto alg = [c, outer](u32, u32 n) { return outer * (n + (u64)c->K); };
-        const u32 groups = a.groups_outer * tiles_of(c);
-        if (a.src_fmt == SRC_DIGITS) launch_runs<ConvL<DIR, true>>(c, 0, c->L, 0, false, groups, tbs, a, s, alg, only);
-        else launch_runs<ConvL<DIR, false>>(c, 0, c->L, 0, false, groups, tbs, a, s, alg, only);
+static void launch_conv(const View* c, ConvArgs a, hipStream_t s, int cls = -1) {
+    const ConvTab& t = DIR == CONV_UP ? c->up : c->dn;
+    a.aop = t.aop, a.aop_part = t.aop_part, a.n_full = t.n_full;
+    switch (t.ks) {
+        case 0: {
+            // four targets share a load of the source unless that leaves fewer than two workgroups per compute unit
+            const u32 wgs = a.groups_outer * (DIR == CONV_UP ? c->dnum : 1) * tiles_of(c) * (((DIR == CONV_UP ? c->D : c->L) + 3) / 4);
+            if (wgs >= 512) launch_conv_runs<ConvL<DIR, 0, 4>, DIR>(c, a, s, cls);
+            else launch_conv_runs<ConvL<DIR, 0, 1>, DIR>(c, a, s, cls);
+            break;
+        }
+        case 1: launch_conv_runs<ConvL<DIR, 1>, DIR>(c, a, s, cls); break;
+        case 2: launch_conv_runs<ConvL<DIR, 2>, DIR>(c, a, s, cls); break;
+        case 4: launch_conv_runs<ConvL<DIR, 4>, DIR>(c, a, s, cls); break;
+        case 5:
+            if constexpr (DIR == CONV_DN) launch_conv_runs<ConvL<DIR, 5>, DIR>(c, a, s, cls);
+            break;
     }
 }
 
 static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t s) {
     const u32 pb = a.sel.prime_base;
     const u64 per = (u64)a.sel.n_inst * 2;
-    launch_runs<FwdContigL>(c, pb, pb + a.sel.n_l, pb, true, tiles_of(c), a.sel.n_inst, a, s,
+    launch_runs<FwdContigL>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s,
                             [per](u32, u32 n) { return per * n; });
 }
 
@@ -1077,7 +958,7 @@ template <int OWN, bool HOISTED, bool FUSED = false>
 static void launch_ks_inner(const View* c, const InnerArgs& a, hipStream_t s, u32 lo, u32 hi) {
     const u64 n_inst = a.n_inst;
     launch_runs<KsInnerL<OWN, HOISTED, FUSED>>(
-        c, lo, hi, 0, true, tiles_of(c), a.n_inst, a, s, [c, n_inst](u32 first, u32 n) {
+        c, lo, hi, 0, tiles_of(c), a.n_inst, a, s, [c, n_inst](u32 first, u32 n) {
             u64 limbs = 0;
             for (u32 i = first; i < first + n; i++) {
                 const bool q = i < c->L;
@@ -1147,7 +1028,7 @@ static void launch_ks_final(const View* c, const FinalArgs& a, hipStream_t s) {
     u64 per;  // algorithmic limbs per q-limb
     if (MODE == FIN_HOISTED) per = (u64)a.n_rot * (2 + 2 + 1 + 1) + (2 + (a.accumulate ? 2 : 0));
     else per = (u64)a.n_inst * 6;
-    launch_runs<KsFinalL<MODE>>(c, 0, c->L, 0, true, tiles_of(c), a.n_inst, a, s, [per](u32, u32 n) { return per * n; });
+    launch_runs<KsFinalL<MODE>>(c, 0, c->L, 0, tiles_of(c), a.n_inst, a, s, [per](u32, u32 n) { return per * n; });
 }
 
 template <int AL>
@@ -1462,10 +1343,10 @@ static int check_ks_args(const View* c, const void* a, const void* b, const void
 // first forward pass of every extended limb.
 static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, bool fp_beside = false) {
     const LimbSel sel = {c->L, groups, c->L, 0, 0, 0};
-    const u32 fmt = conv_on_matrix_cores(c, CONV_UP) ? SRC_DIGITS : SRC_F64;
+    const u32 fmt = conv_src_fmt(c->up, CONV_UP);
     InvStridedArgs a2 = {w.x, sel, SC_UP, fmt};
     launch_inv_strided(c, a2, s);
-    ConvArgs a3 = {w.x, w.dt, groups, fmt};
+    const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0};
     SideStream& sd = c->sh->side;
     if (fp_beside && sd.enabled && c->mixed_classes && !sd.active && side_stream_ready(sd)) {
         // the IntAr targets first, on s; the FpAr targets on the side stream from the moment those are done, beside
@@ -1506,11 +1387,11 @@ static void join_fp_beside(const View* c, hipStream_t s) {
 // ModDown side: w.cp holds the first inverse pass of c' on the special limbs.
 static void moddown_convert(const View* c, const Workspace& w, u32 cg, hipStream_t s) {
     const LimbSel sel = {c->K, cg * 2, c->K, 0, c->L, 0};
-    const u32 fmt = conv_on_matrix_cores(c, CONV_DN) ? SRC_DIGITS : SRC_CANON;
+    const u32 fmt = conv_src_fmt(c->dn, CONV_DN);
     InvStridedArgs a6 = {w.cp, sel, SC_DN, fmt};
     launch_inv_strided(c, a6, s);
     join_side(c, s);  // the conversion reads every special limb
-    ConvArgs a7 = {w.cp, w.cv, cg * 2, fmt};
+    const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, nullptr, nullptr, 0};
     launch_conv<CONV_DN>(c, a7, s);
 }
 

@@ -36,24 +36,13 @@ struct Tables {
     const InvScale* sc_dn;     // [K]  N^-1 * [(P/p_k)^-1]_{p_k}
     const u64* up_hatinv;      // [L][2]  [(Q_j/q_i)^-1]_{q_i} and Shoup companion (stand-alone ModUp)
     const u64* dn_hatinv;      // [K][2]
-    const u64* up_chat;        // [L][D]  (Q_j/q_i) * 2^64 mod m_t   (0 inside the digit)
-    const double* up_chat_fp;  // [L][D]  (Q_j/q_i) mod m_t as a double (FpAr targets)
-    const u32* up_fp_ok;       // [dnum][D] 1 if target t of digit j may convert on the FP64 pipe: target and
-                               //           all sources FpAr primes, largest source <= 2 * target
-    const u64* dn_chat;        // [K][L]  (P/p_k) * 2^64 mod q_i
-    const double* dn_chat_fp;  // [K][L]  (P/p_k) mod q_i as a double (FpAr targets)
-    const u32* dn_fp_ok;       // [L]  1 if q_i may convert on the FP64 pipe (FpAr prime, at least 2^28)
+    const u64* up_chat;        // [L][D]  (Q_j/q_i) * 2^64 mod m_t   (0 inside the digit; stand-alone ModUp)
+    const u64* dn_chat;        // [K][L]  (P/p_k) * 2^64 mod q_i   (stand-alone ModDown)
     const PinvConst* pinv;     // [L]     P^-1 mod q_i
     const u64* pmod;           // [L]     P mod q_i
-    // conversion on the matrix cores (conv_mfma_kernel): target tiles and constant operands per digit; n_tiles = 0
-    // when the view does not use it (fewer than 2 or more than 8 sources, or no FpAr target)
-    const struct ConvTile* up_tiles;  // [dnum][up_tstride]
-    const u64* up_aop;                // [dnum][up_tstride][up_ks][64]
-    const struct ConvTile* dn_tiles;  // [dn_ntiles]
-    const u64* dn_aop;                // [dn_ntiles][dn_ks][64]
-    u32 up_ntiles, up_tstride, up_ks, dn_ntiles, dn_ks;  // tiles in use (most over the digits), tiles stored per digit
     u32 logN, L, K, dnum, alpha, D;
     u32 Lfull;  // q-limbs of the whole prime chain
+    u32 Kfull;  // special limbs of the whole prime chain
     u32 Lq;     // limbs 0 .. Lq-1 of this basis are q-limbs of the chain, the rest its special limbs
     // A Tables value describes one level: the basis q_0..q_{L-1}, p_0..p_{K-1} with L <= Lfull active
     // q-limbs, dnum = ceil(L/alpha) digits (the last one possibly partial) and limb indices 0..D-1 over
@@ -145,6 +134,27 @@ __device__ __forceinline__ void gather_row_cp(const u64* limb, u32 row_off, u32 
 #pragma unroll
     for (int kk = 0; kk < 16; kk++) o[kk] = l[pad16(eval_perm(row_off + cp_word(e0, kk), gal, logN) & 255)];
 }
+
+// Buffer access to memory from a uniform base: address = base + per-lane byte offset + scalar byte offset.  The strided
+// passes step through rows 32 KiB (or 2 KiB) apart; with plain pointers every such access cost two 64-bit additions,
+// six of the seventy vector instructions per output of the conversion kernels, here the step is scalar arithmetic.
+typedef u32 u32x2 __attribute__((ext_vector_type(2)));
+struct Buf {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ explicit Buf(const void* base) : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xffffffffu, 0x00020000)) {}
+    __device__ __forceinline__ u64 ld(u32 lane_bytes, u32 bytes) const {
+        return __builtin_bit_cast(u64, __builtin_amdgcn_raw_buffer_load_b64(r, lane_bytes, bytes, 0));
+    }
+    __device__ __forceinline__ u64 ld_nt(u32 lane_bytes, u32 bytes) const {
+        return __builtin_bit_cast(u64, __builtin_amdgcn_raw_buffer_load_b64(r, lane_bytes, bytes, 2));
+    }
+    __device__ __forceinline__ void st(u64 v, u32 lane_bytes, u32 bytes) const {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, lane_bytes, bytes, 0);
+    }
+    __device__ __forceinline__ void st_nt(u64 v, u32 lane_bytes, u32 bytes) const {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, lane_bytes, bytes, 2);
+    }
+};
 
 // most rotations (each with its own key and Galois element) one launch can be given
 #define CKKS_ROT_CHUNK 16
@@ -323,434 +333,402 @@ __global__ __launch_bounds__(256) void fwd_strided_kernel(FwdStridedArgs a, Tabl
 }
 
 // ============================== base conversion fused into the first forward pass of its targets
-// CONV_UP: group = (b, digit j, tile); sources y [b][L][N] = coefficients times [(Q_j/q_i)^-1], limbs of
-//          FpAr primes stored as doubles; targets = the primes outside digit j; dst dt [b][dnum][D][N].
-// CONV_DN: group = (g, tile); sources y = special limbs [g][K][N] (canonical words); targets = q-limbs;
-//          dst cv [g][L][N].
-// A workgroup converts TB consecutive target primes of the run from one load of the sources (the
-// sources come from L2, whose bandwidth is what bounds a one-target-per-workgroup version), then
-// runs the first forward pass of each target in turn.
+// CONV_UP: group = (b, digit j, tile); sources y [b][L][N] = coefficients times [(Q_j/q_i)^-1]; targets = the primes
+//          outside digit j; dst dt [b][dnum][D][N].
+// CONV_DN: group = (g, tile); sources y = special limbs [g][K][N]; targets = q-limbs; dst cv [g][L][N].
+// Two or more sources convert on the matrix cores (conv_mfma_body), a single one is reduced directly (conv_one_body).
 enum ConvDir { CONV_UP = 1, CONV_DN = 2 };
 struct ConvArgs {
-    const u64* src;
-    u64* dst;
-    u32 groups_outer;  // CONV_UP: batch; CONV_DN: number of g
-    u32 src_fmt;       // SrcFormat of the source words: SRC_DIGITS, or the natural format (the launcher picks the instantiation)
+    const u64* src;       // CONV_UP [b][L][N], CONV_DN [g][K][N], in the format that conv_src_fmt names
+    u64* dst;             // raw forward-lazy words after the first pass: CONV_UP dt [b][dnum][D][N], CONV_DN cv [g][L][N]
+    u32 groups_outer;     // CONV_UP: batch; CONV_DN: number of g
+    u32 blocks;           // workgroups per (group, tile): the run's targets in blocks
+    // matrix cores: constant operands [digit][prime of the chain][KS][2 lane halves][8 digit rows][2 words], and the same
+    // of a shorter last digit, [limb of the level]; digits from n_full on use the latter
+    const u64* aop;
+    const u64* aop_part;
+    u32 n_full;
 };
-// a source word as a canonical integer; DG: the sources are SRC_DIGITS words, else they are in their natural
-// format (FpAr-prime sources of ModUp as doubles, everything else canonical)
-template <bool DG>
-__device__ __forceinline__ u64 conv_src_int(u64 w, bool f64_word) {
-    return DG ? digits_decode(w) : f64_word ? f64_to_u64(FpAr::from_raw(w)) : w;
+
+// Twiddles of the strided pass of one target, W[0 .. R1) of its table, staged in LDS before the pass: a global load
+// issued after the stores of an earlier target waits for those stores (one counter covers both), and with two or three
+// targets per workgroup those waits were a quarter of the conversion kernels' time.  IntAr keeps w and its Shoup
+// companion side by side (one 16-byte LDS read).
+template <class AR, int A>
+struct StridedTw {
+    static constexpr u32 R1 = 1u << A, WORDS = AR::is_fp ? R1 : 2 * R1;
+    static __device__ __forceinline__ void fill(u64* blk, u32 tid, const Tables& tb, u32 pi) {
+        const u32 N = 1u << tb.logN;
+        if (tid < R1) {
+            if constexpr (AR::is_fp) {
+                blk[tid] = __builtin_bit_cast(u64, tb.tw_fp[(size_t)pi * 2 * N + tid]);
+            } else {
+                blk[2 * tid] = tb.tw_int[(size_t)pi * 4 * N + tid];
+                blk[2 * tid + 1] = tb.tw_int[(size_t)pi * 4 * N + N + tid];
+            }
+        }
+    }
+    static __device__ __forceinline__ typename AR::Tw get(const u64* blk, u32 idx) {
+        if constexpr (AR::is_fp) return typename AR::Tw{__builtin_bit_cast(double, blk[idx])};
+        else {
+            const u64x2 t = *reinterpret_cast<const u64x2*>(blk + 2 * idx);
+            return typename AR::Tw{t.x, t.y};
+        }
+    }
+};
+// stages 0-3 of the strided pass on the 16 words of layout SA; integer inputs below 2q leave below 6q
+template <class AR, int A>
+__device__ __forceinline__ void strided_stages_lo(typename AR::T (&x)[16], const u64* tw, const typename AR::Mod& m) {
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+        const int d = 8 >> s;
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            if (k & d) continue;
+            const typename AR::Tw w = StridedTw<AR, A>::get(tw, (1u << s) + (k >> (4 - s)));
+            if (s == 3) AR::template bfly_fwd<true>(x[k], x[k + d], w, m);  // below 4q, 6q, 8q before stages 1, 2, 3
+            else AR::template bfly_fwd<false>(x[k], x[k + d], w, m);
+        }
+    }
+}
+// stages 4 .. A-1 on layout SB (row r1*16 + k)
+template <class AR, int A>
+__device__ __forceinline__ void strided_stages_hi(typename AR::T (&x)[16], const u64* tw, u32 r1, const typename AR::Mod& m) {
+#pragma unroll
+    for (int s = 4; s < A; s++) {
+        const int d = 1 << (A - s - 1);
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            if (k & d) continue;
+            const typename AR::Tw w = StridedTw<AR, A>::get(tw, (1u << s) + ((r1 * 16 + k) >> (A - s)));
+            if (s & 1) AR::template bfly_fwd<true>(x[k], x[k + d], w, m);  // below 6q after stage 3: odd stages reduce
+            else AR::template bfly_fwd<false>(x[k], x[k + d], w, m);
+        }
+    }
 }
 
-template <class AR, int A, int DIR, int TB, bool DG = false>
-__global__ __launch_bounds__(256, AR::is_fp ? 3 : 2) void conv_fwd_strided_kernel(ConvArgs a, Tables tb, LimbRun run) {
-    __shared__ u64 lds[4096];
+// ---- a single source (digits of one limb, one special prime, the rescale): out_t = y mod m_t, the conversion constant is 1.
+// A workgroup keeps the words of one load and reduces them to TB targets in turn: 4 share a load where the launch fills
+// the chip (rescale of 8 ciphertexts at N = 2^16, 23 limbs: 63 -> 53 us against three targets converted before the first
+// is transformed), 1 where it does not and the time is that of one workgroup (launch_conv).
+template <class AR, int A, int DIR, int TB>
+__device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& tb, const LimbRun run) {
     typedef NttCore<AR, A> C;
-    typedef typename AR::T T;
+    typedef StridedTw<AR, A> TW;
     constexpr u32 TILES = (1u << A) / 16;
+    __shared__ u64 lds[A > 4 ? 4096 : 1];
+    __shared__ __align__(16) u64 tws[TB * TW::WORDS];
     const u32 N = 1u << tb.logN, tid = threadIdx.x;
-    const u32 n_inst = (run.count + TB - 1) / TB;
-    u32 group, inst, tile, ns, src_prime, chat_stride;
+    u32 group, inst, own = 0xffffffffu, src_prime;
     const u64* src;
     u64* dst0;  // limb 0 of the destination group
-    const u64* chat;
-    const double* chat_fp;
-    const u32* fp_ok;
-    u32 own_lo = 0xffffffffu, own_hi = 0xffffffffu;  // target primes in [own_lo, own_hi) are skipped
     if (DIR == CONV_UP) {
-        if (!xcd_decode(blockIdx.x, n_inst, a.groups_outer * tb.dnum * TILES, group, inst)) return;
-        tile = group % TILES;
+        if (!xcd_decode(blockIdx.x, a.blocks, a.groups_outer * tb.dnum * TILES, group, inst)) return;
         const u32 bj = group / TILES, j = bj % tb.dnum, b = bj / tb.dnum;
-        src = a.src + ((size_t)b * tb.L + (size_t)j * tb.alpha) * N;
+        src = a.src + ((size_t)b * tb.L + j) * N;
         dst0 = a.dst + ((size_t)b * tb.dnum + j) * tb.D * N;
-        chat = tb.up_chat + (size_t)j * tb.alpha * tb.D;
-        chat_fp = tb.up_chat_fp + (size_t)j * tb.alpha * tb.D;
-        fp_ok = tb.up_fp_ok + (size_t)j * tb.D;
-        // the last digit of a level may hold fewer than alpha limbs
-        own_lo = j * tb.alpha, own_hi = (j + 1) * tb.alpha < tb.L ? (j + 1) * tb.alpha : tb.L;
-        chat_stride = tb.D, ns = own_hi - own_lo, src_prime = own_lo;
+        own = src_prime = j;
     } else {
-        if (!xcd_decode(blockIdx.x, n_inst, a.groups_outer * TILES, group, inst)) return;
-        tile = group % TILES;
+        if (!xcd_decode(blockIdx.x, a.blocks, a.groups_outer * TILES, group, inst)) return;
         const u32 g = group / TILES;
-        src = a.src + (size_t)g * tb.K * N;
+        src = a.src + (size_t)g * N;
         dst0 = a.dst + (size_t)g * tb.L * N;
-        chat = tb.dn_chat;
-        chat_fp = tb.dn_chat_fp;
-        fp_ok = tb.dn_fp_ok;
-        chat_stride = tb.L, ns = tb.K, src_prime = tb.L;
+        src_prime = tb.L;
     }
-    u32 pi[TB];
-    bool valid[TB], any = false, all_fp = AR::is_fp;
-#pragma unroll
-    for (int t = 0; t < TB; t++) {
-        pi[t] = run.first + inst * TB + t;
-        valid[t] = pi[t] < run.first + run.count && !(pi[t] >= own_lo && pi[t] < own_hi);
-        if (!valid[t]) pi[t] = run.first;  // any prime of the run: its result is dropped
-        any = any || valid[t];
-        all_fp = all_fp && (!valid[t] || fp_ok[pi[t]]);
-    }
-    if (!any) return;
+    const u32 tile = group % TILES, first = run.first + inst * TB, end = run.first + run.count;
+    if (TB == 1 && first == own) return;
     const u32 c = tid % C::TC, r0 = tid / C::TC, col = tile * C::TC + c;
-    const u32 rot = ns ? (inst + tile) % ns : 0;  // workgroups sharing sources walk them in different orders
-    T x[TB][16];
-    if (all_fp) {
-        // FP64 pipe: every product reduced lazily (|.| <= 1.25 q), at most 18 of them accumulated between two
-        // reductions of the accumulator (8 sources; ModDown sources count twice).  The 16
-        // words of a lane are converted in two halves so that accumulators and staged sources stay small.
-        FpAr::Mod fm[TB];
+    const bool src_fp = tb.pc[tb.phys(src_prime)].fp;
+    const Buf sb(src);
+    u64 y[16];
 #pragma unroll
-        for (int t = 0; t < TB; t++) fm[t] = FpAr::mod(tb.pc[tb.phys(pi[t])]);
+    for (int k = 0; k < 16; k++) y[k] = sb.ld(8 * (r0 * 256 + col), 8 * 256 * C::RB * k);
 #pragma unroll
-        for (int hf = 0; hf < 2; hf++) {
-            double acc[TB][8];
+    for (int t = 0; t < TB; t++)
+        if (first + t < end) TW::fill(tws + t * TW::WORDS, tid, tb, tb.phys(first + t));
+    // a source of an FpAr prime, below 2^50: a double for FpAr targets (ModUp stores it so), an integer for IntAr ones
+    if (src_fp && AR::is_fp == (DIR == CONV_DN)) {
 #pragma unroll
-            for (int t = 0; t < TB; t++)
+        for (int k = 0; k < 16; k++) y[k] = AR::is_fp ? FpAr::to_raw(u64_to_f64(y[k])) : f64_to_u64(FpAr::from_raw(y[k]));
+    }
+    __syncthreads();
+    bool again = false;
+    for (int t = 0; t < TB; t++) {
+        const u32 vi = first + t;
+        if (vi >= end) break;
+        if (vi == own) continue;
+        const PrimeConst pc = tb.pc[tb.phys(vi)];
+        const typename AR::Mod m = AR::mod(pc);
+        const u64* tw = tws + t * TW::WORDS;
+        typename AR::T x[16];
+        if constexpr (AR::is_fp) {
+            if (src_fp) {
 #pragma unroll
-                for (int k = 0; k < 8; k++) acc[t][k] = 0.0;
-            // the loads of source i+1 are issued before the arithmetic on source i (software pipeline)
-            u64 cur[8], nxt[8];
-            {
-                const u64* s0 = src + (size_t)rot * N;
-#pragma unroll
-                for (int k = 0; k < 8; k++) cur[k] = s0[(size_t)((hf * 8 + k) * C::RB + r0) * 256 + col];
-            }
-            // rounds of 8 sources: with more than 8, the accumulators go back to |acc| <= q/2 between rounds
-            for (u32 g0 = 0; g0 < ns; g0 += 8) {
-                const u32 ge = g0 + 8 < ns ? g0 + 8 : ns;
-                for (u32 i0 = g0; i0 < ge; i0++) {
-                    const u32 i = i0 + rot < ns ? i0 + rot : i0 + rot - ns;
-                    if (i0 + 1 < ns) {
-                        const u32 in = i0 + 1 + rot < ns ? i0 + 1 + rot : i0 + 1 + rot - ns;
-                        const u64* sn = src + (size_t)in * N;
-#pragma unroll
-                        for (int k = 0; k < 8; k++) nxt[k] = sn[(size_t)((hf * 8 + k) * C::RB + r0) * 256 + col];
-                    }
-                    if (DIR == CONV_UP) {  // sources are doubles holding canonical residues of ~the targets' size
-                        double cf[TB];
-#pragma unroll
-                        for (int t = 0; t < TB; t++) cf[t] = chat_fp[(size_t)i * chat_stride + pi[t]];
-#pragma unroll
-                        for (int k = 0; k < 8; k++) {
-                            const double y = DG ? u64_to_f64(digits_decode(cur[k])) : FpAr::from_raw(cur[k]);
-#pragma unroll
-                            for (int t = 0; t < TB; t++) acc[t][k] += FpAr::mulmod_lazy(y, cf[t], fm[t]);
-                        }
-                    } else {  // sources are words below 2^61: brought below the target first, then one product each
-                        double cl[TB];
-#pragma unroll
-                        for (int t = 0; t < TB; t++) cl[t] = chat_fp[(size_t)i * chat_stride + pi[t]];
-#pragma unroll
-                        for (int k = 0; k < 8; k++) {
-                            const u64 y = DG ? digits_decode(cur[k]) : cur[k];
-                            const double ya = (double)(u32)(y >> 30) * 1073741824.0, yl = (double)(u32)(y & 0x3fffffffu);
-#pragma unroll
-                            for (int t = 0; t < TB; t++)
-                                acc[t][k] += FpAr::mulmod_lazy(FpAr::reduce_split(ya, yl, fm[t]), cl[t], fm[t]);
-                        }
-                    }
-#pragma unroll
-                    for (int k = 0; k < 8; k++) cur[k] = nxt[k];
-                }
-                if (ge < ns) {
-#pragma unroll
-                    for (int t = 0; t < TB; t++)
-#pragma unroll
-                        for (int k = 0; k < 8; k++) acc[t][k] = FpAr::reduce(acc[t][k], fm[t]);
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < TB; t++) {
-                const typename AR::Mod m = AR::mod(tb.pc[tb.phys(pi[t])]);
-#pragma unroll
-                for (int k = 0; k < 8; k++) x[t][hf * 8 + k] = AR::from_f64_lazy(acc[t][k], m);
-            }
-        }
-    } else if (!AR::is_fp) {
-        // integer pipe: 128-bit accumulation against Montgomery-form constants, one reduction per target;
-        // in two halves of eight words like the FP64 path
-#pragma unroll
-        for (int hf = 0; hf < 2; hf++) {
-            u128w acc[TB][8];
-#pragma unroll
-            for (int t = 0; t < TB; t++)
-#pragma unroll
-                for (int k = 0; k < 8; k++) acc[t][k] = u128w{0, 0};
-            // 8 terms (each below 2^61 * q) stay below q * 2^64, the bound of the reduction: with more sources,
-            // q * 2^64 is taken off after every round of 8 terms
-            for (u32 g0 = 0; g0 < ns; g0 += 8) {
-                const u32 ge = g0 + 8 < ns ? g0 + 8 : ns;
-                for (u32 i0 = g0; i0 < ge; i0++) {
-                    const u32 i = i0 + rot < ns ? i0 + rot : i0 + rot - ns;
-                    const u64* si = src + (size_t)i * N;
-                    const bool src_fp = DIR == CONV_UP && tb.pc[tb.phys(src_prime + i)].fp;
-                    u64 cc[TB];
-#pragma unroll
-                    for (int t = 0; t < TB; t++) cc[t] = chat[(size_t)i * chat_stride + pi[t]];
-#pragma unroll
-                    for (int k = 0; k < 8; k++) {
-                        const u64 y = conv_src_int<DG>(si[(size_t)((hf * 8 + k) * C::RB + r0) * 256 + col], src_fp);
-#pragma unroll
-                        for (int t = 0; t < TB; t++) mac128(acc[t][k], y, cc[t]);
-                    }
-                }
-                if (ns > 8) {
-#pragma unroll
-                    for (int t = 0; t < TB; t++) {
-                        const u64 qt = tb.pc[tb.phys(pi[t])].q;
-#pragma unroll
-                        for (int k = 0; k < 8; k++) acc[t][k].hi = csub(acc[t][k].hi, qt);
-                    }
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < TB; t++) {
-                const PrimeConst pc = tb.pc[tb.phys(pi[t])];
-                const typename AR::Mod m = AR::mod(pc);
-#pragma unroll
-                for (int k = 0; k < 8; k++) x[t][hf * 8 + k] = AR::from_canon(redc(acc[t][k], pc.q, pc.qneg), m);
-            }
-        }
-    } else {
-        // FpAr targets whose sources do not fit the FP64 bounds: integer conversion, one target at a time
-        for (int t = 0; t < TB; t++) {
-            const PrimeConst pc = tb.pc[tb.phys(pi[t])];
-            const typename AR::Mod m = AR::mod(pc);
-            u128w acc[16];
-#pragma unroll
-            for (int k = 0; k < 16; k++) acc[k] = u128w{0, 0};
-            for (u32 i = 0; i < ns; i++) {
-                const u64* si = src + (size_t)i * N;
-                const bool src_fp = DIR == CONV_UP && tb.pc[tb.phys(src_prime + i)].fp;
-                const u64 cc = chat[(size_t)i * chat_stride + pi[t]];
+                for (int k = 0; k < 16; k++) x[k] = FpAr::reduce(FpAr::from_raw(y[k]), m);
+            } else {
+                // a 61-bit word is first brought below the target, which leaves it at most 0.6 q + 2^30
 #pragma unroll
                 for (int k = 0; k < 16; k++) {
-                    const u64 y = conv_src_int<DG>(si[(size_t)(k * C::RB + r0) * 256 + col], src_fp);
-                    mac128(acc[k], y, cc);
-                }
-                if (ns > 8 && ((i & 7) == 7 || i + 1 == ns)) {
-#pragma unroll
-                    for (int k = 0; k < 16; k++) acc[k].hi = csub(acc[k].hi, pc.q);
+                    if (TB > 1) asm volatile("" : "+v"(y[k]));  // split here, not once for all targets (64 registers)
+                    x[k] = FpAr::reduce(FpAr::reduce_split((double)(u32)(y[k] >> 30) * 1073741824.0, (double)(u32)(y[k] & 0x3fffffffu), m), m);
                 }
             }
+        } else if (src_fp) {  // every FpAr prime is below every IntAr prime: the source is canonical already
 #pragma unroll
-            for (int tt = 0; tt < TB; tt++)
-                if (tt == t) {
+            for (int k = 0; k < 16; k++) x[k] = y[k];
+        } else {
 #pragma unroll
-                    for (int k = 0; k < 16; k++) x[tt][k] = AR::from_canon(redc(acc[k], pc.q, pc.qneg), m);
-                }
+            for (int k = 0; k < 16; k++) {
+                u128w p = {0, 0};
+                mac128(p, y[k], pc.r1);
+                x[k] = redc(p, pc.q, pc.qneg);
+            }
         }
-    }
+        strided_stages_lo<AR, A>(x, tw, m);
+        if constexpr (A > 4) {
+            const Buf dst(dst0 + (size_t)vi * N);
+            if (again) __syncthreads();  // the previous target's exchange has been read
+            again = true;
 #pragma unroll
-    for (int t = 0; t < TB; t++) {
-        if (t) __syncthreads();  // the previous target's exchange must have been read
-        if (valid[t]) fwd_strided_finish<AR, A>(x[t], tb, lds, pi[t], dst0 + (size_t)pi[t] * N, tile);
-        else if (A > 4) __syncthreads();  // keep barrier counts equal (fwd_strided holds one barrier)
+            for (int k = 0; k < 16; k++) lds[k * 256 + tid] = AR::to_raw(AR::round_reduce(x[k], m));
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lds[(r0 * 16 + k) * C::TC + c]);
+            strided_stages_hi<AR, A>(x, tw, r0, m);
+#pragma unroll
+            for (int k = 0; k < 16; k++) dst.st_nt(AR::to_raw(AR::round_reduce(x[k], m)), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
+        } else {
+            u64* dst = dst0 + (size_t)vi * N;
+#pragma unroll
+            for (int k = 0; k < 16; k++) dst[(size_t)(k * C::RB + r0) * 256 + col] = AR::to_raw(AR::round_reduce(x[k], m));
+        }
     }
 }
 
-
-// ===================== base conversion on the matrix cores, fused into the first forward pass of FpAr targets
+// ---- several sources, on the matrix cores.
 // out_t = sum_i y_i * chat_{i,t} mod m_t as an 8-bit integer matrix product.  Every source word arrives as eight
 // signed base-256 digits (SRC_DIGITS), y_i = sum_b d_{i,b} 256^b; the digit weight is folded into the constant,
-// C_{(i,b),t} = centred (chat_{i,t} * 256^b mod m_t), itself cut into seven signed digits C = sum_g c_g 256^g.  Then
-//   S_{t,g}[n] = sum_{(i,b)} c_g(C_{(i,b),t}) * d_{i,b}(y_i[n])          (v_mfma_i32_32x32x32_i8, |S| < 2^21)
-//   out_t[n]  == sum_g 256^g S_{t,g}[n]  (mod m_t),
-// recombined exactly in FP64 (conv_recombine).  One 32x32x32 product handles 32 coefficients (columns) and 32
-// rows = up to 4 targets x 8 digit rows, over 32 values of (i,b) = four sources (lane half h holds the digit words
-// of sources 4*ks + 2*h and 4*ks + 2*h + 1 in its 16 operand bytes, the constant operand the matching bytes);
-// ceil(ns/4) products accumulate all sources.  Row m of the constant tile sits in accumulator a = (m/8)*4 + m%4 of lane half (m/4)%2, so a lane
-// holds all digits of its targets: target slot tl = h * ntt + a/8, digit a%8 (ntt = targets per lane, 1 or 2).
+// C_{(i,b),t} = centred (chat_{i,t} * 256^b mod m_t), itself cut into signed digits C = sum_g c_g 256^g (seven for FpAr
+// targets, eight for IntAr ones).  Then
+//   S_{t,g}[n] = sum_{(i,b)} c_g(C_{(i,b),t}) * d_{i,b}(y_i[n])          (v_mfma_i32_32x32x32_i8, |S| <= 17 * 2^17)
+//   out_t[n]  == V = sum_g 256^g S_{t,g}[n]  (mod m_t),  |V| <= 2^14 m_t
+// recombined exactly (conv_recombine).  One 32x32x32 product handles 32 coefficients (columns) and 32 rows = four
+// targets x 8 digits, over 32 values of (i,b) = four sources (lane half h holds the digit words of sources 4*ks + 2*h and
+// 4*ks + 2*h + 1 in its 16 operand bytes, the constant operand the matching bytes); KS = ceil(ns/4) products accumulate
+// all sources.  Row m of the constant operand sits in accumulator a = (m/8)*4 + m%4 of lane half (m/4)%2: a lane of half h
+// gets the digits of target slot h in accumulators 0..7 and of slot 2 + h in accumulators 8..15.
 //
-// A lane converts, for s = 0, 1 and every k < 16, coefficient (row k*RB + r0, column c) of the tile, with
-// (r0, c) from pp = wave*64 + s*32 + lane%32 exactly as tid maps to (r0, c) in layout SA: the 16 values k of one
-// (s, target) are the inputs of the first four forward stages, which therefore run in the lane that converted
-// them; the exchange for the remaining stages goes through LDS target by target.
+// A lane keeps 2 x 16 converted words, x[u][k], k the coefficient's row block: rows k*RB + r0 of column c, the inputs of
+// the first four forward stages, which therefore run in the lane that converted them; (r0, c) from a position pp of the
+// tile as tid maps to (r0, c) in layout SA.
+//   NTT = 2: four targets per workgroup of 512 lanes; u = target slot 2*u + h, pp = wave*32 + lane%32
+//   NTT = 1: two targets per workgroup of 256 lanes; slot h, u = half of the positions, pp = wave*64 + u*32 + lane%32
+// What bounds it: the source words come from L2, and that traffic (7.3 TB/s with NTT = 1 at batch 8, N = 2^16, six sources;
+// all loads from one cached row: 121 -> 78 us per launch) is the limit rather than the arithmetic, so four targets share a
+// load where the registers allow it: FpAr targets need 128 (four waves per SIMD): 121 -> 111 us ModUp, 84 -> 71 us
+// ModDown.  IntAr targets do not fit 128 (spills, 61 -> 66 us) and take NTT = 1.
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef int v4i __attribute__((ext_vector_type(4)));
-struct ConvTile {
-    u32 target[4];  // limb index of target slot tl within the destination group; 0xffffffff = unused slot
-    u32 ntt;        // targets per lane half (1 or 2); 0 = unused tile
-    u32 pad[3];
-};
-struct MfmaConvArgs {
-    const u64* src;         // SRC_DIGITS words: CONV_UP [b][L][N], CONV_DN [g][K][N]
-    u64* dst;               // raw forward-lazy words after the first pass: CONV_UP dt [b][dnum][D][N], CONV_DN cv [g][L][N]
-    const ConvTile* tiles;  // [digits][n_tiles]
-    const u64* aop;         // [digits][n_tiles][KS][64][2] constant operands, one 16-byte row fragment per lane
-    u32 groups_outer;       // CONV_UP: batch; CONV_DN: number of g
-    u32 n_tiles;            // tiles launched per digit
-    u32 tile_stride;        // tiles stored per digit
-};
-
-// sum_g 256^g S_g reduced to |.| <= (0.5 + 2^-15) m, exactly: lo = digits 0..3 (below 2^46), hi = digits 4..6 times
-// 2^32 (an integer multiple of 2^32 with 38 significant bits: exact); the quotient estimate of (hi + lo) / m is off
-// by less than 2^-15 before rounding, hi - c*m is an integer below 2^53 in magnitude, so the fma and the sum are exact.
-// (Summing the digits with 64-bit integer multiply-adds onto the bit pattern of a double, which avoids the
-// i32 -> f64 conversions, was measured 5 % slower on the kernel.)
-__device__ __forceinline__ double conv_recombine(const v16i& s, int b, const FpAr::Mod& m) {
-    const double lo = __builtin_fma((double)s[b + 3], 16777216.0,
-                                    __builtin_fma((double)s[b + 2], 65536.0, __builtin_fma((double)s[b + 1], 256.0, (double)s[b])));
-    const double hi = __builtin_fma((double)s[b + 6], 281474976710656.0,
-                                    __builtin_fma((double)s[b + 5], 1099511627776.0, (double)s[b + 4] * 4294967296.0));
+// V of an FpAr target reduced to |.| <= (0.5 + 2^-15) m, exactly: pairs of digits are joined as 32-bit integers (below
+// 2^30), lo = digits 0..3 (below 2^47), hi = digits 4..6 times 2^32 (an integer multiple of 2^32 with 38 significant
+// bits: exact); the quotient estimate of (hi + lo) / m is off by less than 2^-15 before rounding, hi - c*m is an integer
+// below 2^53 in magnitude, so the fma and the sum are exact.
+__device__ __forceinline__ double conv_recombine(const v16i& s, int o, const FpAr::Mod& m, const PrimeConst&) {
+    const int p0 = s[o + 0] + s[o + 1] * 256, p1 = s[o + 2] + s[o + 3] * 256, p2 = s[o + 4] + s[o + 5] * 256;
+    const double lo = __builtin_fma((double)p1, 65536.0, (double)p0);
+    const double hi = __builtin_fma((double)s[o + 6], 281474976710656.0, (double)p2 * 4294967296.0);
     const double c = __builtin_rint((hi + lo) * m.qinv);
     return __builtin_fma(-c, m.q, hi) + lo;
 }
+// V of an IntAr target (m >= 3*2^48) as a word in (0.4 m, 1.6 m): V = lo + 2^32 t with |lo| < 2^47, t = digits 4..7 exact
+// in a double (below 2^47); z = 1 - rint(t * 2^32 / m) appears as the low bits of one fma onto 1.5*2^52, |lo| / m < 0.09
+// is what the estimate leaves out, and V + z*m is formed modulo 2^64 with m = mh * 2^32 + (signed low half).  14
+// instructions, where six 128-bit multiply-accumulates and a Montgomery reduction took 62.
+__device__ __forceinline__ u64 conv_recombine(const v16i& s, int o, const IntAr::Mod& m, const PrimeConst& pc) {
+    const int p0 = s[o + 0] + s[o + 1] * 256, p1 = s[o + 2] + s[o + 3] * 256, p2 = s[o + 4] + s[o + 5] * 256, p3 = s[o + 6] + s[o + 7] * 256;
+    const double t = __builtin_fma((double)p3, 65536.0, (double)p2);
+    const int z = (int)(u32)__builtin_bit_cast(u64, __builtin_fma(t, pc.qinv * -4294967296.0, 6755399441055744.0 + 1.0));
+    const int ml = (int)(u32)m.q;
+    const u32 mh = (u32)(m.q >> 32) + (ml < 0 ? 1u : 0u);
+    const u64 lo = (u64)((int64_t)p1 * 65536 + p0 + (int64_t)z * ml);
+    return lo + ((u64)((u32)p2 + ((u32)p3 << 16) + (u32)z * mh) << 32);
+}
 
-template <int A, int KS, int DIR, int NTT>
-__global__ __launch_bounds__(256, NTT == 1 ? 3 : 2) void conv_mfma_kernel(MfmaConvArgs a, Tables tb) {
-    __shared__ u64 lds[4096];
-    typedef NttCore<FpAr, A> C;
-    constexpr u32 TILES = (1u << A) / 16;
+template <class AR, int A, int KS, int DIR, int NTT>
+__device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& tb, const LimbRun run) {
+    typedef NttCore<AR, A> C;
+    typedef StridedTw<AR, A> TW;
+    typedef typename AR::T T;
+    constexpr u32 TILES = (1u << A) / 16, TPW = 2 * NTT;  // targets per workgroup
+    __shared__ u64 lds[A > 4 ? NTT * 4096 : 1];
+    __shared__ __align__(16) u64 tws[TPW * TW::WORDS];
     const u32 N = 1u << tb.logN, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, h = lane >> 5;
     const u32 n_dig = DIR == CONV_UP ? tb.dnum : 1;
     u32 group, inst;
-    if (!xcd_decode(blockIdx.x, a.n_tiles, a.groups_outer * n_dig * TILES, group, inst)) return;
+    if (!xcd_decode(blockIdx.x, a.blocks, a.groups_outer * n_dig * TILES, group, inst)) return;
     const u32 tile = group % TILES;
-    u32 j = 0, ns;
+    u32 j = 0, ns, skip_lo = 0, skip_n = 0;
     const u64* src;
     u64* dst0;
     if (DIR == CONV_UP) {
         const u32 bj = group / TILES, b = bj / tb.dnum;
         j = bj % tb.dnum;
+        // the last digit of a level may hold fewer than alpha limbs
         const u32 own_lo = j * tb.alpha, own_hi = (j + 1) * tb.alpha < tb.L ? (j + 1) * tb.alpha : tb.L;
         ns = own_hi - own_lo;
         src = a.src + ((size_t)b * tb.L + own_lo) * N;
         dst0 = a.dst + ((size_t)b * tb.dnum + j) * tb.D * N;
+        // the digit's own limbs that lie in the run are no targets
+        skip_lo = own_lo > run.first ? own_lo : run.first;
+        const u32 hi = own_hi < run.first + run.count ? own_hi : run.first + run.count;
+        skip_n = hi > skip_lo ? hi - skip_lo : 0;
     } else {
         const u32 g = group / TILES;
         ns = tb.K;
         src = a.src + (size_t)g * tb.K * N;
         dst0 = a.dst + (size_t)g * tb.L * N;
     }
-    const ConvTile ct = a.tiles[j * a.tile_stride + inst];
-    if (ct.ntt == 0) return;  // digits with fewer targets leave their last tiles unused (uniform per workgroup)
-    auto slot_target = [&](u32 tl) { return tl == 0 ? ct.target[0] : tl == 1 ? ct.target[1] : tl == 2 ? ct.target[2] : ct.target[3]; };
+    const u32 left = run.count - skip_n;
+    if (inst * TPW >= left) return;  // digits with fewer targets leave their last blocks unused (uniform per workgroup)
+    const u32 nt = left - inst * TPW < TPW ? left - inst * TPW : TPW;
+    // limb of target slot sl (slots from nt on repeat the first: converted, never stored)
+    auto limb_of = [&](u32 sl) {
+        const u32 t = run.first + inst * TPW + (sl < nt ? sl : 0);
+        return skip_n && t >= skip_lo ? t + skip_n : t;
+    };
     v4i aop[KS];
     {
-        const v4i* ap = reinterpret_cast<const v4i*>(a.aop) + (size_t)(j * a.tile_stride + inst) * KS * 64 + lane;
+        const u32 sl = (NTT == 2 ? (n >> 4) * 2 : 0) + ((n >> 2) & 1), dg = ((n >> 3) & 1) * 4 + (n & 3), t = limb_of(sl);
+        const u64* base = j < a.n_full ? a.aop + ((size_t)j * (tb.Lfull + tb.Kfull) + tb.phys(t)) * KS * 32 : a.aop_part + (size_t)t * KS * 32;
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) aop[ks] = ap[ks * 64];
-    }
-    // this lane's targets: slots h * ntt + tt
-    u32 vi[NTT];
-    FpAr::Mod fm[NTT];
-#pragma unroll
-    for (int tt = 0; tt < NTT; tt++) {
-        vi[tt] = (u32)tt < ct.ntt ? slot_target(h * ct.ntt + tt) : 0xffffffffu;
-        fm[tt] = FpAr::mod(tb.pc[tb.phys(vi[tt] != 0xffffffffu ? vi[tt] : 0)]);
-    }
-    double x[2][NTT][16];
-    // 32 coefficient groups g = s*16 + k per lane.  The source words of group g + PF are requested before the products
-    // of group g are issued; scheduling barriers keep the compiler from hoisting every load of the unrolled loop
-    // (which would spill).
-    constexpr int PF = 2;  // deeper prefetch (4, 6, 8 groups) changes nothing: the words come from L2
-    // this lane half supplies the digits of sources 4*ks + 2*h and the next one; beyond the last source any valid word
-    // will do (the constant rows of those sources are zero)
-    const u64* sp[2 * KS];
-#pragma unroll
-    for (int q = 0; q < 2 * KS; q++) {
-        const u32 i = 4 * (q >> 1) + 2 * h + (q & 1);
-        sp[q] = src + (size_t)(i < ns ? i : ns - 1) * N + tile * C::TC;
-    }
-    auto src_off = [&](int g) {
-        const u32 pp = wave * 64 + (g >> 4) * 32 + n;
-        return (u32)(((g & 15) * C::RB + pp / C::TC) * 256 + pp % C::TC);
-    };
-    u64 bw[PF + 1][2 * KS];
-#pragma unroll
-    for (int g = 0; g < PF; g++) {
-#pragma unroll
-        for (int q = 0; q < 2 * KS; q++) bw[g][q] = sp[q][src_off(g)];
+        for (int ks = 0; ks < KS; ks++) aop[ks] = *reinterpret_cast<const v4i*>(base + ks * 32 + h * 16 + dg * 2);
     }
 #pragma unroll
-    for (int g = 0; g < 32; g++) {
-        if (g + PF < 32) {
+    for (u32 tt = 0; tt < 2; tt++) {
+        const u32 sl = NTT == 2 ? 2 * tt + (tid >> 8) : tt;  // 256 lanes fill one slot's twiddles
+        if (sl < nt) TW::fill(tws + sl * TW::WORDS, tid & 255, tb, tb.phys(limb_of(sl)));
+    }
+    T x[2][16];
+    {
+        const PrimeConst pc0 = tb.pc[tb.phys(limb_of(h))], pc1 = tb.pc[tb.phys(limb_of(NTT == 2 ? 2 + h : h))];
+        const typename AR::Mod m0 = AR::mod(pc0), m1 = AR::mod(pc1);
+        // this lane half supplies the digits of sources 4*ks + 2*h and the next one; beyond the last source any valid
+        // word will do (the constant rows of those sources are zero)
+        const Buf sb(src);
+        u32 so[2 * KS];
+        const u32 pp0 = wave * (NTT == 2 ? 32 : 64) + n;
 #pragma unroll
-            for (int q = 0; q < 2 * KS; q++) bw[(g + PF) % (PF + 1)][q] = sp[q][src_off(g + PF)];
+        for (int q = 0; q < 2 * KS; q++) {
+            const u32 i = 4 * (q >> 1) + 2 * h + (q & 1);
+            so[q] = 8 * ((i < ns ? i : ns - 1) * N + tile * C::TC + (pp0 / C::TC) * 256 + pp0 % C::TC);
         }
-        v16i acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        // NTT = 1: the second half of the positions is 32 on: 32 / TC rows down, or 32 columns on where a row holds more
+        constexpr u32 SET = C::TC >= 64 ? 32 : (32 / C::TC) * 256, GROUPS = NTT == 2 ? 16 : 32, GB = NTT == 1 && KS <= 2 ? 2 : 1;
+        auto src_off = [&](int g) { return 8 * ((u32)((g & 15) * C::RB * 256) + (u32)(g >> 4) * SET); };
+        // GB coefficient groups at a time; the source words of the next ones are requested before the products of these
+        // are issued; scheduling barriers keep the compiler from hoisting every load of the unrolled loop (which would spill)
+        u64 bw[2][GB][2 * KS];
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-            const u64 w0 = bw[g % (PF + 1)][2 * ks], w1 = bw[g % (PF + 1)][2 * ks + 1];
-            const v4i bop = {(int)(u32)w0, (int)(u32)(w0 >> 32), (int)(u32)w1, (int)(u32)(w1 >> 32)};
-            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(aop[ks], bop, acc, 0, 0, 0);
+        for (u32 b = 0; b < GB; b++)
+#pragma unroll
+            for (int q = 0; q < 2 * KS; q++) bw[0][b][q] = sb.ld(so[q], src_off(b));
+#pragma unroll
+        for (u32 g = 0; g < GROUPS; g += GB) {
+            const u32 cur = (g / GB) & 1;
+            if (g + GB < GROUPS) {
+#pragma unroll
+                for (u32 b = 0; b < GB; b++)
+#pragma unroll
+                    for (int q = 0; q < 2 * KS; q++) bw[cur ^ 1][b][q] = sb.ld(so[q], src_off(g + GB + b));
+            }
+            v16i acc[GB];
+#pragma unroll
+            for (u32 b = 0; b < GB; b++) {
+                acc[b] = v16i{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                for (int ks = 0; ks < KS; ks++) {
+                    const u64 w0 = bw[cur][b][2 * ks], w1 = bw[cur][b][2 * ks + 1];
+                    const v4i bop = {(int)(u32)w0, (int)(u32)(w0 >> 32), (int)(u32)w1, (int)(u32)(w1 >> 32)};
+                    acc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(aop[ks], bop, acc[b], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (u32 b = 0; b < GB; b++) {
+                const u32 k = (g + b) & 15;
+                // the empty statements keep a recombination here: sunk to a conditional use it would keep the sums alive
+                if constexpr (NTT == 2) {
+                    x[0][k] = conv_recombine(acc[b], 0, m0, pc0);
+                    x[1][k] = conv_recombine(acc[b], 8, m1, pc1);
+                    asm volatile("" : "+v"(x[0][k]), "+v"(x[1][k]));
+                } else {
+                    x[(g + b) >> 4][k] = conv_recombine(acc[b], 0, m0, pc0);
+                    asm volatile("" : "+v"(x[(g + b) >> 4][k]));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int tt = 0; tt < NTT; tt++) x[g >> 4][tt][g & 15] = conv_recombine(acc, tt * 8, fm[tt]);
-        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();  // the twiddles are in LDS
+        // first four forward stages, in place (FP64: |x| <= 0.51 q on entry, below 7 q after)
+        strided_stages_lo<AR, A>(x[0], tws + h * TW::WORDS, m0);
+        if (NTT == 1) strided_stages_lo<AR, A>(x[1], tws + h * TW::WORDS, m0);
+        else if (nt > 2) strided_stages_lo<AR, A>(x[1], tws + (2 + h) * TW::WORDS, m1);
     }
-    // first four forward stages of every (s, target) set, in place (|x| <= 0.51 q on entry, below 7 q after)
 #pragma unroll
-    for (int tt = 0; tt < NTT; tt++) {
-        if (vi[tt] == 0xffffffffu) continue;
-        const double* tf = tb.tw_fp + (size_t)tb.phys(vi[tt]) * 2 * N;
+    for (u32 u = 0; u < 2; u++) {  // NTT = 2: slots 2u and 2u + 1; NTT = 1: slot u
+        if ((NTT == 2 ? 2 * u : A > 4 ? u : 0) >= nt) break;
+        if constexpr (A > 4) {
+            if (u) __syncthreads();  // the first exchange has been read
+            const typename AR::Mod mx = AR::mod(tb.pc[tb.phys(limb_of(NTT == 2 ? 2 * u + h : h))]);
+            if (NTT == 2) {
 #pragma unroll
-        for (int st = 0; st < 4; st++) {
-            const int d = 8 >> st;
+                for (int k = 0; k < 16; k++) lds[h * 4096 + k * 256 + wave * 32 + n] = AR::to_raw(AR::round_reduce(x[u][k], mx));
+            } else if (h == u) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) {
-                if (k & d) continue;
-                const FpAr::Tw w = FpAr::tw(nullptr, tf, (1u << st) + (k >> (4 - st)), N, false);
+                for (u32 v = 0; v < 2; v++)
 #pragma unroll
-                for (int s = 0; s < 2; s++) FpAr::bfly_fwd<false>(x[s][tt][k], x[s][tt][k + d], w, fm[tt]);
+                    for (int k = 0; k < 16; k++) lds[k * 256 + wave * 64 + v * 32 + n] = AR::to_raw(AR::round_reduce(x[v][k], mx));
+            }
+            __syncthreads();
+            const u32 half = tid >> 8, sl = NTT == 2 ? 2 * u + half : u, st = tid & 255, c = st % C::TC, r1 = st / C::TC;
+            if (sl < nt) {  // uniform per wave
+                const u32 t = limb_of(sl);
+                const typename AR::Mod m = AR::mod(tb.pc[tb.phys(t)]);
+                T y[16];
+#pragma unroll
+                for (int k = 0; k < 16; k++) y[k] = AR::from_raw(lds[half * 4096 + (r1 * 16 + k) * C::TC + c]);
+                strided_stages_hi<AR, A>(y, tws + sl * TW::WORDS, r1, m);
+                u64* dst = dst0 + (size_t)t * N + (size_t)r1 * 16 * 256 + tile * C::TC + c;
+#pragma unroll
+                for (int k = 0; k < 16; k++) __builtin_nontemporal_store(AR::to_raw(AR::round_reduce(y[k], m)), &dst[k * 256]);
+            }
+        } else {
+            const u32 sl = NTT == 2 ? 2 * u + h : h, pp = NTT == 2 ? wave * 32 + n : wave * 64 + u * 32 + n;
+            if (sl < nt) {
+                const u32 t = limb_of(sl);
+                const typename AR::Mod m = AR::mod(tb.pc[tb.phys(t)]);
+                u64* dst = dst0 + (size_t)t * N + (pp / C::TC) * 256 + tile * C::TC + pp % C::TC;
+#pragma unroll
+                for (int k = 0; k < 16; k++) dst[k * C::RB * 256] = AR::to_raw(AR::round_reduce(x[u][k], m));
             }
         }
     }
-    // remaining stages and store, one target at a time
-#pragma unroll
-    for (int tt = 0; tt < NTT; tt++) {
-#pragma unroll
-        for (int hh = 0; hh < 2; hh++) {
-            if ((u32)tt >= ct.ntt) continue;
-            const u32 t_vi = slot_target(hh * ct.ntt + tt);  // uniform over the workgroup
-            if (t_vi == 0xffffffffu) continue;
-            const u32 pi = tb.phys(t_vi);
-            const FpAr::Mod m = FpAr::mod(tb.pc[pi]);
-            u64* dst = dst0 + (size_t)t_vi * N;
-            if constexpr (A > 4) {
-                __syncthreads();  // the previous target's exchange has been read
-                if (h == (u32)hh) {
-#pragma unroll
-                    for (int s = 0; s < 2; s++) {
-                        const u32 pp = wave * 64 + s * 32 + n;
-#pragma unroll
-                        for (int k = 0; k < 16; k++) lds[k * 256 + pp] = FpAr::to_raw(FpAr::reduce(x[s][tt][k], m));
-                    }
-                }
-                __syncthreads();
-                const double* tf = tb.tw_fp + (size_t)pi * 2 * N;
-                const u32 c = tid % C::TC, r1 = tid / C::TC, col = tile * C::TC + c;
-                double y[16];
-#pragma unroll
-                for (int k = 0; k < 16; k++) y[k] = FpAr::from_raw(lds[(r1 * 16 + k) * C::TC + c]);
-#pragma unroll
-                for (int st = 4; st < A; st++) {
-                    const int d = 1 << (A - st - 1);
-#pragma unroll
-                    for (int k = 0; k < 16; k++) {
-                        if (k & d) continue;
-                        FpAr::bfly_fwd<false>(y[k], y[k + d], FpAr::tw(nullptr, tf, (1u << st) + ((r1 * 16 + k) >> (A - st)), N, false), m);
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < 16; k++)
-                    __builtin_nontemporal_store(FpAr::to_raw(FpAr::reduce(y[k], m)), &dst[(size_t)(r1 * 16 + k) * 256 + col]);
-            } else {
-                if (h == (u32)hh) {
-#pragma unroll
-                    for (int s = 0; s < 2; s++) {
-                        const u32 pp = wave * 64 + s * 32 + n, c = pp % C::TC, r0 = pp / C::TC, col = tile * C::TC + c;
-#pragma unroll
-                        for (int k = 0; k < 16; k++)
-                            dst[(size_t)(k * C::RB + r0) * 256 + col] = FpAr::to_raw(FpAr::reduce(x[s][tt][k], m));
-                    }
-                }
-            }
-        }
-    }
+}
+
+// targets per lane of the matrix-core form
+template <class AR>
+constexpr int conv_mfma_ntt() { return AR::is_fp ? 2 : 1; }
+// ONE: a single source, P targets per workgroup.  Else the matrix-core form, P = products per coefficient group + targets
+// per lane.
+template <class AR, int A, int DIR, int P, bool ONE>
+__global__ __launch_bounds__(ONE ? 256 : 256 * conv_mfma_ntt<AR>(), ONE ? (AR::is_fp ? 4 : 3) : !AR::is_fp ? 3 : P <= 4 ? 4 : 2)
+void conv_fwd_strided_kernel(ConvArgs a, Tables tb, LimbRun run) {
+    if constexpr (ONE) conv_one_body<AR, A, DIR, P>(a, tb, run);
+    else conv_mfma_body<AR, A, P - conv_mfma_ntt<AR>(), DIR, conv_mfma_ntt<AR>()>(a, tb, run);
+}
+// ModDown onto FpAr targets, KS products per coefficient group, NTT targets per lane
+template <int A, int KS, int DIR, int NTT>
+__global__ __launch_bounds__(256 * NTT, KS <= 2 ? 4 : 2) void conv_mfma_kernel(ConvArgs a, Tables tb, LimbRun run) {
+    conv_mfma_body<FpAr, A, KS, DIR, NTT>(a, tb, run);
 }
 
 // =========================================================== forward transform, second pass
