@@ -976,29 +976,19 @@ static void launch_ks_inner(const View* c, const InnerArgs& a, hipStream_t s) {
     launch_ks_inner<OWN, HOISTED, false>(c, a, s, 0, c->D);
 }
 
-#define CKKS_DH_EPT 4
-struct DhAccumL {
-    template <class AR, int A>
-    static void go(dim3 g, hipStream_t s, const DhInnerArgs& a, const Tables& tb, LimbRun run) {
-        hipLaunchKernelGGL((dh_accum_kernel<AR, CKKS_DH_EPT>), g, dim3(256), 0, s, a, tb, run);
-    }
-    static std::string name(const char* ar, int) {
-        return std::string("dh_accum_kernel<") + ar + ", " + std::to_string(CKKS_DH_EPT) + ">";
-    }
-};
-
+#define CKKS_BSGS_EPT 4
 struct BsgsMacL {
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const BsgsMacArgs& a, const Tables& tb, LimbRun run) {
-        hipLaunchKernelGGL((bsgs_mac_kernel<AR, CKKS_DH_EPT>), g, dim3(256), 0, s, a, tb, run);
+        hipLaunchKernelGGL((bsgs_mac_kernel<AR, CKKS_BSGS_EPT>), g, dim3(256), 0, s, a, tb, run);
     }
     static std::string name(const char* ar, int) {
-        return std::string("bsgs_mac_kernel<") + ar + ", " + std::to_string(CKKS_DH_EPT) + ">";
+        return std::string("bsgs_mac_kernel<") + ar + ", " + std::to_string(CKKS_BSGS_EPT) + ">";
     }
 };
 
 static void launch_bsgs_mac(const View* c, const BsgsMacArgs& a, hipStream_t s) {
-    const u32 chunks = (1u << c->logN) / (256 * CKKS_DH_EPT);
+    const u32 chunks = (1u << c->logN) / (256 * CKKS_BSGS_EPT);
     for (const ClassRun& cr : class_runs(c, 0, c->D)) {
         const LimbRun run = {cr.first, cr.count};
         hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
@@ -1009,18 +999,17 @@ static void launch_bsgs_mac(const View* c, const BsgsMacArgs& a, hipStream_t s) 
     }
 }
 
-// one workgroup per 256 * CKKS_DH_EPT slots of a limb, all limbs of the extended basis
-static void launch_dh_accum(const View* c, const DhInnerArgs& a, hipStream_t s) {
+// all limbs of the extended basis in one launch; the caller has joined the side stream
+static void launch_dh_accum(const View* c, DhInnerArgs a, hipStream_t s) {
     const u64 n_rot = a.n_rot, acc = a.accumulate ? 2 : 0, dnum = c->dnum;
-    const u32 chunks = (1u << c->logN) / (256 * CKKS_DH_EPT);
-    for (const ClassRun& cr : class_runs(c, 0, c->D)) {
-        const LimbRun run = {cr.first, cr.count};
-        u64 limbs = 0;  // per limb and rotation: the digits, the plaintext, both key components (and b on q-limbs); C_t written
-        for (u32 i = cr.first; i < cr.first + cr.count; i++) limbs += n_rot * (3 * dnum + 1 + (i < c->L ? 1 : 0)) + 2 + acc;
-        hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
-        ProfScope ps(c, c->sh->prof.on ? DhAccumL::name(cr.fp ? "FpAr" : "IntAr", 0) : std::string(), limbs, rs);
-        dispatch_kernel<DhAccumL>(c, cr.fp, dim3(cr.count * chunks), rs, a, run);
-    }
+    // One row per workgroup, its rotations shared by the four wavefronts, or four rows: with fewer than eight rotations the
+    // wavefronts would end up with unequal shares, which only a grid below two workgroups per compute unit makes up for
+    const u32 rows = c->D << (c->logN - 8);
+    a.waves = n_rot >= 8 || (rows / 4 < 512 && n_rot > 1) ? 4 : 1;
+    u64 limbs = 0;  // per limb and rotation: the digits, the plaintext, both key components (and b on q-limbs); C_t written
+    for (u32 i = 0; i < c->D; i++) limbs += n_rot * (3 * dnum + (a.pt ? 1 : 0) + (i < c->L ? 1 : 0)) + (a.each ? 2 * n_rot : 2) + acc;
+    ProfScope ps(c, std::string("dh_accum_kernel"), limbs, s);
+    hipLaunchKernelGGL(dh_accum_kernel, dim3((rows * a.waves / 4 + 7) / 8 * 8), dim3(256), 0, s, a, c->tb);
 }
 
 template <int MODE>
@@ -1695,7 +1684,7 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
         FwdContigArgs p = {w.dt, LimbSel{c->K, c->dnum, c->D, c->L, c->L, 0}};
         launch_fwd_contig(c, p, s);
     }
-    // the special-limb chain (still on the side stream when overlap is on) only reads its own limbs
+    join_side(c, s);  // the accumulation reads the digits of every limb
     for (u32 r0 = 0; r0 < n_rot; r0 += CKKS_DH_CHUNK) {
         const u32 nr = (n_rot - r0) < CKKS_DH_CHUNK ? (n_rot - r0) : CKKS_DH_CHUNK;
         DhInnerArgs ia;
@@ -1812,12 +1801,14 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         launch_fwd_contig(c, p, s);
     }
     // baby steps: R_b = P * Rot_b(ct) in the extended basis (inner product with the key, plus P * sigma_b(b))
-    for (u32 b = 0; b < n1; b++) {
+    join_side(c, s);
+    for (u32 b0 = 0; b0 < n1; b0 += CKKS_DH_CHUNK) {
+        const u32 nb = (n1 - b0) < CKKS_DH_CHUNK ? (n1 - b0) : CKKS_DH_CHUNK;
         DhInnerArgs ia;
         memset(&ia, 0, sizeof(ia));
-        ia.key[0] = h_baby_rk_ptrs[b], ia.galois[0] = h_baby_galois[b];
-        ia.dt = w.dt, ia.ct = d_ct, ia.pt = nullptr, ia.cq = rq + (size_t)b * 2 * LN, ia.cp = rp + (size_t)b * 2 * KN;
-        ia.n_rot = 1, ia.accumulate = 0, ia.split = c->L;
+        for (u32 b = 0; b < nb; b++) ia.key[b] = h_baby_rk_ptrs[b0 + b], ia.galois[b] = h_baby_galois[b0 + b];
+        ia.dt = w.dt, ia.ct = d_ct, ia.pt = nullptr, ia.cq = rq + (size_t)b0 * 2 * LN, ia.cp = rp + (size_t)b0 * 2 * KN;
+        ia.n_rot = nb, ia.each = 1, ia.accumulate = 0, ia.split = c->L;
         launch_dh_accum(c, ia, s);
     }
     // giant-step combinations in the extended basis, then one ModDown per giant step (as a batch)

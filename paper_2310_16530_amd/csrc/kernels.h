@@ -1004,11 +1004,21 @@ __global__ __launch_bounds__(256, 2) void ks_inner_kernel(InnerArgs a, Tables tb
 
 // ===================================================== double-hoisted rotate-multiply-accumulate
 // Over the rotations r of the launch and the digits j, on every limb i of the extended basis:
-//   C_t[i] += (pt_r[i] * sigma_{g_r}(Dh_j)[i]) * rk_r[j][t][i],   t = 0, 1,
-// with Dh_j read by gather from the transformed digits (the polynomial's own limb on the digit that
-// owns limb i).  On q-limbs the term pt_r * sigma_{g_r}(b) * P is added to C_0: ModDown divides it by
-// P exactly, which gives the same words as adding pt_r * sigma_{g_r}(b) after ModDown.
-// C_t is stored canonical, evaluation form: q-limbs in cq, special limbs in cp (ModDown follows).
+//   C_t[i] += pt_r[i] * (sum_j sigma_{g_r}(Dh_j)[i] * rk_r[j][t][i]),   t = 0, 1,
+// with Dh_j the transformed digits (the polynomial's own limb on the digit that owns limb i).  On q-limbs sigma_{g_r}(b) * P
+// joins the sum of t = 0: ModDown divides it by P exactly, which gives the same words as adding pt_r * sigma_{g_r}(b) after
+// ModDown.  C_t is stored canonical, evaluation form: q-limbs in cq, special limbs in cp (ModDown follows).
+//
+// No transform is involved; keys and plaintexts stream from HBM once and bound the kernel.  What it spent besides: a
+// 64-lane gather per digit word (64 cache lines an instruction), digits re-read through the fabric for every rotation, and
+// on IntAr limbs two reduced products per digit.  Hence a wavefront owns one 256-word row (lane l: words 2l, 2l+1, 128+2l,
+// 128+2l+1), loads the source row whole with 16-byte accesses and permutes it in LDS (sigma_g maps rows onto rows, see
+// gather_row_cp); the sum over the digits stays unreduced and meets the plaintext once per rotation; the words of the next
+// term are requested before this one is worked on; each XCD takes a contiguous range of rows, limb after limb, and the
+// four wavefronts of a workgroup share a row (each takes every fourth rotation), so that one limb at a time is in flight
+// per XCD and its digits stay in the L2; and both arithmetics share one launch.  32 rotations at N = 2^16, L + K = 42,
+// dnum = 5 (7.8 GB of keys and plaintexts): 1673 us in two launches -> 1414 us, 5.5 TB/s; without the shared rows 1623 us,
+// without the early requests 1730 us, with the digit reads removed 1386 us.
 #define CKKS_DH_CHUNK 32
 struct DhInnerArgs {
     const u64* dt;   // [dnum][D][N] canonical evaluation form
@@ -1021,81 +1031,161 @@ struct DhInnerArgs {
     u32 n_rot;
     u32 accumulate;  // add to what cq / cp already hold (a call with more rotations than one launch takes)
     u32 split;       // limbs below split go to cq ([2][split][N]), the others to cp ([2][D - split][N])
+    u32 waves;       // wavefronts of a workgroup that share a row, each taking every waves-th rotation: 1 (four rows) or 4
+    u32 each;        // rotations are not summed: rotation r's result goes to cq + r*2*split*N, cp + r*2*(D - split)*N
 };
 
-// No transform is involved, so the work is element-parallel with few registers per lane (many waves in
-// flight hide the gather and key-load latency): work item = (limb i, 256 * EPT consecutive slots), lane
-// `tid` owns slots base + k * 256 + tid.
-template <class AR, int EPT>
-__global__ __launch_bounds__(256) void dh_accum_kernel(DhInnerArgs a, Tables tb, LimbRun run) {
+template <class AR>
+__device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables& tb, const PrimeConst& pc, u64* lds, u32 i, u32 row, u32 wave) {
     typedef typename AR::T T;
-    const u32 N = 1u << tb.logN, tid = threadIdx.x, L = tb.L, D = tb.D;
-    const u32 chunks = N / (256 * EPT);
-    const u32 i = run.first + blockIdx.x / chunks, base = (blockIdx.x % chunks) * (256 * EPT) + tid;
-    if (i >= run.first + run.count) return;
-    const u32 Dkey = tb.Lfull + tb.K, pi = tb.phys(i);
+    typedef typename AR::Wide W;
+    const u32 logN = tb.logN, N = 1u << logN, lane = threadIdx.x & 63, L = tb.L, D = tb.D;
+    const u32 pi = tb.phys(i), Dkey = tb.Lfull + tb.K;
     const bool is_q = i < L;
-    const PrimeConst pc = tb.pc[pi];
     const typename AR::Mod m = AR::mod(pc);
-    const u32 own_digit = is_q ? i / tb.alpha : 0xffffffffu;
+    const u32 own_digit = is_q ? i / tb.alpha : 0xffffffffu, row_off = row * 256;
     const u64 pmod = is_q ? tb.pmod[i] : 0;
-    const u64* bp = a.ct + (size_t)(is_q ? i : 0) * N;
-    T acc0[EPT], acc1[EPT];
+    u64* stage = lds + wave * 256;
+    auto load = [&](const u64* p, u64 (&o)[4], bool nt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < EPT; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
-    u32 terms = 0;
-    for (u32 rr = 0; rr < a.n_rot; rr++) {
-        const u64* key = a.key[rr] + (size_t)pi * N + base;
-        const u32 gal = a.galois[rr];
-        const u64* ptp = a.pt + ((size_t)rr * D + i) * N + base;
-        u64 ptv[EPT];
-        u32 idx[EPT];
-#pragma unroll
-        for (int k = 0; k < EPT; k++) {
-            ptv[k] = a.pt ? __builtin_nontemporal_load(&ptp[k * 256]) : 1;
-            idx[k] = eval_perm(base + k * 256, gal, tb.logN);
+        for (int h = 0; h < 2; h++) {
+            const u64x2* q = reinterpret_cast<const u64x2*>(p + h * 128 + lane * 2);
+            const u64x2 t = nt ? __builtin_nontemporal_load(q) : *q;
+            o[2 * h] = t.x, o[2 * h + 1] = t.y;
         }
-        for (u32 j = 0; j < tb.dnum; j++) {
-            const u64* k0 = key + ((size_t)j * 2 + 0) * Dkey * N;
-            const u64* k1 = key + ((size_t)j * 2 + 1) * Dkey * N;
-            const u64* src = j == own_digit ? a.ct + ((size_t)L + i) * N : a.dt + ((size_t)j * D + i) * N;
-            u64 kv0[EPT], kv1[EPT], sv[EPT];
-#pragma unroll
-            for (int k = 0; k < EPT; k++) {
-                kv0[k] = __builtin_nontemporal_load(&k0[k * 256]);
-                kv1[k] = __builtin_nontemporal_load(&k1[k * 256]);
-                sv[k] = src[idx[k]];
-            }
-#pragma unroll
-            for (int k = 0; k < EPT; k++) {
-                const T w = AR::premul(sv[k], ptv[k], m);
-                AR::acc_mac(acc0[k], w, kv0[k], m);
-                AR::acc_mac(acc1[k], w, kv1[k], m);
-            }
-            if ((++terms & 7) == 0) {
-#pragma unroll
-                for (int k = 0; k < EPT; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
-            }
-        }
-        if (is_q) {
-#pragma unroll
-            for (int k = 0; k < EPT; k++) AR::acc_mac(acc0[k], AR::premul(bp[idx[k]], ptv[k], m), pmod, m);
-            if ((++terms & 7) == 0) {
-#pragma unroll
-                for (int k = 0; k < EPT; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
-            }
-        }
-    }
+    };
     const u32 sp = a.split;
-    u64* o0 = (i < sp ? a.cq + (size_t)i * N : a.cp + (size_t)(i - sp) * N) + base;
-    u64* o1 = (i < sp ? a.cq + ((size_t)sp + i) * N : a.cp + ((size_t)(D - sp) + (i - sp)) * N) + base;
+    auto out = [&](u32 rr, int t) {
+        u64* base = i < sp ? a.cq + ((size_t)t * sp + i) * N : a.cp + ((size_t)t * (D - sp) + (i - sp)) * N;
+        return base + (a.each ? (size_t)rr * 2 * (i < sp ? sp : D - sp) * N : 0) + row_off;
+    };
+    auto store = [&](const T (&acc)[4], u64* o) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < EPT; k++) {
-        u64 r0 = AR::acc_canon(AR::acc_finish2(acc0[k], m), m), r1 = AR::acc_canon(AR::acc_finish2(acc1[k], m), m);
-        if (a.accumulate) r0 = addmod(r0, o0[k * 256], pc.q), r1 = addmod(r1, o1[k * 256], pc.q);
-        o0[k * 256] = r0;
-        o1[k * 256] = r1;
+        for (int h = 0; h < 2; h++) {
+            u64x2* q = reinterpret_cast<u64x2*>(o + h * 128 + lane * 2);
+            u64x2 r;
+            r.x = AR::acc_canon(AR::acc_finish2(acc[2 * h], m), m), r.y = AR::acc_canon(AR::acc_finish2(acc[2 * h + 1], m), m);
+            if (a.accumulate) {
+                const u64x2 p = *q;
+                r.x = addmod(r.x, p.x, pc.q), r.y = addmod(r.y, p.y, pc.q);
+            }
+            *q = r;
+        }
+    };
+    T acc0[4], acc1[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
+    // terms of a rotation: digits 0 .. dnum - 1, then (q-limbs) b times P.  The words of the next term, also across
+    // rotations, are requested before this one is worked on: a wavefront has 12 KiB in flight.
+    const u32 n_terms = tb.dnum + (is_q ? 1 : 0);
+    u64 sv[4], kv0[4], kv1[4], ptv[4] = {1, 1, 1, 1};
+    const u64 *ct = a.ct, *dt = a.dt;
+    auto request = [&](u32 gal, const u64* key_r, const u64* pt_r, u32 j, u64 (&s)[4], u64 (&k0)[4], u64 (&k1)[4],
+                       u64 (&p)[4]) __attribute__((always_inline)) {
+        const u32 src_off = eval_perm(row_off, gal, logN) & ~255u;
+        const bool is_b = j == tb.dnum;
+        load((is_b ? ct + (size_t)i * N : j == own_digit ? ct + ((size_t)L + i) * N : dt + ((size_t)j * D + i) * N) + src_off, s, false);
+        if (!is_b) {
+            const u64* key = key_r + ((size_t)j * 2 * Dkey + pi) * N + row_off;
+            load(key, k0, true);
+            load(key + (size_t)Dkey * N, k1, true);
+        }
+        if (j == 0 && pt_r) load(pt_r + (size_t)i * N + row_off, p, true);
+    };
+    W w0[4], w1[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) w0[k] = w1[k] = AR::wide_zero();
+    u32 folds = 0, in_sum = 0, rr = a.waves == 1 ? 0 : wave, j = 0;
+    const size_t pt_step = (size_t)D * N;
+    if (rr < a.n_rot) request(a.galois[rr], a.key[rr], a.pt ? a.pt + rr * pt_step : nullptr, 0, sv, kv0, kv1, ptv);
+    while (rr < a.n_rot) {
+        u32 idx[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) idx[k] = eval_perm(row_off + (k >> 1) * 128 + lane * 2 + (k & 1), a.galois[rr], logN) & 255;
+        for (; j < n_terms; j++) {
+            const bool last = j + 1 == n_terms;
+            const u32 rn = last ? rr + a.waves : rr, jn = last ? 0 : j + 1;
+            u64 sn[4], kn0[4], kn1[4], pn[4] = {1, 1, 1, 1};
+            if (rn < a.n_rot) request(a.galois[rn], a.key[rn], a.pt ? a.pt + rn * pt_step : nullptr, jn, sn, kn0, kn1, pn);
+            row_sync();  // the previous term's words have been read
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                u64x2 t;
+                t.x = sv[2 * h], t.y = sv[2 * h + 1];
+                *reinterpret_cast<u64x2*>(stage + h * 128 + lane * 2) = t;
+            }
+            row_sync();
+#pragma unroll
+            for (int k = 0; k < 4; k++) sv[k] = stage[idx[k]];
+            if (j == tb.dnum) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) AR::wide_mac(w0[k], sv[k], pmod);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; k++) AR::wide_mac(w0[k], sv[k], kv0[k]), AR::wide_mac(w1[k], sv[k], kv1[k]);
+            }
+            if (++in_sum == AR::wide_terms || last) {
+                in_sum = 0;
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    AR::acc_mac_wide(acc0[k], AR::wide_reduce(w0[k], m), ptv[k], m);
+                    AR::acc_mac_wide(acc1[k], AR::wide_reduce(w1[k], m), ptv[k], m);
+                    w0[k] = w1[k] = AR::wide_zero();
+                }
+                if ((++folds & 7) == 0) {  // FP64: at most 8 products (0.69 q each) between reductions
+#pragma unroll
+                    for (int k = 0; k < 4; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                sv[k] = sn[k], kv0[k] = kn0[k], kv1[k] = kn1[k];
+                if (last) ptv[k] = pn[k];
+            }
+        }
+        if (a.each) {
+            store(acc0, out(rr, 0));
+            store(acc1, out(rr, 1));
+#pragma unroll
+            for (int k = 0; k < 4; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
+            folds = 0;
+        }
+        j = 0, rr += a.waves;
     }
+    if (a.each) return;
+    if (a.waves > 1) {  // the first of the row's four wavefronts joins their sums
+#pragma unroll
+        for (int k = 0; k < 4; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            lds[(wave * 2 + 0) * 256 + k * 64 + lane] = AR::to_raw(acc0[k]);
+            lds[(wave * 2 + 1) * 256 + k * 64 + lane] = AR::to_raw(acc1[k]);
+        }
+        __syncthreads();
+        if (wave) return;
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+#pragma unroll
+            for (int v = 1; v < 4; v++) {
+                acc0[k] = AR::wide_join(acc0[k], AR::from_raw(lds[(v * 2 + 0) * 256 + k * 64 + lane]), m);
+                acc1[k] = AR::wide_join(acc1[k], AR::from_raw(lds[(v * 2 + 1) * 256 + k * 64 + lane]), m);
+            }
+    }
+    store(acc0, out(0, 0));
+    store(acc1, out(0, 1));
+}
+
+__global__ __launch_bounds__(256, 3) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
+    __shared__ __align__(16) u64 lds[2048];  // 256 words per wavefront to permute a row in; 2048 to join four sums
+    const u32 rows_wg = 4 / a.waves, per_limb = ((1u << tb.logN) / 256) / rows_wg, total = tb.D * per_limb, per = (total + 7) / 8;
+    const u32 pos = blockIdx.x >> 3, q = (blockIdx.x & 7) * per + pos;  // workgroups go to the XCDs round-robin
+    if (pos >= per || q >= total) return;
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: addresses stay in scalar registers
+    const u32 i = q / per_limb, row = (q % per_limb) * rows_wg + (a.waves == 1 ? wave : 0);
+    const PrimeConst pc = tb.pc[tb.phys(i)];
+    if (pc.fp) dh_accum_body<FpAr>(a, tb, pc, lds, i, row, wave);
+    else dh_accum_body<IntAr>(a, tb, pc, lds, i, row, wave);
 }
 
 // ==================================================== baby-step giant-step accumulation and sums

@@ -179,7 +179,20 @@ struct IntAr {
         mac128(p, a, b);
         return redc_lazy(p, m.q, m.qneg);
     }
-    // finish of an accumulation whose operands came from premul: removes 2^-128
+    // unreduced sum of products of two canonical residues: at most 8 terms (8 q^2 < q * 2^64), then wide_reduce gives the
+    // sum times 2^-64 in [0, 2q)
+    typedef u128w Wide;
+    static constexpr u32 wide_terms = 8;
+    static HD Wide wide_zero() { return u128w{0, 0}; }
+    static HD void wide_mac(Wide& w, u64 a, u64 b) { mac128(w, a, b); }
+    static HD T wide_reduce(const Wide& w, const Mod& m) { return redc_lazy(w, m.q, m.qneg); }
+    static HD T wide_join(T a, T b, const Mod& m) {  // sum of two such results, in [0, 2q)
+        u64 s = a + b;
+        return s >= m.q2 ? s - m.q2 : s;
+    }
+    // acc_mac of a wide_reduce result with a canonical residue: one more factor 2^-64 (acc_finish2 removes both)
+    static HD void acc_mac_wide(T& acc, T v, u64 b, const Mod& m) { acc_mac(acc, v, b, m); }
+    // finish of an accumulation whose operands came from premul or wide_reduce: removes 2^-128
     static HD T acc_finish2(T acc, const Mod& m) {
         return mul_shoup_lazy(mul_shoup_lazy(acc, m.r1, m.r1_p, m.q), m.r1, m.r1_p, m.q);
     }
@@ -275,5 +288,26 @@ struct FpAr {
         return f64_to_u64(r);
     }
     static HD T premul(u64 a, u64 b, const Mod& m) { return mulmod_lazy(u64_to_f64(a), u64_to_f64(b), m); }  // <= 0.875 q
+    // Unreduced sum of products of two residues, exact, in 4 instructions a term instead of the 7 of a reduced product and
+    // an addition.  t starts at 2^102 and stays in [2^102, 2^103) for at most 6 terms below (3*2^48)^2 < 2^99.2, so it is
+    // always a multiple of 2^50: the step n - t is exact, l collects a*b - (n - t), at most 2^49 a term and so exact.
+    // wide_reduce: H = t - 2^102 exact, c = rint(H / q) off by less than 1.2 before rounding (c < 2^52.2), H - c*q an
+    // integer below 1.7 q, plus |l| < 2^51.6: below 2^53, exact; reduced to at most q/2.
+    struct Wide {
+        double t, l;
+    };
+    static constexpr u32 wide_terms = 6;
+    static HD Wide wide_zero() { return Wide{5070602400912917605986812821504.0, 0.0}; }
+    static HD void wide_mac(Wide& w, u64 a, u64 b) {
+        const double x = u64_to_f64(a), y = u64_to_f64(b), n = __builtin_fma(x, y, w.t), d = n - w.t;
+        w.l += __builtin_fma(x, y, -d);
+        w.t = n;
+    }
+    static HD T wide_reduce(const Wide& w, const Mod& m) {
+        const double h = w.t - 5070602400912917605986812821504.0, c = __builtin_rint(h * m.qinv);
+        return reduce(__builtin_fma(-c, m.q, h) + w.l, m);
+    }
+    static HD T wide_join(T a, T b, const Mod&) { return a + b; }
+    static HD void acc_mac_wide(T& acc, T v, u64 b, const Mod& m) { acc += mulmod_lazy(v, u64_to_f64(b), m); }
     static HD T acc_finish2(T acc, const Mod& m) { return reduce(acc, m); }
 };
