@@ -952,24 +952,36 @@ static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t
                             [per](u32, u32 n) { return per * n; });
 }
 
+// Wavefronts that share the digits of a row in the inner product (InnerArgs::ways) for a launch of `wgs` workgroups of 16
+// rows.  A workgroup's time is about one unit per digit it works through and one per component it ends, two workgroups
+// fit a compute unit: compare rounds times units.  One HMult at N = 2^16, dnum = 4: special limbs, 96 workgroups, 48 -> 28 us;
+// at N = 2^12, dnum = 3: special limb 14 -> 9 us, q-limbs 16 -> 10 us.
+static u32 inner_ways(u32 wgs, u32 dnum) {
+    const u32 one = (wgs + 511) / 512 * (2 * dnum + 4), four = (4 * wgs + 511) / 512 * (2 * ((dnum + 3) / 4) + 3);
+    return dnum > 1 && four < one ? 4 : 1;
+}
+
 // limbs [lo, hi) of the extended basis.  FUSED: the launch also ends the ModDown on its limbs (all below
 // a.split, after the conversion of the special part) and writes the result instead of c'.
 template <int OWN, bool HOISTED, bool FUSED = false>
-static void launch_ks_inner(const View* c, const InnerArgs& a, hipStream_t s, u32 lo, u32 hi) {
+static void launch_ks_inner(const View* c, InnerArgs a, hipStream_t s, u32 lo, u32 hi) {
     const u64 n_inst = a.n_inst;
-    launch_runs<KsInnerL<OWN, HOISTED, FUSED>>(
-        c, lo, hi, 0, tiles_of(c), a.n_inst, a, s, [c, n_inst](u32 first, u32 n) {
-            u64 limbs = 0;
-            for (u32 i = first; i < first + n; i++) {
-                const bool q = i < c->L;
-                limbs += n_inst * ((u64)c->dnum - (q ? 1 : 0)            // extended digits outside their own limbs
-                                   + (q ? (OWN == OWN_TENSOR ? 4 : 1) : 0)  // the switched polynomial (HMult: both inputs) on its own limb
-                                   + 2                                     // c' (or the result) written
-                                   + (FUSED ? 2 + (OWN == OWN_ROT ? 1 : 0) : 0))  // converted special part (+ sigma_g(b))
-                         + (HOISTED ? n_inst : 1) * 2 * (u64)c->dnum;      // key limbs
-            }
-            return limbs;
-        });
+    typedef KsInnerL<OWN, HOISTED, FUSED> L;
+    for (const ClassRun& cr : class_runs(c, lo, hi)) {
+        a.ways = HOISTED ? 1 : inner_ways(cr.count * tiles_of(c) * a.n_inst, c->dnum);
+        hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
+        u64 limbs = 0;
+        for (u32 i = cr.first; i < cr.first + cr.count; i++) {
+            const bool q = i < c->L;
+            limbs += n_inst * ((u64)c->dnum - (q ? 1 : 0)            // extended digits outside their own limbs
+                               + (q ? (OWN == OWN_TENSOR ? 4 : 1) : 0)  // the switched polynomial (HMult: both inputs) on its own limb
+                               + 2                                     // c' (or the result) written
+                               + (FUSED ? 2 + (OWN == OWN_ROT ? 1 : 0) : 0))  // converted special part (+ sigma_g(b))
+                     + (HOISTED ? n_inst : 1) * 2 * (u64)c->dnum;      // key limbs
+        }
+        ProfScope ps(c, c->sh->prof.on ? L::name(cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(), limbs, rs);
+        dispatch_kernel<L>(c, cr.fp, dim3(xcd_grid(cr.count * tiles_of(c) * a.ways, a.n_inst)), rs, a, LimbRun{cr.first, cr.count});
+    }
 }
 template <int OWN, bool HOISTED>
 static void launch_ks_inner(const View* c, const InnerArgs& a, hipStream_t s) {

@@ -795,6 +795,10 @@ struct InnerArgs {
     const u64* cv;              // [inst][2][split][N] converted special part, first forward pass done
     u64* out;                   // [inst][2][split][N]
     const PinvConst* fin_pinv;  // [split] inverse of the product of the ModDown's source primes
+    // 1: a workgroup owns 16 rows.  4: it owns 4, each of its wavefronts all of them for every fourth digit; the sums are
+    // joined in LDS and the first two wavefronts end a component each.  For grids that leave the chip idle, where the
+    // time is that of one wavefront and its dnum + 2 passes run one after the other (inner_ways).
+    u32 ways;
 };
 
 // Twiddles of one row's second forward pass, kept in LDS for kernels that run that pass several times on the same
@@ -832,7 +836,8 @@ template <class AR, int A, int OWN, bool HOISTED, bool FUSED>
 __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& tb, u64* lds, u32 i, u32 tile,
                                               u32 inst) {
     typedef typename AR::T T;
-    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r = tile * 16 + ch;
+    const u32 ways = HOISTED ? 1 : a.ways, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r = ways == 1 ? tile * 16 + ch : tile * 4 + (ch & 3);
     const u32 L = tb.L, D = tb.D;
     const u32 pi = tb.phys(i), Dkey = tb.Lfull + tb.K;  // keys are laid out over the whole chain
     const PrimeConst pc = tb.pc[pi];
@@ -851,7 +856,8 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
     T acc0[16], acc1[16];  // layout CP
 #pragma unroll
     for (int k = 0; k < 16; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
-    for (u32 j = 0; j < tb.dnum; j++) {
+    u32 since = 0;
+    for (u32 j = ways == 1 ? 0 : wave; j < tb.dnum; j += ways) {
         const u64* k0 = key + ((size_t)j * 2 + 0) * Dkey * N;
         const u64* k1 = key + ((size_t)j * 2 + 1) * Dkey * N;
         u64 kv0[16], kv1[16];
@@ -922,10 +928,33 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         if constexpr (!EARLY1) load_row_cp<false>(k1, e0, kv1);
 #pragma unroll
         for (int k = 0; k < 16; k++) AR::acc_mac(acc1[k], v[k], kv1[k], m);
-        if ((j & 7) == 7) {  // FpAr sums at most 8 lazily reduced products (0.69 q each) between reductions
+        if ((++since & 7) == 0) {  // FpAr sums at most 8 lazily reduced products (0.69 q each) between reductions
 #pragma unroll
             for (int k = 0; k < 16; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
         }
+    }
+    if (!HOISTED && ways != 1) {  // wavefront t of the four gets component t of the joined sums
+#pragma unroll
+        for (u32 t = 0; t < 2; t++) {
+            __syncthreads();
+            if (wave != t) {
+#pragma unroll
+                for (int k = 0; k < 16; k++) lds[wave * 1024 + k * 64 + (tid & 63)] = AR::to_raw(AR::acc_fold(t ? acc1[k] : acc0[k], m));
+            }
+            __syncthreads();
+            if (wave == t) {
+#pragma unroll
+                for (int k = 0; k < 16; k++) {
+                    T s = AR::acc_fold(t ? acc1[k] : acc0[k], m);
+#pragma unroll
+                    for (u32 v = 1; v < 4; v++) s = AR::wide_join(s, AR::from_raw(lds[((t + v) & 3) * 1024 + k * 64 + (tid & 63)]), m);
+                    if (t) acc1[k] = s;
+                    else acc0[k] = s;
+                }
+            }
+        }
+        __syncthreads();
+        if (wave > 1) return;
     }
     if (FUSED) {
         // c' stays in registers: out = (c' - second forward pass of the converted special part) * P^-1
@@ -936,11 +965,12 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         // it is computed before the accumulation loop, which has no registers to spare.
         u32 e0f = e0, chf = ch, gal_fin = gal;
         asm volatile("" : "+v"(e0f), "+v"(chf), "+s"(gal_fin));
-        const u32 rf = tile * 16 + chf, row_off_f = rf * 256;
+        const u32 rf = ways == 1 ? tile * 16 + chf : tile * 4 + (chf & 3), row_off_f = rf * 256;
         u64* lrow_f = lds + chf * 272;
         const PinvConst pinv = a.fin_pinv[i];
 #pragma unroll
         for (int t = 0; t < 2; t++) {
+            if (ways != 1 && wave != (u32)t) continue;
             T v[16];
             const u64* p = a.cv + (((size_t)inst * 2 + t) * a.split + i) * N + row_off_f;
 #pragma unroll
@@ -974,6 +1004,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         u64 res[16];
 #pragma unroll
         for (int t = 0; t < 2; t++) {
+            if (ways != 1 && wave != (u32)t) continue;
 #pragma unroll
             for (int k = 0; k < 16; k++) res[k] = AR::acc_canon(AR::acc_finish(t ? acc1[k] : acc0[k], m), m);
             store_row_cp(a.cq + (((size_t)inst * 2 + t) * a.split + i) * N + row_off, e0, res);
@@ -981,6 +1012,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
     } else {
 #pragma unroll
         for (int t = 0; t < 2; t++) {
+            if (ways != 1 && wave != (u32)t) continue;
             T x[16];
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = AR::acc_finish(t ? acc1[k] : acc0[k], m);
@@ -996,7 +1028,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
 template <class AR, int A, int OWN, bool HOISTED, bool FUSED>
 __global__ __launch_bounds__(256, 2) void ks_inner_kernel(InnerArgs a, Tables tb, LimbRun run) {
     __shared__ u64 lds[NTT_LDS_WORDS + (AR::is_fp && !HOISTED ? 16 * CKKS_ROW_TW_WORDS : 0)];
-    constexpr u32 TILES = (1u << A) / 16;
+    const u32 TILES = (1u << A) / 16 * (HOISTED ? 1 : a.ways);
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.n_inst, run.count * TILES, group, inst)) return;
     ks_inner_body<AR, A, OWN, HOISTED, FUSED>(a, tb, lds, run.first + group / TILES, group % TILES, inst);
