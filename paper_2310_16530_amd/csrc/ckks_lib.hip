@@ -779,10 +779,28 @@ static std::string kname(const char* base, const char* ar, int A, const char* ta
 // One launch per arithmetic run of the primes [lo, hi).  limb_base converts a prime index into the kernel's limb index;
 // groups = run limbs x groups_n, instances = inst_n.  alg(first, count) gives the algorithmic limbs (read + written once)
 // of the launch covering primes [first, first+count).
+// A range that mixes the arithmetics is one launch of the AnyAr form where the launcher has one (L::any: the plain passes)
+// and the integer limbs do not run on the side stream.
 template <class L, class ArgT, class AlgFn>
 static void launch_runs(const View* c, u32 lo, u32 hi, u32 limb_base, u32 groups_n, u32 inst_n, const ArgT& a, hipStream_t s,
                         AlgFn alg) {
-    for (const ClassRun& cr : class_runs(c, lo, hi)) {
+    const std::vector<ClassRun> runs = class_runs(c, lo, hi);
+    if constexpr (L::any) {
+        if (runs.size() > 1 && !c->sh->side.active) {
+            const LimbRun run = {lo - limb_base, hi - lo};
+            const dim3 grid(xcd_grid((hi - lo) * groups_n, inst_n));
+            ProfScope ps(c, c->sh->prof.on ? L::name("AnyAr", (int)c->logN - 8) : std::string(), c->sh->prof.on ? alg(lo, hi - lo) : 0, s);
+            switch (c->logN - 8) {
+                case 4: L::template go<AnyAr, 4>(grid, s, a, c->tb, run); break;
+                case 5: L::template go<AnyAr, 5>(grid, s, a, c->tb, run); break;
+                case 6: L::template go<AnyAr, 6>(grid, s, a, c->tb, run); break;
+                case 7: L::template go<AnyAr, 7>(grid, s, a, c->tb, run); break;
+                case 8: L::template go<AnyAr, 8>(grid, s, a, c->tb, run); break;
+            }
+            return;
+        }
+    }
+    for (const ClassRun& cr : runs) {
         const LimbRun run = {cr.first - limb_base, cr.count};
         hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
         ProfScope ps(c, c->sh->prof.on ? L::name(cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(),
@@ -793,15 +811,17 @@ static void launch_runs(const View* c, u32 lo, u32 hi, u32 limb_base, u32 groups
 
 template <int LOAD>
 struct InvContigL {
+    static constexpr bool any = LOAD == INV_PLAIN;
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const InvContigArgs& a, const Tables& tb, LimbRun run) {
-        hipLaunchKernelGGL((inv_contig_kernel<AR, A, LOAD>), g, dim3(256), 0, s, a, tb, run);
+        hipLaunchKernelGGL((inv_contig_kernel<AR, A, LOAD>), g, dim3(inv_one_kernel(A) ? 16 << A : 256), 0, s, a, tb, run);
     }
     static std::string name(const char* ar, int A) {
         return kname("inv_contig_kernel", ar, A, LOAD == 0 ? ", 0" : LOAD == 1 ? ", 1" : ", 2");
     }
 };
 struct InvStridedL {
+    static constexpr bool any = true;
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const InvStridedArgs& a, const Tables& tb, LimbRun run) {
         hipLaunchKernelGGL((inv_strided_kernel<AR, A>), g, dim3(256), 0, s, a, tb, run);
@@ -809,6 +829,7 @@ struct InvStridedL {
     static std::string name(const char* ar, int A) { return kname("inv_strided_kernel", ar, A, ""); }
 };
 struct FwdStridedL {
+    static constexpr bool any = true;
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const FwdStridedArgs& a, const Tables& tb, LimbRun run) {
         hipLaunchKernelGGL((fwd_strided_kernel<AR, A>), g, dim3(256), 0, s, a, tb, run);
@@ -839,6 +860,7 @@ struct ConvL {
     }
 };
 struct FwdContigL {
+    static constexpr bool any = true;
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const FwdContigArgs& a, const Tables& tb, LimbRun run) {
         hipLaunchKernelGGL((fwd_contig_kernel<AR, A>), g, dim3(256), 0, s, a, tb, run);
@@ -859,6 +881,7 @@ struct KsInnerL {
 };
 template <int MODE>
 struct KsFinalL {
+    static constexpr bool any = false;
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const FinalArgs& a, const Tables& tb, LimbRun run) {
         hipLaunchKernelGGL((ks_final_kernel<AR, A, MODE>), g, dim3(256), 0, s, a, tb, run);
@@ -872,7 +895,7 @@ template <int LOAD>
 static void launch_inv_contig(const View* c, const InvContigArgs& a, hipStream_t s) {
     const u32 pb = a.sel.prime_base;
     const u64 per = (u64)a.sel.n_inst * (LOAD == INV_TENSOR ? 3 : 2);
-    launch_runs<InvContigL<LOAD>>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s,
+    launch_runs<InvContigL<LOAD>>(c, pb, pb + a.sel.n_l, pb, inv_one_kernel((int)c->logN - 8) ? 1 : tiles_of(c), a.sel.n_inst, a, s,
                                   [per](u32, u32 n) { return per * n; });
 }
 
@@ -881,6 +904,16 @@ static void launch_inv_strided(const View* c, const InvStridedArgs& a, hipStream
     const u64 per = (u64)a.sel.n_inst * 2;
     launch_runs<InvStridedL>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s,
                              [per](u32, u32 n) { return per * n; });
+}
+
+// The inverse transform of a.sel's limbs into a.dst
+template <int LOAD>
+static void launch_inverse(const View* c, InvContigArgs a, u32 scale, u32 out_fmt, hipStream_t s) {
+    a.scale = scale, a.out_fmt = out_fmt;
+    launch_inv_contig<LOAD>(c, a, s);
+    if (inv_one_kernel((int)c->logN - 8)) return;
+    const InvStridedArgs a2 = {a.dst, a.dsel, scale, out_fmt};
+    launch_inv_strided(c, a2, s);
 }
 
 static void launch_fwd_strided(const View* c, const FwdStridedArgs& a, hipStream_t s) {
@@ -950,6 +983,24 @@ static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t
     const u64 per = (u64)a.sel.n_inst * 2;
     launch_runs<FwdContigL>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s,
                             [per](u32, u32 n) { return per * n; });
+}
+
+// forward transform in place: one kernel where a workgroup holds a limb, else two passes
+static void launch_forward(const View* c, u64* d_x, const LimbSel& sel, hipStream_t s) {
+    const FwdContigArgs a2 = {d_x, sel};
+    if (!inv_one_kernel((int)c->logN - 8)) {
+        const FwdStridedArgs a1 = {d_x, d_x, sel};
+        launch_fwd_strided(c, a1, s);
+        launch_fwd_contig(c, a2, s);
+        return;
+    }
+    ProfScope ps(c, c->sh->prof.on ? "fwd_whole_kernel<" + std::to_string((int)c->logN - 8) + ">" : std::string(), (u64)sel.n_l * sel.n_inst * 2, s);
+    const dim3 grid(xcd_grid(sel.n_l, sel.n_inst)), block(1u << (c->logN - 4));
+    const LimbRun run = {0, sel.n_l};
+    switch (c->logN - 8) {
+        case 4: hipLaunchKernelGGL(fwd_whole_kernel<4>, grid, block, 0, s, a2, c->tb, run); break;
+        case 5: hipLaunchKernelGGL(fwd_whole_kernel<5>, grid, block, 0, s, a2, c->tb, run); break;
+    }
 }
 
 // Wavefronts that share the digits of a row in the inner product (InnerArgs::ways) for a launch of `wgs` workgroups of 16
@@ -1185,15 +1236,10 @@ static int ntt_entry(ckks_ctx* ctx, uint64_t* d_x, uint32_t prime_first, uint32_
     hipStream_t s = (hipStream_t)stream;
     const LimbSel sel = {n_limbs, batch, n_limbs, 0, prime_first, 0};
     if (!inverse) {
-        FwdStridedArgs a1 = {d_x, d_x, sel};
-        launch_fwd_strided(c, a1, s);
-        FwdContigArgs a2 = {d_x, sel};
-        launch_fwd_contig(c, a2, s);
+        launch_forward(c, d_x, sel, s);
     } else {
         InvContigArgs a1 = {d_x, nullptr, d_x, sel, sel, {1}, 0};
-        launch_inv_contig<INV_PLAIN>(c, a1, s);
-        InvStridedArgs a2 = {d_x, sel, SC_PLAIN, 0};
-        launch_inv_strided(c, a2, s);
+        launch_inverse<INV_PLAIN>(c, a1, SC_PLAIN, SRC_CANON, s);
     }
     return hip_check(c, inverse ? "ckks_intt" : "ckks_ntt");
 }
@@ -1339,14 +1385,13 @@ static int check_ks_args(const View* c, const void* a, const void* b, const void
     return CKKS_OK;
 }
 
-// ModUp side shared by every key switch: w.x holds the first inverse pass of the polynomial(s).
-// Second inverse pass (scaled by the conversion pre-factor), then conversion fused into the
-// first forward pass of every extended limb.
+// ModUp side shared by every key switch: w.x holds the coefficients of the polynomial(s) times the conversion pre-factor
+// (launch_decompose_inverse); conversion fused into the first forward pass of every extended limb.
+template <int LOAD>
+static void launch_decompose_inverse(const View* c, const InvContigArgs& a, hipStream_t s) {
+    launch_inverse<LOAD>(c, a, SC_UP, conv_src_fmt(c->up, CONV_UP), s);
+}
 static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, bool fp_beside = false) {
-    const LimbSel sel = {c->L, groups, c->L, 0, 0, 0};
-    const u32 fmt = conv_src_fmt(c->up, CONV_UP);
-    InvStridedArgs a2 = {w.x, sel, SC_UP, fmt};
-    launch_inv_strided(c, a2, s);
     const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0};
     SideStream& sd = c->sh->side;
     if (fp_beside && sd.enabled && c->mixed_classes && !sd.active && side_stream_ready(sd)) {
@@ -1385,12 +1430,13 @@ static void join_fp_beside(const View* c, hipStream_t s) {
     }
 }
 
-// ModDown side: w.cp holds the first inverse pass of c' on the special limbs.
-static void moddown_convert(const View* c, const Workspace& w, u32 cg, hipStream_t s) {
-    const LimbSel sel = {c->K, cg * 2, c->K, 0, c->L, 0};
-    const u32 fmt = conv_src_fmt(c->dn, CONV_DN);
-    InvStridedArgs a6 = {w.cp, sel, SC_DN, fmt};
-    launch_inv_strided(c, a6, s);
+// ModDown side: w.cp holds c' on the special limbs after the first inverse pass (done = false) or as coefficients times the
+// conversion pre-factor.
+static void moddown_convert(const View* c, const Workspace& w, u32 cg, hipStream_t s, bool done = false) {
+    if (!done) {
+        const InvStridedArgs a6 = {w.cp, LimbSel{c->K, cg * 2, c->K, 0, c->L, 0}, SC_DN, conv_src_fmt(c->dn, CONV_DN)};
+        launch_inv_strided(c, a6, s);
+    }
     join_side(c, s);  // the conversion reads every special limb
     const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, nullptr, nullptr, 0};
     launch_conv<CONV_DN>(c, a7, s);
@@ -1418,7 +1464,7 @@ static void keyswitch_pipeline(const View* c, const View* cm, const u64* in1, co
         for (u32 b = 0; b < batch; b++)
             a1.galois[b] = ia.galois[b] = multi_galois[b], ia.key[b] = multi_keys[b];
     }
-    launch_inv_contig<LOAD>(c, a1, s);
+    launch_decompose_inverse<LOAD>(c, a1, s);
     decompose_extend(c, w, batch, s, true);
     ia.dt = w.dt, ia.own = in1, ia.own2 = in2;
     ia.cq = w.cq, ia.cp = w.cp, ia.n_inst = batch, ia.split = cm->L;
@@ -1549,8 +1595,8 @@ static int rescale_impl(ckks_ctx* ctx, uint32_t level, const uint64_t* d_ct, uin
     const LimbSel src = {1, batch * 2, level, level - 1, level - 1, 0};  // limb level-1 of every component
     const LimbSel dst = {1, batch * 2, 1, 0, level - 1, 0};
     InvContigArgs a1 = {d_ct, nullptr, w.cp, src, dst, {1}, 0};
-    launch_inv_contig<INV_PLAIN>(c, a1, s);
-    moddown_convert(c, w, batch, s);
+    launch_inverse<INV_PLAIN>(c, a1, SC_DN, conv_src_fmt(c->dn, CONV_DN), s);
+    moddown_convert(c, w, batch, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
     fa.cq = d_ct, fa.cq_L = level, fa.cv = w.cv, fa.out = d_out, fa.n_inst = batch;
@@ -1607,7 +1653,7 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
         const LimbSel src = {c->L, 1, c->L, c->L, 0, 0};  // limbs L .. 2L-1 of ct, primes 0 .. L-1
         const LimbSel dst = {c->L, 1, c->L, 0, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
-        launch_inv_contig<INV_PLAIN>(c, a1, s);
+        launch_decompose_inverse<INV_PLAIN>(c, a1, s);
         decompose_extend(c, w, 1, s);
         if (c->dnum > 1) {
             FwdContigArgs q = {w.dt, LimbSel{c->L, c->dnum - 1, c->D, 0, 0, c->alpha}};
@@ -1687,7 +1733,7 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
         const LimbSel src = {c->L, 1, c->L, c->L, 0, 0};
         const LimbSel dst = {c->L, 1, c->L, 0, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
-        launch_inv_contig<INV_PLAIN>(c, a1, s);
+        launch_decompose_inverse<INV_PLAIN>(c, a1, s);
         decompose_extend(c, w, 1, s);
         if (c->dnum > 1) {
             FwdContigArgs q = {w.dt, LimbSel{c->L, c->dnum - 1, c->D, 0, 0, c->alpha}};
@@ -1709,9 +1755,9 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
     {  // ModDown of the sum: first inverse pass of its source limbs, then the shared tail
         const LimbSel sel = {cm->K, 2, cm->K, 0, cm->L, 0};
         InvContigArgs ic = {w.cp, nullptr, w.cp, sel, sel, {1}, 0};
-        launch_inv_contig<INV_PLAIN>(cm, ic, s);
+        launch_inverse<INV_PLAIN>(cm, ic, SC_DN, conv_src_fmt(cm->dn, CONV_DN), s);
     }
-    moddown_convert(cm, w, 1, s);
+    moddown_convert(cm, w, 1, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
     fa.cq = w.cq, fa.cq_L = cm->L, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 1;
@@ -1803,7 +1849,7 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         const LimbSel src = {c->L, 1, c->L, c->L, 0, 0};
         const LimbSel dst = {c->L, 1, c->L, 0, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
-        launch_inv_contig<INV_PLAIN>(c, a1, s);
+        launch_decompose_inverse<INV_PLAIN>(c, a1, s);
         decompose_extend(c, w, 1, s);
         if (c->dnum > 1) {
             FwdContigArgs q = {w.dt, LimbSel{c->L, c->dnum - 1, c->D, 0, 0, c->alpha}};
@@ -1829,9 +1875,9 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
     {
         const LimbSel sel = {c->K, n2 * 2, c->K, 0, c->L, 0};
         InvContigArgs ic = {w.cp, nullptr, w.cp, sel, sel, {1}, 0};
-        launch_inv_contig<INV_PLAIN>(c, ic, s);
+        launch_inverse<INV_PLAIN>(c, ic, SC_DN, conv_src_fmt(c->dn, CONV_DN), s);
     }
-    moddown_convert(c, w, n2, s);
+    moddown_convert(c, w, n2, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
     fa.cq = w.cq, fa.cq_L = c->L, fa.cv = w.cv, fa.out = inner, fa.n_inst = n2;

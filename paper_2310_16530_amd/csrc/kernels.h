@@ -168,20 +168,21 @@ struct InvContigArgs {
     LimbSel sel, dsel;
     u32 galois[CKKS_ROT_CHUNK];  // ROT: [0], or one per instance when per_inst is set
     u32 per_inst;
+    u32 scale, out_fmt;  // of the second pass, where the kernel runs it too (inv_one_kernel): InvScaleSel, SrcFormat
 };
+// N <= 2^13: a workgroup of N / 16 lanes holds the limb in its registers and the first inverse pass's kernel runs the
+// second pass as well, fwd_whole_kernel both forward ones: the limb crosses LDS between the passes instead of HBM, one
+// launch instead of two, half the traffic.  At N = 2^14 the one workgroup of a limb (1024 lanes) takes longer than two
+// launches that spread it over four: ten limbs 14.8 us against 11.5.
+constexpr bool inv_one_kernel(int A) { return A <= 5; }
+enum InvScaleSel { SC_PLAIN = 0, SC_UP = 1, SC_DN = 2 };
 
-template <class AR, int A, int LOAD>
-__device__ __forceinline__ void inv_contig_body(const InvContigArgs& a, const Tables& tb, u64* lds, u32 l, u32 tile,
-                                                u32 inst) {
-    typedef typename AR::T T;
-    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r = tile * 16 + ch;
-    const u32 pi = tb.phys(a.sel.prime_base + l);
-    const PrimeConst pc = tb.pc[pi];
+// row r of limb l of instance `inst`, in layout CB
+template <class AR, int LOAD>
+__device__ __forceinline__ void inv_load_row(typename AR::T (&x)[16], const InvContigArgs& a, const Tables& tb, const PrimeConst& pc,
+                                             u64* lrow, u32 l, u32 r, u32 e0, u32 inst) {
+    const u32 N = 1u << tb.logN;
     const typename AR::Mod m = AR::mod(pc);
-    const u64* ti = tb.tw_int + (size_t)pi * 4 * N;
-    const double* tf = tb.tw_fp + (size_t)pi * 2 * N;
-    u64* lrow = lds + ch * 272;
-    T x[16];
     // operands arrive in layout CP (16-byte accesses) and are brought into the pass's layout CB by the exchange
     // that the pass needs anyway; a rotation applies its permutation in that exchange
     if (LOAD == INV_PLAIN) {
@@ -212,6 +213,20 @@ __device__ __forceinline__ void inv_contig_body(const InvContigArgs& a, const Ta
         for (int k = 0; k < 16; k++)
             x[k] = AR::round_reduce(AR::from_canon(lrow[pad16(eval_perm(r * 256 + e0 * 16 + k, gal, tb.logN) & 255)], m), m);
     }
+}
+
+template <class AR, int A, int LOAD>
+__device__ __forceinline__ void inv_contig_body(const InvContigArgs& a, const Tables& tb, u64* lds, u32 l, u32 tile,
+                                                u32 inst) {
+    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r = tile * 16 + ch;
+    const u32 pi = tb.phys(a.sel.prime_base + l);
+    const PrimeConst pc = tb.pc[pi];
+    const typename AR::Mod m = AR::mod(pc);
+    const u64* ti = tb.tw_int + (size_t)pi * 4 * N;
+    const double* tf = tb.tw_fp + (size_t)pi * 2 * N;
+    u64* lrow = lds + ch * 272;
+    typename AR::T x[16];
+    inv_load_row<AR, LOAD>(x, a, tb, pc, lrow, l, r, e0, inst);
     NttCore<AR, A>::inv_contig(x, lrow, e0, r, ti, tf, N, m);
     u64* o = a.dst + limb_offset(a.dsel, inst, l) * N + (size_t)r * 256;
 #pragma unroll
@@ -219,22 +234,63 @@ __device__ __forceinline__ void inv_contig_body(const InvContigArgs& a, const Ta
 }
 
 // Every transform kernel is compiled once per arithmetic and launched on a run of consecutive
-// limbs [run.first, run.first + run.count) whose primes all use that arithmetic.
+// limbs [run.first, run.first + run.count) whose primes all use that arithmetic.  The plain passes exist for AR = AnyAr
+// too, where a workgroup picks the arithmetic of its limb: a range that mixes both is then one launch, whose
+// memory-bound FP64 workgroups and instruction-bound integer ones share the chip instead of taking turns.
 struct LimbRun {
     u32 first, count;
 };
+struct AnyAr {};
+#define CKKS_BY_ARITHMETIC(AR, prime, CALL)                                              \
+    if constexpr (!__is_same(AR, AnyAr)) { typedef AR AR_; CALL; }                       \
+    else if (tb.pc[tb.phys(prime)].fp) { typedef FpAr AR_; CALL; }                       \
+    else { typedef IntAr AR_; CALL; }
 
 template <class AR, int A, int LOAD>
-__global__ __launch_bounds__(256) void inv_contig_kernel(InvContigArgs a, Tables tb, LimbRun run) {
-    __shared__ u64 lds[NTT_LDS_WORDS];
-    constexpr u32 TILES = (1u << A) / 16;
+__device__ __forceinline__ void inv_whole_body(const InvContigArgs& a, const Tables& tb, u64* lds, u32 l, u32 inst) {
+    typedef NttCore<AR, A> C;
+    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, r = tid / 16;
+    const u32 vi = a.sel.prime_base + l, pi = tb.phys(vi);
+    const PrimeConst pc = tb.pc[pi];
+    const typename AR::Mod m = AR::mod(pc);
+    const u64* ti = tb.tw_int + (size_t)pi * 4 * N;
+    const double* tf = tb.tw_fp + (size_t)pi * 2 * N;
+    u64* lrow = lds + r * 272;
+    typename AR::T x[16];
+    inv_load_row<AR, LOAD>(x, a, tb, pc, lrow, l, r, e0, inst);
+    C::inv_contig(x, lrow, e0, r, ti, tf, N, m);
+    row_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) lrow[pad16(k * 16 + e0)] = AR::to_raw(AR::round_reduce(x[k], m));
+    __syncthreads();
+    const u32 g = tid >> 8, t = tid & 255, c = t % C::TC, r0 = t / C::TC, col = g * C::TC + c;
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lds[(A > 4 ? r0 * 16 + k : k) * 272 + pad16(col)]);
+    if (A > 4) __syncthreads();  // the pass exchanges through the same memory
+    C::inv_strided_but_last(x, lds + g * 4096, t, ti, tf, N, m);
+    const InvScale sc = a.scale == SC_PLAIN ? tb.sc_plain[pi] : a.scale == SC_UP ? tb.sc_up[vi] : tb.sc_dn[vi - tb.L];
+    u64* base = a.dst + limb_offset(a.dsel, inst, l) * N + (size_t)r0 * 256 + col;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        u64 ox, oy;
+        AR::bfly_inv_last(x[k], x[k + 8], sc, m, a.out_fmt, ox, oy);
+        base[(size_t)k * C::RB * 256] = ox;
+        base[(size_t)(k + 8) * C::RB * 256] = oy;
+    }
+}
+template <class AR, int A, int LOAD>
+__global__ __launch_bounds__(inv_one_kernel(A) ? 16 << A : 256) void inv_contig_kernel(InvContigArgs a, Tables tb, LimbRun run) {
+    constexpr bool ONE = inv_one_kernel(A);
+    __shared__ u64 lds[ONE ? (1 << A) * 272 : NTT_LDS_WORDS];
+    constexpr u32 TILES = ONE ? 1 : (1u << A) / 16;
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
-    inv_contig_body<AR, A, LOAD>(a, tb, lds, run.first + group / TILES, group % TILES, inst);
+    const u32 l = run.first + group / TILES;
+    if constexpr (ONE) { CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (inv_whole_body<AR_, A, LOAD>(a, tb, lds, l, inst))) }
+    else { CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (inv_contig_body<AR_, A, LOAD>(a, tb, lds, l, group % TILES, inst))) }
 }
 
 // =========================================================== inverse transform, second pass
-enum InvScaleSel { SC_PLAIN = 0, SC_UP = 1, SC_DN = 2 };
 struct InvStridedArgs {
     u64* data;  // in place: raw inverse-lazy words in, canonical coefficients (times the scale) out
     LimbSel sel;
@@ -277,12 +333,13 @@ __device__ __forceinline__ void inv_strided_body(const InvStridedArgs& a, const 
 #define CKKS_INV_STRIDED_WAVES 6
 #endif
 template <class AR, int A>
-__global__ __launch_bounds__(256, (A == 8 && INV_STRIDED_HALF_EXCHANGE) ? CKKS_INV_STRIDED_WAVES : 4) void inv_strided_kernel(InvStridedArgs a, Tables tb, LimbRun run) {
+__global__ __launch_bounds__(256, (A == 8 && INV_STRIDED_HALF_EXCHANGE && !__is_same(AR, AnyAr)) ? CKKS_INV_STRIDED_WAVES : 4) void inv_strided_kernel(InvStridedArgs a, Tables tb, LimbRun run) {
     __shared__ u64 lds[(A == 8 && INV_STRIDED_HALF_EXCHANGE) ? 2048 : 4096];
     constexpr u32 TILES = (1u << A) / 16;
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
-    inv_strided_body<AR, A>(a, tb, lds, run.first + group / TILES, group % TILES, inst);
+    const u32 l = run.first + group / TILES;
+    CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (inv_strided_body<AR_, A>(a, tb, lds, l, group % TILES, inst)))
 }
 
 // ============================================================ forward transform, first pass
@@ -315,14 +372,9 @@ __device__ __forceinline__ void fwd_strided_finish(typename AR::T (&x)[16], cons
 }
 
 template <class AR, int A>
-__global__ __launch_bounds__(256) void fwd_strided_kernel(FwdStridedArgs a, Tables tb, LimbRun run) {
-    __shared__ u64 lds[4096];
+__device__ __forceinline__ void fwd_strided_body(const FwdStridedArgs& a, const Tables& tb, u64* lds, u32 l, u32 tile, u32 inst) {
     typedef NttCore<AR, A> C;
-    constexpr u32 TILES = (1u << A) / 16;
-    const u32 N = 1u << tb.logN, tid = threadIdx.x;
-    u32 group, inst;
-    if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
-    const u32 l = run.first + group / TILES, tile = group % TILES, pi = a.sel.prime_base + l;
+    const u32 N = 1u << tb.logN, tid = threadIdx.x, pi = a.sel.prime_base + l;
     const size_t off = limb_offset(a.sel, inst, l) * N;
     const typename AR::Mod m = AR::mod(tb.pc[tb.phys(pi)]);
     const u32 c = tid % C::TC, r0 = tid / C::TC, col = tile * C::TC + c;
@@ -330,6 +382,15 @@ __global__ __launch_bounds__(256) void fwd_strided_kernel(FwdStridedArgs a, Tabl
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = AR::from_canon(a.src[off + (size_t)(k * C::RB + r0) * 256 + col], m);
     fwd_strided_finish<AR, A>(x, tb, lds, pi, a.dst + off, tile);
+}
+template <class AR, int A>
+__global__ __launch_bounds__(256) void fwd_strided_kernel(FwdStridedArgs a, Tables tb, LimbRun run) {
+    __shared__ u64 lds[4096];
+    constexpr u32 TILES = (1u << A) / 16;
+    u32 group, inst;
+    if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
+    const u32 l = run.first + group / TILES;
+    CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (fwd_strided_body<AR_, A>(a, tb, lds, l, group % TILES, inst)))
 }
 
 // ============================== base conversion fused into the first forward pass of its targets
@@ -768,7 +829,50 @@ __global__ __launch_bounds__(256) void fwd_contig_kernel(FwdContigArgs a, Tables
     constexpr u32 TILES = (1u << A) / 16;
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
-    fwd_contig_body<AR, A>(a, tb, lds, run.first + group / TILES, group % TILES, inst);
+    const u32 l = run.first + group / TILES;
+    CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (fwd_contig_body<AR_, A>(a, tb, lds, l, group % TILES, inst)))
+}
+
+// ============================================== forward transform of a limb that one workgroup holds
+template <class AR, int A>
+__device__ __forceinline__ void fwd_whole_body(const FwdContigArgs& a, const Tables& tb, u64* lds, u32 l, u32 inst) {
+    typedef NttCore<AR, A> C;
+    const u32 N = 1u << tb.logN, tid = threadIdx.x, pi = tb.phys(a.sel.prime_base + l);
+    const typename AR::Mod m = AR::mod(tb.pc[pi]);
+    const u64* ti = tb.tw_int + (size_t)pi * 4 * N;
+    const double* tf = tb.tw_fp + (size_t)pi * 2 * N;
+    const u32 g = tid >> 8, t = tid & 255, c = t % C::TC, r0 = t / C::TC, col = g * C::TC + c;
+    u64* limb = a.data + limb_offset(a.sel, inst, l) * N;
+    typename AR::T x[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = AR::from_canon(limb[(size_t)(k * C::RB + r0) * 256 + col], m);
+    C::fwd_strided(x, lds + g * 4096, t, ti, tf, N, m);
+    if (A > 4) __syncthreads();  // the pass's exchange has been read
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[(A > 4 ? r0 * 16 + k : k) * 272 + pad16(col)] = AR::to_raw(AR::round_reduce(x[k], m));
+    __syncthreads();
+    const u32 e0 = tid % 16, r = tid / 16;
+    u64* lrow = lds + r * 272;
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lrow[pad16(k * 16 + e0)]);
+    row_sync();
+    C::fwd_contig(x, lrow, e0, r, ti, tf, N, m);
+    row_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) lrow[pad16(e0 * 16 + k)] = AR::canon_fwd(x[k], m);
+    row_sync();
+    u64 res[16];
+#pragma unroll
+    for (int kk = 0; kk < 16; kk++) res[kk] = lrow[pad16(cp_word(e0, kk))];
+    store_row_cp<false>(limb + (size_t)r * 256, e0, res);
+}
+template <int A>
+__global__ __launch_bounds__(16 << A) void fwd_whole_kernel(FwdContigArgs a, Tables tb, LimbRun run) {
+    __shared__ u64 lds[(1 << A) * 272];
+    u32 group, inst;
+    if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count, group, inst)) return;
+    const u32 l = run.first + group;
+    CKKS_BY_ARITHMETIC(AnyAr, a.sel.prime_base + l, (fwd_whole_body<AR_, A>(a, tb, lds, l, inst)))
 }
 
 // ==================================================================== key inner product
