@@ -923,6 +923,20 @@ static void launch_fwd_strided(const View* c, const FwdStridedArgs& a, hipStream
                              [per](u32, u32 n) { return per * n; });
 }
 
+// largest number of targets of the run over the digits, and their sum: a digit's own limbs are none of its targets
+static u32 conv_up_targets(const View* c, const ClassRun& cr, u32& total) {
+    u32 most = 0;
+    total = 0;
+    for (u32 j = 0; j < c->dnum; j++) {
+        const u32 own_hi = (j + 1) * c->alpha < c->L ? (j + 1) * c->alpha : c->L;
+        const u32 lo = j * c->alpha > cr.first ? j * c->alpha : cr.first, hi = own_hi < cr.first + cr.count ? own_hi : cr.first + cr.count;
+        const u32 n = cr.count - (hi > lo ? hi - lo : 0);
+        total += n;
+        if (n > most) most = n;
+    }
+    return most;
+}
+
 // one launch per arithmetic run of the targets
 // only: -1 = every run, 0 = IntAr runs only, 1 = FpAr runs only
 template <class L, int DIR>
@@ -930,18 +944,8 @@ static void launch_conv_runs(const View* c, ConvArgs a, hipStream_t s, int only)
     for (const ClassRun& cr : class_runs(c, 0, DIR == CONV_UP ? c->D : c->L)) {
         if (only >= 0 && (int)cr.fp != only) continue;
         const u32 blk = cr.fp ? L::template per_block<FpAr>() : L::template per_block<IntAr>();
-        // targets of the run: a digit's own limbs are none of its targets
         u32 most = cr.count, written = cr.count;
-        if (DIR == CONV_UP) {
-            most = written = 0;
-            for (u32 j = 0; j < c->dnum; j++) {
-                const u32 own_hi = (j + 1) * c->alpha < c->L ? (j + 1) * c->alpha : c->L;
-                const u32 lo = j * c->alpha > cr.first ? j * c->alpha : cr.first, hi = own_hi < cr.first + cr.count ? own_hi : cr.first + cr.count;
-                const u32 n = cr.count - (hi > lo ? hi - lo : 0);
-                written += n;
-                if (n > most) most = n;
-            }
-        }
+        if (DIR == CONV_UP) most = conv_up_targets(c, cr, written);
         if (!most) continue;
         a.blocks = ((L::packed ? most : cr.count) + blk - 1) / blk;
         const dim3 grid(xcd_grid(a.groups_outer * (DIR == CONV_UP ? c->dnum : 1) * tiles_of(c), a.blocks));
@@ -951,6 +955,34 @@ static void launch_conv_runs(const View* c, ConvArgs a, hipStream_t s, int only)
                      (u64)a.groups_outer * (written + (DIR == CONV_UP ? c->L : c->K)), rs);
         dispatch_kernel<L>(c, cr.fp, grid, rs, a, LimbRun{cr.first, cr.count});
     }
+}
+
+// ModUp onto both arithmetics in one launch, where the chain is FpAr limbs followed by IntAr limbs and all workgroups fit the
+// chip at once (512 = two per compute unit).  One ciphertext at N = 2^16, L = 24, dnum = 4: 24 + 17 us in two launches -> 37 us,
+// the call 163 -> 158 us; at level 13 the call 120 -> 115 us.  At N = 2^15 (three ciphertexts, level 17) it is 1 % slower: the
+// integer part pays for its 128 registers and the launches it saves are shorter.  Returns false where it does not apply.
+static bool conv_up_both(const View* c, const ConvArgs& base, hipStream_t s) {
+    const u32 ks = c->up.ks;
+    if (c->logN != 16 || (ks != 1 && ks != 2)) return false;
+    const std::vector<ClassRun> runs = class_runs(c, 0, c->D);
+    if (runs.size() != 2 || !runs[0].fp) return false;
+    ConvBothArgs a;
+    a.fp = base;
+    a.fp.aop = c->up.aop, a.fp.aop_part = c->up.aop_part, a.fp.n_full = c->up.n_full;
+    a.in = a.fp;
+    u32 w0, w1;
+    a.fp.blocks = (conv_up_targets(c, runs[0], w0) + 3) / 4, a.in.blocks = (conv_up_targets(c, runs[1], w1) + 1) / 2;
+    if (!a.fp.blocks || !a.in.blocks) return false;
+    a.run_fp = LimbRun{runs[0].first, runs[0].count}, a.run_in = LimbRun{runs[1].first, runs[1].count};
+    const u32 groups = base.groups_outer * c->dnum * tiles_of(c);
+    a.grid_fp = xcd_grid(groups, a.fp.blocks);
+    const u32 grid = a.grid_fp + xcd_grid(groups / 2, a.in.blocks);
+    if (grid > 512) return false;
+    ProfScope ps(c, c->sh->prof.on ? "conv_up_both_kernel<" + std::to_string((int)c->logN - 8) + ", " + std::to_string(ks) + ">" : std::string(),
+                 (u64)base.groups_outer * (w0 + w1 + c->L), s);
+    if (ks == 1) hipLaunchKernelGGL((conv_up_both_kernel<8, 1>), dim3(grid), dim3(512), 0, s, a, c->tb);
+    else hipLaunchKernelGGL((conv_up_both_kernel<8, 2>), dim3(grid), dim3(512), 0, s, a, c->tb);
+    return true;
 }
 
 // word format in which the last inverse stage leaves the sources of a conversion
@@ -1394,6 +1426,10 @@ static void launch_decompose_inverse(const View* c, const InvContigArgs& a, hipS
 static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, bool fp_beside = false) {
     const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0};
     SideStream& sd = c->sh->side;
+    if (conv_up_both(c, a3, s)) {  // before a fork: what follows on either stream comes after it
+        if (!fp_beside) fork_side(c, s);
+        return;
+    }
     if (fp_beside && sd.enabled && c->mixed_classes && !sd.active && side_stream_ready(sd)) {
         // the IntAr targets first, on s; the FpAr targets on the side stream from the moment those are done, beside
         // whatever s runs next (the caller joins before it reads the FpAr limbs of dt)

@@ -616,17 +616,13 @@ __device__ __forceinline__ u64 conv_recombine(const v16i& s, int o, const IntAr:
 }
 
 template <class AR, int A, int KS, int DIR, int NTT>
-__device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& tb, const LimbRun run) {
+__device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& tb, const LimbRun run, u64* lds, u64* tws, const u32 tid,
+                                               const u32 group, const u32 inst) {
     typedef NttCore<AR, A> C;
     typedef StridedTw<AR, A> TW;
     typedef typename AR::T T;
     constexpr u32 TILES = (1u << A) / 16, TPW = 2 * NTT;  // targets per workgroup
-    __shared__ u64 lds[A > 4 ? NTT * 4096 : 1];
-    __shared__ __align__(16) u64 tws[TPW * TW::WORDS];
-    const u32 N = 1u << tb.logN, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, h = lane >> 5;
-    const u32 n_dig = DIR == CONV_UP ? tb.dnum : 1;
-    u32 group, inst;
-    if (!xcd_decode(blockIdx.x, a.blocks, a.groups_outer * n_dig * TILES, group, inst)) return;
+    const u32 N = 1u << tb.logN, lane = tid & 63, wave = tid >> 6, n = lane & 31, h = lane >> 5;
     const u32 tile = group % TILES;
     u32 j = 0, ns, skip_lo = 0, skip_n = 0;
     const u64* src;
@@ -775,6 +771,19 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
     }
 }
 
+// LDS words of conv_mfma_body: the exchange, and the twiddles of its targets
+template <class AR, int A, int NTT>
+struct ConvLds {
+    static constexpr u32 exch = A > 4 ? NTT * 4096 : 2, tw = 2 * NTT * StridedTw<AR, A>::WORDS;
+};
+template <class AR, int A, int KS, int DIR, int NTT>
+__device__ __forceinline__ void conv_mfma_workgroup(const ConvArgs& a, const Tables& tb, const LimbRun run) {
+    __shared__ __align__(16) u64 lds[ConvLds<AR, A, NTT>::exch + ConvLds<AR, A, NTT>::tw];
+    u32 group, inst;
+    if (!xcd_decode(blockIdx.x, a.blocks, a.groups_outer * (DIR == CONV_UP ? tb.dnum : 1) * ((1u << A) / 16), group, inst)) return;
+    conv_mfma_body<AR, A, KS, DIR, NTT>(a, tb, run, lds, lds + ConvLds<AR, A, NTT>::exch, threadIdx.x, group, inst);
+}
+
 // targets per lane of the matrix-core form
 template <class AR>
 constexpr int conv_mfma_ntt() { return AR::is_fp ? 2 : 1; }
@@ -784,12 +793,37 @@ template <class AR, int A, int DIR, int P, bool ONE>
 __global__ __launch_bounds__(ONE ? 256 : 256 * conv_mfma_ntt<AR>(), ONE ? (AR::is_fp ? 4 : 3) : !AR::is_fp ? 3 : P <= 4 ? 4 : 2)
 void conv_fwd_strided_kernel(ConvArgs a, Tables tb, LimbRun run) {
     if constexpr (ONE) conv_one_body<AR, A, DIR, P>(a, tb, run);
-    else conv_mfma_body<AR, A, P - conv_mfma_ntt<AR>(), DIR, conv_mfma_ntt<AR>()>(a, tb, run);
+    else conv_mfma_workgroup<AR, A, P - conv_mfma_ntt<AR>(), DIR, conv_mfma_ntt<AR>()>(a, tb, run);
 }
 // ModDown onto FpAr targets, KS products per coefficient group, NTT targets per lane
 template <int A, int KS, int DIR, int NTT>
 __global__ __launch_bounds__(256 * NTT, KS <= 2 ? 4 : 2) void conv_mfma_kernel(ConvArgs a, Tables tb, LimbRun run) {
-    conv_mfma_body<FpAr, A, KS, DIR, NTT>(a, tb, run);
+    conv_mfma_workgroup<FpAr, A, KS, DIR, NTT>(a, tb, run);
+}
+// ModUp onto both classes of targets in one launch: the first workgroups convert to the FpAr run, the others to the IntAr
+// run, whose 256-lane form runs twice side by side on two tiles of one limb (same targets, hence the same barriers).  For
+// grids that fit the chip at once (conv_up_both): the two launches would take turns there, each as long as one workgroup.
+struct ConvBothArgs {
+    ConvArgs fp, in;  // differ in `blocks`
+    LimbRun run_fp, run_in;
+    u32 grid_fp;  // workgroups of the FpAr part, a multiple of 8
+};
+template <int A, int KS>
+__global__ __launch_bounds__(512, 4) void conv_up_both_kernel(ConvBothArgs a, Tables tb) {
+    static_assert(A > 4, "two tiles per limb");
+    constexpr u32 FP_WORDS = ConvLds<FpAr, A, 2>::exch + ConvLds<FpAr, A, 2>::tw, EX = ConvLds<IntAr, A, 1>::exch, TWI = ConvLds<IntAr, A, 1>::tw;
+    constexpr u32 INT_WORDS = 2 * (EX + TWI), TILES = (1u << A) / 16;
+    __shared__ __align__(16) u64 lds[FP_WORDS > INT_WORDS ? FP_WORDS : INT_WORDS];
+    u32 group, inst;
+    if (blockIdx.x < a.grid_fp) {
+        if (!xcd_decode(blockIdx.x, a.fp.blocks, a.fp.groups_outer * tb.dnum * TILES, group, inst)) return;
+        conv_mfma_body<FpAr, A, KS, CONV_UP, 2>(a.fp, tb, a.run_fp, lds, lds + ConvLds<FpAr, A, 2>::exch, threadIdx.x, group, inst);
+    } else {
+        if (!xcd_decode(blockIdx.x - a.grid_fp, a.in.blocks, a.in.groups_outer * tb.dnum * (TILES / 2), group, inst)) return;
+        const u32 half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+        conv_mfma_body<IntAr, A, KS, CONV_UP, 1>(a.in, tb, a.run_in, lds + half * (EX + TWI), lds + half * (EX + TWI) + EX, threadIdx.x & 255,
+                                                 group * 2 + half, inst);
+    }
 }
 
 // =========================================================== forward transform, second pass

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 # (logN, L, K, dnum, q bits, p bits, batch)
 SHAPES = [(12, 3, 1, 3, 49, 59, 2), (13, 5, 2, 3, 49, 59, 2), (12, 7, 4, 2, 49, 59, 2), (13, 9, 5, 2, 49, 59, 1),
           (12, 9, 8, 1, 49, 59, 2), (14, 10, 9, 2, 55, 59, 1), (12, 17, 16, 2, 49, 59, 1), (12, 18, 16, 2, 55, 59, 1),
-          (13, 4, 3, 2, 35, 40, 2), (16, 5, 4, 2, 49, 59, 1), (15, 4, 1, 4, 48, 49, 14)]
+          (13, 4, 3, 2, 35, 40, 2), (14, 6, 3, 2, 49, 59, 1), (15, 9, 5, 2, 49, 59, 1), (14, 7, 2, 4, 49, 59, 3),
+          (16, 5, 4, 2, 49, 59, 1), (15, 4, 1, 4, 48, 49, 14)]
 
 
 def _extreme(rng, primes, N, lead):
