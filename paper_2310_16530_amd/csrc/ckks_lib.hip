@@ -772,6 +772,17 @@ static void dispatch_kernel(const View* c, bool fp, dim3 grid, hipStream_t s, co
 #undef CKKS_CASE_A
 }
 
+template <class L, class ArgT>
+static void dispatch_any(const View* c, dim3 grid, hipStream_t s, const ArgT& a, LimbRun run) {
+    switch (c->logN - 8) {
+        case 4: L::template go<AnyAr, 4>(grid, s, a, c->tb, run); break;
+        case 5: L::template go<AnyAr, 5>(grid, s, a, c->tb, run); break;
+        case 6: L::template go<AnyAr, 6>(grid, s, a, c->tb, run); break;
+        case 7: L::template go<AnyAr, 7>(grid, s, a, c->tb, run); break;
+        case 8: L::template go<AnyAr, 8>(grid, s, a, c->tb, run); break;
+    }
+}
+
 static std::string kname(const char* base, const char* ar, int A, const char* tail) {
     return std::string(base) + "<" + ar + ", " + std::to_string(A) + tail + ">";
 }
@@ -790,13 +801,7 @@ static void launch_runs(const View* c, u32 lo, u32 hi, u32 limb_base, u32 groups
             const LimbRun run = {lo - limb_base, hi - lo};
             const dim3 grid(xcd_grid((hi - lo) * groups_n, inst_n));
             ProfScope ps(c, c->sh->prof.on ? L::name("AnyAr", (int)c->logN - 8) : std::string(), c->sh->prof.on ? alg(lo, hi - lo) : 0, s);
-            switch (c->logN - 8) {
-                case 4: L::template go<AnyAr, 4>(grid, s, a, c->tb, run); break;
-                case 5: L::template go<AnyAr, 5>(grid, s, a, c->tb, run); break;
-                case 6: L::template go<AnyAr, 6>(grid, s, a, c->tb, run); break;
-                case 7: L::template go<AnyAr, 7>(grid, s, a, c->tb, run); break;
-                case 8: L::template go<AnyAr, 8>(grid, s, a, c->tb, run); break;
-            }
+            dispatch_any<L>(c, grid, s, a, run);
             return;
         }
     }
@@ -1019,7 +1024,7 @@ static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t
 
 // forward transform in place: one kernel where a workgroup holds a limb, else two passes
 static void launch_forward(const View* c, u64* d_x, const LimbSel& sel, hipStream_t s) {
-    const FwdContigArgs a2 = {d_x, sel};
+    const FwdContigArgs a2 = {d_x, sel, 0, 0};
     if (!inv_one_kernel((int)c->logN - 8)) {
         const FwdStridedArgs a1 = {d_x, d_x, sel};
         launch_fwd_strided(c, a1, s);
@@ -1050,7 +1055,13 @@ template <int OWN, bool HOISTED, bool FUSED = false>
 static void launch_ks_inner(const View* c, InnerArgs a, hipStream_t s, u32 lo, u32 hi) {
     const u64 n_inst = a.n_inst;
     typedef KsInnerL<OWN, HOISTED, FUSED> L;
-    for (const ClassRun& cr : class_runs(c, lo, hi)) {
+    std::vector<ClassRun> runs = class_runs(c, lo, hi);
+    // hoisted rotations: the FP64 limbs stream keys and digits, the integer limbs are bound by instructions; in one launch
+    // they share the chip (17 rotations at N = 2^16, L = 24, in launches of 9
+    // and 8: 242 + 95 and 196 + 78 us -> 325 and 271 us)
+    const bool any = HOISTED && runs.size() > 1 && !c->sh->side.active;
+    if (any) runs.assign(1, ClassRun{lo, hi - lo, true});
+    for (const ClassRun& cr : runs) {
         a.ways = HOISTED ? 1 : inner_ways(cr.count * tiles_of(c) * a.n_inst, c->dnum);
         hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
         u64 limbs = 0;
@@ -1062,8 +1073,14 @@ static void launch_ks_inner(const View* c, InnerArgs a, hipStream_t s, u32 lo, u
                                + (FUSED ? 2 + (OWN == OWN_ROT ? 1 : 0) : 0))  // converted special part (+ sigma_g(b))
                      + (HOISTED ? n_inst : 1) * 2 * (u64)c->dnum;      // key limbs
         }
-        ProfScope ps(c, c->sh->prof.on ? L::name(cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(), limbs, rs);
-        dispatch_kernel<L>(c, cr.fp, dim3(xcd_grid(cr.count * tiles_of(c) * a.ways, a.n_inst)), rs, a, LimbRun{cr.first, cr.count});
+        const dim3 grid(xcd_grid(cr.count * tiles_of(c) * a.ways, a.n_inst));
+        ProfScope ps(c, c->sh->prof.on ? L::name(any ? "AnyAr" : cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(), limbs, rs);
+        if constexpr (HOISTED)
+            if (any) {
+                dispatch_any<L>(c, grid, rs, a, LimbRun{cr.first, cr.count});
+                continue;
+            }
+        dispatch_kernel<L>(c, cr.fp, grid, rs, a, LimbRun{cr.first, cr.count});
     }
 }
 template <int OWN, bool HOISTED>
@@ -1266,7 +1283,7 @@ static int ntt_entry(ckks_ctx* ctx, uint64_t* d_x, uint32_t prime_first, uint32_
     int rc = check_limb_range(c, prime_first, n_limbs, batch);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    const LimbSel sel = {n_limbs, batch, n_limbs, 0, prime_first, 0};
+    const LimbSel sel = {n_limbs, batch, n_limbs, 0, prime_first};
     if (!inverse) {
         launch_forward(c, d_x, sel, s);
     } else {
@@ -1470,12 +1487,18 @@ static void join_fp_beside(const View* c, hipStream_t s) {
 // conversion pre-factor.
 static void moddown_convert(const View* c, const Workspace& w, u32 cg, hipStream_t s, bool done = false) {
     if (!done) {
-        const InvStridedArgs a6 = {w.cp, LimbSel{c->K, cg * 2, c->K, 0, c->L, 0}, SC_DN, conv_src_fmt(c->dn, CONV_DN)};
+        const InvStridedArgs a6 = {w.cp, LimbSel{c->K, cg * 2, c->K, 0, c->L}, SC_DN, conv_src_fmt(c->dn, CONV_DN)};
         launch_inv_strided(c, a6, s);
     }
     join_side(c, s);  // the conversion reads every special limb
     const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, nullptr, nullptr, 0};
     launch_conv<CONV_DN>(c, a7, s);
+}
+
+// second forward pass of every extended digit of one decomposition
+static void launch_extended_fwd_contig(const View* c, const Workspace& w, hipStream_t s) {
+    const FwdContigArgs a = {w.dt, LimbSel{c->D, c->dnum, c->D, 0, 0}, c->alpha, c->L};
+    launch_fwd_contig(c, a, s);
 }
 
 // cm: the view whose ModDown ends the pipeline: c itself, or the merged view of c's level (the ModDown then
@@ -1488,7 +1511,7 @@ static void keyswitch_pipeline(const View* c, const View* cm, const u64* in1, co
     Workspace w = carve(c, ws, batch, batch, batch, false);
     if (cm != c)  // cv shrinks by one limb per component, cp grows by one: still inside the level's workspace
         w.cv = w.cp + ((size_t)batch * 2 * cm->K << c->logN);
-    const LimbSel sel = {c->L, batch, c->L, 0, 0, 0};
+    const LimbSel sel = {c->L, batch, c->L, 0, 0};
     InvContigArgs a1;
     memset(&a1, 0, sizeof(a1));
     a1.src = in1, a1.src2 = in2, a1.dst = w.x, a1.sel = sel, a1.dsel = sel, a1.galois[0] = galois;
@@ -1628,8 +1651,8 @@ static int rescale_impl(ckks_ctx* ctx, uint32_t level, const uint64_t* d_ct, uin
     w.x = w.dt = w.cq = nullptr;
     w.cp = (u64*)d_ws;                    // [b][2][1][N]
     w.cv = w.cp + (size_t)batch * 2 * N;  // [b][2][level-1][N]
-    const LimbSel src = {1, batch * 2, level, level - 1, level - 1, 0};  // limb level-1 of every component
-    const LimbSel dst = {1, batch * 2, 1, 0, level - 1, 0};
+    const LimbSel src = {1, batch * 2, level, level - 1, level - 1};  // limb level-1 of every component
+    const LimbSel dst = {1, batch * 2, 1, 0, level - 1};
     InvContigArgs a1 = {d_ct, nullptr, w.cp, src, dst, {1}, 0};
     launch_inverse<INV_PLAIN>(c, a1, SC_DN, conv_src_fmt(c->dn, CONV_DN), s);
     moddown_convert(c, w, batch, s, true);
@@ -1686,17 +1709,12 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
     const Workspace w = carve(c, d_ws, 1, 1, chunk_max);
     // hoisted part: decompose a = ct[1] once and finish the transform of every extended limb
     {
-        const LimbSel src = {c->L, 1, c->L, c->L, 0, 0};  // limbs L .. 2L-1 of ct, primes 0 .. L-1
-        const LimbSel dst = {c->L, 1, c->L, 0, 0, 0};
+        const LimbSel src = {c->L, 1, c->L, c->L, 0};  // limbs L .. 2L-1 of ct, primes 0 .. L-1
+        const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
         launch_decompose_inverse<INV_PLAIN>(c, a1, s);
         decompose_extend(c, w, 1, s);
-        if (c->dnum > 1) {
-            FwdContigArgs q = {w.dt, LimbSel{c->L, c->dnum - 1, c->D, 0, 0, c->alpha}};
-            launch_fwd_contig(c, q, s);
-        }
-        FwdContigArgs p = {w.dt, LimbSel{c->K, c->dnum, c->D, c->L, c->L, 0}};
-        launch_fwd_contig(c, p, s);
+        launch_extended_fwd_contig(c, w, s);
     }
     // rotations go through the ModDown side in chunks of at most CKKS_ROT_CHUNK, sized evenly
     const u32 n_chunks = (n_rot + CKKS_ROT_CHUNK - 1) / CKKS_ROT_CHUNK;
@@ -1766,17 +1784,12 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
         w.cv = w.cp + (size_t)2 * cm->K * N;
     }
     {  // hoisted part, as in ckks_hrot_hoisted_mac
-        const LimbSel src = {c->L, 1, c->L, c->L, 0, 0};
-        const LimbSel dst = {c->L, 1, c->L, 0, 0, 0};
+        const LimbSel src = {c->L, 1, c->L, c->L, 0};
+        const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
         launch_decompose_inverse<INV_PLAIN>(c, a1, s);
         decompose_extend(c, w, 1, s);
-        if (c->dnum > 1) {
-            FwdContigArgs q = {w.dt, LimbSel{c->L, c->dnum - 1, c->D, 0, 0, c->alpha}};
-            launch_fwd_contig(c, q, s);
-        }
-        FwdContigArgs p = {w.dt, LimbSel{c->K, c->dnum, c->D, c->L, c->L, 0}};
-        launch_fwd_contig(c, p, s);
+        launch_extended_fwd_contig(c, w, s);
     }
     join_side(c, s);  // the accumulation reads the digits of every limb
     for (u32 r0 = 0; r0 < n_rot; r0 += CKKS_DH_CHUNK) {
@@ -1789,7 +1802,7 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
         launch_dh_accum(c, ia, s);
     }
     {  // ModDown of the sum: first inverse pass of its source limbs, then the shared tail
-        const LimbSel sel = {cm->K, 2, cm->K, 0, cm->L, 0};
+        const LimbSel sel = {cm->K, 2, cm->K, 0, cm->L};
         InvContigArgs ic = {w.cp, nullptr, w.cp, sel, sel, {1}, 0};
         launch_inverse<INV_PLAIN>(cm, ic, SC_DN, conv_src_fmt(cm->dn, CONV_DN), s);
     }
@@ -1882,17 +1895,12 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
     u64* rot = inner + (size_t)n2 * 2 * LN;
     void* ks_ws = rot + (size_t)n2 * 2 * LN;
     {  // decomposition of the input, shared by every baby step
-        const LimbSel src = {c->L, 1, c->L, c->L, 0, 0};
-        const LimbSel dst = {c->L, 1, c->L, 0, 0, 0};
+        const LimbSel src = {c->L, 1, c->L, c->L, 0};
+        const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
         launch_decompose_inverse<INV_PLAIN>(c, a1, s);
         decompose_extend(c, w, 1, s);
-        if (c->dnum > 1) {
-            FwdContigArgs q = {w.dt, LimbSel{c->L, c->dnum - 1, c->D, 0, 0, c->alpha}};
-            launch_fwd_contig(c, q, s);
-        }
-        FwdContigArgs p = {w.dt, LimbSel{c->K, c->dnum, c->D, c->L, c->L, 0}};
-        launch_fwd_contig(c, p, s);
+        launch_extended_fwd_contig(c, w, s);
     }
     // baby steps: R_b = P * Rot_b(ct) in the extended basis (inner product with the key, plus P * sigma_b(b))
     join_side(c, s);
@@ -1909,7 +1917,7 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
     BsgsMacArgs ma = {rq, rp, d_pt, w.cq, w.cp, n1, n2};
     launch_bsgs_mac(c, ma, s);
     {
-        const LimbSel sel = {c->K, n2 * 2, c->K, 0, c->L, 0};
+        const LimbSel sel = {c->K, n2 * 2, c->K, 0, c->L};
         InvContigArgs ic = {w.cp, nullptr, w.cp, sel, sel, {1}, 0};
         launch_inverse<INV_PLAIN>(c, ic, SC_DN, conv_src_fmt(c->dn, CONV_DN), s);
     }

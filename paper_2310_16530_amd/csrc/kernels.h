@@ -63,16 +63,11 @@ __device__ __forceinline__ u32 eval_perm(u32 j, u32 g, u32 logN) {
 }
 
 // Limb addressing of the plain transform passes: instance `inst`, limb l of n_l:
-//   word offset (inst'*gs + first + l) * N, prime index prime_base + l, where inst' = inst unless
-//   skip_alpha != 0: then instances enumerate the digits that do NOT own limb first + l
-//   (inst' = inst + 1 from the owning digit (first + l) / skip_alpha on).
+//   word offset (inst*gs + first + l) * N, prime index prime_base + l.
 struct LimbSel {
-    u32 n_l, n_inst, gs, first, prime_base, skip_alpha;
+    u32 n_l, n_inst, gs, first, prime_base;
 };
-__device__ __forceinline__ size_t limb_offset(const LimbSel& s, u32 inst, u32 l) {
-    if (s.skip_alpha && inst >= (s.first + l) / s.skip_alpha) inst++;
-    return (size_t)inst * s.gs + s.first + l;
-}
+__device__ __forceinline__ size_t limb_offset(const LimbSel& s, u32 inst, u32 l) { return (size_t)inst * s.gs + s.first + l; }
 
 // Layout CP of the 16 words of a lane in a 256-word row (lane e0 of the row's 16): register kk holds word
 // (kk/2)*32 + e0*2 + kk%2, i.e. eight adjacent pairs: every global access of the inner product that does not feed a
@@ -830,6 +825,7 @@ __global__ __launch_bounds__(512, 4) void conv_up_both_kernel(ConvBothArgs a, Ta
 struct FwdContigArgs {
     u64* data;  // in place: raw forward-lazy words in, canonical evaluation form out
     LimbSel sel;
+    u32 own_alpha, own_L;  // own_alpha != 0: instances are digits, limb l < own_L has nothing to do in digit l / own_alpha
 };
 
 template <class AR, int A>
@@ -864,6 +860,7 @@ __global__ __launch_bounds__(256) void fwd_contig_kernel(FwdContigArgs a, Tables
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
     const u32 l = run.first + group / TILES;
+    if (a.own_alpha && l < a.own_L && l / a.own_alpha == inst) return;
     CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (fwd_contig_body<AR_, A>(a, tb, lds, l, group % TILES, inst)))
 }
 
@@ -1165,11 +1162,15 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
 
 template <class AR, int A, int OWN, bool HOISTED, bool FUSED>
 __global__ __launch_bounds__(256, 2) void ks_inner_kernel(InnerArgs a, Tables tb, LimbRun run) {
-    __shared__ u64 lds[NTT_LDS_WORDS + (AR::is_fp && !HOISTED ? 16 * CKKS_ROW_TW_WORDS : 0)];
+    constexpr bool ANY = __is_same(AR, AnyAr), TWL = !HOISTED && !__is_same(AR, IntAr);
+    static_assert(HOISTED || !ANY, "the twiddle block in LDS belongs to one arithmetic");
+    __shared__ u64 lds[NTT_LDS_WORDS + (TWL ? 16 * CKKS_ROW_TW_WORDS : 0)];
     const u32 TILES = (1u << A) / 16 * (HOISTED ? 1 : a.ways);
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.n_inst, run.count * TILES, group, inst)) return;
-    ks_inner_body<AR, A, OWN, HOISTED, FUSED>(a, tb, lds, run.first + group / TILES, group % TILES, inst);
+    // both arithmetics in one launch: the special limbs, the longer workgroups, first
+    const u32 i = ANY ? run.first + run.count - 1 - group / TILES : run.first + group / TILES;
+    CKKS_BY_ARITHMETIC(AR, i, (ks_inner_body<AR_, A, OWN, HOISTED, FUSED>(a, tb, lds, i, group % TILES, inst)))
 }
 
 // ===================================================== double-hoisted rotate-multiply-accumulate
