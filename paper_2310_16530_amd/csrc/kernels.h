@@ -2,10 +2,13 @@
 // the major, memory-bound kernels and fuses several jobs into each memory load; here every
 // producer and consumer of a transform is fused into one of the two NTT passes:
 //
-//   inv_contig_kernel   load (copy | a1*a2 | sigma_g gather) -> first inverse pass
+//   inv_contig_kernel   load (copy | a1*a2 | sigma_g gather) -> first inverse pass (N <= 2^13: both)
 //   inv_strided_kernel  second inverse pass -> scale by N^-1 (* base-conversion pre-factor)
-//   fwd_strided_kernel  load (plain | base conversion from the digit / special limbs) -> first forward pass
+//   conv_fwd_strided_kernel, conv_mfma_kernel, conv_up_both_kernel
+//                       base conversion from the digit / special limbs -> first forward pass of the targets
+//   fwd_strided_kernel  load -> first forward pass
 //   fwd_contig_kernel   second forward pass -> canonical store
+//   fwd_whole_kernel    both forward passes, N <= 2^13
 //   ks_inner_kernel     second forward pass of every extended digit -> key inner product accumulated over
 //                       the digits in registers (+ P * tensor terms of HMult) -> special limbs: first inverse
 //                       pass of ModDown; q-limbs, launched after the ModDown conversion: second forward pass
@@ -18,7 +21,7 @@
 //
 // Levels below L, rescale and the ModDown merged with a rescale reuse these kernels on per-level tables.
 //
-// Every kernel picks its arithmetic per limb: FpAr for primes below 3*2^48, IntAr otherwise.
+// Every limb has its arithmetic: FpAr for primes below 3*2^48, IntAr otherwise.
 #pragma once
 #include "ntt.h"
 
@@ -583,33 +586,7 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
 // all loads from one cached row: 121 -> 78 us per launch) is the limit rather than the arithmetic, so four targets share a
 // load where the registers allow it: FpAr targets need 128 (four waves per SIMD): 121 -> 111 us ModUp, 84 -> 71 us
 // ModDown.  IntAr targets do not fit 128 (spills, 61 -> 66 us) and take NTT = 1.
-typedef int v16i __attribute__((ext_vector_type(16)));
 typedef int v4i __attribute__((ext_vector_type(4)));
-// V of an FpAr target reduced to |.| <= (0.5 + 2^-15) m, exactly: pairs of digits are joined as 32-bit integers (below
-// 2^30), lo = digits 0..3 (below 2^47), hi = digits 4..6 times 2^32 (an integer multiple of 2^32 with 38 significant
-// bits: exact); the quotient estimate of (hi + lo) / m is off by less than 2^-15 before rounding, hi - c*m is an integer
-// below 2^53 in magnitude, so the fma and the sum are exact.
-__device__ __forceinline__ double conv_recombine(const v16i& s, int o, const FpAr::Mod& m, const PrimeConst&) {
-    const int p0 = s[o + 0] + s[o + 1] * 256, p1 = s[o + 2] + s[o + 3] * 256, p2 = s[o + 4] + s[o + 5] * 256;
-    const double lo = __builtin_fma((double)p1, 65536.0, (double)p0);
-    const double hi = __builtin_fma((double)s[o + 6], 281474976710656.0, (double)p2 * 4294967296.0);
-    const double c = __builtin_rint((hi + lo) * m.qinv);
-    return __builtin_fma(-c, m.q, hi) + lo;
-}
-// V of an IntAr target (m >= 3*2^48) as a word in (0.4 m, 1.6 m): V = lo + 2^32 t with |lo| < 2^47, t = digits 4..7 exact
-// in a double (below 2^47); z = 1 - rint(t * 2^32 / m) appears as the low bits of one fma onto 1.5*2^52, |lo| / m < 0.09
-// is what the estimate leaves out, and V + z*m is formed modulo 2^64 with m = mh * 2^32 + (signed low half).  14
-// instructions, where six 128-bit multiply-accumulates and a Montgomery reduction took 62.
-__device__ __forceinline__ u64 conv_recombine(const v16i& s, int o, const IntAr::Mod& m, const PrimeConst& pc) {
-    const int p0 = s[o + 0] + s[o + 1] * 256, p1 = s[o + 2] + s[o + 3] * 256, p2 = s[o + 4] + s[o + 5] * 256, p3 = s[o + 6] + s[o + 7] * 256;
-    const double t = __builtin_fma((double)p3, 65536.0, (double)p2);
-    const int z = (int)(u32)__builtin_bit_cast(u64, __builtin_fma(t, pc.qinv * -4294967296.0, 6755399441055744.0 + 1.0));
-    const int ml = (int)(u32)m.q;
-    const u32 mh = (u32)(m.q >> 32) + (ml < 0 ? 1u : 0u);
-    const u64 lo = (u64)((int64_t)p1 * 65536 + p0 + (int64_t)z * ml);
-    return lo + ((u64)((u32)p2 + ((u32)p3 << 16) + (u32)z * mh) << 32);
-}
-
 template <class AR, int A, int KS, int DIR, int NTT>
 __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& tb, const LimbRun run, u64* lds, u64* tws, const u32 tid,
                                                const u32 group, const u32 inst) {

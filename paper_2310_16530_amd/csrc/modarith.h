@@ -125,7 +125,6 @@ struct IntAr {
     static HD T from_canon(u64 v, const Mod&) { return v; }
     static HD T from_raw(u64 v) { return v; }
     static HD u64 to_raw(T v) { return v; }
-    static HD T from_f64_lazy(double, const Mod&) { return 0; }  // FP64 conversion path is FpAr-only
     // product of two canonical residues, as a value the transforms accept
     static HD T mul_canon(u64 a, u64 b, const PrimeConst& p, const Mod&) { return mulmod_var(a, b, p.q, p.qneg, p.r2); }
     // forward: values in [0, 8q) (8q < 2^64 for primes below 2^61).  A stage adds less than 2q to its inputs
@@ -173,12 +172,6 @@ struct IntAr {
         return mul_shoup_lazy(acc, m.r1, m.r1_p, m.q);
     }
     static HD u64 acc_canon(T fin, const Mod& m) { return csub(fin, m.q); }
-    // product of two canonical residues as an acc_mac operand carrying one more factor 2^-64 (in [0, 2q))
-    static HD T premul(u64 a, u64 b, const Mod& m) {
-        u128w p = {0, 0};
-        mac128(p, a, b);
-        return redc_lazy(p, m.q, m.qneg);
-    }
     // unreduced sum of products of two canonical residues: at most 8 terms (8 q^2 < q * 2^64), then wide_reduce gives the
     // sum times 2^-64 in [0, 2q)
     typedef u128w Wide;
@@ -192,7 +185,7 @@ struct IntAr {
     }
     // acc_mac of a wide_reduce result with a canonical residue: one more factor 2^-64 (acc_finish2 removes both)
     static HD void acc_mac_wide(T& acc, T v, u64 b, const Mod& m) { acc_mac(acc, v, b, m); }
-    // finish of an accumulation whose operands came from premul or wide_reduce: removes 2^-128
+    // finish of an accumulation whose operands came from wide_reduce: removes 2^-128
     static HD T acc_finish2(T acc, const Mod& m) {
         return mul_shoup_lazy(mul_shoup_lazy(acc, m.r1, m.r1_p, m.q), m.r1, m.r1_p, m.q);
     }
@@ -243,7 +236,6 @@ struct FpAr {
     static HD T from_canon(u64 v, const Mod&) { return u64_to_f64(v); }
     static HD T from_raw(u64 v) { return __builtin_bit_cast(double, v); }
     static HD u64 to_raw(T v) { return __builtin_bit_cast(u64, v); }
-    static HD T from_f64_lazy(double v, const Mod& m) { return reduce(v, m); }
     static HD T mul_canon(u64 a, u64 b, const PrimeConst&, const Mod& m) {
         return mulmod_lazy(u64_to_f64(a), u64_to_f64(b), m);  // |result| <= 0.875 q
     }
@@ -311,3 +303,32 @@ struct FpAr {
     static HD void acc_mac_wide(T& acc, T v, u64 b, const Mod& m) { acc += mulmod_lazy(v, u64_to_f64(b), m); }
     static HD T acc_finish2(T acc, const Mod& m) { return reduce(acc, m); }
 };
+
+// ------------------------------------------- recombination of a base conversion's digit sums (see conv_mfma_body)
+// s[o + g] = S_g, the sum over sources and source digits of (digit g of the folded constant) * (source digit);
+// |S_g| <= 17 * 2^17, V = sum_g 256^g S_g, |V| <= 2^14 m.
+typedef int v16i __attribute__((ext_vector_type(16)));
+// V of an FpAr target reduced to |.| <= (0.5 + 2^-15) m, exactly: pairs of digits are joined as 32-bit integers (below
+// 2^30), lo = digits 0..3 (below 2^47), hi = digits 4..6 times 2^32 (an integer multiple of 2^32 with 38 significant
+// bits: exact); the quotient estimate of (hi + lo) / m is off by less than 2^-15 before rounding, hi - c*m is an integer
+// below 2^53 in magnitude, so the fma and the sum are exact.
+HD double conv_recombine(const v16i& s, int o, const FpAr::Mod& m, const PrimeConst&) {
+    const int p0 = s[o + 0] + s[o + 1] * 256, p1 = s[o + 2] + s[o + 3] * 256, p2 = s[o + 4] + s[o + 5] * 256;
+    const double lo = __builtin_fma((double)p1, 65536.0, (double)p0);
+    const double hi = __builtin_fma((double)s[o + 6], 281474976710656.0, (double)p2 * 4294967296.0);
+    const double c = __builtin_rint((hi + lo) * m.qinv);
+    return __builtin_fma(-c, m.q, hi) + lo;
+}
+// V of an IntAr target (m >= 3*2^48) as a word in (0.4 m, 1.6 m): V = lo + 2^32 t with |lo| < 2^47, t = digits 4..7 exact
+// in a double (below 2^47); z = 1 - rint(t * 2^32 / m) appears as the low bits of one fma onto 1.5*2^52, |lo| / m < 0.09
+// is what the estimate leaves out, and V + z*m is formed modulo 2^64 with m = mh * 2^32 + (signed low half).  14
+// instructions, where six 128-bit multiply-accumulates and a Montgomery reduction took 62.
+HD u64 conv_recombine(const v16i& s, int o, const IntAr::Mod& m, const PrimeConst& pc) {
+    const int p0 = s[o + 0] + s[o + 1] * 256, p1 = s[o + 2] + s[o + 3] * 256, p2 = s[o + 4] + s[o + 5] * 256, p3 = s[o + 6] + s[o + 7] * 256;
+    const double t = __builtin_fma((double)p3, 65536.0, (double)p2);
+    const int z = (int)(u32)__builtin_bit_cast(u64, __builtin_fma(t, pc.qinv * -4294967296.0, 6755399441055744.0 + 1.0));
+    const int ml = (int)(u32)m.q;
+    const u32 mh = (u32)(m.q >> 32) + (ml < 0 ? 1u : 0u);
+    const u64 lo = (u64)((int64_t)p1 * 65536 + p0 + (int64_t)z * ml);
+    return lo + ((u64)((u32)p2 + ((u32)p3 << 16) + (u32)z * mh) << 32);
+}
