@@ -225,7 +225,7 @@ __device__ __forceinline__ void inv_contig_body(const InvContigArgs& a, const Ta
     u64* lrow = lds + ch * 272;
     typename AR::T x[16];
     inv_load_row<AR, LOAD>(x, a, tb, pc, lrow, l, r, e0, inst);
-    NttCore<AR, A>::inv_contig(x, lrow, e0, r, ti, tf, N, m);
+    NttCore<AR, A>::template inv_contig<true>(x, lrow, e0, r, ti, tf, N, m);
     u64* o = a.dst + limb_offset(a.dsel, inst, l) * N + (size_t)r * 256;
 #pragma unroll
     for (int k = 0; k < 16; k++) o[k * 16 + e0] = AR::to_raw(AR::round_reduce(x[k], m));
