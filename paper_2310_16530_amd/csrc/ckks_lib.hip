@@ -752,6 +752,12 @@ static std::vector<ClassRun> class_runs(const View* c, u32 lo, u32 hi) {
     return r;
 }
 
+static bool any_fp_prime(const View* c, u32 lo, u32 hi) {
+    for (u32 i = lo; i < hi; i++)
+        if (c->primes[i] < CKKS_FP_PRIME_LIMIT) return true;
+    return false;
+}
+
 // A launcher type L provides
 //   template <class AR, int A> static void go(grid, stream, args, tables, run)   the launch
 //   static std::string name(const char* ar, int A)                               the profiler's kernel name
@@ -837,7 +843,8 @@ struct FwdStridedL {
     static constexpr bool any = true;
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const FwdStridedArgs& a, const Tables& tb, LimbRun run) {
-        hipLaunchKernelGGL((fwd_strided_kernel<AR, A>), g, dim3(256), 0, s, a, tb, run);
+        if constexpr (!inv_one_kernel(A) || (A == 5 && __is_same(AR, IntAr)))  // what launch_forward sends here
+            hipLaunchKernelGGL((fwd_strided_kernel<AR, A>), g, dim3(256), 0, s, a, tb, run);
     }
     static std::string name(const char* ar, int A) { return kname("fwd_strided_kernel", ar, A, ""); }
 };
@@ -911,12 +918,28 @@ static void launch_inv_strided(const View* c, const InvStridedArgs& a, hipStream
                              [per](u32, u32 n) { return per * n; });
 }
 
+// At N = 2^13 a few integer limbs are faster in two passes over twice the workgroups than in one kernel each: the workgroup
+// of a limb then is all of the time, and its integer butterflies, two wavefronts a SIMD, take longer than a launch.  Forward /
+// inverse, 1 limb: 12.2 against 14.0 us / 14.5 against 15.1; 24 limbs 13.2 against 14.5 / 15.5 against 15.6; 64 limbs 14.5 against
+// 14.9 / 16.9 against 16.0; 80 limbs 15.0 against 15.1.  FP64 limbs: one kernel at every size (1 limb 10.8 against 7.7 / 10.6
+// against 8.6), a range that mixes both likewise.
+static bool spread_limbs(const View* c, const LimbSel& sel, u32 most) {
+    return c->logN == 13 && sel.n_l * sel.n_inst <= most && !any_fp_prime(c, sel.prime_base, sel.prime_base + sel.n_l);
+}
+
 // The inverse transform of a.sel's limbs into a.dst
 template <int LOAD>
 static void launch_inverse(const View* c, InvContigArgs a, u32 scale, u32 out_fmt, hipStream_t s) {
     a.scale = scale, a.out_fmt = out_fmt;
-    launch_inv_contig<LOAD>(c, a, s);
-    if (inv_one_kernel((int)c->logN - 8)) return;
+    if (LOAD == INV_PLAIN && spread_limbs(c, a.sel, 24)) {
+        hipStream_t rs = c->sh->side.active ? c->sh->side.stream : s;
+        ProfScope ps(c, c->sh->prof.on ? kname("inv_contig_rows_kernel", "IntAr", 5, ", 0") : std::string(), (u64)a.sel.n_l * a.sel.n_inst * 2, rs);
+        hipLaunchKernelGGL((inv_contig_rows_kernel<IntAr, 5, INV_PLAIN>), dim3(xcd_grid(a.sel.n_l * tiles_of(c), a.sel.n_inst)), dim3(256), 0, rs,
+                           a, c->tb, LimbRun{0, a.sel.n_l});
+    } else {
+        launch_inv_contig<LOAD>(c, a, s);
+        if (inv_one_kernel((int)c->logN - 8)) return;
+    }
     const InvStridedArgs a2 = {a.dst, a.dsel, scale, out_fmt};
     launch_inv_strided(c, a2, s);
 }
@@ -1025,7 +1048,7 @@ static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t
 // forward transform in place: one kernel where a workgroup holds a limb, else two passes
 static void launch_forward(const View* c, u64* d_x, const LimbSel& sel, hipStream_t s) {
     const FwdContigArgs a2 = {d_x, sel, 0, 0};
-    if (!inv_one_kernel((int)c->logN - 8)) {
+    if (!inv_one_kernel((int)c->logN - 8) || spread_limbs(c, sel, 64)) {
         const FwdStridedArgs a1 = {d_x, d_x, sel};
         launch_fwd_strided(c, a1, s);
         launch_fwd_contig(c, a2, s);
@@ -1463,12 +1486,6 @@ static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipS
     }
     fork_side(c, s);  // from here the special-limb (IntAr) chain runs beside the q-limb chain
     launch_conv<CONV_UP>(c, a3, s);
-}
-
-static bool any_fp_prime(const View* c, u32 lo, u32 hi) {
-    for (u32 i = lo; i < hi; i++)
-        if (c->primes[i] < CKKS_FP_PRIME_LIMIT) return true;
-    return false;
 }
 
 // s waits for the FpAr conversion that decompose_extend put on the side stream

@@ -288,6 +288,16 @@ __global__ __launch_bounds__(inv_one_kernel(A) ? 16 << A : 256) void inv_contig_
     else { CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (inv_contig_body<AR_, A, LOAD>(a, tb, lds, l, group % TILES, inst))) }
 }
 
+// the first pass alone where inv_contig_kernel would run both (spread_limbs on the host)
+template <class AR, int A, int LOAD>
+__global__ __launch_bounds__(256) void inv_contig_rows_kernel(InvContigArgs a, Tables tb, LimbRun run) {
+    __shared__ u64 lds[NTT_LDS_WORDS];
+    constexpr u32 TILES = (1u << A) / 16;
+    u32 group, inst;
+    if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
+    inv_contig_body<AR, A, LOAD>(a, tb, lds, run.first + group / TILES, group % TILES, inst);
+}
+
 // =========================================================== inverse transform, second pass
 struct InvStridedArgs {
     u64* data;  // in place: raw inverse-lazy words in, canonical coefficients (times the scale) out
