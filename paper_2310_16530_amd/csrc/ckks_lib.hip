@@ -1134,7 +1134,7 @@ static void launch_bsgs_mac(const View* c, const BsgsMacArgs& a, hipStream_t s) 
     }
 }
 
-// all limbs of the extended basis in one launch; the caller has joined the side stream
+// all limbs of the extended basis in one launch
 static void launch_dh_accum(const View* c, DhInnerArgs a, hipStream_t s) {
     const u64 n_rot = a.n_rot, acc = a.accumulate ? 2 : 0, dnum = c->dnum;
     // One row per workgroup, its rotations shared by the four wavefronts, or four rows: with fewer than eight rotations the
@@ -1463,14 +1463,17 @@ template <int LOAD>
 static void launch_decompose_inverse(const View* c, const InvContigArgs& a, hipStream_t s) {
     launch_inverse<LOAD>(c, a, SC_UP, conv_src_fmt(c->up, CONV_UP), s);
 }
-static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, bool fp_beside = false) {
+// What follows the ModUp: PLAIN on one stream; BESIDE the FpAr targets may run on the side stream (keyswitch_pipeline); FORK the
+// integer limbs take the side stream from here on.
+enum ExtendMode { EXTEND_PLAIN, EXTEND_BESIDE, EXTEND_FORK };
+static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, ExtendMode mode) {
     const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0};
     SideStream& sd = c->sh->side;
     if (conv_up_both(c, a3, s)) {  // before a fork: what follows on either stream comes after it
-        if (!fp_beside) fork_side(c, s);
+        if (mode == EXTEND_FORK) fork_side(c, s);
         return;
     }
-    if (fp_beside && sd.enabled && c->mixed_classes && !sd.active && side_stream_ready(sd)) {
+    if (mode == EXTEND_BESIDE && sd.enabled && c->mixed_classes && !sd.active && side_stream_ready(sd)) {
         // the IntAr targets first, on s; the FpAr targets on the side stream from the moment those are done, beside
         // whatever s runs next (the caller joins before it reads the FpAr limbs of dt)
         launch_conv<CONV_UP>(c, a3, s, 0);
@@ -1484,7 +1487,7 @@ static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipS
         launch_conv<CONV_UP>(c, a3, s, 1);
         return;
     }
-    fork_side(c, s);  // from here the special-limb (IntAr) chain runs beside the q-limb chain
+    if (mode == EXTEND_FORK) fork_side(c, s);
     launch_conv<CONV_UP>(c, a3, s);
 }
 
@@ -1541,7 +1544,7 @@ static void keyswitch_pipeline(const View* c, const View* cm, const u64* in1, co
             a1.galois[b] = ia.galois[b] = multi_galois[b], ia.key[b] = multi_keys[b];
     }
     launch_decompose_inverse<LOAD>(c, a1, s);
-    decompose_extend(c, w, batch, s, true);
+    decompose_extend(c, w, batch, s, EXTEND_BESIDE);
     ia.dt = w.dt, ia.own = in1, ia.own2 = in2;
     ia.cq = w.cq, ia.cp = w.cp, ia.n_inst = batch, ia.split = cm->L;
     // the limbs that feed the ModDown conversion first; the q-limbs then finish in one kernel, c' in registers.
@@ -1724,18 +1727,23 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
     const size_t N = (size_t)1 << c->logN;
     const u32 chunk_max = n_rot < CKKS_ROT_CHUNK ? n_rot : CKKS_ROT_CHUNK;
     const Workspace w = carve(c, d_ws, 1, 1, chunk_max);
+    // rotations go through the ModDown side in chunks of at most CKKS_ROT_CHUNK, sized evenly
+    const u32 n_chunks = (n_rot + CKKS_ROT_CHUNK - 1) / CKKS_ROT_CHUNK;
+    const u32 chunk = (n_rot + n_chunks - 1) / n_chunks;
+    // Second stream: the special-limb (IntAr) chain of a chunk beside its q-limb chain, where the inner product is at least five
+    // rounds of workgroups.  Below, the launches that both classes share on one stream gain more than the events cost.
+    // N = 2^16, one stream / two: L + K = 30, 7 rotations (3360 workgroups) 550 / 526 us, 3 (1440) 303 / 314, 1 182 / 198;
+    // 13 + 6, chunks of 9 (2736) 730 / 710; 10 + 5, chunks of 9 (2160) 546 / 567.
+    const bool fork = chunk * c->D * tiles_of(c) >= 5 * 512;
     // hoisted part: decompose a = ct[1] once and finish the transform of every extended limb
     {
         const LimbSel src = {c->L, 1, c->L, c->L, 0};  // limbs L .. 2L-1 of ct, primes 0 .. L-1
         const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
         launch_decompose_inverse<INV_PLAIN>(c, a1, s);
-        decompose_extend(c, w, 1, s);
+        decompose_extend(c, w, 1, s, fork ? EXTEND_FORK : EXTEND_PLAIN);
         launch_extended_fwd_contig(c, w, s);
     }
-    // rotations go through the ModDown side in chunks of at most CKKS_ROT_CHUNK, sized evenly
-    const u32 n_chunks = (n_rot + CKKS_ROT_CHUNK - 1) / CKKS_ROT_CHUNK;
-    const u32 chunk = (n_rot + n_chunks - 1) / n_chunks;
     for (u32 r0 = 0; r0 < n_rot; r0 += chunk) {
         const u32 nr = (n_rot - r0) < chunk ? (n_rot - r0) : chunk;
         InnerArgs ia;
@@ -1748,7 +1756,7 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
             fa.galois[r] = h_galois[r0 + r];
         }
         ia.dt = w.dt, ia.own = d_ct, ia.cq = w.cq, ia.cp = w.cp, ia.n_inst = nr, ia.split = c->L;
-        fork_side(c, s);  // no-op in the first chunk (still forked); later chunks wait for the previous ModDown
+        if (fork) fork_side(c, s);  // no-op in the first chunk (still forked); later chunks wait for the previous ModDown
         launch_ks_inner<OWN_COPY, true>(c, ia, s);
         moddown_convert(c, w, nr, s);
         fa.cq = w.cq, fa.cq_L = c->L, fa.cv = w.cv, fa.ct1 = d_ct, fa.pt = d_pt + (size_t)r0 * c->L * N, fa.out = d_out;
@@ -1805,10 +1813,9 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
         const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
         launch_decompose_inverse<INV_PLAIN>(c, a1, s);
-        decompose_extend(c, w, 1, s);
+        decompose_extend(c, w, 1, s, EXTEND_PLAIN);
         launch_extended_fwd_contig(c, w, s);
     }
-    join_side(c, s);  // the accumulation reads the digits of every limb
     for (u32 r0 = 0; r0 < n_rot; r0 += CKKS_DH_CHUNK) {
         const u32 nr = (n_rot - r0) < CKKS_DH_CHUNK ? (n_rot - r0) : CKKS_DH_CHUNK;
         DhInnerArgs ia;
@@ -1916,11 +1923,10 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
         launch_decompose_inverse<INV_PLAIN>(c, a1, s);
-        decompose_extend(c, w, 1, s);
+        decompose_extend(c, w, 1, s, EXTEND_PLAIN);
         launch_extended_fwd_contig(c, w, s);
     }
     // baby steps: R_b = P * Rot_b(ct) in the extended basis (inner product with the key, plus P * sigma_b(b))
-    join_side(c, s);
     for (u32 b0 = 0; b0 < n1; b0 += CKKS_DH_CHUNK) {
         const u32 nb = (n1 - b0) < CKKS_DH_CHUNK ? (n1 - b0) : CKKS_DH_CHUNK;
         DhInnerArgs ia;

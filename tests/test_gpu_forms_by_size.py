@@ -39,3 +39,56 @@ def test_few_integer_limbs_at_n_2_13_take_two_passes(orc, n, batch):
     y = synth.uniform_residues(rng, ps.primes[:2], ps.N, lead=(2,))
     got, names = _kernels(ctx, lambda: ctx.intt(dev(y)))
     assert np.array_equal(got, orc.ntt_batch(y, P, 0, inverse=True)) and len(names) == 1, names
+
+
+def test_second_stream_leaves_the_joint_launches_of_hoisted_calls_whole(orc):
+    """The decomposition of a double-hoisted or baby-step giant-step call, and a small hoisted call, launch the same kernels
+    with the second stream on: split by arithmetic over two streams they took up to a tenth longer."""
+    ps = synth.small_params(13, 6, 3, 2)
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(77)
+    gs = [synth.galois_element(r, ps.logN) for r in (1, 2, 3)]
+    rks = [synth.uniform_residues(rng, ps.primes, ps.N, lead=(ps.dnum, 2)) for _ in gs]
+    d_rks = [dev(k) for k in rks]
+    ct = synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(2,))
+    pt = synth.uniform_residues(rng, ps.primes, ps.N, lead=(3,))
+    ptq = np.ascontiguousarray(pt[:, :ps.L])
+    calls = ((lambda: ctx.hrot_dh_mac(dev(ct), gs, d_rks, dev(pt)), orc.hrot_dh_mac_level(ct, gs, rks, pt, P)),
+             (lambda: ctx.hrot_hoisted_mac(dev(ct), gs, d_rks, dev(ptq)), orc.hrot_hoisted_mac(ct, gs, rks, ptq, P)))
+    for call, want in calls:
+        got, one = _kernels(ctx, call)
+        assert np.array_equal(got, want)
+        ctx.set_overlap(True)
+        try:
+            got, two = _kernels(ctx, call)
+        finally:
+            ctx.set_overlap(False)
+        assert np.array_equal(got, want) and two == one, two ^ one
+
+
+@pytest.mark.parametrize("n_rot", [16, 32])
+def test_hoisted_rotations_with_the_second_stream_at_work(orc, n_rot):
+    """From five rounds of inner-product workgroups on (16 rotations, L + K = 10, N = 2^16) the integer limbs run on the second
+    stream; 32 rotations fork once more after the first chunk's ModDown."""
+    ps = synth.small_params(16, 8, 2, 2)
+    ctx = gpu_ctx(ps)
+    rng = np.random.default_rng(1616)
+    gs = [synth.galois_element(r + 1, ps.logN) for r in range(n_rot)]
+    keys = [synth.uniform_residues(rng, ps.primes, ps.N, lead=(ps.dnum, 2)) for _ in range(3)]
+    d_keys = [dev(k) for k in keys]
+    ct, pt = synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(2,)), synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(n_rot,))
+    d_ct, d_pt = dev(ct), dev(pt)
+    call = lambda: ctx.hrot_hoisted_mac(d_ct, gs, [d_keys[r % 3] for r in range(n_rot)], d_pt)
+    print("rotations", n_rot, flush=True)
+    want = host(call())
+    if n_rot == 16:
+        assert np.array_equal(want, orc.hrot_hoisted_mac(ct, gs, [keys[r % 3] for r in range(n_rot)], pt, orc_params(orc, ps)))
+    ctx.set_overlap(True)
+    try:
+        got, names = _kernels(ctx, call)
+        assert np.array_equal(got, want)
+        assert "ks_inner_kernel<IntAr, 8, 0, true, false>" in names, names
+        for _ in range(2):
+            assert np.array_equal(host(call()), want)
+    finally:
+        ctx.set_overlap(False)
