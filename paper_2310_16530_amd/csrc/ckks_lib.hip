@@ -1134,17 +1134,26 @@ static void launch_bsgs_mac(const View* c, const BsgsMacArgs& a, hipStream_t s) 
     }
 }
 
-// all limbs of the extended basis in one launch
+// All limbs of the extended basis in one launch.  Chains of integer primes alone take the narrow form: with few digits the
+// unreduced sums save an integer limb no products, and three waves per SIMD leave it waiting where FP64 limbs beside it would
+// fill in.  9 rotations at N = 2^16, L + K = 12 + 4, dnum = 3: the call 248 us before the wide form, 268 with it, 257 with
+// the narrow one; at N = 2^15, 27 + 3, dnum = 9, 5 rotations: 346, 365, 346.  On mixed chains the wide form is the faster one
+// (18 rotations, 24 + 6, dnum = 4: 669 against 683 us).
 static void launch_dh_accum(const View* c, DhInnerArgs a, hipStream_t s) {
     const u64 n_rot = a.n_rot, acc = a.accumulate ? 2 : 0, dnum = c->dnum;
-    // One row per workgroup, its rotations shared by the four wavefronts, or four rows: with fewer than eight rotations the
-    // wavefronts would end up with unequal shares, which only a grid below two workgroups per compute unit makes up for
-    const u32 rows = c->D << (c->logN - 8);
-    a.waves = n_rot >= 8 || (rows / 4 < 512 && n_rot > 1) ? 4 : 1;
+    const bool narrow = !any_fp_prime(c, 0, c->D);
+    const u32 rows = c->D * ((1u << c->logN) / (64 * (narrow ? dh_words<IntAr>() : dh_words<AnyAr>())));
+    // Four rows per workgroup, or one whose rotations the four wavefronts share.  Narrow: fewer rounds of the 1280 resident
+    // workgroups times rotations per wavefront.  Wide: with fewer than eight rotations the wavefronts would end up with
+    // unequal shares, which only a grid below two workgroups per compute unit makes up for.
+    if (narrow) a.waves = (rows + 1279) / 1280 * ((a.n_rot + 3) / 4) < (rows / 4 + 1279) / 1280 * a.n_rot ? 4 : 1;
+    else a.waves = n_rot >= 8 || (rows / 4 < 512 && n_rot > 1) ? 4 : 1;
     u64 limbs = 0;  // per limb and rotation: the digits, the plaintext, both key components (and b on q-limbs); C_t written
     for (u32 i = 0; i < c->D; i++) limbs += n_rot * (3 * dnum + (a.pt ? 1 : 0) + (i < c->L ? 1 : 0)) + (a.each ? 2 * n_rot : 2) + acc;
-    ProfScope ps(c, std::string("dh_accum_kernel"), limbs, s);
-    hipLaunchKernelGGL(dh_accum_kernel, dim3((rows * a.waves / 4 + 7) / 8 * 8), dim3(256), 0, s, a, c->tb);
+    ProfScope ps(c, c->sh->prof.on ? std::string(narrow ? "dh_accum_kernel<IntAr>" : "dh_accum_kernel<AnyAr>") : std::string(), limbs, s);
+    const dim3 grid((rows * a.waves / 4 + 7) / 8 * 8);
+    if (narrow) hipLaunchKernelGGL(dh_accum_kernel<IntAr>, grid, dim3(256), 0, s, a, c->tb);
+    else hipLaunchKernelGGL(dh_accum_kernel<AnyAr>, grid, dim3(256), 0, s, a, c->tb);
 }
 
 template <int MODE>

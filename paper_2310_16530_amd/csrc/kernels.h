@@ -1193,20 +1193,44 @@ struct DhInnerArgs {
     u32 each;        // rotations are not summed: rotation r's result goes to cq + r*2*split*N, cp + r*2*(D - split)*N
 };
 
+// words per lane; a row, a wavefront's share, is 64 times that
 template <class AR>
+constexpr int dh_words() { return __is_same(AR, AnyAr) ? 4 : 2; }
+// Sum over the rotations of (unreduced digit sum, reduced) * plaintext, at most 8 terms between folds
+template <class AR, int W>
+struct DhSum {
+    typename AR::T s;
+    __device__ __forceinline__ DhSum() : s(AR::acc_zero()) {}
+    __device__ __forceinline__ void add(typename AR::T v, u64 b, const typename AR::Mod& m) { AR::acc_mac_wide(s, v, b, m); }
+    __device__ __forceinline__ void fold(const typename AR::Mod& m) { s = AR::acc_fold(s, m); }
+    __device__ __forceinline__ typename AR::T get(const typename AR::Mod&) const { return s; }
+};
+// 128 bits where the registers allow it: one reduction at the end instead of one per term.  v < 2q and b < q < 2^61 make a term
+// less than q * 2^62, eight of them on hi < q less than 3q * 2^64; multiples of q * 2^64 are taken off by hi alone.
+template <>
+struct DhSum<IntAr, 2> {
+    u128w s;
+    __device__ __forceinline__ DhSum() : s{0, 0} {}
+    __device__ __forceinline__ void add(u64 v, u64 b, const IntAr::Mod&) { mac128(s, v, b); }
+    __device__ __forceinline__ void fold(const IntAr::Mod& m) { s.hi = csub(csub(s.hi, m.q2), m.q); }
+    __device__ __forceinline__ u64 get(const IntAr::Mod& m) const { return redc_lazy(u128w{s.lo, csub(csub(s.hi, m.q2), m.q)}, m.q, m.qneg); }
+};
+
+template <class AR, int W>
 __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables& tb, const PrimeConst& pc, u64* lds, u32 i, u32 row, u32 wave) {
     typedef typename AR::T T;
-    typedef typename AR::Wide W;
+    typedef typename AR::Wide Wide;
+    constexpr u32 ROW = 64 * W;
     const u32 logN = tb.logN, N = 1u << logN, lane = threadIdx.x & 63, L = tb.L, D = tb.D;
     const u32 pi = tb.phys(i), Dkey = tb.Lfull + tb.K;
     const bool is_q = i < L;
     const typename AR::Mod m = AR::mod(pc);
-    const u32 own_digit = is_q ? i / tb.alpha : 0xffffffffu, row_off = row * 256;
+    const u32 own_digit = is_q ? i / tb.alpha : 0xffffffffu, row_off = row * ROW;
     const u64 pmod = is_q ? tb.pmod[i] : 0;
-    u64* stage = lds + wave * 256;
-    auto load = [&](const u64* p, u64 (&o)[4], bool nt) __attribute__((always_inline)) {
+    u64* stage = lds + wave * ROW;
+    auto load = [&](const u64* p, u64 (&o)[W], bool nt) __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
+        for (int h = 0; h < W / 2; h++) {
             const u64x2* q = reinterpret_cast<const u64x2*>(p + h * 128 + lane * 2);
             const u64x2 t = nt ? __builtin_nontemporal_load(q) : *q;
             o[2 * h] = t.x, o[2 * h + 1] = t.y;
@@ -1217,9 +1241,9 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
         u64* base = i < sp ? a.cq + ((size_t)t * sp + i) * N : a.cp + ((size_t)t * (D - sp) + (i - sp)) * N;
         return base + (a.each ? (size_t)rr * 2 * (i < sp ? sp : D - sp) * N : 0) + row_off;
     };
-    auto store = [&](const T (&acc)[4], u64* o) __attribute__((always_inline)) {
+    auto store = [&](const T (&acc)[W], u64* o) __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
+        for (int h = 0; h < W / 2; h++) {
             u64x2* q = reinterpret_cast<u64x2*>(o + h * 128 + lane * 2);
             u64x2 r;
             r.x = AR::acc_canon(AR::acc_finish2(acc[2 * h], m), m), r.y = AR::acc_canon(AR::acc_finish2(acc[2 * h + 1], m), m);
@@ -1230,120 +1254,146 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
             *q = r;
         }
     };
-    T acc0[4], acc1[4];
-#pragma unroll
-    for (int k = 0; k < 4; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
+    DhSum<AR, W> acc0[W], acc1[W];
     // terms of a rotation: digits 0 .. dnum - 1, then (q-limbs) b times P.  The words of the next term, also across
-    // rotations, are requested before this one is worked on: a wavefront has 12 KiB in flight.
+    // rotations, are requested before this one is worked on: a wavefront of the wide form has 12 KiB in flight.
     const u32 n_terms = tb.dnum + (is_q ? 1 : 0);
-    u64 sv[4], kv0[4], kv1[4], ptv[4] = {1, 1, 1, 1};
+    u64 sv[W], kv0[W], kv1[W], ptv[W];
     const u64 *ct = a.ct, *dt = a.dt;
-    auto request = [&](u32 gal, const u64* key_r, const u64* pt_r, u32 j, u64 (&s)[4], u64 (&k0)[4], u64 (&k1)[4],
-                       u64 (&p)[4]) __attribute__((always_inline)) {
-        const u32 src_off = eval_perm(row_off, gal, logN) & ~255u;
-        const bool is_b = j == tb.dnum;
-        load((is_b ? ct + (size_t)i * N : j == own_digit ? ct + ((size_t)L + i) * N : dt + ((size_t)j * D + i) * N) + src_off, s, false);
-        if (!is_b) {
-            const u64* key = key_r + ((size_t)j * 2 * Dkey + pi) * N + row_off;
-            load(key, k0, true);
-            load(key + (size_t)Dkey * N, k1, true);
-        }
-        if (j == 0 && pt_r) load(pt_r + (size_t)i * N + row_off, p, true);
-    };
-    W w0[4], w1[4];
 #pragma unroll
-    for (int k = 0; k < 4; k++) w0[k] = w1[k] = AR::wide_zero();
-    u32 folds = 0, in_sum = 0, rr = a.waves == 1 ? 0 : wave, j = 0;
+    for (int k = 0; k < W; k++) ptv[k] = 1;
     const size_t pt_step = (size_t)D * N;
-    if (rr < a.n_rot) request(a.galois[rr], a.key[rr], a.pt ? a.pt + rr * pt_step : nullptr, 0, sv, kv0, kv1, ptv);
-    while (rr < a.n_rot) {
-        u32 idx[4];
+    // EVEN: every request is the same number of loads, and what a term does not need is the source row once more (L2): behind
+    // a branch that may skip some, the compiler waits for all of them before the previous term's words are used.  The narrow
+    // form gains (18 rotations, L + K = 12 + 4, dnum = 3: 360 -> 354 us), the wide one loses by the extra loads (24 + 6: 672 -> 684).
+    constexpr bool EVEN = W == 2;
+    auto request = [&](u32 r, u32 j, u64 (&s)[W], u64 (&k0)[W], u64 (&k1)[W], u64 (&p)[W]) __attribute__((always_inline)) {
+        const u32 src_off = eval_perm(row_off, a.galois[r], logN) & ~(ROW - 1);
+        const bool is_b = j == tb.dnum;
+        const u64* src = (is_b ? ct + (size_t)i * N : j == own_digit ? ct + ((size_t)L + i) * N : dt + ((size_t)j * D + i) * N) + src_off;
+        const u64* key = a.key[r] + ((size_t)j * 2 * Dkey + pi) * N + row_off;
+        const u64* pt = a.pt + r * pt_step + (size_t)i * N + row_off;
+        if constexpr (EVEN) {
+            typedef const u64 __attribute__((address_space(1))) * Global;  // known to be global behind the opaque selection
+            Global kp = (Global)(is_b ? src : key), kp1 = (Global)(is_b ? src : key + (size_t)Dkey * N), pp = (Global)(j == 0 && a.pt ? pt : src);
+            asm volatile("" : "+s"(kp), "+s"(kp1), "+s"(pp));  // addresses selected, not loads skipped
+            load(src, s, false);
+            load((const u64*)kp, k0, true);
+            load((const u64*)kp1, k1, true);
+            load((const u64*)pp, p, true);
+        } else {
+            load(src, s, false);
+            if (!is_b) {
+                load(key, k0, true);
+                load(key + (size_t)Dkey * N, k1, true);
+            }
+            if (j == 0 && a.pt) load(pt, p, true);
+        }
+    };
+    Wide w0[W], w1[W];
 #pragma unroll
-        for (int k = 0; k < 4; k++) idx[k] = eval_perm(row_off + (k >> 1) * 128 + lane * 2 + (k & 1), a.galois[rr], logN) & 255;
+    for (int k = 0; k < W; k++) w0[k] = w1[k] = AR::wide_zero();
+    u32 folds = 0, in_sum = 0, rr = a.waves == 1 ? 0 : wave, j = 0;
+    if (rr < a.n_rot) request(rr, 0, sv, kv0, kv1, ptv);
+    while (rr < a.n_rot) {
+        u32 idx[W];
+#pragma unroll
+        for (int k = 0; k < W; k++) idx[k] = eval_perm(row_off + (k >> 1) * 128 + lane * 2 + (k & 1), a.galois[rr], logN) & (ROW - 1);
         for (; j < n_terms; j++) {
             const bool last = j + 1 == n_terms;
-            const u32 rn = last ? rr + a.waves : rr, jn = last ? 0 : j + 1;
-            u64 sn[4], kn0[4], kn1[4], pn[4] = {1, 1, 1, 1};
-            if (rn < a.n_rot) request(a.galois[rn], a.key[rn], a.pt ? a.pt + rn * pt_step : nullptr, jn, sn, kn0, kn1, pn);
+            const bool more = !last || rr + a.waves < a.n_rot;  // else (EVEN) this term once more, unused
+            u64 sn[W], kn0[W], kn1[W], pn[W];
+#pragma unroll
+            for (int k = 0; k < W; k++) pn[k] = 1;
+            if (EVEN || more) request(more && last ? rr + a.waves : rr, !more ? j : last ? 0 : j + 1, sn, kn0, kn1, pn);
             row_sync();  // the previous term's words have been read
 #pragma unroll
-            for (int h = 0; h < 2; h++) {
+            for (int h = 0; h < W / 2; h++) {
                 u64x2 t;
                 t.x = sv[2 * h], t.y = sv[2 * h + 1];
                 *reinterpret_cast<u64x2*>(stage + h * 128 + lane * 2) = t;
             }
             row_sync();
 #pragma unroll
-            for (int k = 0; k < 4; k++) sv[k] = stage[idx[k]];
+            for (int k = 0; k < W; k++) sv[k] = stage[idx[k]];
             if (j == tb.dnum) {
 #pragma unroll
-                for (int k = 0; k < 4; k++) AR::wide_mac(w0[k], sv[k], pmod);
+                for (int k = 0; k < W; k++) AR::wide_mac(w0[k], sv[k], pmod);
             } else {
 #pragma unroll
-                for (int k = 0; k < 4; k++) AR::wide_mac(w0[k], sv[k], kv0[k]), AR::wide_mac(w1[k], sv[k], kv1[k]);
+                for (int k = 0; k < W; k++) AR::wide_mac(w0[k], sv[k], kv0[k]), AR::wide_mac(w1[k], sv[k], kv1[k]);
             }
             if (++in_sum == AR::wide_terms || last) {
                 in_sum = 0;
 #pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    AR::acc_mac_wide(acc0[k], AR::wide_reduce(w0[k], m), ptv[k], m);
-                    AR::acc_mac_wide(acc1[k], AR::wide_reduce(w1[k], m), ptv[k], m);
+                for (int k = 0; k < W; k++) {
+                    const u64 ptk = EVEN && !a.pt ? 1 : ptv[k];
+                    acc0[k].add(AR::wide_reduce(w0[k], m), ptk, m);
+                    acc1[k].add(AR::wide_reduce(w1[k], m), ptk, m);
                     w0[k] = w1[k] = AR::wide_zero();
                 }
                 if ((++folds & 7) == 0) {  // FP64: at most 8 products (0.69 q each) between reductions
 #pragma unroll
-                    for (int k = 0; k < 4; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
+                    for (int k = 0; k < W; k++) acc0[k].fold(m), acc1[k].fold(m);
                 }
             }
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
+            for (int k = 0; k < W; k++) {
                 sv[k] = sn[k], kv0[k] = kn0[k], kv1[k] = kn1[k];
                 if (last) ptv[k] = pn[k];
             }
         }
         if (a.each) {
-            store(acc0, out(rr, 0));
-            store(acc1, out(rr, 1));
+            T t0[W], t1[W];
 #pragma unroll
-            for (int k = 0; k < 4; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
+            for (int k = 0; k < W; k++) t0[k] = acc0[k].get(m), t1[k] = acc1[k].get(m), acc0[k] = acc1[k] = DhSum<AR, W>();
+            store(t0, out(rr, 0));
+            store(t1, out(rr, 1));
             folds = 0;
         }
         j = 0, rr += a.waves;
     }
     if (a.each) return;
+    T t0[W], t1[W];
+#pragma unroll
+    for (int k = 0; k < W; k++) t0[k] = acc0[k].get(m), t1[k] = acc1[k].get(m);
     if (a.waves > 1) {  // the first of the row's four wavefronts joins their sums
 #pragma unroll
-        for (int k = 0; k < 4; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
+        for (int k = 0; k < W; k++) t0[k] = AR::acc_fold(t0[k], m), t1[k] = AR::acc_fold(t1[k], m);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            lds[(wave * 2 + 0) * 256 + k * 64 + lane] = AR::to_raw(acc0[k]);
-            lds[(wave * 2 + 1) * 256 + k * 64 + lane] = AR::to_raw(acc1[k]);
+        for (int k = 0; k < W; k++) {
+            lds[(wave * 2 + 0) * ROW + k * 64 + lane] = AR::to_raw(t0[k]);
+            lds[(wave * 2 + 1) * ROW + k * 64 + lane] = AR::to_raw(t1[k]);
         }
         __syncthreads();
         if (wave) return;
 #pragma unroll
-        for (int k = 0; k < 4; k++)
+        for (int k = 0; k < W; k++)
 #pragma unroll
             for (int v = 1; v < 4; v++) {
-                acc0[k] = AR::wide_join(acc0[k], AR::from_raw(lds[(v * 2 + 0) * 256 + k * 64 + lane]), m);
-                acc1[k] = AR::wide_join(acc1[k], AR::from_raw(lds[(v * 2 + 1) * 256 + k * 64 + lane]), m);
+                t0[k] = AR::wide_join(t0[k], AR::from_raw(lds[(v * 2 + 0) * ROW + k * 64 + lane]), m);
+                t1[k] = AR::wide_join(t1[k], AR::from_raw(lds[(v * 2 + 1) * ROW + k * 64 + lane]), m);
             }
     }
-    store(acc0, out(0, 0));
-    store(acc1, out(0, 1));
+    store(t0, out(0, 0));
+    store(t1, out(0, 1));
 }
 
-__global__ __launch_bounds__(256, 3) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
-    __shared__ __align__(16) u64 lds[2048];  // 256 words per wavefront to permute a row in; 2048 to join four sums
-    const u32 rows_wg = 4 / a.waves, per_limb = ((1u << tb.logN) / 256) / rows_wg, total = tb.D * per_limb, per = (total + 7) / 8;
+// AR = AnyAr: rows of 256 words, FP64 and integer limbs in one launch.  AR = IntAr, for chains of integer primes alone: rows of
+// 128 words (sigma_g maps every aligned block of 2^m slots onto one), 85 registers instead of 158 and five waves per SIMD
+// instead of three, see launch_dh_accum.
+template <class AR>
+__global__ __launch_bounds__(256, __is_same(AR, AnyAr) ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
+    constexpr int W = dh_words<AR>();
+    __shared__ __align__(16) u64 lds[512 * W];  // a row per wavefront to permute it in; eight to join four pairs of sums
+    const u32 rows_wg = 4 / a.waves, per_limb = ((1u << tb.logN) / (64 * W)) / rows_wg, total = tb.D * per_limb, per = (total + 7) / 8;
     const u32 pos = blockIdx.x >> 3, q = (blockIdx.x & 7) * per + pos;  // workgroups go to the XCDs round-robin
     if (pos >= per || q >= total) return;
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: addresses stay in scalar registers
     const u32 i = q / per_limb, row = (q % per_limb) * rows_wg + (a.waves == 1 ? wave : 0);
     const PrimeConst pc = tb.pc[tb.phys(i)];
-    if (pc.fp) dh_accum_body<FpAr>(a, tb, pc, lds, i, row, wave);
-    else dh_accum_body<IntAr>(a, tb, pc, lds, i, row, wave);
+    CKKS_BY_ARITHMETIC(AR, i, (dh_accum_body<AR_, W>(a, tb, pc, lds, i, row, wave)))
 }
 
 // ==================================================== baby-step giant-step accumulation and sums

@@ -92,3 +92,45 @@ def test_hoisted_rotations_with_the_second_stream_at_work(orc, n_rot):
             assert np.array_equal(host(call()), want)
     finally:
         ctx.set_overlap(False)
+
+
+def _below(bound, two_n, count):
+    """the `count` largest primes = 1 mod two_n below bound"""
+    out, c = [], (bound - 2) // two_n * two_n + 1
+    while len(out) < count:
+        if synth.is_prime(c):
+            out.append(c)
+        c -= two_n
+    return tuple(out)
+
+
+@pytest.mark.parametrize("logN,L,K,dnum,counts", [(12, 3, 1, 3, (1, 3, 9, 33)), (12, 9, 2, 9, (2, 17)), (13, 2, 7, 1, (4, 40)),
+                                                  (16, 17, 4, 6, (9, 20)), (16, 13, 3, 3, (9, 18))])
+def test_double_hoisted_sum_on_integer_chains(orc, logN, L, K, dnum, counts):
+    """Chains of integer primes alone, the largest the library takes, so that every bound of the unreduced sums is met:
+    rotation counts around the eight terms between two folds, one and four wavefronts per row (N = 2^16: few / many rotations),
+    digit counts around the eight terms of a digit sum, more rotations than one launch takes, baby steps stored singly."""
+    primes = _below(1 << 61, 2 << logN, L + K)
+    ps = synth.ExplicitParamSet("below_2_61", logN, dnum, primes[:L], primes[L:])
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(6100 + logN + L)
+    n = max(counts)
+    gs = [synth.galois_element((-1) ** r * (r // 2 + 1), logN) for r in range(n)]
+    keys = [synth.uniform_residues(rng, ps.primes, ps.N, lead=(dnum, 2)) for _ in range(3)]
+    ct, pt = synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(2,)), synth.uniform_residues(rng, ps.primes, ps.N, lead=(n,))
+    for i, p in enumerate(ps.primes):
+        for k in keys:
+            k[:, :, i, : ps.N // 2] = p - 1
+        pt[:, i, : ps.N // 4] = p - 1
+        if i < L:
+            ct[:, i, : ps.N // 8] = p - 1
+    d_keys, d_ct = [dev(k) for k in keys], dev(ct)
+    for m in counts:
+        print(logN, L, K, dnum, "rotations", m, flush=True)
+        got, names = _kernels(ctx, lambda: ctx.hrot_dh_mac(d_ct, gs[:m], [d_keys[r % 3] for r in range(m)], dev(pt[:m])))
+        assert np.array_equal(got, orc.hrot_dh_mac_level(ct, gs[:m], [keys[r % 3] for r in range(m)], pt[:m], P)), m
+        assert "dh_accum_kernel<IntAr>" in names and "dh_accum_kernel<AnyAr>" not in names
+    if logN == 12:
+        d_pt = dev(np.ascontiguousarray(pt[:2]).reshape(1, 2, L + K, ps.N))
+        got = host(ctx.lintrans_bsgs_at(L, d_ct, gs[:2], d_keys[:2], gs[2:3], d_keys[2:], d_pt))
+        assert np.array_equal(got, orc.lintrans_bsgs_level(ct, gs[:2], keys[:2], gs[2:3], keys[2:], pt[:2].reshape(1, 2, L + K, ps.N), P))
