@@ -849,16 +849,18 @@ struct FwdStridedL {
     static std::string name(const char* ar, int A) { return kname("fwd_strided_kernel", ar, A, ""); }
 };
 // Conversions: KS products per coefficient group on the matrix cores, or (KS = 0) a single source and TB targets per
-// workgroup
+// workgroup (one for IntAr)
 template <int DIR, int KS, int TB = 0>
 struct ConvL {
     static constexpr bool packed = KS > 0;  // blocks are numbered over the targets alone, without a digit's own limbs
     template <class AR>
-    static constexpr int per_block() { return KS ? 2 * conv_mfma_ntt<AR>() : TB; }
+    static constexpr int single() { return AR::is_fp ? TB : 1; }
+    template <class AR>
+    static constexpr int per_block() { return KS ? 2 * conv_mfma_ntt<AR>() : single<AR>(); }
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const ConvArgs& a, const Tables& tb, LimbRun run) {
         constexpr int NTT = conv_mfma_ntt<AR>();
-        if constexpr (KS == 0) hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, TB, true>), g, dim3(256), 0, s, a, tb, run);
+        if constexpr (KS == 0) hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, single<AR>(), true>), g, dim3(256), 0, s, a, tb, run);
         else if constexpr (AR::is_fp && DIR == CONV_DN)
             hipLaunchKernelGGL((conv_mfma_kernel<A, KS, DIR, NTT>), g, dim3(256 * NTT), 0, s, a, tb, run);
         else hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, KS + NTT, false>), g, dim3(256 * NTT), 0, s, a, tb, run);
@@ -868,7 +870,7 @@ struct ConvL {
         const int ntt = fp ? conv_mfma_ntt<FpAr>() : conv_mfma_ntt<IntAr>();
         const std::string dir = std::to_string(DIR);
         if (KS && fp && DIR == CONV_DN) return "conv_mfma_kernel<" + std::to_string(A) + ", " + std::to_string(KS) + ", " + dir + ", " + std::to_string(ntt) + ">";
-        return kname("conv_fwd_strided_kernel", ar, A, (", " + dir + ", " + std::to_string(KS ? KS + ntt : TB) + (KS ? ", false" : ", true")).c_str());
+        return kname("conv_fwd_strided_kernel", ar, A, (", " + dir + ", " + std::to_string(KS ? KS + ntt : fp ? TB : 1) + (KS ? ", false" : ", true")).c_str());
     }
 };
 struct FwdContigL {
@@ -1023,7 +1025,9 @@ static void launch_conv(const View* c, ConvArgs a, hipStream_t s, int cls = -1) 
     a.aop = t.aop, a.aop_part = t.aop_part, a.n_full = t.n_full;
     switch (t.ks) {
         case 0: {
-            // four targets share a load of the source unless that leaves fewer than two workgroups per compute unit
+            // Four FP64 targets share a load of the source unless that leaves fewer than two workgroups per compute unit.  Integer
+            // targets are converted singly: two or four per workgroup need 146 registers, three waves per SIMD, and end in
+            // half-empty rounds (rescale of 7 ciphertexts at N = 2^15, 19 integer limbs: 106 us singly, 116 with four).
             const u32 wgs = a.groups_outer * (DIR == CONV_UP ? c->dnum : 1) * tiles_of(c) * (((DIR == CONV_UP ? c->D : c->L) + 3) / 4);
             if (wgs >= 512) launch_conv_runs<ConvL<DIR, 0, 4>, DIR>(c, a, s, cls);
             else launch_conv_runs<ConvL<DIR, 0, 1>, DIR>(c, a, s, cls);

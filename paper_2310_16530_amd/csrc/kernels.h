@@ -477,9 +477,9 @@ __device__ __forceinline__ void strided_stages_hi(typename AR::T (&x)[16], const
 }
 
 // ---- a single source (digits of one limb, one special prime, the rescale): out_t = y mod m_t, the conversion constant is 1.
-// A workgroup keeps the words of one load and reduces them to TB targets in turn: 4 share a load where the launch fills
-// the chip (rescale of 8 ciphertexts at N = 2^16, 23 limbs: 63 -> 53 us against three targets converted before the first
-// is transformed), 1 where it does not and the time is that of one workgroup (launch_conv).
+// A workgroup keeps the words of one load and reduces them to TB targets in turn: 4 FP64 targets share a load where the
+// launch fills the chip (rescale of 8 ciphertexts at N = 2^16, 23 limbs: 63 -> 53 us against three targets converted before
+// the first is transformed), 1 where it does not and the time is that of one workgroup; integer targets always 1 (launch_conv).
 template <class AR, int A, int DIR, int TB>
 __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& tb, const LimbRun run) {
     typedef NttCore<AR, A> C;

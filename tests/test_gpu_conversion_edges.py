@@ -46,3 +46,48 @@ def test_conversions_at_the_edges_of_their_forms(orc, shape):
             assert np.array_equal(hr[b], orc.hrot_level(ct1[b], g, key, P)), (ell, b)
             assert np.array_equal(hm[b], orc.hmult_relin_rescale_level(ct1[b], ct2[b], key, P)), (ell, b)
         assert np.array_equal(host(ctx.rescale(ell, dev(ct1))), orc.rescale(ct1, P)), ell
+
+
+# (logN, q floors, p floors, batch): digits of one limb and one special prime, grids on both sides of 512 workgroups of four
+# targets; floors from 50 bits on are integer arithmetic
+SINGLE = [(15, (49, 49, 49, 49), 59, 3), (15, (49, 49, 49, 49), 59, 14), (15, (49, 49, 49, 49), 59, 32),
+          (14, (49, 50, 58, 55, 55, 58, 60), 48, 32), (13, (55, 56, 57, 58, 59, 60), 60, 8), (13, (55, 56, 57, 58, 59, 60), 60, 40)]
+
+
+@pytest.mark.parametrize("logN,q,p,batch", SINGLE)
+def test_single_source_conversions_share_a_load_for_fp64_targets_only(orc, logN, q, p, batch):
+    """ModUp, ModDown and rescale from one limb: FP64 targets four per workgroup from 512 workgroups on, integer ones singly."""
+    ps = synth.mixed_params(logN, list(q), [p], len(q), "single")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(5120 + logN + batch)
+    key = synth.uniform_residues(rng, ps.primes, ps.N, lead=(ps.dnum, 2))
+    d_key = dev(key)
+    g = synth.galois_element(3, ps.logN)
+    tiles, A = ps.N >> 12, logN - 8
+
+    def check(call, up_targets, dn_targets):
+        ctx.profile_enable(True)
+        try:
+            got, names = host(call()), set(ctx.profile_read())
+        finally:
+            ctx.profile_enable(False)
+        forms = {n for n in names if n.startswith("conv_fwd_strided_kernel") and n.endswith("true>")}
+        wgs = {1: batch * ps.dnum * tiles * -(-up_targets // 4), 2: 2 * batch * tiles * -(-dn_targets // 4)}
+        allowed = {"conv_fwd_strided_kernel<%s, %d, %d, %d, true>" % (ar, A, d, 4 if ar == "FpAr" and wgs[d] >= 512 else 1)
+                   for ar in ("FpAr", "IntAr") for d in (1, 2)}
+        assert forms and forms <= allowed, (forms, wgs)
+        return got, forms
+
+    for ell in (ps.L, ps.L - 1):
+        print(logN, "batch", batch, "level", ell, flush=True)
+        ct1, ct2 = (_extreme(rng, ps.q_primes[:ell], ps.N, (batch, 2)) for _ in range(2))
+        if ell == ps.L:
+            got, forms = check(lambda: ctx.hrot_at(ell, dev(ct1), g, d_key), ell + 1, ell)
+            assert len(forms) == 2 * len({b >= 50 for b in q}) + (p < 50 <= min(q)) + (max(q) < 50 <= p), forms
+            for b in range(0, batch, 6):
+                assert np.array_equal(got[b], orc.hrot_level(ct1[b], g, key, P)), (ell, b)
+        got, _ = check(lambda: ctx.rescale(ell, dev(ct1)), ell + 1, ell - 1)
+        assert np.array_equal(got[::6], orc.rescale(ct1[::6], P)), ell
+        hm = host(ctx.hmult_relin_rescale_at(ell, dev(ct1), dev(ct2), d_key))
+        for b in range(0, batch, 6):
+            assert np.array_equal(hm[b], orc.hmult_relin_rescale_level(ct1[b], ct2[b], key, P)), (ell, b)
