@@ -923,7 +923,8 @@ static void launch_inv_strided(const View* c, const InvStridedArgs& a, hipStream
 // At N = 2^13 a few integer limbs are faster in two passes over twice the workgroups than in one kernel each: the workgroup
 // of a limb then is all of the time, and its integer butterflies, two wavefronts a SIMD, take longer than a launch.  Forward /
 // inverse, 1 limb: 12.2 against 14.0 us / 14.5 against 15.1; 24 limbs 13.2 against 14.5 / 15.5 against 15.6; 64 limbs 14.5 against
-// 14.9 / 16.9 against 16.0; 80 limbs 15.0 against 15.1.  FP64 limbs: one kernel at every size (1 limb 10.8 against 7.7 / 10.6
+// 14.9 / 16.9 against 16.0; 80 limbs 15.0 against 15.1; 96 limbs 15.8 against 15.2.  FP64 limbs: one kernel at every size
+// (1 limb 10.8 against 7.7 / 10.6
 // against 8.6), a range that mixes both likewise.
 static bool spread_limbs(const View* c, const LimbSel& sel, u32 most) {
     return c->logN == 13 && sel.n_l * sel.n_inst <= most && !any_fp_prime(c, sel.prime_base, sel.prime_base + sel.n_l);
@@ -1052,7 +1053,7 @@ static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t
 // forward transform in place: one kernel where a workgroup holds a limb, else two passes
 static void launch_forward(const View* c, u64* d_x, const LimbSel& sel, hipStream_t s) {
     const FwdContigArgs a2 = {d_x, sel, 0, 0};
-    if (!inv_one_kernel((int)c->logN - 8) || spread_limbs(c, sel, 64)) {
+    if (!inv_one_kernel((int)c->logN - 8) || spread_limbs(c, sel, 80)) {
         const FwdStridedArgs a1 = {d_x, d_x, sel};
         launch_fwd_strided(c, a1, s);
         launch_fwd_contig(c, a2, s);
