@@ -924,8 +924,7 @@ static void launch_inv_strided(const View* c, const InvStridedArgs& a, hipStream
 // of a limb then is all of the time, and its integer butterflies, two wavefronts a SIMD, take longer than a launch.  Forward /
 // inverse, 1 limb: 12.2 against 14.0 us / 14.5 against 15.1; 24 limbs 13.2 against 14.5 / 15.5 against 15.6; 64 limbs 14.5 against
 // 14.9 / 16.9 against 16.0; 80 limbs 15.0 against 15.1; 96 limbs 15.8 against 15.2.  FP64 limbs: one kernel at every size
-// (1 limb 10.8 against 7.7 / 10.6
-// against 8.6), a range that mixes both likewise.
+// (1 limb 10.8 against 7.7 / 10.6 against 8.6), a range that mixes both likewise.
 static bool spread_limbs(const View* c, const LimbSel& sel, u32 most) {
     return c->logN == 13 && sel.n_l * sel.n_inst <= most && !any_fp_prime(c, sel.prime_base, sel.prime_base + sel.n_l);
 }

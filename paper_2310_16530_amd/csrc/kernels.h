@@ -282,7 +282,7 @@ __global__ __launch_bounds__(inv_one_kernel(A) ? 16 << A : 256) void inv_contig_
     __shared__ u64 lds[ONE ? (1 << A) * 272 : NTT_LDS_WORDS];
     constexpr u32 TILES = ONE ? 1 : (1u << A) / 16;
     u32 group, inst;
-    if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
+    if (ONE ? !whole_decode(blockIdx.x, a.sel.n_inst, run.count, group, inst) : !xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
     const u32 l = run.first + group / TILES;
     if constexpr (ONE) { CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (inv_whole_body<AR_, A, LOAD>(a, tb, lds, l, inst))) }
     else { CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (inv_contig_body<AR_, A, LOAD>(a, tb, lds, l, group % TILES, inst))) }
@@ -888,7 +888,7 @@ template <int A>
 __global__ __launch_bounds__(16 << A) void fwd_whole_kernel(FwdContigArgs a, Tables tb, LimbRun run) {
     __shared__ u64 lds[(1 << A) * 272];
     u32 group, inst;
-    if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count, group, inst)) return;
+    if (!whole_decode(blockIdx.x, a.sel.n_inst, run.count, group, inst)) return;
     const u32 l = run.first + group;
     CKKS_BY_ARITHMETIC(AnyAr, a.sel.prime_base + l, (fwd_whole_body<AR_, A>(a, tb, lds, l, inst)))
 }

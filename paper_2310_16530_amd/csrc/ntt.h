@@ -228,9 +228,17 @@ struct NttCore {
 // so ids congruent modulo 8 share an L2.  Work is organised as `groups` groups of `S` instances
 // that read the same tables / sources; all instances of a group get ids on one XCD, adjacent
 // in dispatch order.  The grid must hold ceil(groups/8)*8*S workgroups; returns false for padding.
-__device__ __forceinline__ bool xcd_decode(u32 bid, u32 S, u32 groups, u32& group, u32& inst) {
+HD bool xcd_decode(u32 bid, u32 S, u32 groups, u32& group, u32& inst) {
     const u32 xcd = bid & 7, pos = bid >> 3;
     inst = pos % S;
     group = (pos / S) * 8 + xcd;
     return group < groups;
+}
+// Workgroups that hold a limb each: the instances of a limb share an XCD and its L2 only where the limbs fill the eight XCDs
+// evenly enough.  N = 2^13, inverse, FP64 limbs, shared against spread: 1 limb x 128 30.9 / 10.2 us, 12 x 64 33.7 / 28.5, 24 x 16
+// 16.6 / 17.8; integer limbs: 12 x 64 54.7 / 45.4, 20 x 16 27.9 / 30.9.
+HD bool whole_decode(u32 bid, u32 n_inst, u32 limbs, u32& l, u32& inst) {
+    if (limbs * 5 >= (limbs + 7) / 8 * 8 * 4) return xcd_decode(bid, n_inst, limbs, l, inst);
+    l = bid / n_inst, inst = bid % n_inst;
+    return l < limbs;
 }

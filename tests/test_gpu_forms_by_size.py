@@ -134,3 +134,22 @@ def test_double_hoisted_sum_on_integer_chains(orc, logN, L, K, dnum, counts):
         d_pt = dev(np.ascontiguousarray(pt[:2]).reshape(1, 2, L + K, ps.N))
         got = host(ctx.lintrans_bsgs_at(L, d_ct, gs[:2], d_keys[:2], gs[2:3], d_keys[2:], d_pt))
         assert np.array_equal(got, orc.lintrans_bsgs_level(ct, gs[:2], keys[:2], gs[2:3], keys[2:], pt[:2].reshape(1, 2, L + K, ps.N), P))
+
+
+@pytest.mark.parametrize("logN", [12, 13])
+@pytest.mark.parametrize("q", [(49,) * 3, (55, 56, 57), (49, 55) * 5, (49,) * 7 + (58,) * 5, (49,) * 26], ids=lambda q: str(len(q)))
+def test_workgroups_of_a_limb_each_at_any_share_of_the_chip(orc, logN, q):
+    """Limb counts that fill the eight dies evenly (7, 8, 14, 16, 26) and that do not (1, 3, 10, 12, 17), one to many instances:
+    every workgroup finds its limb and instance either way, also with limbs of both arithmetics and an offset."""
+    ps = synth.mixed_params(logN, list(q), [59], len(q), "whole")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(808 + logN + len(q))
+    for n in sorted({1, 3, 7, 8, 10, 12, 14, 16, 17, 26} & set(range(len(q) + 1))):
+        for batch in (1, 5, 33):
+            first = (len(q) - n) // 2
+            x = synth.uniform_residues(rng, ps.primes[first:first + n], ps.N, lead=(batch,))
+            assert np.array_equal(host(ctx.ntt(dev(x), first)), orc.ntt_batch(x, P, first)), (n, batch)
+            assert np.array_equal(host(ctx.intt(dev(x), first)), orc.ntt_batch(x, P, first, inverse=True)), (n, batch)
+    print(logN, len(q), "limbs", flush=True)
+    ct = synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(9, 2))
+    assert np.array_equal(host(ctx.rescale(len(q), dev(ct))), orc.rescale(ct, P))
