@@ -1145,8 +1145,11 @@ static void launch_bsgs_mac(const View* c, const BsgsMacArgs& a, hipStream_t s) 
 // (18 rotations, 24 + 6, dnum = 4: 669 against 683 us).
 static void launch_dh_accum(const View* c, DhInnerArgs a, hipStream_t s) {
     const u64 n_rot = a.n_rot, acc = a.accumulate ? 2 : 0, dnum = c->dnum;
-    const bool narrow = !any_fp_prime(c, 0, c->D);
-    const u32 rows = c->D * ((1u << c->logN) / (64 * (narrow ? dh_words<IntAr>() : dh_words<AnyAr>())));
+    // With few rotations the accumulation is a chain of a few waits on the keys, which more wavefronts in flight shorten
+    // (N = 2^16, 26 + 6 limbs, dnum 5: 3 rotations 317 us wide, 310 narrow, 6 rotations 441 / 425, 8 rotations 507 / 497); from
+    // about ten on the wide rows of a mixed chain are even or up to 3 % faster.
+    const bool all_int = !any_fp_prime(c, 0, c->D), narrow = all_int || n_rot <= 8;
+    const u32 rows = c->D * ((1u << c->logN) / (64 * (narrow ? 2 : 4)));
     // Four rows per workgroup, or one whose rotations the four wavefronts share.  Narrow: fewer rounds of the 1280 resident
     // workgroups times rotations per wavefront.  Wide: with fewer than eight rotations the wavefronts would end up with
     // unequal shares, which only a grid below two workgroups per compute unit makes up for.
@@ -1154,10 +1157,11 @@ static void launch_dh_accum(const View* c, DhInnerArgs a, hipStream_t s) {
     else a.waves = n_rot >= 8 || (rows / 4 < 512 && n_rot > 1) ? 4 : 1;
     u64 limbs = 0;  // per limb and rotation: the digits, the plaintext, both key components (and b on q-limbs); C_t written
     for (u32 i = 0; i < c->D; i++) limbs += n_rot * (3 * dnum + (a.pt ? 1 : 0) + (i < c->L ? 1 : 0)) + (a.each ? 2 * n_rot : 2) + acc;
-    ProfScope ps(c, c->sh->prof.on ? std::string(narrow ? "dh_accum_kernel<IntAr>" : "dh_accum_kernel<AnyAr>") : std::string(), limbs, s);
+    ProfScope ps(c, c->sh->prof.on ? std::string(all_int ? "dh_accum_kernel<IntAr, 2>" : narrow ? "dh_accum_kernel<AnyAr, 2>" : "dh_accum_kernel<AnyAr, 4>") : std::string(), limbs, s);
     const dim3 grid((rows * a.waves / 4 + 7) / 8 * 8);
-    if (narrow) hipLaunchKernelGGL(dh_accum_kernel<IntAr>, grid, dim3(256), 0, s, a, c->tb);
-    else hipLaunchKernelGGL(dh_accum_kernel<AnyAr>, grid, dim3(256), 0, s, a, c->tb);
+    if (all_int) hipLaunchKernelGGL((dh_accum_kernel<IntAr, 2>), grid, dim3(256), 0, s, a, c->tb);
+    else if (narrow) hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 2>), grid, dim3(256), 0, s, a, c->tb);
+    else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 4>), grid, dim3(256), 0, s, a, c->tb);
 }
 
 template <int MODE>

@@ -1193,9 +1193,6 @@ struct DhInnerArgs {
     u32 each;        // rotations are not summed: rotation r's result goes to cq + r*2*split*N, cp + r*2*(D - split)*N
 };
 
-// words per lane; a row, a wavefront's share, is 64 times that
-template <class AR>
-constexpr int dh_words() { return __is_same(AR, AnyAr) ? 4 : 2; }
 // Sum over the rotations of (unreduced digit sum, reduced) * plaintext, at most 8 terms between folds
 template <class AR, int W>
 struct DhSum {
@@ -1380,12 +1377,11 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
     store(t1, out(0, 1));
 }
 
-// AR = AnyAr: rows of 256 words, FP64 and integer limbs in one launch.  AR = IntAr, for chains of integer primes alone: rows of
-// 128 words (sigma_g maps every aligned block of 2^m slots onto one), 85 registers instead of 158 and five waves per SIMD
-// instead of three, see launch_dh_accum.
-template <class AR>
-__global__ __launch_bounds__(256, __is_same(AR, AnyAr) ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
-    constexpr int W = dh_words<AR>();
+// W words per lane; a row, a wavefront's share, is 64 times that (sigma_g maps every aligned block of 2^m slots onto one).
+// AnyAr, FP64 and integer limbs in one launch: rows of 256 words, 12 KiB in flight per wavefront and three waves per SIMD, or
+// of 128 and five.  IntAr, for chains of integer primes alone: rows of 128 words.  launch_dh_accum has the rule.
+template <class AR, int W>
+__global__ __launch_bounds__(256, W == 4 ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
     __shared__ __align__(16) u64 lds[512 * W];  // a row per wavefront to permute it in; eight to join four pairs of sums
     const u32 rows_wg = 4 / a.waves, per_limb = ((1u << tb.logN) / (64 * W)) / rows_wg, total = tb.D * per_limb, per = (total + 7) / 8;
     const u32 pos = blockIdx.x >> 3, q = (blockIdx.x & 7) * per + pos;  // workgroups go to the XCDs round-robin

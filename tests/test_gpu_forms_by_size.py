@@ -129,11 +129,39 @@ def test_double_hoisted_sum_on_integer_chains(orc, logN, L, K, dnum, counts):
         print(logN, L, K, dnum, "rotations", m, flush=True)
         got, names = _kernels(ctx, lambda: ctx.hrot_dh_mac(d_ct, gs[:m], [d_keys[r % 3] for r in range(m)], dev(pt[:m])))
         assert np.array_equal(got, orc.hrot_dh_mac_level(ct, gs[:m], [keys[r % 3] for r in range(m)], pt[:m], P)), m
-        assert "dh_accum_kernel<IntAr>" in names and "dh_accum_kernel<AnyAr>" not in names
+        assert "dh_accum_kernel<IntAr, 2>" in names and not any(k.startswith("dh_accum_kernel<AnyAr") for k in names)
     if logN == 12:
         d_pt = dev(np.ascontiguousarray(pt[:2]).reshape(1, 2, L + K, ps.N))
         got = host(ctx.lintrans_bsgs_at(L, d_ct, gs[:2], d_keys[:2], gs[2:3], d_keys[2:], d_pt))
         assert np.array_equal(got, orc.lintrans_bsgs_level(ct, gs[:2], keys[:2], gs[2:3], keys[2:], pt[:2].reshape(1, 2, L + K, ps.N), P))
+
+
+@pytest.mark.parametrize("logN,q,p,dnum,counts", [(12, (49, 49, 49), (59,), 3, (1, 4, 5, 8, 9)), (12, (49, 50, 60, 49, 58), (48, 60), 3, (3, 8, 9, 41)),
+                                                  (16, (49,) * 17, (59,) * 4, 5, (2, 5, 8, 9)), (13, (49,) * 9, (49, 60), 9, (7,))])
+def test_double_hoisted_sum_on_mixed_chains(orc, logN, q, p, dnum, counts):
+    """Chains with FP64 limbs: up to eight rotations take the narrow rows, more the wide ones, 41 = a wide launch and nine more in
+    a second; a unit plaintext and baby steps stored singly on narrow rows too."""
+    ps = synth.mixed_params(logN, list(q), list(p), dnum, "mixed_dh")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(4900 + logN + len(q))
+    n = max(counts)
+    gs = [synth.galois_element((-1) ** r * (r // 2 + 1), logN) for r in range(n)]
+    keys = [synth.uniform_residues(rng, ps.primes, ps.N, lead=(dnum, 2)) for _ in range(3)]
+    ct, pt = synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(2,)), synth.uniform_residues(rng, ps.primes, ps.N, lead=(n,))
+    for x, primes in ((ct, ps.q_primes), (pt, ps.primes), *((k, ps.primes) for k in keys)):
+        for i, m in enumerate(primes):
+            x[..., i, : ps.N // 2] = m - 1
+    d_ct, d_keys = dev(ct), [dev(k) for k in keys]
+    for count in counts:
+        print(logN, "rotations", count, flush=True)
+        got, names = _kernels(ctx, lambda: ctx.hrot_dh_mac(d_ct, gs[:count], [d_keys[r % 3] for r in range(count)], dev(pt[:count])))
+        assert np.array_equal(got, orc.hrot_dh_mac_level(ct, gs[:count], [keys[r % 3] for r in range(count)], pt[:count], P)), count
+        chunks = [min(32, count - f) for f in range(0, count, 32)]
+        assert {k for k in names if k.startswith("dh_")} == {"dh_accum_kernel<AnyAr, %d>" % (2 if k <= 8 else 4) for k in chunks}, names
+    if logN == 12:
+        d_pt = dev(np.ascontiguousarray(pt[:2]).reshape(1, 2, -1, ps.N))
+        got = host(ctx.lintrans_bsgs_at(ps.L, d_ct, gs[:2], d_keys[:2], gs[2:3], d_keys[2:], d_pt))
+        assert np.array_equal(got, orc.lintrans_bsgs_level(ct, gs[:2], keys[:2], gs[2:3], keys[2:], pt[:2].reshape(1, 2, -1, ps.N), P))
 
 
 @pytest.mark.parametrize("logN", [12, 13])
