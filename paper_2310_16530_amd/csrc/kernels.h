@@ -777,9 +777,11 @@ void conv_fwd_strided_kernel(ConvArgs a, Tables tb, LimbRun run) {
     if constexpr (ONE) conv_one_body<AR, A, DIR, P>(a, tb, run);
     else conv_mfma_workgroup<AR, A, P - conv_mfma_ntt<AR>(), DIR, conv_mfma_ntt<AR>()>(a, tb, run);
 }
-// ModDown onto FpAr targets, KS products per coefficient group, NTT targets per lane
+// ModDown onto FpAr targets, KS products per coefficient group, NTT targets per lane: a name of its own, so that profiles tell
+// it from ModUp
 template <int A, int KS, int DIR, int NTT>
 __global__ __launch_bounds__(256 * NTT, KS <= 2 ? 4 : 2) void conv_mfma_kernel(ConvArgs a, Tables tb, LimbRun run) {
+    static_assert(DIR == CONV_DN && NTT == conv_mfma_ntt<FpAr>(), "the other conversions are conv_fwd_strided_kernel");
     conv_mfma_workgroup<FpAr, A, KS, DIR, NTT>(a, tb, run);
 }
 // ModUp onto both classes of targets in one launch: the first workgroups convert to the FpAr run, the others to the IntAr

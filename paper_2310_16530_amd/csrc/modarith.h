@@ -83,7 +83,6 @@ HD u64 mulmod_var(u64 a, u64 b, u64 q, u64 qneg, u64 r2) {
 enum SrcFormat { SRC_CANON = 0, SRC_F64 = 1, SRC_DIGITS = 2 };
 #define CKKS_DIGIT_BIAS 0x8080808080808080ull
 HD u64 digits_encode(u64 y) { return (y + CKKS_DIGIT_BIAS) ^ CKKS_DIGIT_BIAS; }
-HD u64 digits_decode(u64 w) { return (w ^ CKKS_DIGIT_BIAS) - CKKS_DIGIT_BIAS; }
 
 // ------------------------------------------------------------------ per-prime constants
 struct PrimeConst {
@@ -150,7 +149,6 @@ struct IntAr {
     }
     static HD T round_reduce(T v, const Mod&) { return v; }  // lazy ranges are invariants: nothing to do
     static HD u64 canon_fwd(T v, const Mod& m) { return csub(csub(csub(v, m.q2 + m.q2), m.q2), m.q); }  // from [0, 8q)
-    static HD u64 canon_inv(T v, const Mod& m) { return csub(v, m.q); }
     // last inverse stage with scaling, canonical results (fmt: SRC_CANON or SRC_DIGITS; SRC_F64 does not apply)
     static HD void bfly_inv_last(T& X, T& Y, const InvScale& s, const Mod& m, u32 fmt, u64& ox, u64& oy) {
         u64 a = X + Y, d = X - Y + m.q2;
@@ -226,9 +224,10 @@ struct FpAr {
         return __builtin_fma(-c, m.q, x);
     }
     // A word y < 2^61 given as ya + yl with ya = (y >> 30) * 2^30 (31 significant bits, an exact double) and
-    // yl = y mod 2^30: an integer-valued double congruent to y modulo q with |result| <= (0.5 + 2^-19) q + 2^30.
-    // The quotient ya / q is below 2^33 for q >= 2^28, so its estimate is off by less than 2^-19 before
-    // rounding; ya - c*q is an integer below 2^50 in magnitude, hence the fma and the sum are exact.
+    // yl = y mod 2^30: an integer-valued double congruent to y modulo q with |result| <= (0.5 + 2^-4) q + 2^30.
+    // q > 2N >= 2^13, so the quotient ya / q is below 2^48 and its estimate off by less than 2^-4 before rounding
+    // (q >= 2^28: 2^-19); ya - c*q is an integer below 2^50 in magnitude, hence the fma and the sum are exact.  reduce()
+    // of the result is again within q/2: the result over q is below 2^17 + 1.
     static HD T reduce_split(double ya, double yl, const Mod& m) {
         double c = __builtin_rint(ya * m.qinv);
         return __builtin_fma(-c, m.q, ya) + yl;
@@ -258,7 +257,6 @@ struct FpAr {
         return f64_to_u64(r);
     }
     static HD u64 canon_fwd(T v, const Mod& m) { return canon(v, m); }
-    static HD u64 canon_inv(T v, const Mod& m) { return canon(v, m); }
     static HD double canon_f64(T v, const Mod& m) {
         double r = reduce(v, m);
         return r < 0.0 ? r + m.q : r;
@@ -309,7 +307,7 @@ struct FpAr {
 // |S_g| <= 17 * 2^17, V = sum_g 256^g S_g, |V| <= 2^14 m.
 typedef int v16i __attribute__((ext_vector_type(16)));
 // V of an FpAr target reduced to |.| <= (0.5 + 2^-15) m, exactly: pairs of digits are joined as 32-bit integers (below
-// 2^30), lo = digits 0..3 (below 2^47), hi = digits 4..6 times 2^32 (an integer multiple of 2^32 with 38 significant
+// 2^30), lo = digits 0..3 (below 2^46), hi = digits 4..6 times 2^32 (an integer multiple of 2^32 with 38 significant
 // bits: exact); the quotient estimate of (hi + lo) / m is off by less than 2^-15 before rounding, hi - c*m is an integer
 // below 2^53 in magnitude, so the fma and the sum are exact.
 HD double conv_recombine(const v16i& s, int o, const FpAr::Mod& m, const PrimeConst&) {
@@ -319,7 +317,7 @@ HD double conv_recombine(const v16i& s, int o, const FpAr::Mod& m, const PrimeCo
     const double c = __builtin_rint((hi + lo) * m.qinv);
     return __builtin_fma(-c, m.q, hi) + lo;
 }
-// V of an IntAr target (m >= 3*2^48) as a word in (0.4 m, 1.6 m): V = lo + 2^32 t with |lo| < 2^47, t = digits 4..7 exact
+// V of an IntAr target (m >= 3*2^48) as a word in (0.4 m, 1.6 m): V = lo + 2^32 t with |lo| < 2^46, t = digits 4..7 exact
 // in a double (below 2^47); z = 1 - rint(t * 2^32 / m) appears as the low bits of one fma onto 1.5*2^52, |lo| / m < 0.09
 // is what the estimate leaves out, and V + z*m is formed modulo 2^64 with m = mh * 2^32 + (signed low half).  14
 // instructions, where six 128-bit multiply-accumulates and a Montgomery reduction took 62.

@@ -84,7 +84,7 @@ int main(int argc, char** argv) {
                     printf("FpAr recombination q=%llu ns=%d r=%.0f\n", (unsigned long long)q, ns, r); return 1; }
             } else {
                 const u64 r = conv_recombine(v, o, IntAr::mod(pc), pc);
-                if (r >= 2 * q || r % q != want) { printf("IntAr recombination q=%llu ns=%d\n", (unsigned long long)q, ns); return 1; }
+                if (5 * (u128)r <= 2 * (u128)q || 5 * (u128)r >= 8 * (u128)q || r % q != want) { printf("IntAr recombination q=%llu ns=%d\n", (unsigned long long)q, ns); return 1; }
             }
             count++;
         }

@@ -28,6 +28,6 @@ def checker(tmp_path_factory):
 def test_fp64_arithmetic_is_exact_on_the_supported_range(checker):
     limit = 3 << 48  # primes strictly below this use the FP64 arithmetic
     moduli = [synth.CFG2.q_primes[0], synth.CFG4.q_primes[-1], synth.CFG0.q_primes[0], synth.CFG0.p_primes[0],
-              limit - 1, limit - 7, 12289, (1 << 49) - 1]
+              limit - 1, limit - 7, 12289, (1 << 49) - 1, 8193, 40961, (1 << 28) - 57, (1 << 28) + 3]
     out = subprocess.run([checker] + [str(m) for m in moduli], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0 and out.stdout.startswith("OK"), out.stdout + out.stderr

@@ -1,9 +1,8 @@
 """Parity on prime chains that mix sizes and arithmetic classes (needs an MI355X).
 
 The benchmark chains are uniform (50-bit q-limbs, 60-bit special limbs).  Here neighbouring limbs
-alternate between the FP64 and the integer arithmetic, some conversion targets are too small for
-their sources to be converted on the FP64 pipe (the library then converts them with integers), one
-prime lies below 2^28, and two pairs straddle the bound between the two arithmetics.  Everything is
+alternate between the FP64 and the integer arithmetic, some conversion targets are far smaller
+than their sources, one prime lies below 2^28, and two pairs straddle the bound between the two arithmetics.  Everything is
 compared bit for bit with the oracle; nothing here depends on noise being small.
 """
 import numpy as np
@@ -130,8 +129,8 @@ def test_random_chains_levels_and_operations(orc, seed):
 
 
 def _edge_case(seed):
-    """Primes drawn from the edges of what a context accepts: the smallest = 1 mod 2N, either side of 2^28 (below it
-    a conversion target is converted with integers), either side of 3*2^48 (the FP64 / integer bound), 53-54 bits,
+    """Primes drawn from the edges of what a context accepts: the smallest = 1 mod 2N, either side of 2^28
+    (below it the first quotient of a 61-bit source word is estimated less closely), either side of 3*2^48 (the FP64 / integer bound), 53-54 bits,
     and just below 2^61."""
     rng = np.random.default_rng(47000 + seed)
     logN = int(rng.choice([12, 12, 13, 14]))

@@ -1,4 +1,4 @@
-"""Parity of the transforms where their forms change (needs an MI355X): limbs that one workgroup holds (N <= 2^14) and limbs
+"""Parity of the transforms where their forms change (needs an MI355X): limbs that one workgroup holds (N <= 2^13) and limbs
 in two passes, ranges of one arithmetic and ranges that mix both, with and without the second stream, every load of the
 inverse transform (plain, product of two ciphertexts, rotation).  Bit for bit against the oracle, extreme residues planted.
 """
