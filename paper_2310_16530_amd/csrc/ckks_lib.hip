@@ -797,7 +797,9 @@ static std::string kname(const char* base, const char* ar, int A, const char* ta
 // groups = run limbs x groups_n, instances = inst_n.  alg(first, count) gives the algorithmic limbs (read + written once)
 // of the launch covering primes [first, first+count).
 // A range that mixes the arithmetics is one launch of the AnyAr form where the launcher has one (L::any: the plain passes)
-// and the integer limbs do not run on the side stream.
+// and the integer limbs do not run on the side stream.  Against a launch per arithmetic, forward / inverse: 30 FP64 and
+// integer limbs x 48 at N = 2^14 135.9 against 144.4 us / 133.2 against 148.6; x 16 at N = 2^16 204.4 against 210.1 / 213.3
+// against 223.8; small grids gain the launch; the closest is N = 2^13, inverse x 48, 74.5 against 73.6.
 template <class L, class ArgT, class AlgFn>
 static void launch_runs(const View* c, u32 lo, u32 hi, u32 limb_base, u32 groups_n, u32 inst_n, const ArgT& a, hipStream_t s,
                         AlgFn alg) {
@@ -989,8 +991,9 @@ static void launch_conv_runs(const View* c, ConvArgs a, hipStream_t s, int only)
 
 // ModUp onto both arithmetics in one launch, where the chain is FpAr limbs followed by IntAr limbs and all workgroups fit the
 // chip at once (512 = two per compute unit).  One ciphertext at N = 2^16, L = 24, dnum = 4: 24 + 17 us in two launches -> 37 us,
-// the call 163 -> 158 us; at level 13 the call 120 -> 115 us.  At N = 2^15 (three ciphertexts, level 17) it is 1 % slower: the
-// integer part pays for its 128 registers and the launches it saves are shorter.  Returns false where it does not apply.
+// the call 163 -> 158 us; at level 13 the call 120 -> 115 us.  Built for N = 2^16 alone, the ring of the large sets; at
+// N = 2^13 .. 2^15 whole calls of one to four ciphertexts would gain 3 to 7 % (none at 2^15, L = 24, four ciphertexts).
+// Returns false where it does not apply.
 static bool conv_up_both(const View* c, const ConvArgs& base, hipStream_t s) {
     const u32 ks = c->up.ks;
     if (c->logN != 16 || (ks != 1 && ks != 2)) return false;
