@@ -349,9 +349,9 @@ int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64_t* d_ct, u
  * ckks_hrot and their _at / _multi / _rescale forms run the ModUp conversion of the floating-point-arithmetic
  * limbs there, beside the inner product and ModDown conversion of the integer-arithmetic limbs (primes of
  * 50 bits and more, normally the special limbs), unless one launch converts both (small calls at N = 2^16);
- * hoisted calls of many rotations (enough to fill the GPU several times) run the launches on
- * integer-arithmetic limbs there, beside those on floating-point-arithmetic limbs; smaller hoisted calls and
- * the decompositions of double-hoisted and baby-step giant-step calls stay on the caller's stream.
+ * hoisted calls of many rotations and double-hoisted calls of large decompositions (enough to fill the GPU
+ * several times) run the launches on integer-arithmetic limbs there, beside those on floating-point-arithmetic
+ * limbs; smaller ones and the decomposition of baby-step giant-step calls stay on the caller's stream.
  * Needs both classes of primes in the chain, otherwise nothing changes.  Results are identical; the call
  * still completes in stream order on the caller's stream.  Not to be changed while a call of this context
  * is being issued.

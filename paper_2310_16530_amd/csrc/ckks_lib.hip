@@ -1146,25 +1146,31 @@ static void launch_bsgs_mac(const View* c, const BsgsMacArgs& a, hipStream_t s) 
 // fill in.  9 rotations at N = 2^16, L + K = 12 + 4, dnum = 3: the call 248 us before the wide form, 268 with it, 257 with
 // the narrow one; at N = 2^15, 27 + 3, dnum = 9, 5 rotations: 346, 365, 346.  On mixed chains the wide form is the faster one
 // (18 rotations, 24 + 6, dnum = 4: 669 against 683 us).
-static void launch_dh_accum(const View* c, DhInnerArgs a, hipStream_t s) {
+static void launch_dh_accum_run(const View* c, DhInnerArgs a, u32 first, u32 count, bool all_int, hipStream_t s) {
     const u64 n_rot = a.n_rot, acc = a.accumulate ? 2 : 0, dnum = c->dnum;
+    a.first = first, a.count = count;
     // With few rotations the accumulation is a chain of a few waits on the keys, which more wavefronts in flight shorten
     // (N = 2^16, 26 + 6 limbs, dnum 5: 3 rotations 317 us wide, 310 narrow, 6 rotations 441 / 425, 8 rotations 507 / 497); from
     // about ten on the wide rows of a mixed chain are even or up to 3 % faster.
-    const bool all_int = !any_fp_prime(c, 0, c->D), narrow = all_int || n_rot <= 8;
-    const u32 rows = c->D * ((1u << c->logN) / (64 * (narrow ? 2 : 4)));
+    const bool narrow = all_int || n_rot <= 8;
+    const u32 rows = count * ((1u << c->logN) / (64 * (narrow ? 2 : 4)));
     // Four rows per workgroup, or one whose rotations the four wavefronts share.  Narrow: fewer rounds of the 1280 resident
     // workgroups times rotations per wavefront.  Wide: with fewer than eight rotations the wavefronts would end up with
     // unequal shares, which only a grid below two workgroups per compute unit makes up for.
     if (narrow) a.waves = (rows + 1279) / 1280 * ((a.n_rot + 3) / 4) < (rows / 4 + 1279) / 1280 * a.n_rot ? 4 : 1;
     else a.waves = n_rot >= 8 || (rows / 4 < 512 && n_rot > 1) ? 4 : 1;
     u64 limbs = 0;  // per limb and rotation: the digits, the plaintext, both key components (and b on q-limbs); C_t written
-    for (u32 i = 0; i < c->D; i++) limbs += n_rot * (3 * dnum + (a.pt ? 1 : 0) + (i < c->L ? 1 : 0)) + (a.each ? 2 * n_rot : 2) + acc;
+    for (u32 i = first; i < first + count; i++) limbs += n_rot * (3 * dnum + (a.pt ? 1 : 0) + (i < c->L ? 1 : 0)) + (a.each ? 2 * n_rot : 2) + acc;
     ProfScope ps(c, c->sh->prof.on ? std::string(all_int ? "dh_accum_kernel<IntAr, 2>" : narrow ? "dh_accum_kernel<AnyAr, 2>" : "dh_accum_kernel<AnyAr, 4>") : std::string(), limbs, s);
     const dim3 grid((rows * a.waves / 4 + 7) / 8 * 8);
     if (all_int) hipLaunchKernelGGL((dh_accum_kernel<IntAr, 2>), grid, dim3(256), 0, s, a, c->tb);
     else if (narrow) hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 2>), grid, dim3(256), 0, s, a, c->tb);
     else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 4>), grid, dim3(256), 0, s, a, c->tb);
+}
+// one launch, or one per arithmetic while the integer limbs have the side stream
+static void launch_dh_accum(const View* c, const DhInnerArgs& a, hipStream_t s) {
+    if (!c->sh->side.active) return launch_dh_accum_run(c, a, 0, c->D, !any_fp_prime(c, 0, c->D), s);
+    for (const ClassRun& r : class_runs(c, 0, c->D)) launch_dh_accum_run(c, a, r.first, r.count, !r.fp, r.fp ? s : c->sh->side.stream);
 }
 
 template <int MODE>
@@ -1833,7 +1839,11 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
         const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
         launch_decompose_inverse<INV_PLAIN>(c, a1, s);
-        decompose_extend(c, w, 1, s, EXTEND_PLAIN);
+        // From five rounds of extended workgroups on the integer limbs take the second stream up to the ModDown conversion (rotations:
+        // one stream / two, us; N = 2^16: 40 + 10 limbs, dnum 4 (3200 workgroups) 1: 317 / 281, 6: 566 / 533, 24: 1325 / 1305; 26 + 6,
+        // dnum 5 (2560) 1: 221 / 216, 6: 426 / 411).  Below, splitting the joint launches costs more (24 + 6, dnum 4 (1920) 1: 186 /
+        // 196, 12: 514 / 512; level 13 (912) 1: 129 / 146, 6: 218 / 228, 12: 313 / 300).
+        decompose_extend(c, w, 1, s, c->dnum * c->D * tiles_of(c) >= 5 * 512 ? EXTEND_FORK : EXTEND_PLAIN);
         launch_extended_fwd_contig(c, w, s);
     }
     for (u32 r0 = 0; r0 < n_rot; r0 += CKKS_DH_CHUNK) {

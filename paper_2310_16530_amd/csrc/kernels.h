@@ -1196,6 +1196,7 @@ struct DhInnerArgs {
     u32 accumulate;  // add to what cq / cp already hold (a call with more rotations than one launch takes)
     u32 split;       // limbs below split go to cq ([2][split][N]), the others to cp ([2][D - split][N])
     u32 waves;       // wavefronts of a workgroup that share a row, each taking every waves-th rotation: 1 (four rows) or 4
+    u32 first, count;  // limbs of this launch
     u32 each;        // rotations are not summed: rotation r's result goes to cq + r*2*split*N, cp + r*2*(D - split)*N
 };
 
@@ -1389,11 +1390,11 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
 template <class AR, int W>
 __global__ __launch_bounds__(256, W == 4 ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
     __shared__ __align__(16) u64 lds[512 * W];  // a row per wavefront to permute it in; eight to join four pairs of sums
-    const u32 rows_wg = 4 / a.waves, per_limb = ((1u << tb.logN) / (64 * W)) / rows_wg, total = tb.D * per_limb, per = (total + 7) / 8;
+    const u32 rows_wg = 4 / a.waves, per_limb = ((1u << tb.logN) / (64 * W)) / rows_wg, total = a.count * per_limb, per = (total + 7) / 8;
     const u32 pos = blockIdx.x >> 3, q = (blockIdx.x & 7) * per + pos;  // workgroups go to the XCDs round-robin
     if (pos >= per || q >= total) return;
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: addresses stay in scalar registers
-    const u32 i = q / per_limb, row = (q % per_limb) * rows_wg + (a.waves == 1 ? wave : 0);
+    const u32 i = a.first + q / per_limb, row = (q % per_limb) * rows_wg + (a.waves == 1 ? wave : 0);
     const PrimeConst pc = tb.pc[tb.phys(i)];
     CKKS_BY_ARITHMETIC(AR, i, (dh_accum_body<AR_, W>(a, tb, pc, lds, i, row, wave)))
 }

@@ -164,6 +164,38 @@ def test_double_hoisted_sum_on_mixed_chains(orc, logN, q, p, dnum, counts):
         assert np.array_equal(got, orc.lintrans_bsgs_level(ct, gs[:2], keys[:2], gs[2:3], keys[2:], pt[:2].reshape(1, 2, -1, ps.N), P))
 
 
+@pytest.mark.parametrize("logN,q,p,dnum,two", [(16, (49,) * 26, (59,) * 6, 5, True), (16, (49,) * 25, (59,) * 6, 5, False), (14, (49, 55) * 12, (48, 60, 49), 24, True),
+                                               (14, (55,) * 12 + (49,) * 11, (60, 59), 23, False)])
+def test_double_hoisted_calls_with_the_second_stream_at_work(orc, logN, q, p, dnum, two):
+    """From dnum * (L + K) * N / 2^12 = 2560 workgroups on the integer limbs run on the second stream up to the ModDown: integer and FP64
+    special limbs, alternating limbs, more rotations than one launch takes, the merged rescale, repeated calls."""
+    ps = synth.mixed_params(logN, list(q), list(p), dnum, "dh_two")
+    assert (dnum * (ps.L + ps.K) * (ps.N >> 12) >= 2560) == two
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(2560 + logN + len(q))
+    keys = [synth.uniform_residues(rng, ps.primes, ps.N, lead=(ps.dnum, 2)) for _ in range(2)]
+    d_keys = [dev(k) for k in keys]
+    n = 3 if logN == 16 else 35
+    gs = [synth.galois_element((-1) ** r * (r + 1), logN) for r in range(n)]
+    ct, pt = synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(2,)), synth.uniform_residues(rng, ps.primes, ps.N, lead=(n,))
+    d_ct, d_pt = dev(ct), dev(pt)
+    for count in (1, n):
+        print(logN, "rotations", count, flush=True)
+        args = d_ct, gs[:count], [d_keys[r % 2] for r in range(count)], d_pt[:count].contiguous()
+        want = orc.hrot_dh_mac_level(ct, gs[:count], [keys[r % 2] for r in range(count)], pt[:count], P)
+        merged = host(ctx.hrot_dh_mac_rescale_at(ps.L, *args))
+        ctx.set_overlap(True)
+        try:
+            got, names = _kernels(ctx, lambda: ctx.hrot_dh_mac(*args))
+            assert np.array_equal(got, want), count
+            assert ("dh_accum_kernel<IntAr, 2>" in names) == two, names
+            for _ in range(3):
+                assert np.array_equal(host(ctx.hrot_dh_mac_rescale_at(ps.L, *args)), merged), count
+                assert np.array_equal(host(ctx.hrot_dh_mac(*args)), want), count
+        finally:
+            ctx.set_overlap(False)
+
+
 @pytest.mark.parametrize("logN", [12, 13])
 @pytest.mark.parametrize("q", [(49,) * 3, (55, 56, 57), (49, 55) * 5, (49,) * 7 + (58,) * 5, (49,) * 26], ids=lambda q: str(len(q)))
 def test_workgroups_of_a_limb_each_at_any_share_of_the_chip(orc, logN, q):
