@@ -1113,11 +1113,6 @@ static void launch_ks_inner(const View* c, InnerArgs a, hipStream_t s, u32 lo, u
         dispatch_kernel<L>(c, cr.fp, grid, rs, a, LimbRun{cr.first, cr.count});
     }
 }
-template <int OWN, bool HOISTED>
-static void launch_ks_inner(const View* c, const InnerArgs& a, hipStream_t s) {
-    launch_ks_inner<OWN, HOISTED, false>(c, a, s, 0, c->D);
-}
-
 #define CKKS_BSGS_EPT 4
 struct BsgsMacL {
     template <class AR, int A>
@@ -1167,16 +1162,17 @@ static void launch_dh_accum_run(const View* c, DhInnerArgs a, u32 first, u32 cou
     else if (narrow) hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 2>), grid, dim3(256), 0, s, a, c->tb);
     else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 4>), grid, dim3(256), 0, s, a, c->tb);
 }
-// one launch, or one per arithmetic while the integer limbs have the side stream
-static void launch_dh_accum(const View* c, const DhInnerArgs& a, hipStream_t s) {
-    if (!c->sh->side.active) return launch_dh_accum_run(c, a, 0, c->D, !any_fp_prime(c, 0, c->D), s);
-    for (const ClassRun& r : class_runs(c, 0, c->D)) launch_dh_accum_run(c, a, r.first, r.count, !r.fp, r.fp ? s : c->sh->side.stream);
+// limbs [0, hi) in one launch, or one per arithmetic while the integer limbs have the side stream
+static void launch_dh_accum(const View* c, const DhInnerArgs& a, hipStream_t s, u32 hi) {
+    if (!c->sh->side.active) return launch_dh_accum_run(c, a, 0, hi, !any_fp_prime(c, 0, hi), s);
+    for (const ClassRun& r : class_runs(c, 0, hi)) launch_dh_accum_run(c, a, r.first, r.count, !r.fp, r.fp ? s : c->sh->side.stream);
 }
 
 template <int MODE>
 static void launch_ks_final(const View* c, const FinalArgs& a, hipStream_t s) {
     u64 per;  // algorithmic limbs per q-limb
     if (MODE == FIN_HOISTED) per = (u64)a.n_rot * (2 + 2 + 1 + 1) + (2 + (a.accumulate ? 2 : 0));
+    else if (MODE == FIN_SUMMED) per = (u64)a.n_rot * (2 + 1) + (2 + 2 + (a.accumulate ? 2 : 0));
     else per = (u64)a.n_inst * 6;
     launch_runs<KsFinalL<MODE>>(c, 0, c->L, 0, tiles_of(c), a.n_inst, a, s, [per](u32, u32 n) { return per * n; });
 }
@@ -1572,7 +1568,7 @@ static void keyswitch_pipeline(const View* c, const View* cm, const u64* in1, co
     launch_decompose_inverse<LOAD>(c, a1, s);
     decompose_extend(c, w, batch, s, EXTEND_BESIDE);
     ia.dt = w.dt, ia.own = in1, ia.own2 = in2;
-    ia.cq = w.cq, ia.cp = w.cp, ia.n_inst = batch, ia.split = cm->L;
+    ia.cp = w.cp, ia.n_inst = batch, ia.split = cm->L;
     // the limbs that feed the ModDown conversion first; the q-limbs then finish in one kernel, c' in registers.
     // Those of them that are FpAr primes (special primes below the FP64 limit; limb cm->L of the merged rescale) take
     // their digits from the FpAr conversion, which may still be running on the side stream.
@@ -1751,6 +1747,59 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     const size_t N = (size_t)1 << c->logN;
+    const SideStream& sd = c->sh->side;
+    // decompose a = ct[1] once and finish the transform of every extended limb
+    auto decompose = [&](const Workspace& w, ExtendMode mode) {
+        const LimbSel src = {c->L, 1, c->L, c->L, 0};  // limbs L .. 2L-1 of ct, primes 0 .. L-1
+        const LimbSel dst = {c->L, 1, c->L, 0, 0};
+        InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
+        launch_decompose_inverse<INV_PLAIN>(c, a1, s);
+        decompose_extend(c, w, 1, s, mode);
+        launch_extended_fwd_contig(c, w, s);
+    };
+    // Many rotations: the plaintext products of c' are summed before the ModDowns' converted parts join them (FIN_SUMMED), which takes
+    // the round trip of every rotation's c' away and costs one launch and the joint launch of both arithmetics.  More rotations
+    // than one launch of the other form takes: always faster (us, N = 2^16, 17 rotations, 24 + 6 limbs 1162 / 1043, level 13 725 /
+    // 674; 20 rotations, 6 + 6 limbs 449 / 411; N = 2^15, level 7, 20 rotations 324 / 312).  Up to 16 rotations, N = 2^16: 12, 24 + 6
+    // 820 / 770, 9 + 3 373 / 362, 6 + 6 265 / 269; 8, 9 + 3 267 / 269; N = 2^15, 12, 24 + 6 434 / 440, level 7 196 / 207.
+    if (n_rot > CKKS_ROT_CHUNK || (c->logN == 16 && n_rot >= 12 && c->L >= 9)) {
+        // Evenly sized chunks of as many rotations as the workspace has room for: x and dt, then the sum on the q-limbs ([2][L])
+        // and, per rotation, the special limbs ([2][K]) and the converted part ([2][L]).
+        Workspace w = carve(c, d_ws, 1, 1, 1);
+        u64 *const cq = w.cq, *const cp = cq + (size_t)2 * c->L * N;
+        const size_t fit = (need / sizeof(u64) / N - 3 * (size_t)c->L - (size_t)c->dnum * c->D) / (2 * (size_t)c->D);
+        const u32 most = fit < CKKS_DH_CHUNK ? (u32)fit : CKKS_DH_CHUNK, n_chunks = (n_rot + most - 1) / most;
+        const u32 chunk = (n_rot + n_chunks - 1) / n_chunks;
+        // second stream: the integer special limbs' inner products and inverse transforms beside the sum on the q-limbs
+        const bool fork = sd.enabled && c->mixed_classes && chunk * c->D * tiles_of(c) >= 5 * 512;
+        decompose(w, fork ? EXTEND_FORK : EXTEND_PLAIN);
+        for (u32 r0 = 0; r0 < n_rot; r0 += chunk) {
+            const u32 nr = (n_rot - r0) < chunk ? (n_rot - r0) : chunk;
+            DhInnerArgs da;
+            memset(&da, 0, sizeof(da));
+            for (u32 r = 0; r < nr; r++) da.key[r] = h_rk_ptrs[r0 + r], da.galois[r] = h_galois[r0 + r];
+            da.dt = w.dt, da.ct = d_ct, da.pt = d_pt + (size_t)r0 * c->L * N, da.pt_limbs = c->L, da.cq = cq;
+            da.n_rot = nr, da.split = c->L;
+            if (fork) fork_side(c, s);  // no-op in the first chunk (still forked); later chunks wait for the previous ModDown
+            launch_dh_accum(c, da, s, c->L);
+            for (u32 f = 0; f < nr; f += CKKS_ROT_CHUNK) {
+                InnerArgs ia;
+                memset(&ia, 0, sizeof(ia));
+                ia.n_inst = nr - f < CKKS_ROT_CHUNK ? nr - f : CKKS_ROT_CHUNK;
+                for (u32 r = 0; r < ia.n_inst; r++) ia.key[r] = da.key[f + r], ia.galois[r] = da.galois[f + r];
+                ia.dt = w.dt, ia.own = d_ct, ia.cp = cp + (size_t)f * 2 * c->K * N, ia.split = c->L;
+                launch_ks_inner<OWN_COPY, true>(c, ia, s, c->L, c->D);
+            }
+            w.cp = cp, w.cv = cp + (size_t)nr * 2 * c->K * N;
+            moddown_convert(c, w, nr, s);
+            FinalArgs fa;
+            memset(&fa, 0, sizeof(fa));
+            fa.cq = cq, fa.cv = w.cv, fa.pt = da.pt, fa.out = d_out;
+            fa.n_inst = 2, fa.n_rot = nr, fa.accumulate = r0 ? 1 : 0;
+            launch_ks_final<FIN_SUMMED>(c, fa, s);
+        }
+        return hip_check(c, "ckks_hrot_hoisted_mac");
+    }
     const u32 chunk_max = n_rot < CKKS_ROT_CHUNK ? n_rot : CKKS_ROT_CHUNK;
     const Workspace w = carve(c, d_ws, 1, 1, chunk_max);
     // rotations go through the ModDown side in chunks of at most CKKS_ROT_CHUNK, sized evenly
@@ -1761,15 +1810,7 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
     // N = 2^16, one stream / two: L + K = 30, 7 rotations (3360 workgroups) 550 / 526 us, 3 (1440) 303 / 314, 1 182 / 198;
     // 13 + 6, chunks of 9 (2736) 730 / 710; 10 + 5, chunks of 9 (2160) 546 / 567.
     const bool fork = chunk * c->D * tiles_of(c) >= 5 * 512;
-    // hoisted part: decompose a = ct[1] once and finish the transform of every extended limb
-    {
-        const LimbSel src = {c->L, 1, c->L, c->L, 0};  // limbs L .. 2L-1 of ct, primes 0 .. L-1
-        const LimbSel dst = {c->L, 1, c->L, 0, 0};
-        InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
-        launch_decompose_inverse<INV_PLAIN>(c, a1, s);
-        decompose_extend(c, w, 1, s, fork ? EXTEND_FORK : EXTEND_PLAIN);
-        launch_extended_fwd_contig(c, w, s);
-    }
+    decompose(w, fork ? EXTEND_FORK : EXTEND_PLAIN);
     for (u32 r0 = 0; r0 < n_rot; r0 += chunk) {
         const u32 nr = (n_rot - r0) < chunk ? (n_rot - r0) : chunk;
         InnerArgs ia;
@@ -1783,7 +1824,7 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
         }
         ia.dt = w.dt, ia.own = d_ct, ia.cq = w.cq, ia.cp = w.cp, ia.n_inst = nr, ia.split = c->L;
         if (fork) fork_side(c, s);  // no-op in the first chunk (still forked); later chunks wait for the previous ModDown
-        launch_ks_inner<OWN_COPY, true>(c, ia, s);
+        launch_ks_inner<OWN_COPY, true>(c, ia, s, 0, c->D);
         moddown_convert(c, w, nr, s);
         fa.cq = w.cq, fa.cq_L = c->L, fa.cv = w.cv, fa.ct1 = d_ct, fa.pt = d_pt + (size_t)r0 * c->L * N, fa.out = d_out;
         fa.n_inst = 2, fa.n_rot = nr, fa.accumulate = r0 ? 1 : 0;
@@ -1852,8 +1893,8 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
         memset(&ia, 0, sizeof(ia));
         for (u32 r = 0; r < nr; r++) ia.key[r] = h_rk_ptrs[r0 + r], ia.galois[r] = h_galois[r0 + r];
         ia.dt = w.dt, ia.ct = d_ct, ia.pt = d_pt + (size_t)r0 * c->D * N, ia.cq = w.cq, ia.cp = w.cp;
-        ia.n_rot = nr, ia.accumulate = r0 ? 1 : 0, ia.split = cm->L;
-        launch_dh_accum(c, ia, s);
+        ia.n_rot = nr, ia.accumulate = r0 ? 1 : 0, ia.split = cm->L, ia.pt_limbs = c->D;
+        launch_dh_accum(c, ia, s, c->D);
     }
     {  // ModDown of the sum: first inverse pass of its source limbs, then the shared tail
         const LimbSel sel = {cm->K, 2, cm->K, 0, cm->L};
@@ -1964,7 +2005,7 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         for (u32 b = 0; b < nb; b++) ia.key[b] = h_baby_rk_ptrs[b0 + b], ia.galois[b] = h_baby_galois[b0 + b];
         ia.dt = w.dt, ia.ct = d_ct, ia.pt = nullptr, ia.cq = rq + (size_t)b0 * 2 * LN, ia.cp = rp + (size_t)b0 * 2 * KN;
         ia.n_rot = nb, ia.each = 1, ia.accumulate = 0, ia.split = c->L;
-        launch_dh_accum(c, ia, s);
+        launch_dh_accum(c, ia, s, c->D);
     }
     // giant-step combinations in the extended basis, then one ModDown per giant step (as a batch)
     BsgsMacArgs ma = {rq, rp, d_pt, w.cq, w.cp, n1, n2};

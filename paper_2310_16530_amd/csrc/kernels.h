@@ -1187,7 +1187,8 @@ __global__ __launch_bounds__(256, 2) void ks_inner_kernel(InnerArgs a, Tables tb
 struct DhInnerArgs {
     const u64* dt;   // [dnum][D][N] canonical evaluation form
     const u64* ct;   // [2][L][N]
-    const u64* pt;   // [n_rot][D][N] canonical evaluation form, extended basis; null = the constant 1
+    const u64* pt;   // [n_rot][pt_limbs][N] canonical evaluation form; null = the constant 1
+    u32 pt_limbs;    // D: extended basis; L: q-limbs, for a launch on those alone
     const u64* key[CKKS_DH_CHUNK];
     u32 galois[CKKS_DH_CHUNK];
     u64* cq;         // [2][L][N]
@@ -1266,7 +1267,7 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
     const u64 *ct = a.ct, *dt = a.dt;
 #pragma unroll
     for (int k = 0; k < W; k++) ptv[k] = 1;
-    const size_t pt_step = (size_t)D * N;
+    const size_t pt_step = (size_t)a.pt_limbs * N;
     // EVEN: every request is the same number of loads, and what a term does not need is the source row once more (L2): behind
     // a branch that may skip some, the compiler waits for all of them before the previous term's words are used.  The narrow
     // form gains (18 rotations, L + K = 12 + 4, dnum = 3: 360 -> 354 us), the wide one loses by the extra loads (24 + 6: 672 -> 684).
@@ -1479,19 +1480,22 @@ __global__ __launch_bounds__(256) void sum_instances_kernel(const u64* __restric
 // ks_t[i] = (c'_t[i] - NTT(conv_t)[i]) * P^-1 mod q_i, the NTT's second pass done here, then
 //   FIN_KS     : out[inst][t][i] = ks
 //   FIN_HOISTED: out[t][i] (+)= sum_r pt_r[i] * (ks_r + (t == 0 ? sigma_{g_r}(b) : 0)); work item (i, tile, t)
+//   FIN_SUMMED : the same words as (C_t - sum_r pt_r * NTT(conv_{r,t})) * P^-1 with C_t = sum_r pt_r * (c'_{r,t} + P * (t == 0 ?
+//                sigma_{g_r}(b) : 0)), which dh_accum_kernel has left in cq: on a q-limb everything after the conversions is linear,
+//                so neither c' nor sigma_{g_r}(b) of a single rotation reaches memory; work item (i, tile, t)
 // (HMult, HRot and the plain key switch end inside the inner-product kernel, which also adds the tensor
 // terms or sigma_g(b).)  The numbering keeps kernel names stable.
-enum FinalMode { FIN_KS = 0, FIN_HOISTED = 3 };
+enum FinalMode { FIN_KS = 0, FIN_HOISTED = 3, FIN_SUMMED = 4 };
 struct FinalArgs {
-    const u64* cq;   // [g][2][L][N] canonical
+    const u64* cq;   // [g][2][L][N] canonical; SUMMED: C [2][L][N]
     const u64* cv;   // [g][2][L][N] raw forward-lazy (first pass done)
     const u64* ct1;  // HOISTED: ct
-    const u64* pt;   // HOISTED: plaintexts of this chunk [n_rot][L][N]
+    const u64* pt;   // HOISTED, SUMMED: plaintexts of this chunk [n_rot][L][N]
     u64* out;
-    u32 galois[CKKS_ROT_CHUNK];
-    u32 n_inst;      // batch (or 2 for HOISTED: the component t)
-    u32 n_rot;       // HOISTED
-    u32 accumulate;  // HOISTED: add to what out already holds
+    u32 galois[CKKS_ROT_CHUNK];  // HOISTED
+    u32 n_inst;      // batch (or 2 for HOISTED and SUMMED: the component t)
+    u32 n_rot;       // HOISTED, SUMMED
+    u32 accumulate;  // HOISTED, SUMMED: add to what out already holds
     u32 cq_L;        // limbs per component of cq (L, or L + 1 when cq is a ciphertext about to lose its last limb)
 };
 
@@ -1582,6 +1586,58 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
         store_row_cp(o, e0, res);
         return;
     }
+    if (MODE == FIN_SUMMED) {
+        const u32 t = inst;
+        double facc[AR::is_fp ? 16 : 1];
+        u128w iacc[AR::is_fp ? 1 : 16];
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            if constexpr (AR::is_fp) facc[k] = 0.0;
+            else iacc[k] = u128w{0, 0};
+        }
+        for (u32 rr = 0; rr < a.n_rot; rr++) {
+            T v[16];
+            const u64* p = a.cv + (((size_t)rr * 2 + t) * L + i) * N + row_off;
+#pragma unroll
+            for (int k = 0; k < 16; k++) v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
+            u64 ptw[16];
+            load_row_cp<true>(a.pt + ((size_t)rr * L + i) * N + row_off, e0, ptw);
+            NttCore<AR, A>::fwd_contig(v, lrow, e0, r, ti, tf, N, m);
+            exchange_cb_to_cp<AR>(v, lrow, e0);
+#pragma unroll
+            for (int k = 0; k < 16; k++) {
+                // FP64: reduced to <= q/2 so that the at most 8 products accumulated between folds stay below 6 q.  Integers: a
+                // term below 2q * q < q * 2^62, eight of them on hi < q below 3q * 2^64; hi alone takes multiples of q * 2^64 off
+                if constexpr (AR::is_fp) facc[k] += FpAr::mulmod_lazy(FpAr::reduce(v[k], FpAr::mod(pc)), u64_to_f64(ptw[k]), FpAr::mod(pc));
+                else mac128(iacc[k], csub(csub(v[k], 4 * q), 2 * q), ptw[k]);
+            }
+            if ((rr & 7) == 7) {
+#pragma unroll
+                for (int k = 0; k < 16; k++) {
+                    if constexpr (AR::is_fp) facc[k] = FpAr::reduce(facc[k], FpAr::mod(pc));
+                    else iacc[k].hi = csub(csub(iacc[k].hi, 2 * q), q);
+                }
+            }
+        }
+        u64* o = a.out + ((size_t)t * L + i) * N + row_off;
+        u64 c[16], prev[16], res[16];
+        load_row_cp<true>(a.cq + ((size_t)t * L + i) * N + row_off, e0, c);
+        if (a.accumulate) load_row_cp<false>(o, e0, prev);
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            if constexpr (AR::is_fp) {
+                const FpAr::Mod fm = FpAr::mod(pc);
+                double x = FpAr::mulmod_lazy(u64_to_f64(c[k]) - FpAr::reduce(facc[k], fm), pinv.d, fm);
+                if (a.accumulate) x += u64_to_f64(prev[k]);
+                res[k] = FpAr::canon(x, fm);
+            } else {
+                res[k] = mul_shoup(submod(c[k], reduce128(iacc[k], q, pc.qneg, pc.r2), q), pinv.w, pinv.wp, q);
+                if (a.accumulate) res[k] = addmod(res[k], prev[k], q);
+            }
+        }
+        store_row_cp(o, e0, res);
+        return;
+    }
 #pragma unroll
     for (int t = 0; t < 2; t++) {
         T v[16];
@@ -1606,7 +1662,7 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
 }
 
 template <class AR, int A, int MODE>
-__global__ __launch_bounds__(256, MODE == FIN_HOISTED ? (AR::is_fp ? 3 : 2) : 4) void ks_final_kernel(FinalArgs a, Tables tb, LimbRun run) {
+__global__ __launch_bounds__(256, MODE != FIN_KS ? (AR::is_fp ? 3 : 2) : 4) void ks_final_kernel(FinalArgs a, Tables tb, LimbRun run) {
     __shared__ u64 lds[NTT_LDS_WORDS];
     constexpr u32 TILES = (1u << A) / 16;
     u32 group, inst;

@@ -1,0 +1,55 @@
+"""Parity where sums over rotations are formed before the ModDown's converted part joins them (needs an MI355X): rotation counts on
+both sides of the rules and of every chunk, chains of either arithmetic, extreme residues, both stream modes.  Bit for bit
+against the oracle, which follows the definition rotation by rotation.
+"""
+import numpy as np
+import pytest
+
+from paper_2310_16530_amd import synth
+
+from test_gpu_forms_by_size import _below, _kernels
+from test_gpu_parity import dev, gpu_ctx, host, orc_params
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(ps, n, n_keys, seed, pt_primes, lead):
+    rng = np.random.default_rng(seed)
+    gs = [synth.galois_element((-1) ** r * (r // 2 + 1), ps.logN) for r in range(n)]
+    keys = [synth.uniform_residues(rng, ps.primes, ps.N, lead=(ps.dnum, 2)) for _ in range(n_keys)]
+    ct, pt = synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(2,)), synth.uniform_residues(rng, pt_primes, ps.N, lead=lead)
+    for x, primes in ((ct, ps.q_primes), (pt, pt_primes), *((k, ps.primes) for k in keys)):
+        for i, m in enumerate(primes):
+            x[..., i, : ps.N // 2] = m - 1
+    return gs, keys, ct, pt
+
+
+@pytest.mark.parametrize("logN,q,p,dnum,counts", [
+    (12, (49,) * 3, (59,), 3, (16, 17, 24, 41)),          # three digits of one limb, one special prime
+    (12, (49, 60, 50, 58), (48, 60), 2, (17, 33)),        # both arithmetics among q-limbs and special limbs
+    (13, (49, 49), (59,) * 7, 1, (17, 18, 35)),           # more special than ciphertext limbs: little room per chunk
+    (12, None, 2, 2, (17, 26)),                           # integer primes just below 2^61
+    (16, (49,) * 9, (59,) * 3, 3, (11, 12)),              # both sides of the rule up to 16 rotations
+])
+def test_hoisted_sums_before_the_mod_down(orc, logN, q, p, dnum, counts):
+    if q is None:
+        primes = _below(1 << 61, 2 << logN, 6 + p)
+        ps = synth.ExplicitParamSet("below_2_61", logN, dnum, primes[:6], primes[6:])
+    else:
+        ps = synth.mixed_params(logN, list(q), list(p), dnum, "sums")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    n = max(counts)
+    gs, keys, ct, pt = _inputs(ps, n, 3, 1700 + logN + dnum, ps.q_primes, (n,))
+    d_ct, d_pt, d_keys = dev(ct), dev(pt), [dev(k) for k in keys]
+    for m in counts:
+        print(logN, "rotations", m, flush=True)
+        want = orc.hrot_hoisted_mac(ct, gs[:m], [keys[r % 3] for r in range(m)], pt[:m], P)
+        for overlap in (False, True):
+            ctx.set_overlap(overlap)
+            try:
+                got, names = _kernels(ctx, lambda: ctx.hrot_hoisted_mac(d_ct, gs[:m], [d_keys[r % 3] for r in range(m)], d_pt[:m].contiguous()))
+            finally:
+                ctx.set_overlap(False)
+            assert np.array_equal(got, want), (m, overlap)
+            summed = m > 16 or (logN == 16 and m >= 12 and ps.L >= 9)
+            assert any(k.startswith("ks_final_kernel") and k.endswith(", 4>") for k in names) == summed, names
