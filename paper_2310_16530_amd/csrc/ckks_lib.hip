@@ -841,6 +841,14 @@ struct InvStridedL {
     }
     static std::string name(const char* ar, int A) { return kname("inv_strided_kernel", ar, A, ""); }
 };
+struct InvStridedSumL {
+    static constexpr bool any = false;
+    template <class AR, int A>
+    static void go(dim3 g, hipStream_t s, const InvStridedSumArgs& a, const Tables& tb, LimbRun run) {
+        hipLaunchKernelGGL((inv_strided_sum_kernel<AR, A>), g, dim3(1024), 0, s, a, tb, run);
+    }
+    static std::string name(const char* ar, int A) { return kname("inv_strided_sum_kernel", ar, A, ""); }
+};
 struct FwdStridedL {
     static constexpr bool any = true;
     template <class AR, int A>
@@ -1092,16 +1100,19 @@ static void launch_ks_inner(const View* c, InnerArgs a, hipStream_t s, u32 lo, u
     const bool any = HOISTED && runs.size() > 1 && !c->sh->side.active;
     if (any) runs.assign(1, ClassRun{lo, hi - lo, true});
     for (const ClassRun& cr : runs) {
-        a.ways = HOISTED ? 1 : inner_ways(cr.count * tiles_of(c) * a.n_inst, c->dnum);
+        const u32 terms = (OWN == OWN_ROT_SUM ? a.n_sum : 1) * c->dnum;
+        a.ways = HOISTED ? 1 : inner_ways(cr.count * tiles_of(c) * a.n_inst, terms);
         hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
         u64 limbs = 0;
         for (u32 i = cr.first; i < cr.first + cr.count; i++) {
             const bool q = i < c->L;
-            limbs += n_inst * ((u64)c->dnum - (q ? 1 : 0)            // extended digits outside their own limbs
-                               + (q ? (OWN == OWN_TENSOR ? 4 : 1) : 0)  // the switched polynomial (HMult: both inputs) on its own limb
+            const u64 sums = OWN == OWN_ROT_SUM ? a.n_sum : 1;
+            limbs += n_inst * (sums * ((u64)c->dnum - (q ? 1 : 0)        // extended digits outside their own limbs
+                                       + (q ? (OWN == OWN_TENSOR ? 4 : 1) : 0)       // the switched polynomial (HMult: both inputs) on its own limb
+                                       + (OWN == OWN_ROT || OWN == OWN_ROT_SUM ? FUSED : 0))  // sigma_g(b)
                                + 2                                     // c' (or the result) written
-                               + (FUSED ? 2 + (OWN == OWN_ROT ? 1 : 0) : 0))  // converted special part (+ sigma_g(b))
-                     + (HOISTED ? n_inst : 1) * 2 * (u64)c->dnum;      // key limbs
+                               + (FUSED ? 2 : 0))                      // converted special part
+                     + (HOISTED ? n_inst : sums) * 2 * (u64)c->dnum;   // key limbs
         }
         const dim3 grid(xcd_grid(cr.count * tiles_of(c) * a.ways, a.n_inst));
         ProfScope ps(c, c->sh->prof.on ? L::name(any ? "AnyAr" : cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(), limbs, rs);
@@ -1142,25 +1153,37 @@ static void launch_bsgs_mac(const View* c, const BsgsMacArgs& a, hipStream_t s) 
 // the narrow one; at N = 2^15, 27 + 3, dnum = 9, 5 rotations: 346, 365, 346.  On mixed chains the wide form is the faster one
 // (18 rotations, 24 + 6, dnum = 4: 669 against 683 us).
 static void launch_dh_accum_run(const View* c, DhInnerArgs a, u32 first, u32 count, bool all_int, hipStream_t s) {
-    const u64 n_rot = a.n_rot, acc = a.accumulate ? 2 : 0, dnum = c->dnum;
+    const u64 n_rot = a.n_rot, acc = a.accumulate ? 2 : 0, dnum = c->dnum, sums = a.sums ? a.sums : 1;
     a.first = first, a.count = count;
     // With few rotations the accumulation is a chain of a few waits on the keys, which more wavefronts in flight shorten
     // (N = 2^16, 26 + 6 limbs, dnum 5: 3 rotations 317 us wide, 310 narrow, 6 rotations 441 / 425, 8 rotations 507 / 497); from
-    // about ten on the wide rows of a mixed chain are even or up to 3 % faster.
-    const bool narrow = all_int || n_rot <= 8;
+    // about ten on the wide rows of a mixed chain are even or up to 3 % faster.  Several sums: narrow rows, for the registers (four
+    // sums with the products inside the digit loop spilled: 577 us, after it 390).
+    const bool narrow = all_int || n_rot <= 8 || sums > 1;
     const u32 rows = count * ((1u << c->logN) / (64 * (narrow ? 2 : 4)));
     // Four rows per workgroup, or one whose rotations the four wavefronts share.  Narrow: fewer rounds of the 1280 resident
-    // workgroups times rotations per wavefront.  Wide: with fewer than eight rotations the wavefronts would end up with
-    // unequal shares, which only a grid below two workgroups per compute unit makes up for.
-    if (narrow) a.waves = (rows + 1279) / 1280 * ((a.n_rot + 3) / 4) < (rows / 4 + 1279) / 1280 * a.n_rot ? 4 : 1;
+    // workgroups (768 with several sums) times rotations per wavefront.  Wide: with fewer than eight rotations the wavefronts
+    // would end up with unequal shares, which only a grid below two workgroups per compute unit makes up for.
+    const u32 resident = sums > 1 ? 768 : 1280;
+    if (narrow) a.waves = (rows + resident - 1) / resident * ((a.n_rot + 3) / 4) < (rows / 4 + resident - 1) / resident * a.n_rot ? 4 : 1;
     else a.waves = n_rot >= 8 || (rows / 4 < 512 && n_rot > 1) ? 4 : 1;
-    u64 limbs = 0;  // per limb and rotation: the digits, the plaintext, both key components (and b on q-limbs); C_t written
-    for (u32 i = first; i < first + count; i++) limbs += n_rot * (3 * dnum + (a.pt ? 1 : 0) + (i < c->L ? 1 : 0)) + (a.each ? 2 * n_rot : 2) + acc;
-    ProfScope ps(c, c->sh->prof.on ? std::string(all_int ? "dh_accum_kernel<IntAr, 2>" : narrow ? "dh_accum_kernel<AnyAr, 2>" : "dh_accum_kernel<AnyAr, 4>") : std::string(), limbs, s);
+    u64 limbs = 0;  // per limb and rotation: the digits, the plaintexts, both key components (and b on q-limbs); C_t written
+    for (u32 i = first; i < first + count; i++) limbs += n_rot * (3 * dnum + (a.pt ? sums : 0) + (i < c->L ? 1 : 0)) + (a.each ? 2 * n_rot : 2 * sums) + acc;
+    const std::string form = std::string(all_int ? "IntAr, " : "AnyAr, ") + (narrow ? "2" : "4") + (sums > 1 ? ", " + std::to_string(sums) : std::string());
+    ProfScope ps(c, c->sh->prof.on ? "dh_accum_kernel<" + form + ">" : std::string(), limbs, s);
     const dim3 grid((rows * a.waves / 4 + 7) / 8 * 8);
-    if (all_int) hipLaunchKernelGGL((dh_accum_kernel<IntAr, 2>), grid, dim3(256), 0, s, a, c->tb);
-    else if (narrow) hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 2>), grid, dim3(256), 0, s, a, c->tb);
-    else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 4>), grid, dim3(256), 0, s, a, c->tb);
+#define CKKS_DH(W, G)                                                                                          \
+    if (all_int) hipLaunchKernelGGL((dh_accum_kernel<IntAr, W, G>), grid, dim3(256), 0, s, a, c->tb);          \
+    else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, W, G>), grid, dim3(256), 0, s, a, c->tb)
+    switch (sums) {
+        case 2: CKKS_DH(2, 2); break;
+        case 3: CKKS_DH(2, 3); break;
+        case 4: CKKS_DH(2, 4); break;
+        default:
+            if (narrow) { CKKS_DH(2, 1); }
+            else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 4, 1>), grid, dim3(256), 0, s, a, c->tb);
+    }
+#undef CKKS_DH
 }
 // limbs [0, hi) in one launch, or one per arithmetic while the integer limbs have the side stream
 static void launch_dh_accum(const View* c, const DhInnerArgs& a, hipStream_t s, u32 hi) {
@@ -1546,6 +1569,37 @@ static void launch_extended_fwd_contig(const View* c, const Workspace& w, hipStr
 // cm: the view whose ModDown ends the pipeline: c itself, or the merged view of c's level (the ModDown then
 // also divides by the last q-limb: limb c->L - 1 joins the special limbs and the output has c->L - 1 limbs)
 // multi_galois / multi_keys (rotations only, batch <= CKKS_ROT_CHUNK): one Galois element and key per instance.
+// most rotations whose special parts may be added as integers: the eight digits of a conversion's source word hold the sum
+static u32 summed_rotations_max(const View* c) {
+    u64 most = 0;
+    for (u32 i = c->L; i < c->D; i++) most = c->primes[i] > most ? c->primes[i] : most;
+    const u64 fit = CKKS_DIGIT_MAX / most;
+    return fit < CKKS_ROT_CHUNK ? (u32)fit : CKKS_ROT_CHUNK;
+}
+
+// out = the sum of n (at most CKKS_ROT_CHUNK) rotated ciphertexts, each with its own element and key
+static void summed_rotations(const View* c, const u64* in, u32 n, const u32* galois, const u64* const* keys, u64* out, void* ws, hipStream_t s) {
+    const Workspace w = carve(c, ws, n, n, n, false);
+    const LimbSel sel = {c->L, n, c->L, 0, 0};
+    InvContigArgs a1;
+    memset(&a1, 0, sizeof(a1));
+    a1.src = in, a1.dst = w.x, a1.sel = sel, a1.dsel = sel, a1.per_inst = 1;
+    InnerArgs ia;
+    memset(&ia, 0, sizeof(ia));
+    ia.dt = w.dt, ia.own = in, ia.cp = w.cp, ia.n_inst = n, ia.split = c->L, ia.per_inst = 1;
+    for (u32 g = 0; g < n; g++) a1.galois[g] = ia.galois[g] = galois[g], ia.key[g] = keys[g];
+    launch_decompose_inverse<INV_ROT>(c, a1, s);
+    decompose_extend(c, w, n, s, EXTEND_BESIDE);
+    if (any_fp_prime(c, c->L, c->D)) join_fp_beside(c, s);  // as in keyswitch_pipeline
+    launch_ks_inner<OWN_COPY, false, false>(c, ia, s, c->L, c->D);
+    const InvStridedSumArgs a2 = {w.cp, LimbSel{c->K, 2, c->K, 0, c->L}, SC_DN, n};
+    launch_runs<InvStridedSumL>(c, c->L, c->D, c->L, tiles_of(c), 2, a2, s, [n](u32, u32 limbs) { return (u64)2 * limbs * (n + 1); });
+    moddown_convert(c, w, 1, s, true);
+    ia.cv = w.cv, ia.out = out, ia.fin_pinv = c->tb.pinv, ia.n_inst = 1, ia.n_sum = n;
+    join_fp_beside(c, s);
+    launch_ks_inner<OWN_ROT_SUM, false, true>(c, ia, s, 0, c->L);
+}
+
 template <int LOAD, int OWN>
 static void keyswitch_pipeline(const View* c, const View* cm, const u64* in1, const u64* in2, const u64* key, u64* out,
                                u32 batch, u32 galois, void* ws, hipStream_t s, const u32* multi_galois = nullptr,
@@ -1987,7 +2041,7 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
     w.cp = w.cq + (size_t)n2 * 2 * LN;
     w.cv = w.cp + (size_t)n2 * 2 * KN;
     u64* inner = w.cv + (size_t)n2 * 2 * LN;
-    u64* rot = inner + (size_t)n2 * 2 * LN;
+    u64* rot = inner + (size_t)n2 * 2 * LN;  // results to be added
     void* ks_ws = rot + (size_t)n2 * 2 * LN;
     {  // decomposition of the input, shared by every baby step
         const LimbSel src = {c->L, 1, c->L, c->L, 0};
@@ -1997,19 +2051,31 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         decompose_extend(c, w, 1, s, EXTEND_PLAIN);
         launch_extended_fwd_contig(c, w, s);
     }
-    // baby steps: R_b = P * Rot_b(ct) in the extended basis (inner product with the key, plus P * sigma_b(b))
-    for (u32 b0 = 0; b0 < n1; b0 += CKKS_DH_CHUNK) {
-        const u32 nb = (n1 - b0) < CKKS_DH_CHUNK ? (n1 - b0) : CKKS_DH_CHUNK;
+    // Baby steps and combinations in one kernel where its registers hold the sums (8 x 4, N = 2^16, 24 + 6 limbs: 468 -> 390 us; 8 x 3
+    // the call 1032 -> 880)
+    if (n2 <= CKKS_DH_SUMS && n1 <= CKKS_DH_CHUNK) {
         DhInnerArgs ia;
         memset(&ia, 0, sizeof(ia));
-        for (u32 b = 0; b < nb; b++) ia.key[b] = h_baby_rk_ptrs[b0 + b], ia.galois[b] = h_baby_galois[b0 + b];
-        ia.dt = w.dt, ia.ct = d_ct, ia.pt = nullptr, ia.cq = rq + (size_t)b0 * 2 * LN, ia.cp = rp + (size_t)b0 * 2 * KN;
-        ia.n_rot = nb, ia.each = 1, ia.accumulate = 0, ia.split = c->L;
+        for (u32 b = 0; b < n1; b++) ia.key[b] = h_baby_rk_ptrs[b], ia.galois[b] = h_baby_galois[b];
+        ia.dt = w.dt, ia.ct = d_ct, ia.pt = d_pt, ia.pt_limbs = c->D, ia.cq = w.cq, ia.cp = w.cp;
+        ia.n_rot = n1, ia.sums = n2, ia.split = c->L;
         launch_dh_accum(c, ia, s, c->D);
+    } else {
+        // baby steps: R_b = P * Rot_b(ct) in the extended basis (inner product with the key, plus P * sigma_b(b))
+        for (u32 b0 = 0; b0 < n1; b0 += CKKS_DH_CHUNK) {
+            const u32 nb = (n1 - b0) < CKKS_DH_CHUNK ? (n1 - b0) : CKKS_DH_CHUNK;
+            DhInnerArgs ia;
+            memset(&ia, 0, sizeof(ia));
+            for (u32 b = 0; b < nb; b++) ia.key[b] = h_baby_rk_ptrs[b0 + b], ia.galois[b] = h_baby_galois[b0 + b];
+            ia.dt = w.dt, ia.ct = d_ct, ia.pt = nullptr, ia.cq = rq + (size_t)b0 * 2 * LN, ia.cp = rp + (size_t)b0 * 2 * KN;
+            ia.n_rot = nb, ia.each = 1, ia.accumulate = 0, ia.split = c->L;
+            launch_dh_accum(c, ia, s, c->D);
+        }
+        // giant-step combinations in the extended basis
+        BsgsMacArgs ma = {rq, rp, d_pt, w.cq, w.cp, n1, n2};
+        launch_bsgs_mac(c, ma, s);
     }
-    // giant-step combinations in the extended basis, then one ModDown per giant step (as a batch)
-    BsgsMacArgs ma = {rq, rp, d_pt, w.cq, w.cp, n1, n2};
-    launch_bsgs_mac(c, ma, s);
+    // one ModDown per giant step (as a batch)
     {
         const LimbSel sel = {c->K, n2 * 2, c->K, 0, c->L};
         InvContigArgs ic = {w.cp, nullptr, w.cp, sel, sel, {1}, 0};
@@ -2020,17 +2086,23 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
     memset(&fa, 0, sizeof(fa));
     fa.cq = w.cq, fa.cq_L = c->L, fa.cv = w.cv, fa.out = inner, fa.n_inst = n2;
     launch_ks_final<FIN_KS>(c, fa, s);
-    // giant rotations, each inner sum with its own key, then the sum
-    for (u32 g0 = 0; g0 < n2; g0 += CKKS_ROT_CHUNK) {
-        const u32 ng = (n2 - g0) < CKKS_ROT_CHUNK ? (n2 - g0) : CKKS_ROT_CHUNK;
-        keyswitch_pipeline<INV_ROT, OWN_ROT>(c, c, inner + (size_t)g0 * 2 * LN, nullptr, nullptr,
-                                                       rot + (size_t)g0 * 2 * LN, ng, 1, ks_ws, s, h_giant_galois + g0,
-                                                       h_giant_rk_ptrs + g0);
+    // Giant rotations, each inner sum with its own key, and their sum.  Their ModDowns are one (summed_rotations; 8 x 4 at N = 2^16,
+    // 24 + 6 limbs: conversions, inverse pass, q-limb product and
+    // sum 300 -> 241 us, the call 1080 -> 1008; 8 x 8 1783 -> 1627) for as many at a time as the digits of its sources allow; with
+    // one special prime there are no digits and every rotation ends by itself.
+    const u32 at_once = c->dn.ks ? summed_rotations_max(c) : CKKS_ROT_CHUNK, n_chunks = (n2 + at_once - 1) / at_once;
+    const u32 chunk = (n2 + n_chunks - 1) / n_chunks, n_sums = c->dn.ks ? n_chunks : n2;
+    for (u32 g0 = 0, k = 0; g0 < n2; g0 += chunk, k++) {
+        const u32 ng = (n2 - g0) < chunk ? (n2 - g0) : chunk;
+        const u64* in = inner + (size_t)g0 * 2 * LN;
+        if (c->dn.ks) summed_rotations(c, in, ng, h_giant_galois + g0, h_giant_rk_ptrs + g0, n_sums == 1 ? d_out : rot + (size_t)k * 2 * LN, ks_ws, s);
+        else keyswitch_pipeline<INV_ROT, OWN_ROT>(c, c, in, nullptr, nullptr, rot + (size_t)g0 * 2 * LN, ng, 1, ks_ws, s, h_giant_galois + g0,
+                                                  h_giant_rk_ptrs + g0);
     }
-    {
-        ProfScope ps(c, std::string("sum_instances_kernel"), (u64)(n2 + 1) * 2 * c->L, s);
+    if (!c->dn.ks || n_sums > 1) {
+        ProfScope ps(c, std::string("sum_instances_kernel"), (u64)(n_sums + 1) * 2 * c->L, s);
         hipLaunchKernelGGL(sum_instances_kernel, dim3((1u << c->logN) / 256, 2 * c->L), dim3(256), 0, s, rot, d_out,
-                           c->tb.pc, c->logN, c->L, 2 * c->L, n2);
+                           c->tb.pc, c->logN, c->L, 2 * c->L, n_sums);
     }
     return hip_check(c, "ckks_lintrans_bsgs");
 }

@@ -18,7 +18,9 @@
 //                       not this kernel or is followed by a plaintext multiply-accumulate over rotations
 //   dh_accum_kernel     double hoisting: plaintext products of all rotations accumulated in the extended basis (rows of 128
 //                       words on integer chains and for few rotations, of 256 otherwise)
-//   bsgs_mac_kernel     giant-step combinations of baby-step rotations kept in the extended basis
+//   bsgs_mac_kernel     giant-step combinations of baby-step rotations kept in the extended basis (more than four giant steps;
+//                       up to four are sums of dh_accum_kernel)
+//   inv_strided_sum_kernel  second inverse pass of several instances, their words added as integers: one ModDown for a sum
 //   modup_kernel / moddown_kernel / automorph kernels: the stand-alone coefficient-form entry points.
 //
 // Levels below L, rescale and the ModDown merged with a rescale reuse these kernels on per-level tables.
@@ -350,6 +352,64 @@ __global__ __launch_bounds__(256, (A == 8 && INV_STRIDED_HALF_EXCHANGE && !__is_
     if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
     const u32 l = run.first + group / TILES;
     CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (inv_strided_body<AR_, A>(a, tb, lds, l, group % TILES, inst)))
+}
+
+// The same pass on several instances of a limb at once: what is stored, as digits, is the sum of the instances' canonical words as
+// an integer.  A conversion is linear over the integers, so the ModDowns of ciphertexts that are only ever added need one
+// conversion of that sum.  A workgroup holds the same columns of four instances, 256 lanes each, and takes further ones in turn;
+// the sums are joined in LDS.  The caller sees to it that n_sum primes fit the digit format (CKKS_DIGIT_MAX).
+struct InvStridedSumArgs {
+    u64* data;  // [n_sum][sel.n_inst][sel.gs][N]; the sums replace instance 0
+    LimbSel sel;
+    u32 scale, n_sum;
+};
+template <class AR, int A>
+__global__ __launch_bounds__(1024) void inv_strided_sum_kernel(InvStridedSumArgs a, Tables tb, LimbRun run) {
+    typedef NttCore<AR, A> C;
+    __shared__ u64 all[4 * 4096];  // of each part: its exchange, then its sums
+    constexpr u32 TILES = (1u << A) / 16;
+    const u32 N = 1u << tb.logN, tid = threadIdx.x & 255, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    u32 group, inst;
+    if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
+    const u32 l = run.first + group / TILES, vi = a.sel.prime_base + l, pi = tb.phys(vi);
+    const typename AR::Mod m = AR::mod(tb.pc[pi]);
+    const u64* ti = tb.tw_int + (size_t)pi * 4 * N;
+    const double* tf = tb.tw_fp + (size_t)pi * 2 * N;
+    const InvScale sc = a.scale == SC_PLAIN ? tb.sc_plain[pi] : a.scale == SC_UP ? tb.sc_up[vi] : tb.sc_dn[vi - tb.L];
+    const u32 c = tid % C::TC, r0 = tid / C::TC, col = (group % TILES) * C::TC + c;
+    const size_t step = (size_t)a.sel.n_inst * a.sel.gs * N;
+    u64* limb = a.data + limb_offset(a.sel, inst, l) * N;
+    u64* lds = all + part * 4096;
+    u64 sum[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) sum[k] = 0;
+    for (u32 g0 = 0; g0 < a.n_sum; g0 += 4) {  // the same barriers in every part: one that has no instance repeats the first
+        const bool has = g0 + part < a.n_sum;
+        const u64* base = limb + (has ? g0 + part : 0) * step;
+        typename AR::T x[16];
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = AR::from_raw(base[(size_t)(A > 4 ? r0 * 16 + k : k * C::RB + r0) * 256 + col]);
+        if (g0) __syncthreads();  // the previous exchange has been read
+        C::inv_strided_but_last(x, lds, tid, ti, tf, N, m);
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            u64 ox, oy;
+            AR::bfly_inv_last(x[k], x[k + 8], sc, m, SRC_CANON, ox, oy);
+            if (has) sum[k] += ox, sum[k + 8] += oy;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[k * 256 + tid] = sum[k];
+    __syncthreads();
+#pragma unroll
+    for (u32 k4 = 0; k4 < 4; k4++) {
+        const u32 k = part * 4 + k4;
+        u64 y = 0;
+#pragma unroll
+        for (u32 v = 0; v < 4; v++) y += all[v * 4096 + k * 256 + tid];
+        limb[(size_t)(k * C::RB + r0) * 256 + col] = digits_encode(y);
+    }
 }
 
 // ============================================================ forward transform, first pass
@@ -906,7 +966,9 @@ __global__ __launch_bounds__(16 << A) void fwd_whole_kernel(FwdContigArgs a, Tab
 // digit's own limbs, the switched polynomial itself (copy | a1*a2 | sigma_g(a)) -- multiplied by
 // the two key components and accumulated.  q-limbs: c' is stored canonical.  Special limbs: the
 // first inverse pass of ModDown runs on the accumulators and raw words are stored.
-enum OwnLoad { OWN_COPY = 0, OWN_TENSOR = 1, OWN_ROT = 2 };
+// OWN_ROT_SUM: the rotations of n_sum ciphertexts, added: everything after the ModDowns' conversions is linear, so the sum over the
+// digits runs over all instances' and ends in one ModDown (of the sum of the special parts, see inv_strided_sum_kernel).
+enum OwnLoad { OWN_COPY = 0, OWN_TENSOR = 1, OWN_ROT = 2, OWN_ROT_SUM = 3 };
 struct InnerArgs {
     const u64* dt;    // [inst or 1][dnum][D][N]: raw forward-lazy (NTT_INSIDE) or canonical eval (hoisted)
     const u64* own;   // COPY: d [inst][L][N]; TENSOR: ct1; ROT: ct ([inst][2][L][N]); hoisted: ct [2][L][N]
@@ -919,6 +981,7 @@ struct InnerArgs {
     u32 split;    // limbs below split are stored to cq ([inst][2][split][N]), the others continue to cp: the number
                   // of q-limbs, or one less when the ModDown that follows also divides by the last q-limb
     u32 per_inst;    // not hoisted: every instance has its own key and Galois element (at most CKKS_ROT_CHUNK instances)
+    u32 n_sum;       // OWN_ROT_SUM: instances added (n_inst is 1)
     // FUSED (limbs below split only, launched after the ModDown conversion): the kernel also ends the ModDown
     const u64* cv;              // [inst][2][split][N] converted special part, first forward pass done
     u64* out;                   // [inst][2][split][N]
@@ -974,9 +1037,10 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
     const double* tf = tb.tw_fp + (size_t)pi * 2 * N;
     u64* lrow = lds + ch * 272;
     const u32 row_off = r * 256;
+    constexpr bool SUM = OWN == OWN_ROT_SUM;
     const u32 kidx = (HOISTED || a.per_inst) ? inst : 0;
-    const u64* key = a.key[kidx] + (size_t)pi * N + row_off;
-    const u32 gal = a.galois[kidx];
+    const u64* key = SUM ? nullptr : a.key[kidx] + (size_t)pi * N + row_off;
+    u32 gal = SUM ? 0 : a.galois[kidx];
     const u32 own_digit = i < L ? i / tb.alpha : 0xffffffffu;
     constexpr bool TWL = AR::is_fp && !HOISTED;  // the row's forward twiddles live in LDS
     u64* twblk = lds + NTT_LDS_WORDS + ch * CKKS_ROW_TW_WORDS;
@@ -985,7 +1049,12 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
 #pragma unroll
     for (int k = 0; k < 16; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
     u32 since = 0;
-    for (u32 j = ways == 1 ? 0 : wave; j < tb.dnum; j += ways) {
+    for (u32 jj = ways == 1 ? 0 : wave; jj < (SUM ? a.n_sum : 1) * tb.dnum; jj += ways) {
+        u32 j = jj, src = inst;
+        if constexpr (SUM) {  // digits in rotated order: the cheap own digits spread over the wavefronts that share the row
+            src = jj / tb.dnum, j = (jj + src) % tb.dnum;
+            key = a.key[src] + (size_t)pi * N + row_off, gal = a.galois[src];
+        }
         const u64* k0 = key + ((size_t)j * 2 + 0) * Dkey * N;
         const u64* k1 = key + ((size_t)j * 2 + 1) * Dkey * N;
         u64 kv0[16], kv1[16];
@@ -1031,7 +1100,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
                 }
             } else {
                 u64 w[16];
-                gather_row_cp(a.own + (((size_t)inst * 2 + 1) * L + i) * N, row_off, gal, tb.logN, lrow, e0, w);
+                gather_row_cp(a.own + (((size_t)src * 2 + 1) * L + i) * N, row_off, gal, tb.logN, lrow, e0, w);
 #pragma unroll
                 for (int k = 0; k < 16; k++) v[k] = AR::round_reduce(AR::from_canon(w[k], m), m);
             }
@@ -1041,7 +1110,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
 #pragma unroll
             for (int k = 0; k < 16; k++) v[k] = AR::round_reduce(AR::from_canon(w[k], m), m);
         } else {
-            const u64* p = a.dt + (((size_t)inst * tb.dnum + j) * D + i) * N + row_off;
+            const u64* p = a.dt + (((size_t)src * tb.dnum + j) * D + i) * N + row_off;
 #pragma unroll
             for (int k = 0; k < 16; k++) v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
             if constexpr (TWL) NttCore<AR, A>::fwd_contig_with(v, lrow, e0, RowTwLds{twblk, e0}, m);
@@ -1112,6 +1181,17 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
                 const T fin = AR::acc_finish(t ? acc1[k] : acc0[k], m);
                 if constexpr (AR::is_fp) res[k] = AR::to_raw(FpAr::mulmod_lazy(fin - v[k], pinv.d, FpAr::mod(pc)));
                 else res[k] = mul_shoup(submod(AR::acc_canon(fin, m), AR::canon_fwd(v[k], m), pc.q), pinv.w, pinv.wp, pc.q);
+            }
+            if (SUM && t == 0) {
+                for (u32 g = 0; g < a.n_sum; g++) {
+                    u64 bw[16];
+                    gather_row_cp(a.own + ((size_t)g * 2 * L + i) * N, row_off_f, a.galois[g], tb.logN, lrow_f, e0f, bw);
+#pragma unroll
+                    for (int k = 0; k < 16; k++) {  // FP64: at most 2.9 q + 1, then 1.5 q
+                        if constexpr (AR::is_fp) res[k] = AR::to_raw(FpAr::reduce(AR::from_raw(res[k]) + u64_to_f64(bw[k]), FpAr::mod(pc)));
+                        else res[k] = addmod(res[k], bw[k], pc.q);
+                    }
+                }
             }
             if (OWN == OWN_ROT && t == 0) {
                 u64 bw[16];
@@ -1184,6 +1264,7 @@ __global__ __launch_bounds__(256, 2) void ks_inner_kernel(InnerArgs a, Tables tb
 // dnum = 5 (7.8 GB of keys and plaintexts): 1673 us in two launches -> 1414 us, 5.5 TB/s; without the shared rows 1623 us,
 // without the early requests 1730 us, with the digit reads removed 1386 us.
 #define CKKS_DH_CHUNK 32
+#define CKKS_DH_SUMS 4
 struct DhInnerArgs {
     const u64* dt;   // [dnum][D][N] canonical evaluation form
     const u64* ct;   // [2][L][N]
@@ -1199,6 +1280,7 @@ struct DhInnerArgs {
     u32 waves;       // wavefronts of a workgroup that share a row, each taking every waves-th rotation: 1 (four rows) or 4
     u32 first, count;  // limbs of this launch
     u32 each;        // rotations are not summed: rotation r's result goes to cq + r*2*split*N, cp + r*2*(D - split)*N
+    u32 sums;        // G > 1: G; sum g takes the plaintexts pt[g][n_rot][pt_limbs][N] and goes to cq + g*2*split*N, cp likewise
 };
 
 // Sum over the rotations of (unreduced digit sum, reduced) * plaintext, at most 8 terms between folds
@@ -1221,7 +1303,10 @@ struct DhSum<IntAr, 2> {
     __device__ __forceinline__ u64 get(const IntAr::Mod& m) const { return redc_lazy(u128w{s.lo, csub(csub(s.hi, m.q2), m.q)}, m.q, m.qneg); }
 };
 
-template <class AR, int W>
+// G > 1: up to G sums of the same rotations, each with plaintexts of its own (the giant steps of a transform): the rotations, kept
+// in the extended basis, meet all of them in registers instead of making a round trip through memory.  The plaintexts of a
+// rotation are requested when it begins and used when its digits are done.
+template <class AR, int W, int G>
 __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables& tb, const PrimeConst& pc, u64* lds, u32 i, u32 row, u32 wave) {
     typedef typename AR::T T;
     typedef typename AR::Wide Wide;
@@ -1244,7 +1329,7 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
     const u32 sp = a.split;
     auto out = [&](u32 rr, int t) {
         u64* base = i < sp ? a.cq + ((size_t)t * sp + i) * N : a.cp + ((size_t)t * (D - sp) + (i - sp)) * N;
-        return base + (a.each ? (size_t)rr * 2 * (i < sp ? sp : D - sp) * N : 0) + row_off;
+        return base + (a.each || G > 1 ? (size_t)rr * 2 * (i < sp ? sp : D - sp) * N : 0) + row_off;
     };
     auto store = [&](const T (&acc)[W], u64* o) __attribute__((always_inline)) {
 #pragma unroll
@@ -1259,19 +1344,20 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
             *q = r;
         }
     };
-    DhSum<AR, W> acc0[W], acc1[W];
+    typedef DhSum<AR, G == 1 ? W : 0> Sum;  // G > 1: no registers for 128-bit sums
+    Sum acc0[G][W], acc1[G][W];
     // terms of a rotation: digits 0 .. dnum - 1, then (q-limbs) b times P.  The words of the next term, also across
     // rotations, are requested before this one is worked on: a wavefront of the wide form has 12 KiB in flight.
     const u32 n_terms = tb.dnum + (is_q ? 1 : 0);
-    u64 sv[W], kv0[W], kv1[W], ptv[W];
+    u64 sv[W], kv0[W], kv1[W], ptv[G][W];
     const u64 *ct = a.ct, *dt = a.dt;
 #pragma unroll
-    for (int k = 0; k < W; k++) ptv[k] = 1;
+    for (int k = 0; k < W; k++) ptv[0][k] = 1;
     const size_t pt_step = (size_t)a.pt_limbs * N;
     // EVEN: every request is the same number of loads, and what a term does not need is the source row once more (L2): behind
     // a branch that may skip some, the compiler waits for all of them before the previous term's words are used.  The narrow
     // form gains (18 rotations, L + K = 12 + 4, dnum = 3: 360 -> 354 us), the wide one loses by the extra loads (24 + 6: 672 -> 684).
-    constexpr bool EVEN = W == 2;
+    constexpr bool EVEN = W == 2 && G == 1;
     auto request = [&](u32 r, u32 j, u64 (&s)[W], u64 (&k0)[W], u64 (&k1)[W], u64 (&p)[W]) __attribute__((always_inline)) {
         const u32 src_off = eval_perm(row_off, a.galois[r], logN) & ~(ROW - 1);
         const bool is_b = j == tb.dnum;
@@ -1292,18 +1378,28 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
                 load(key, k0, true);
                 load(key + (size_t)Dkey * N, k1, true);
             }
-            if (j == 0 && a.pt) load(pt, p, true);
+            if (G == 1 && j == 0 && a.pt) load(pt, p, true);
         }
     };
     Wide w0[W], w1[W];
 #pragma unroll
     for (int k = 0; k < W; k++) w0[k] = w1[k] = AR::wide_zero();
     u32 folds = 0, in_sum = 0, rr = a.waves == 1 ? 0 : wave, j = 0;
-    if (rr < a.n_rot) request(rr, 0, sv, kv0, kv1, ptv);
+    if (rr < a.n_rot) request(rr, 0, sv, kv0, kv1, ptv[0]);
     while (rr < a.n_rot) {
+        if constexpr (G > 1) {
+#pragma unroll
+            for (int g = 0; g < G; g++)
+                load(a.pt + ((size_t)g * a.n_rot + rr) * pt_step + (size_t)i * N + row_off, ptv[g], true);
+        }
         u32 idx[W];
 #pragma unroll
         for (int k = 0; k < W; k++) idx[k] = eval_perm(row_off + (k >> 1) * 128 + lane * 2 + (k & 1), a.galois[rr], logN) & (ROW - 1);
+        T d0[W], d1[W];  // G > 1: the rotation's digit sums
+        if constexpr (G > 1) {
+#pragma unroll
+            for (int k = 0; k < W; k++) d0[k] = d1[k] = AR::acc_zero();
+        }
         for (; j < n_terms; j++) {
             const bool last = j + 1 == n_terms;
             const bool more = !last || rr + a.waves < a.n_rot;  // else (EVEN) this term once more, unused
@@ -1330,66 +1426,94 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
             }
             if (++in_sum == AR::wide_terms || last) {
                 in_sum = 0;
+                if constexpr (G > 1) {
 #pragma unroll
-                for (int k = 0; k < W; k++) {
-                    const u64 ptk = EVEN && !a.pt ? 1 : ptv[k];
-                    acc0[k].add(AR::wide_reduce(w0[k], m), ptk, m);
-                    acc1[k].add(AR::wide_reduce(w1[k], m), ptk, m);
-                    w0[k] = w1[k] = AR::wide_zero();
-                }
-                if ((++folds & 7) == 0) {  // FP64: at most 8 products (0.69 q each) between reductions
+                    for (int k = 0; k < W; k++) {
+                        d0[k] = AR::wide_join(d0[k], AR::wide_reduce(w0[k], m), m);
+                        d1[k] = AR::wide_join(d1[k], AR::wide_reduce(w1[k], m), m);
+                        w0[k] = w1[k] = AR::wide_zero();
+                    }
+                } else {
 #pragma unroll
-                    for (int k = 0; k < W; k++) acc0[k].fold(m), acc1[k].fold(m);
+                    for (int k = 0; k < W; k++) {
+                        const u64 ptk = EVEN && !a.pt ? 1 : ptv[0][k];
+                        acc0[0][k].add(AR::wide_reduce(w0[k], m), ptk, m);
+                        acc1[0][k].add(AR::wide_reduce(w1[k], m), ptk, m);
+                        w0[k] = w1[k] = AR::wide_zero();
+                    }
+                    if ((++folds & 7) == 0) {  // FP64: at most 8 products (0.69 q each) between reductions
+#pragma unroll
+                        for (int k = 0; k < W; k++) acc0[0][k].fold(m), acc1[0][k].fold(m);
+                    }
                 }
             }
 #pragma unroll
             for (int k = 0; k < W; k++) {
                 sv[k] = sn[k], kv0[k] = kn0[k], kv1[k] = kn1[k];
-                if (last) ptv[k] = pn[k];
+                if (G == 1 && last) ptv[0][k] = pn[k];
             }
         }
-        if (a.each) {
+        if constexpr (G > 1) {
+            // FP64: the digit sum, joined from at most three parts of q/2, times a plaintext is at most 1.07 q
+            ++folds;
+#pragma unroll
+            for (int k = 0; k < W; k++)
+#pragma unroll
+                for (int g = 0; g < G; g++) {
+                    acc0[g][k].add(d0[k], ptv[g][k], m);
+                    acc1[g][k].add(d1[k], ptv[g][k], m);
+                    if ((folds & 7) == 0) acc0[g][k].fold(m), acc1[g][k].fold(m);
+                    __builtin_amdgcn_sched_barrier(0);  // one product's temporaries at a time
+                }
+        }
+        if (G == 1 && a.each) {
             T t0[W], t1[W];
 #pragma unroll
-            for (int k = 0; k < W; k++) t0[k] = acc0[k].get(m), t1[k] = acc1[k].get(m), acc0[k] = acc1[k] = DhSum<AR, W>();
+            for (int k = 0; k < W; k++) t0[k] = acc0[0][k].get(m), t1[k] = acc1[0][k].get(m), acc0[0][k] = acc1[0][k] = Sum();
             store(t0, out(rr, 0));
             store(t1, out(rr, 1));
             folds = 0;
         }
         j = 0, rr += a.waves;
     }
-    if (a.each) return;
-    T t0[W], t1[W];
+    if (G == 1 && a.each) return;
 #pragma unroll
-    for (int k = 0; k < W; k++) t0[k] = acc0[k].get(m), t1[k] = acc1[k].get(m);
-    if (a.waves > 1) {  // the first of the row's four wavefronts joins their sums
+    for (int g = 0; g < G; g++) {
+        T t0[W], t1[W];
 #pragma unroll
-        for (int k = 0; k < W; k++) t0[k] = AR::acc_fold(t0[k], m), t1[k] = AR::acc_fold(t1[k], m);
-        __syncthreads();
+        for (int k = 0; k < W; k++) t0[k] = acc0[g][k].get(m), t1[k] = acc1[g][k].get(m);
+        if (a.waves > 1) {  // the first of the row's four wavefronts joins their sums
 #pragma unroll
-        for (int k = 0; k < W; k++) {
-            lds[(wave * 2 + 0) * ROW + k * 64 + lane] = AR::to_raw(t0[k]);
-            lds[(wave * 2 + 1) * ROW + k * 64 + lane] = AR::to_raw(t1[k]);
-        }
-        __syncthreads();
-        if (wave) return;
+            for (int k = 0; k < W; k++) t0[k] = AR::acc_fold(t0[k], m), t1[k] = AR::acc_fold(t1[k], m);
+            __syncthreads();
 #pragma unroll
-        for (int k = 0; k < W; k++)
-#pragma unroll
-            for (int v = 1; v < 4; v++) {
-                t0[k] = AR::wide_join(t0[k], AR::from_raw(lds[(v * 2 + 0) * ROW + k * 64 + lane]), m);
-                t1[k] = AR::wide_join(t1[k], AR::from_raw(lds[(v * 2 + 1) * ROW + k * 64 + lane]), m);
+            for (int k = 0; k < W; k++) {
+                lds[(wave * 2 + 0) * ROW + k * 64 + lane] = AR::to_raw(t0[k]);
+                lds[(wave * 2 + 1) * ROW + k * 64 + lane] = AR::to_raw(t1[k]);
             }
+            __syncthreads();
+            if (wave == 0) {
+#pragma unroll
+                for (int k = 0; k < W; k++)
+#pragma unroll
+                    for (int v = 1; v < 4; v++) {
+                        t0[k] = AR::wide_join(t0[k], AR::from_raw(lds[(v * 2 + 0) * ROW + k * 64 + lane]), m);
+                        t1[k] = AR::wide_join(t1[k], AR::from_raw(lds[(v * 2 + 1) * ROW + k * 64 + lane]), m);
+                    }
+            }
+        }
+        if (a.waves == 1 || wave == 0) {
+            store(t0, out(g, 0));
+            store(t1, out(g, 1));
+        }
     }
-    store(t0, out(0, 0));
-    store(t1, out(0, 1));
 }
 
 // W words per lane; a row, a wavefront's share, is 64 times that (sigma_g maps every aligned block of 2^m slots onto one).
 // AnyAr, FP64 and integer limbs in one launch: rows of 256 words, 12 KiB in flight per wavefront and three waves per SIMD, or
 // of 128 and five.  IntAr, for chains of integer primes alone: rows of 128 words.  launch_dh_accum has the rule.
-template <class AR, int W>
-__global__ __launch_bounds__(256, W == 4 ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
+template <class AR, int W, int G = 1>
+__global__ __launch_bounds__(256, G > 1 || W == 4 ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
     __shared__ __align__(16) u64 lds[512 * W];  // a row per wavefront to permute it in; eight to join four pairs of sums
     const u32 rows_wg = 4 / a.waves, per_limb = ((1u << tb.logN) / (64 * W)) / rows_wg, total = a.count * per_limb, per = (total + 7) / 8;
     const u32 pos = blockIdx.x >> 3, q = (blockIdx.x & 7) * per + pos;  // workgroups go to the XCDs round-robin
@@ -1397,7 +1521,7 @@ __global__ __launch_bounds__(256, W == 4 ? 3 : 5) void dh_accum_kernel(DhInnerAr
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: addresses stay in scalar registers
     const u32 i = a.first + q / per_limb, row = (q % per_limb) * rows_wg + (a.waves == 1 ? wave : 0);
     const PrimeConst pc = tb.pc[tb.phys(i)];
-    CKKS_BY_ARITHMETIC(AR, i, (dh_accum_body<AR_, W>(a, tb, pc, lds, i, row, wave)))
+    CKKS_BY_ARITHMETIC(AR, i, (dh_accum_body<AR_, W, G>(a, tb, pc, lds, i, row, wave)))
 }
 
 // ==================================================== baby-step giant-step accumulation and sums

@@ -79,9 +79,10 @@ HD u64 mulmod_var(u64 a, u64 b, u64 q, u64 qneg, u64 r2) {
 //   SRC_CANON  canonical integer            SRC_F64  canonical integer as a double (FpAr primes only)
 //   SRC_DIGITS eight signed base-256 digits d_k in [-128, 127], y = sum d_k 256^k, digit k stored in byte k as
 //              d_k + 128 with the top bit flipped, i.e. as the two's-complement byte the matrix cores read:
-//              word = (y + B) ^ B with B = 0x80 in every byte (y < 2^63 - B, here y < 2^61).
+//              word = (y + B) ^ B with B = 0x80 in every byte (y <= CKKS_DIGIT_MAX).
 enum SrcFormat { SRC_CANON = 0, SRC_F64 = 1, SRC_DIGITS = 2 };
 #define CKKS_DIGIT_BIAS 0x8080808080808080ull
+#define CKKS_DIGIT_MAX 0x7f7f7f7f7f7f7f7full  // the largest word eight such digits can hold
 HD u64 digits_encode(u64 y) { return (y + CKKS_DIGIT_BIAS) ^ CKKS_DIGIT_BIAS; }
 
 // ------------------------------------------------------------------ per-prime constants

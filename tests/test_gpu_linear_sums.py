@@ -53,3 +53,40 @@ def test_hoisted_sums_before_the_mod_down(orc, logN, q, p, dnum, counts):
             assert np.array_equal(got, want), (m, overlap)
             summed = m > 16 or (logN == 16 and m >= 12 and ps.L >= 9)
             assert any(k.startswith("ks_final_kernel") and k.endswith(", 4>") for k in names) == summed, names
+
+
+@pytest.mark.parametrize("logN,q,p,dnum,level,steps", [
+    (12, (49,) * 6, (59, 59), 3, 6, ((1, 1), (3, 2), (2, 3), (5, 4), (2, 5), (3, 16), (33, 2))),
+    (12, (49, 60, 50, 58, 49), (48, 60), 3, 4, ((2, 1), (3, 4), (2, 6))),   # both arithmetics, a partial last digit
+    (13, (49,) * 3, (59,), 3, 3, ((2, 1), (2, 4))),                         # one special prime: rotations end singly
+    (12, None, 2, 2, 6, ((2, 3), (2, 4), (3, 7))),                          # primes just below 2^61: three sums fit the digits
+    (14, (49,) * 16, (59,) * 2, 8, 15, ((2, 2), (1, 4))),                   # more digits than one unreduced sum takes
+    (16, (49,) * 8, (59,) * 4, 2, 8, ((8, 4), (3, 3))),
+])
+def test_baby_step_giant_step_sums(orc, logN, q, p, dnum, level, steps):
+    if q is None:
+        primes = _below(1 << 61, 2 << logN, 6 + p)
+        ps = synth.ExplicitParamSet("below_2_61", logN, dnum, primes[:6], primes[6:])
+    else:
+        ps = synth.mixed_params(logN, list(q), list(p), dnum, "sums")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    ext = list(ps.primes[:level]) + list(ps.primes[ps.L:])
+    n1, n2 = max(s[0] for s in steps), max(s[1] for s in steps)
+    gs, keys, ct, pt = _inputs(ps, n1 + n2, 3, 2600 + logN + dnum, ext, (n2, n1))
+    ct = np.ascontiguousarray(ct[:, :level])
+    d_ct, d_keys = dev(ct), [dev(k) for k in keys]
+    for a, b in steps:
+        print(logN, "baby", a, "giant", b, flush=True)
+        use = np.ascontiguousarray(pt[:b, :a])
+        baby, giant = [keys[r % 3] for r in range(a)], [keys[(r + 1) % 3] for r in range(b)]
+        want = orc.lintrans_bsgs_level(ct, gs[:a], baby, gs[n1:n1 + b], giant, use, P)
+        for overlap in (False, True):
+            ctx.set_overlap(overlap)
+            try:
+                got, names = _kernels(ctx, lambda: ctx.lintrans_bsgs_at(level, d_ct, gs[:a], [d_keys[r % 3] for r in range(a)], gs[n1:n1 + b],
+                                                                        [d_keys[(r + 1) % 3] for r in range(b)], dev(use)))
+            finally:
+                ctx.set_overlap(False)
+            assert np.array_equal(got, want), (a, b, overlap)
+            assert any(k.startswith("inv_strided_sum_kernel") for k in names) == (ps.K > 1), names
+            assert any(k.startswith("bsgs_mac_kernel") for k in names) == (a > 32 or b > 4), names
