@@ -233,6 +233,9 @@ struct ConvTab {
     const u64* aop_part = nullptr;
     u32 n_full = 0;
     u32 ks = 0;  // products per coefficient group; 0 = few sources, converted directly
+    u32 sources = 0;
+    // a lane half loads one word fewer than the products take
+    bool fewer() const { return ks && ks <= 2 && (sources + 1) / 2 < 2 * ks; }
 };
 
 // One level of the context: everything a launch needs.  `primes` is the level's basis in limb order.
@@ -409,9 +412,9 @@ static u64 prod_except(const std::vector<u64>& src, size_t skip, u64 m) {
 static void build_aop(u64* aop, const std::vector<u64>& hat, u64 m) {
     for (u32 i = 0; i < hat.size(); i++) {
         u64 c = hat[i] % m;
-        // source i travels in product i / 4, lane half (i / 2) % 2, word i % 2; digit row dg: byte bb = digit dg of
+        // source i travels in product i / 4, lane half i % 2, word (i / 2) % 2; digit row dg: byte bb = digit dg of
         // hat * 256^bb
-        u64* rows = aop + (size_t)(i / 4) * 32 + (i / 2) % 2 * 16 + i % 2;
+        u64* rows = aop + (size_t)(i / 4) * 32 + i % 2 * 16 + (i / 2) % 2;
         for (u32 bb = 0; bb < 8; bb++) {
             const int64_t centred = c > m / 2 ? (int64_t)c - (int64_t)m : (int64_t)c;
             const u64 z = (u64)centred + CKKS_DIGIT_BIAS;
@@ -589,8 +592,8 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         tb.pinv = (const PinvConst*)(dbase + ll.pinv);
         tb.pmod = (const u64*)(dbase + ll.pmod);
         tb.L = ell, tb.K = K, tb.dnum = beta, tb.alpha = alpha, tb.D = Dl, tb.Lfull = L, tb.Kfull = K, tb.Lq = ell;
-        v.up = ConvTab{(const u64*)(dbase + lay.up_aop), (const u64*)(dbase + ll.up_aop), ell / alpha, up_ks};
-        v.dn = ConvTab{(const u64*)(dbase + lay.dn_aop), nullptr, 1, dn_ks};
+        v.up = ConvTab{(const u64*)(dbase + lay.up_aop), (const u64*)(dbase + ll.up_aop), ell / alpha, up_ks, alpha};
+        v.dn = ConvTab{(const u64*)(dbase + lay.dn_aop), nullptr, 1, dn_ks, K};
         if (up_ks && ell % alpha) {  // the last digit of this level is shorter than the chain's
             const std::vector<u64> digit(c->primes.begin() + ell / alpha * alpha, c->primes.begin() + ell);
             for (u32 t = 0; t < Dl; t++)
@@ -657,7 +660,7 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         tb.dn_hatinv = nullptr;
         tb.pinv = (const PinvConst*)(dbase + ml.pinv);
         tb.L = T, tb.K = S, tb.dnum = 1, tb.alpha = T, tb.D = ell + K, tb.Lfull = L, tb.Kfull = K, tb.Lq = ell;
-        v.dn = ConvTab{(const u64*)(dbase + ml.dn_aop), nullptr, 1, mfma_ks(S)};
+        v.dn = ConvTab{(const u64*)(dbase + ml.dn_aop), nullptr, 1, mfma_ks(S), S};
         for (u32 t = 0; t < T; t++)
             build_aop((u64*)(hb + ml.dn_aop) + t * aop_words(v.dn.ks), hats(src, c->primes[t]), c->primes[t]);
     }
@@ -859,28 +862,30 @@ struct FwdStridedL {
     static std::string name(const char* ar, int A) { return kname("fwd_strided_kernel", ar, A, ""); }
 };
 // Conversions: KS products per coefficient group on the matrix cores, or (KS = 0) a single source and TB targets per
-// workgroup (one for IntAr)
-template <int DIR, int KS, int TB = 0>
+// workgroup (one for IntAr).  KS > 0 and TB = 1: ModDown with two FpAr targets per workgroup instead of four
+template <int DIR, int KS, int TB = 0, int... NW>
 struct ConvL {
     static constexpr bool packed = KS > 0;  // blocks are numbered over the targets alone, without a digit's own limbs
     template <class AR>
     static constexpr int single() { return AR::is_fp ? TB : 1; }
     template <class AR>
-    static constexpr int per_block() { return KS ? 2 * conv_mfma_ntt<AR>() : single<AR>(); }
+    static constexpr int ntt() { return DIR == CONV_DN && TB ? 1 : conv_mfma_ntt<AR>(); }
+    template <class AR>
+    static constexpr int per_block() { return KS ? 2 * ntt<AR>() : single<AR>(); }
     template <class AR, int A>
     static void go(dim3 g, hipStream_t s, const ConvArgs& a, const Tables& tb, LimbRun run) {
-        constexpr int NTT = conv_mfma_ntt<AR>();
+        constexpr int NTT = ntt<AR>();
         if constexpr (KS == 0) hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, single<AR>(), true>), g, dim3(256), 0, s, a, tb, run);
         else if constexpr (AR::is_fp && DIR == CONV_DN)
-            hipLaunchKernelGGL((conv_mfma_kernel<A, KS, DIR, NTT>), g, dim3(256 * NTT), 0, s, a, tb, run);
-        else hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, KS + NTT, false>), g, dim3(256 * NTT), 0, s, a, tb, run);
+            hipLaunchKernelGGL((conv_mfma_kernel<A, KS, DIR, NTT, NW...>), g, dim3(512), 0, s, a, tb, run);
+        else hipLaunchKernelGGL((conv_fwd_strided_kernel<AR, A, DIR, KS + NTT, false, NW...>), g, dim3(512), 0, s, a, tb, run);
     }
     static std::string name(const char* ar, int A) {
         const bool fp = ar[0] == 'F';
-        const int ntt = fp ? conv_mfma_ntt<FpAr>() : conv_mfma_ntt<IntAr>();
-        const std::string dir = std::to_string(DIR);
-        if (KS && fp && DIR == CONV_DN) return "conv_mfma_kernel<" + std::to_string(A) + ", " + std::to_string(KS) + ", " + dir + ", " + std::to_string(ntt) + ">";
-        return kname("conv_fwd_strided_kernel", ar, A, (", " + dir + ", " + std::to_string(KS ? KS + ntt : fp ? TB : 1) + (KS ? ", false" : ", true")).c_str());
+        const int t = fp ? ntt<FpAr>() : ntt<IntAr>();
+        const std::string dir = std::to_string(DIR), words = sizeof...(NW) ? ", " + std::to_string(conv_words(KS, NW...)) : std::string();
+        if (KS && fp && DIR == CONV_DN) return "conv_mfma_kernel<" + std::to_string(A) + ", " + std::to_string(KS) + ", " + dir + ", " + std::to_string(t) + words + ">";
+        return kname("conv_fwd_strided_kernel", ar, A, (", " + dir + ", " + std::to_string(KS ? KS + t : fp ? TB : 1) + (KS ? ", false" : ", true") + words).c_str());
     }
 };
 struct FwdContigL {
@@ -997,14 +1002,15 @@ static void launch_conv_runs(const View* c, ConvArgs a, hipStream_t s, int only)
     }
 }
 
-// ModUp onto both arithmetics in one launch, where the chain is FpAr limbs followed by IntAr limbs and all workgroups fit the
-// chip at once (512 = two per compute unit).  One ciphertext at N = 2^16, L = 24, dnum = 4: 24 + 17 us in two launches -> 37 us,
-// the call 163 -> 158 us; at level 13 the call 120 -> 115 us.  Built for N = 2^16 alone, the ring of the large sets; at
-// N = 2^13 .. 2^15 whole calls of one to four ciphertexts would gain 3 to 7 % (none at 2^15, L = 24, four ciphertexts).
-// Returns false where it does not apply.
-static bool conv_up_both(const View* c, const ConvArgs& base, hipStream_t s) {
+// ModUp onto both arithmetics in one launch, where the chain is FpAr limbs followed by IntAr limbs (N >= 2^14; below, and with more
+// than eight sources, no such kernel is built).  Two launches / one, whole calls on one stream, us: one rotation at N = 2^16, 24 + 6
+// limbs 146.5 / 134, level 13 113 / 108; 2 of them 224 / 211, 8 683 / 681; N = 2^15, level 17, 3 135 (one) against 145, 8 262 / 251;
+// N = 2^14, 24 + 6, 12 296 / 284.  Where the targets would otherwise run beside each other on the second stream, up to `most`
+// workgroups: with BESIDE 1024 (N = 2^16, 24 + 6, 2 rotations (1024) 218 / 212, 4 (2048) 361 / 374; level 13, 2 157 / 145), with
+// FORK 512 (dh, 35 + 7 limbs (880), one rotation 258 / 263).  Returns false where it does not apply.
+static bool conv_up_both(const View* c, const ConvArgs& base, hipStream_t s, u32 most) {
     const u32 ks = c->up.ks;
-    if (c->logN != 16 || (ks != 1 && ks != 2)) return false;
+    if (c->logN < 14 || (ks != 1 && ks != 2)) return false;
     const std::vector<ClassRun> runs = class_runs(c, 0, c->D);
     if (runs.size() != 2 || !runs[0].fp) return false;
     ConvBothArgs a;
@@ -1012,17 +1018,32 @@ static bool conv_up_both(const View* c, const ConvArgs& base, hipStream_t s) {
     a.fp.aop = c->up.aop, a.fp.aop_part = c->up.aop_part, a.fp.n_full = c->up.n_full;
     a.in = a.fp;
     u32 w0, w1;
-    a.fp.blocks = (conv_up_targets(c, runs[0], w0) + 3) / 4, a.in.blocks = (conv_up_targets(c, runs[1], w1) + 1) / 2;
-    if (!a.fp.blocks || !a.in.blocks) return false;
+    const u32 groups = base.groups_outer * c->dnum * tiles_of(c), targets_fp = conv_up_targets(c, runs[0], w0);
+    a.in.blocks = (conv_up_targets(c, runs[1], w1) + 1) / 2;
+    if (!targets_fp || !a.in.blocks) return false;
     a.run_fp = LimbRun{runs[0].first, runs[0].count}, a.run_in = LimbRun{runs[1].first, runs[1].count};
-    const u32 groups = base.groups_outer * c->dnum * tiles_of(c);
-    a.grid_fp = xcd_grid(groups, a.fp.blocks);
-    const u32 grid = a.grid_fp + xcd_grid(groups / 2, a.in.blocks);
-    if (grid > 512) return false;
-    ProfScope ps(c, c->sh->prof.on ? "conv_up_both_kernel<" + std::to_string((int)c->logN - 8) + ", " + std::to_string(ks) + ">" : std::string(),
+    a.grid_in = xcd_grid(groups, a.in.blocks);
+    a.fp.blocks = (targets_fp + 3) / 4;
+    const u32 grid = a.grid_in + xcd_grid(groups, a.fp.blocks);
+    if (grid > most) return false;
+    const bool fewer = c->up.fewer();
+    ProfScope ps(c, c->sh->prof.on ? "conv_up_both_kernel<" + std::to_string((int)c->logN - 8) + ", " + std::to_string(ks) + (fewer ? ks == 1 ? ", 1>" : ", 3>" : ">") : std::string(),
                  (u64)base.groups_outer * (w0 + w1 + c->L), s);
-    if (ks == 1) hipLaunchKernelGGL((conv_up_both_kernel<8, 1>), dim3(grid), dim3(512), 0, s, a, c->tb);
-    else hipLaunchKernelGGL((conv_up_both_kernel<8, 2>), dim3(grid), dim3(512), 0, s, a, c->tb);
+#define CKKS_BOTH_AS(...) hipLaunchKernelGGL((conv_up_both_kernel<__VA_ARGS__>), dim3(grid), dim3(512), 0, s, a, c->tb)
+#define CKKS_BOTH(AV)                                \
+    case AV:                                         \
+        if (ks == 1 && fewer) CKKS_BOTH_AS(AV, 1, 1);   \
+        else if (ks == 1) CKKS_BOTH_AS(AV, 1);       \
+        else if (fewer) CKKS_BOTH_AS(AV, 2, 3);      \
+        else CKKS_BOTH_AS(AV, 2);                    \
+        break;
+    switch (c->logN - 8) {
+        CKKS_BOTH(6)
+        CKKS_BOTH(7)
+        CKKS_BOTH(8)
+    }
+#undef CKKS_BOTH
+#undef CKKS_BOTH_AS
     return true;
 }
 
@@ -1034,23 +1055,35 @@ template <int DIR>
 static void launch_conv(const View* c, ConvArgs a, hipStream_t s, int cls = -1) {
     const ConvTab& t = DIR == CONV_UP ? c->up : c->dn;
     a.aop = t.aop, a.aop_part = t.aop_part, a.n_full = t.n_full;
+    const u32 groups = a.groups_outer * (DIR == CONV_UP ? c->dnum : 1) * tiles_of(c), fours = groups * (((DIR == CONV_UP ? c->D : c->L) + 3) / 4);
+    // ModDown onto FpAr limbs: two targets per workgroup instead of four while that leaves one workgroup per compute unit (calls
+    // of one ciphertext at N = 2^16, 24 + 6 limbs: level 13 (256 workgroups of two) 107.7 -> 104.1 us, level 24 (384) 136.8 -> 137.3)
+    const bool narrow = DIR == CONV_DN && fours <= 128;
+#define CKKS_CONV(KS, ...)                                                                         \
+    if (DIR == CONV_DN && narrow) launch_conv_runs<ConvL<DIR, KS, DIR == CONV_DN, ##__VA_ARGS__>, DIR>(c, a, s, cls); \
+    else launch_conv_runs<ConvL<DIR, KS, 0, ##__VA_ARGS__>, DIR>(c, a, s, cls)
     switch (t.ks) {
-        case 0: {
+        case 0:
             // Four FP64 targets share a load of the source unless that leaves fewer than two workgroups per compute unit.  Integer
             // targets are converted singly: two or four per workgroup need 146 registers, three waves per SIMD, and end in
             // half-empty rounds (rescale of 7 ciphertexts at N = 2^15, 19 integer limbs: 106 us singly, 116 with four).
-            const u32 wgs = a.groups_outer * (DIR == CONV_UP ? c->dnum : 1) * tiles_of(c) * (((DIR == CONV_UP ? c->D : c->L) + 3) / 4);
-            if (wgs >= 512) launch_conv_runs<ConvL<DIR, 0, 4>, DIR>(c, a, s, cls);
+            if (fours >= 512) launch_conv_runs<ConvL<DIR, 0, 4>, DIR>(c, a, s, cls);
             else launch_conv_runs<ConvL<DIR, 0, 1>, DIR>(c, a, s, cls);
             break;
-        }
-        case 1: launch_conv_runs<ConvL<DIR, 1>, DIR>(c, a, s, cls); break;
-        case 2: launch_conv_runs<ConvL<DIR, 2>, DIR>(c, a, s, cls); break;
+        case 1:
+            if (t.fewer()) { CKKS_CONV(1, 1); }
+            else { CKKS_CONV(1); }
+            break;
+        case 2:
+            if (t.fewer()) { CKKS_CONV(2, 3); }
+            else { CKKS_CONV(2); }
+            break;
         case 4: launch_conv_runs<ConvL<DIR, 4>, DIR>(c, a, s, cls); break;
         case 5:
             if constexpr (DIR == CONV_DN) launch_conv_runs<ConvL<DIR, 5>, DIR>(c, a, s, cls);
             break;
     }
+#undef CKKS_CONV
 }
 
 static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t s) {
@@ -1514,7 +1547,8 @@ enum ExtendMode { EXTEND_PLAIN, EXTEND_BESIDE, EXTEND_FORK };
 static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, ExtendMode mode) {
     const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0};
     SideStream& sd = c->sh->side;
-    if (conv_up_both(c, a3, s)) {  // before a fork: what follows on either stream comes after it
+    const bool second = mode != EXTEND_PLAIN && sd.enabled && c->mixed_classes;
+    if (conv_up_both(c, a3, s, !second ? 0xffffffffu : mode == EXTEND_BESIDE ? 1024 : 512)) {  // before a fork: what follows on either stream comes after it
         if (mode == EXTEND_FORK) fork_side(c, s);
         return;
     }

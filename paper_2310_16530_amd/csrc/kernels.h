@@ -644,22 +644,24 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
 //   S_{t,g}[n] = sum_{(i,b)} c_g(C_{(i,b),t}) * d_{i,b}(y_i[n])          (v_mfma_i32_32x32x32_i8, |S| <= 17 * 2^17)
 //   out_t[n]  == V = sum_g 256^g S_{t,g}[n]  (mod m_t),  |V| <= 2^14 m_t
 // recombined exactly (conv_recombine).  One 32x32x32 product handles 32 coefficients (columns) and 32 rows = four
-// targets x 8 digits, over 32 values of (i,b) = four sources (lane half h holds the digit words of sources 4*ks + 2*h and
-// 4*ks + 2*h + 1 in its 16 operand bytes, the constant operand the matching bytes); KS = ceil(ns/4) products accumulate
+// targets x 8 digits, over 32 values of (i,b) = four sources (lane half h holds the digit words of sources 4*ks + h and
+// 4*ks + 2 + h in its 16 operand bytes, the constant operand the matching bytes); KS = ceil(ns/4) products accumulate
 // all sources.  Row m of the constant operand sits in accumulator a = (m/8)*4 + m%4 of lane half (m/4)%2: a lane of half h
 // gets the digits of target slot h in accumulators 0..7 and of slot 2 + h in accumulators 8..15.
 //
-// A lane keeps 2 x 16 converted words, x[u][k], k the coefficient's row block: rows k*RB + r0 of column c, the inputs of
-// the first four forward stages, which therefore run in the lane that converted them; (r0, c) from a position pp of the
-// tile as tid maps to (r0, c) in layout SA.
-//   NTT = 2: four targets per workgroup of 512 lanes; u = target slot 2*u + h, pp = wave*32 + lane%32
-//   NTT = 1: two targets per workgroup of 256 lanes; slot h, u = half of the positions, pp = wave*64 + u*32 + lane%32
-// What bounds it: the source words come from L2, and that traffic (7.3 TB/s with NTT = 1 at batch 8, N = 2^16, six sources;
+// A lane keeps NTT x 16 converted words, x[u][k], k the coefficient's row block: rows k*RB + r0 of column c, the inputs of the
+// first four forward stages, which therefore run in the lane that converted them; (r0, c) from a position pp = wave*32 + lane%32
+// of the tile as tid maps to (r0, c) in layout SA.  A workgroup has 512 lanes and 2*NTT targets, u = target slot 2*u + h.
+// What bounds it: the source words come from L2, and that traffic (7.3 TB/s with two targets at batch 8, N = 2^16, six sources;
 // all loads from one cached row: 121 -> 78 us per launch) is the limit rather than the arithmetic, so four targets share a
 // load where the registers allow it: FpAr targets need 128 (four waves per SIMD): 121 -> 111 us ModUp, 84 -> 71 us
-// ModDown.  IntAr targets do not fit 128 (spills, 61 -> 66 us) and take NTT = 1.
+// ModDown.  IntAr targets do not fit 128 with NTT = 2 (spills, 61 -> 66 us) and take NTT = 1: in workgroups of 256 lanes that kept
+// twice the words each they needed 144 registers and, with their long butterflies, were the time of every small launch (one
+// ciphertext at N = 2^16: conv_up_both_kernel 37 -> 25 us, at level 13 27 -> 22, one HMult 153 -> 140).
+// Source i travels in word (i / 2) % 2 of lane half i % 2, so that six sources take three loads a lane half and not four (NW; both
+// conversions of a batch of 8 108 -> 105 and 71 -> 68 us with the second batch of loads in flight, AHEAD).
 typedef int v4i __attribute__((ext_vector_type(4)));
-template <class AR, int A, int KS, int DIR, int NTT>
+template <class AR, int A, int KS, int DIR, int NTT, int NW, int AHEAD>
 __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& tb, const LimbRun run, u64* lds, u64* tws, const u32 tid,
                                                const u32 group, const u32 inst) {
     typedef NttCore<AR, A> C;
@@ -705,92 +707,71 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
         for (int ks = 0; ks < KS; ks++) aop[ks] = *reinterpret_cast<const v4i*>(base + ks * 32 + h * 16 + dg * 2);
     }
 #pragma unroll
-    for (u32 tt = 0; tt < 2; tt++) {
-        const u32 sl = NTT == 2 ? 2 * tt + (tid >> 8) : tt;  // 256 lanes fill one slot's twiddles
+    for (u32 tt = 0; tt < NTT; tt++) {
+        const u32 sl = 2 * tt + (tid >> 8);  // 256 lanes fill one slot's twiddles
         if (sl < nt) TW::fill(tws + sl * TW::WORDS, tid & 255, tb, tb.phys(limb_of(sl)));
     }
-    T x[2][16];
+    T x[NTT][16];
     {
         const PrimeConst pc0 = tb.pc[tb.phys(limb_of(h))], pc1 = tb.pc[tb.phys(limb_of(NTT == 2 ? 2 + h : h))];
         const typename AR::Mod m0 = AR::mod(pc0), m1 = AR::mod(pc1);
-        // this lane half supplies the digits of sources 4*ks + 2*h and the next one; beyond the last source any valid
-        // word will do (the constant rows of those sources are zero)
+        // word q of this lane half: the digits of source 4*(q/2) + 2*(q%2) + h; beyond the last source any valid word will do (the
+        // constant rows of those sources are zero)
         const Buf sb(src);
-        u32 so[2 * KS];
-        const u32 pp0 = wave * (NTT == 2 ? 32 : 64) + n;
+        u32 so[NW];
+        const u32 pp0 = wave * 32 + n;
 #pragma unroll
-        for (int q = 0; q < 2 * KS; q++) {
-            const u32 i = 4 * (q >> 1) + 2 * h + (q & 1);
+        for (int q = 0; q < NW; q++) {
+            const u32 i = 4 * (q >> 1) + 2 * (q & 1) + h;
             so[q] = 8 * ((i < ns ? i : ns - 1) * N + tile * C::TC + (pp0 / C::TC) * 256 + pp0 % C::TC);
         }
-        // NTT = 1: the second half of the positions is 32 on: 32 / TC rows down, or 32 columns on where a row holds more
-        constexpr u32 SET = C::TC >= 64 ? 32 : (32 / C::TC) * 256, GROUPS = NTT == 2 ? 16 : 32, GB = NTT == 1 && KS <= 2 ? 2 : 1;
-        auto src_off = [&](int g) { return 8 * ((u32)((g & 15) * C::RB * 256) + (u32)(g >> 4) * SET); };
-        // GB coefficient groups at a time; the source words of the next ones are requested before the products of these
+        auto src_off = [&](int k) { return 8 * (u32)(k * C::RB * 256); };
+        // one row block (32 coefficients a wave) at a time; the source words of the next AHEAD ones are requested before its products
         // are issued; scheduling barriers keep the compiler from hoisting every load of the unrolled loop (which would spill)
-        u64 bw[2][GB][2 * KS];
+        u64 bw[AHEAD + 1][NW];
 #pragma unroll
-        for (u32 b = 0; b < GB; b++)
+        for (int f = 0; f < AHEAD; f++)
 #pragma unroll
-            for (int q = 0; q < 2 * KS; q++) bw[0][b][q] = sb.ld(so[q], src_off(b));
+            for (int q = 0; q < NW; q++) bw[f][q] = sb.ld(so[q], src_off(f));
 #pragma unroll
-        for (u32 g = 0; g < GROUPS; g += GB) {
-            const u32 cur = (g / GB) & 1;
-            if (g + GB < GROUPS) {
+        for (int k = 0; k < 16; k++) {
+            if (k + AHEAD < 16) {
 #pragma unroll
-                for (u32 b = 0; b < GB; b++)
-#pragma unroll
-                    for (int q = 0; q < 2 * KS; q++) bw[cur ^ 1][b][q] = sb.ld(so[q], src_off(g + GB + b));
+                for (int q = 0; q < NW; q++) bw[(k + AHEAD) % (AHEAD + 1)][q] = sb.ld(so[q], src_off(k + AHEAD));
             }
-            v16i acc[GB];
+            const u64* w = bw[k % (AHEAD + 1)];
+            v16i acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-            for (u32 b = 0; b < GB; b++) {
-                acc[b] = v16i{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-                for (int ks = 0; ks < KS; ks++) {
-                    const u64 w0 = bw[cur][b][2 * ks], w1 = bw[cur][b][2 * ks + 1];
-                    const v4i bop = {(int)(u32)w0, (int)(u32)(w0 >> 32), (int)(u32)w1, (int)(u32)(w1 >> 32)};
-                    acc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(aop[ks], bop, acc[b], 0, 0, 0);
-                }
+            for (int ks = 0; ks < KS; ks++) {
+                const u64 w0 = w[2 * ks], w1 = 2 * ks + 1 < NW ? w[2 * ks + 1 < NW ? 2 * ks + 1 : 0] : 0;
+                const v4i bop = {(int)(u32)w0, (int)(u32)(w0 >> 32), (int)(u32)w1, (int)(u32)(w1 >> 32)};
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(aop[ks], bop, acc, 0, 0, 0);
             }
-#pragma unroll
-            for (u32 b = 0; b < GB; b++) {
-                const u32 k = (g + b) & 15;
-                // the empty statements keep a recombination here: sunk to a conditional use it would keep the sums alive
-                if constexpr (NTT == 2) {
-                    x[0][k] = conv_recombine(acc[b], 0, m0, pc0);
-                    x[1][k] = conv_recombine(acc[b], 8, m1, pc1);
-                    asm volatile("" : "+v"(x[0][k]), "+v"(x[1][k]));
-                } else {
-                    x[(g + b) >> 4][k] = conv_recombine(acc[b], 0, m0, pc0);
-                    asm volatile("" : "+v"(x[(g + b) >> 4][k]));
-                }
+            // the empty statements keep a recombination here: sunk to a conditional use it would keep the sums alive
+            x[0][k] = conv_recombine(acc, 0, m0, pc0);
+            asm volatile("" : "+v"(x[0][k]));
+            if constexpr (NTT == 2) {
+                x[1][k] = conv_recombine(acc, 8, m1, pc1);
+                asm volatile("" : "+v"(x[1][k]));
             }
             __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();  // the twiddles are in LDS
         // first four forward stages, in place (FP64: |x| <= 0.51 q on entry, below 7 q after)
         strided_stages_lo<AR, A>(x[0], tws + h * TW::WORDS, m0);
-        if (NTT == 1) strided_stages_lo<AR, A>(x[1], tws + h * TW::WORDS, m0);
-        else if (nt > 2) strided_stages_lo<AR, A>(x[1], tws + (2 + h) * TW::WORDS, m1);
+        if constexpr (NTT == 2)
+            if (nt > 2) strided_stages_lo<AR, A>(x[1], tws + (2 + h) * TW::WORDS, m1);
     }
 #pragma unroll
-    for (u32 u = 0; u < 2; u++) {  // NTT = 2: slots 2u and 2u + 1; NTT = 1: slot u
-        if ((NTT == 2 ? 2 * u : A > 4 ? u : 0) >= nt) break;
+    for (u32 u = 0; u < NTT; u++) {  // slots 2u and 2u + 1
+        if (2 * u >= nt) break;
         if constexpr (A > 4) {
             if (u) __syncthreads();  // the first exchange has been read
-            const typename AR::Mod mx = AR::mod(tb.pc[tb.phys(limb_of(NTT == 2 ? 2 * u + h : h))]);
-            if (NTT == 2) {
+            const typename AR::Mod mx = AR::mod(tb.pc[tb.phys(limb_of(2 * u + h))]);
 #pragma unroll
-                for (int k = 0; k < 16; k++) lds[h * 4096 + k * 256 + wave * 32 + n] = AR::to_raw(AR::round_reduce(x[u][k], mx));
-            } else if (h == u) {
-#pragma unroll
-                for (u32 v = 0; v < 2; v++)
-#pragma unroll
-                    for (int k = 0; k < 16; k++) lds[k * 256 + wave * 64 + v * 32 + n] = AR::to_raw(AR::round_reduce(x[v][k], mx));
-            }
+            for (int k = 0; k < 16; k++) lds[h * 4096 + k * 256 + wave * 32 + n] = AR::to_raw(AR::round_reduce(x[u][k], mx));
             __syncthreads();
-            const u32 half = tid >> 8, sl = NTT == 2 ? 2 * u + half : u, st = tid & 255, c = st % C::TC, r1 = st / C::TC;
+            const u32 half = tid >> 8, sl = 2 * u + half, st = tid & 255, c = st % C::TC, r1 = st / C::TC;
             if (sl < nt) {  // uniform per wave
                 const u32 t = limb_of(sl);
                 const typename AR::Mod m = AR::mod(tb.pc[tb.phys(t)]);
@@ -803,7 +784,7 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
                 for (int k = 0; k < 16; k++) __builtin_nontemporal_store(AR::to_raw(AR::round_reduce(y[k], m)), &dst[k * 256]);
             }
         } else {
-            const u32 sl = NTT == 2 ? 2 * u + h : h, pp = NTT == 2 ? wave * 32 + n : wave * 64 + u * 32 + n;
+            const u32 sl = 2 * u + h, pp = wave * 32 + n;
             if (sl < nt) {
                 const u32 t = limb_of(sl);
                 const typename AR::Mod m = AR::mod(tb.pc[tb.phys(t)]);
@@ -815,17 +796,19 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
     }
 }
 
+// row blocks whose source words are requested ahead: two where the registers allow it
+constexpr int conv_ahead(int KS, int NW) { return KS <= 2 && NW <= 3 ? 2 : 1; }
 // LDS words of conv_mfma_body: the exchange, and the twiddles of its targets
 template <class AR, int A, int NTT>
 struct ConvLds {
-    static constexpr u32 exch = A > 4 ? NTT * 4096 : 2, tw = 2 * NTT * StridedTw<AR, A>::WORDS;
+    static constexpr u32 exch = A > 4 ? 2 * 4096 : 2, tw = 2 * NTT * StridedTw<AR, A>::WORDS;
 };
-template <class AR, int A, int KS, int DIR, int NTT>
+template <class AR, int A, int KS, int DIR, int NTT, int NW>
 __device__ __forceinline__ void conv_mfma_workgroup(const ConvArgs& a, const Tables& tb, const LimbRun run) {
     __shared__ __align__(16) u64 lds[ConvLds<AR, A, NTT>::exch + ConvLds<AR, A, NTT>::tw];
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.blocks, a.groups_outer * (DIR == CONV_UP ? tb.dnum : 1) * ((1u << A) / 16), group, inst)) return;
-    conv_mfma_body<AR, A, KS, DIR, NTT>(a, tb, run, lds, lds + ConvLds<AR, A, NTT>::exch, threadIdx.x, group, inst);
+    conv_mfma_body<AR, A, KS, DIR, NTT, NW, conv_ahead(KS, NW)>(a, tb, run, lds, lds + ConvLds<AR, A, NTT>::exch, threadIdx.x, group, inst);
 }
 
 // targets per lane of the matrix-core form, for every number of sources from two on: with 9 to 16 sources it is 1.1 to 1.9
@@ -833,44 +816,43 @@ __device__ __forceinline__ void conv_mfma_workgroup(const ConvArgs& a, const Tab
 // K = 12, dnum 3, batch 2: 396 -> 358; a rotation, L = 27, K = 9, dnum 3: 205 -> 168)
 template <class AR>
 constexpr int conv_mfma_ntt() { return AR::is_fp ? 2 : 1; }
+// source words a lane half loads per coefficient: half of what KS products take, unless the sources need fewer (a last template
+// argument of the kernels: six sources three words instead of four, two sources one instead of two)
+constexpr int conv_words(int KS) { return 2 * KS; }
+constexpr int conv_words(int, int NW) { return NW; }
 // ONE: a single source, P targets per workgroup.  Else the matrix-core form, P = products per coefficient group + targets
 // per lane.
-template <class AR, int A, int DIR, int P, bool ONE>
-__global__ __launch_bounds__(ONE ? 256 : 256 * conv_mfma_ntt<AR>(), ONE ? (AR::is_fp ? 4 : 3) : !AR::is_fp ? 3 : P <= 4 ? 4 : 2)
+template <class AR, int A, int DIR, int P, bool ONE, int... NW>
+__global__ __launch_bounds__(ONE ? 256 : 512, ONE ? (AR::is_fp ? 4 : 3) : !AR::is_fp ? 4 : P <= 4 ? 4 : 2)
 void conv_fwd_strided_kernel(ConvArgs a, Tables tb, LimbRun run) {
     if constexpr (ONE) conv_one_body<AR, A, DIR, P>(a, tb, run);
-    else conv_mfma_workgroup<AR, A, P - conv_mfma_ntt<AR>(), DIR, conv_mfma_ntt<AR>()>(a, tb, run);
+    else conv_mfma_workgroup<AR, A, P - conv_mfma_ntt<AR>(), DIR, conv_mfma_ntt<AR>(), conv_words(P - conv_mfma_ntt<AR>(), NW...)>(a, tb, run);
 }
 // ModDown onto FpAr targets, KS products per coefficient group, NTT targets per lane: a name of its own, so that profiles tell
 // it from ModUp
-template <int A, int KS, int DIR, int NTT>
-__global__ __launch_bounds__(256 * NTT, KS <= 2 ? 4 : 2) void conv_mfma_kernel(ConvArgs a, Tables tb, LimbRun run) {
-    static_assert(DIR == CONV_DN && NTT == conv_mfma_ntt<FpAr>(), "the other conversions are conv_fwd_strided_kernel");
-    conv_mfma_workgroup<FpAr, A, KS, DIR, NTT>(a, tb, run);
+template <int A, int KS, int DIR, int NTT, int... NW>
+__global__ __launch_bounds__(512, KS <= 2 ? 4 : 2) void conv_mfma_kernel(ConvArgs a, Tables tb, LimbRun run) {
+    static_assert(DIR == CONV_DN, "the other conversions are conv_fwd_strided_kernel");
+    conv_mfma_workgroup<FpAr, A, KS, DIR, NTT, conv_words(KS, NW...)>(a, tb, run);
 }
-// ModUp onto both classes of targets in one launch: the first workgroups convert to the FpAr run, the others to the IntAr
-// run, whose 256-lane form runs twice side by side on two tiles of one limb (same targets, hence the same barriers).  For
-// grids that fit the chip at once (conv_up_both): the two launches would take turns there, each as long as one workgroup.
+// ModUp onto both classes of targets in one launch: the first workgroups convert to the IntAr run, the longer ones, the others to
+// the FpAr run; bound by instructions and by source words from L2, they share the compute units (conv_up_both has the figures).
 struct ConvBothArgs {
     ConvArgs fp, in;  // differ in `blocks`
     LimbRun run_fp, run_in;
-    u32 grid_fp;  // workgroups of the FpAr part, a multiple of 8
+    u32 grid_in;  // workgroups of the IntAr part, a multiple of 8
 };
-template <int A, int KS>
+template <int A, int KS, int... NW>
 __global__ __launch_bounds__(512, 4) void conv_up_both_kernel(ConvBothArgs a, Tables tb) {
-    static_assert(A > 4, "two tiles per limb");
-    constexpr u32 FP_WORDS = ConvLds<FpAr, A, 2>::exch + ConvLds<FpAr, A, 2>::tw, EX = ConvLds<IntAr, A, 1>::exch, TWI = ConvLds<IntAr, A, 1>::tw;
-    constexpr u32 INT_WORDS = 2 * (EX + TWI), TILES = (1u << A) / 16;
-    __shared__ __align__(16) u64 lds[FP_WORDS > INT_WORDS ? FP_WORDS : INT_WORDS];
+    constexpr u32 EXCH = ConvLds<FpAr, A, 2>::exch, TWF = ConvLds<FpAr, A, 2>::tw, TWI = ConvLds<IntAr, A, 1>::tw, TILES = (1u << A) / 16;
+    __shared__ __align__(16) u64 lds[EXCH + (TWF > TWI ? TWF : TWI)];
     u32 group, inst;
-    if (blockIdx.x < a.grid_fp) {
-        if (!xcd_decode(blockIdx.x, a.fp.blocks, a.fp.groups_outer * tb.dnum * TILES, group, inst)) return;
-        conv_mfma_body<FpAr, A, KS, CONV_UP, 2>(a.fp, tb, a.run_fp, lds, lds + ConvLds<FpAr, A, 2>::exch, threadIdx.x, group, inst);
+    if (blockIdx.x >= a.grid_in) {
+        if (!xcd_decode(blockIdx.x - a.grid_in, a.fp.blocks, a.fp.groups_outer * tb.dnum * TILES, group, inst)) return;
+        conv_mfma_body<FpAr, A, KS, CONV_UP, 2, conv_words(KS, NW...), 1>(a.fp, tb, a.run_fp, lds, lds + EXCH, threadIdx.x, group, inst);
     } else {
-        if (!xcd_decode(blockIdx.x - a.grid_fp, a.in.blocks, a.in.groups_outer * tb.dnum * (TILES / 2), group, inst)) return;
-        const u32 half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-        conv_mfma_body<IntAr, A, KS, CONV_UP, 1>(a.in, tb, a.run_in, lds + half * (EX + TWI), lds + half * (EX + TWI) + EX, threadIdx.x & 255,
-                                                 group * 2 + half, inst);
+        if (!xcd_decode(blockIdx.x, a.in.blocks, a.in.groups_outer * tb.dnum * TILES, group, inst)) return;
+        conv_mfma_body<IntAr, A, KS, CONV_UP, 1, conv_words(KS, NW...), 1>(a.in, tb, a.run_in, lds, lds + EXCH, threadIdx.x, group, inst);
     }
 }
 

@@ -91,3 +91,36 @@ def test_single_source_conversions_share_a_load_for_fp64_targets_only(orc, logN,
         hm = host(ctx.hmult_relin_rescale_at(ell, dev(ct1), dev(ct2), d_key))
         for b in range(0, batch, 6):
             assert np.array_equal(hm[b], orc.hmult_relin_rescale_level(ct1[b], ct2[b], key, P)), (ell, b)
+
+
+@pytest.mark.parametrize("logN,L,K,dnum,batch,order", [
+    (14, 10, 2, 5, 1, "fp first"), (14, 12, 5, 3, 1, "fp first"), (15, 11, 6, 2, 2, "fp first"), (14, 14, 7, 2, 3, "fp first"),
+    (14, 16, 8, 2, 1, "fp first"), (14, 9, 3, 3, 30, "fp first"), (15, 13, 6, 3, 5, "alternating"), (16, 6, 2, 3, 1, "fp first"),
+    (16, 13, 6, 3, 1, "fp first"), (12, 12, 6, 2, 1, "fp first"), (13, 7, 5, 2, 40, "fp first")])
+def test_source_words_and_joint_conversions(orc, logN, L, K, dnum, batch, order):
+    """Two, three and five to eight sources (a lane half loads half of them, rounded up), both classes of targets in one launch where
+    the FP64 limbs come first and N >= 2^14, ModDowns with two FP64 targets per workgroup and with four, target counts that
+    leave the last workgroup one to three, a partial last digit; both stream modes, extreme residues."""
+    q = [49] * L if order == "fp first" else [(49, 55)[i % 2] for i in range(L)]
+    ps = synth.mixed_params(logN, q, [59] * K, dnum, "words")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(100 * logN + L)
+    ct, key = synth.uniform_residues(rng, ps.q_primes, ps.N, lead=(2, 2)), synth.uniform_residues(rng, ps.primes, ps.N, lead=(dnum, 2))
+    for i, p in enumerate(ps.primes):
+        key[..., i, : ps.N // 2] = p - 1
+        if i < L:
+            ct[0, :, i, ps.N // 4:] = p - 1
+    d_ct, d_key, g = dev(np.concatenate([ct[:1]] * (batch - 1) + [ct[1:]])), dev(key), synth.galois_element(5, logN)
+    want = [orc.hrot(c, g, key, P) for c in ct]
+    for overlap in (False, True):
+        ctx.set_overlap(overlap)
+        ctx.profile_enable(True)
+        try:
+            got, names = host(ctx.hrot(d_ct, g, d_key)), set(ctx.profile_read())
+        finally:
+            ctx.profile_enable(False)
+            ctx.set_overlap(False)
+        print(logN, L, K, dnum, batch, order, overlap, flush=True)
+        assert np.array_equal(got[-1], want[1]) and all(np.array_equal(x, want[0]) for x in got[:-1])
+        joint = any(k.startswith("conv_up_both_kernel") for k in names)
+        assert joint == (order == "fp first" and logN >= 14 and not (overlap and batch == 30)), names
