@@ -1113,11 +1113,17 @@ static void launch_forward(const View* c, u64* d_x, const LimbSel& sel, hipStrea
 
 // Wavefronts that share the digits of a row in the inner product (InnerArgs::ways) for a launch of `wgs` workgroups of 16
 // rows.  A workgroup's time is about one unit per digit it works through and one per component it ends, two workgroups
-// fit a compute unit: compare rounds times units.  One HMult at N = 2^16, dnum = 4: special limbs, 96 workgroups, 48 -> 28 us;
-// at N = 2^12, dnum = 3: special limb 14 -> 9 us, q-limbs 16 -> 10 us.
+// fit a compute unit: compare rounds times units.  One HMult at N = 2^16, dnum = 4: special limbs, 96 workgroups, 48 -> 28 us (four);
+// at N = 2^12, dnum = 3: special limb 14 -> 9 us, q-limbs 16 -> 10 us (four); HMult at N = 2^15, level 17, batch 3, special limbs, 144
+// workgroups: the call 141 -> 133 us (two); N = 2^16, 12 + 2 limbs, dnum = 6, q-limbs, 192 workgroups: 123 -> 113 (two).  On more
+// than one round of workgroups two are no gain whatever the rounds say: 768 workgroups, N = 2^16, dnum = 6, 235 -> 242 us.
 static u32 inner_ways(u32 wgs, u32 dnum) {
-    const u32 one = (wgs + 511) / 512 * (2 * dnum + 4), four = (4 * wgs + 511) / 512 * (2 * ((dnum + 3) / 4) + 3);
-    return dnum > 1 && four < one ? 4 : 1;
+    u32 best = 1, least = (wgs + 511) / 512 * (2 * dnum + 4);
+    for (u32 ways = 2; ways <= 4 && dnum > 1; ways *= 2) {
+        const u32 t = (ways * wgs + 511) / 512 * (2 * ((dnum + ways - 1) / ways) + 3);
+        if (t < least && (ways == 4 || wgs <= 512)) best = ways, least = t;
+    }
+    return best;
 }
 
 // limbs [lo, hi) of the extended basis.  FUSED: the launch also ends the ModDown on its limbs (all below
@@ -1129,8 +1135,10 @@ static void launch_ks_inner(const View* c, InnerArgs a, hipStream_t s, u32 lo, u
     std::vector<ClassRun> runs = class_runs(c, lo, hi);
     // hoisted rotations: the FP64 limbs stream keys and digits, the integer limbs are bound by instructions; in one launch
     // they share the chip (17 rotations at N = 2^16, L = 24, in launches of 9
-    // and 8: 242 + 95 and 196 + 78 us -> 325 and 271 us)
-    const bool any = HOISTED && runs.size() > 1 && !c->sh->side.active;
+    // and 8: 242 + 95 and 196 + 78 us -> 325 and 271 us).  Merged rescale: limb L - 1 beside the special limbs (HMult, N = 2^15,
+    // level 17, batch 3: 148 -> 136 us; N = 2^16, 24 + 6 limbs, batch 3: 330 -> 319).
+    constexpr bool JOINT = HOISTED || (OWN == OWN_TENSOR && !FUSED);
+    const bool any = JOINT && runs.size() > 1 && !c->sh->side.active;
     if (any) runs.assign(1, ClassRun{lo, hi - lo, true});
     for (const ClassRun& cr : runs) {
         const u32 terms = (OWN == OWN_ROT_SUM ? a.n_sum : 1) * c->dnum;
@@ -1149,7 +1157,7 @@ static void launch_ks_inner(const View* c, InnerArgs a, hipStream_t s, u32 lo, u
         }
         const dim3 grid(xcd_grid(cr.count * tiles_of(c) * a.ways, a.n_inst));
         ProfScope ps(c, c->sh->prof.on ? L::name(any ? "AnyAr" : cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(), limbs, rs);
-        if constexpr (HOISTED)
+        if constexpr (JOINT)
             if (any) {
                 dispatch_any<L>(c, grid, rs, a, LimbRun{cr.first, cr.count});
                 continue;
@@ -1229,7 +1237,7 @@ static void launch_ks_final(const View* c, const FinalArgs& a, hipStream_t s) {
     u64 per;  // algorithmic limbs per q-limb
     if (MODE == FIN_HOISTED) per = (u64)a.n_rot * (2 + 2 + 1 + 1) + (2 + (a.accumulate ? 2 : 0));
     else if (MODE == FIN_SUMMED) per = (u64)a.n_rot * (2 + 1) + (2 + 2 + (a.accumulate ? 2 : 0));
-    else per = (u64)a.n_inst * 6;
+    else per = (u64)a.n_inst * 3;
     launch_runs<KsFinalL<MODE>>(c, 0, c->L, 0, tiles_of(c), a.n_inst, a, s, [per](u32, u32 n) { return per * n; });
 }
 
@@ -1788,7 +1796,7 @@ static int rescale_impl(ckks_ctx* ctx, uint32_t level, const uint64_t* d_ct, uin
     moddown_convert(c, w, batch, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
-    fa.cq = d_ct, fa.cq_L = level, fa.cv = w.cv, fa.out = d_out, fa.n_inst = batch;
+    fa.cq = d_ct, fa.cq_L = level, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 2 * batch;
     launch_ks_final<FIN_KS>(c, fa, s);
     return hip_check(c, "ckks_rescale");
 }
@@ -1992,7 +2000,7 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
     moddown_convert(cm, w, 1, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
-    fa.cq = w.cq, fa.cq_L = cm->L, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 1;
+    fa.cq = w.cq, fa.cq_L = cm->L, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 2;
     launch_ks_final<FIN_KS>(cm, fa, s);
     return hip_check(c, "ckks_hrot_dh_mac");
 }
@@ -2118,7 +2126,7 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
     moddown_convert(c, w, n2, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
-    fa.cq = w.cq, fa.cq_L = c->L, fa.cv = w.cv, fa.out = inner, fa.n_inst = n2;
+    fa.cq = w.cq, fa.cq_L = c->L, fa.cv = w.cv, fa.out = inner, fa.n_inst = 2 * n2;
     launch_ks_final<FIN_KS>(c, fa, s);
     // Giant rotations, each inner sum with its own key, and their sum.  Their ModDowns are one (summed_rotations; 8 x 4 at N = 2^16,
     // 24 + 6 limbs: conversions, inverse pass, q-limb product and

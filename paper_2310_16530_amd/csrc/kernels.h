@@ -968,9 +968,10 @@ struct InnerArgs {
     const u64* cv;              // [inst][2][split][N] converted special part, first forward pass done
     u64* out;                   // [inst][2][split][N]
     const PinvConst* fin_pinv;  // [split] inverse of the product of the ModDown's source primes
-    // 1: a workgroup owns 16 rows.  4: it owns 4, each of its wavefronts all of them for every fourth digit; the sums are
-    // joined in LDS and the first two wavefronts end a component each.  For grids that leave the chip idle, where the
-    // time is that of one wavefront and its dnum + 2 passes run one after the other (inner_ways).
+    // 1: a workgroup owns 16 rows.  2, 4: it owns 8 or 4, and a team of two or four wavefronts works on four of them, each on every
+    // second or fourth digit; the sums are joined in LDS and the first two wavefronts of a team end a component each.  For grids
+    // that leave the chip idle, where the time is that of one wavefront and its dnum + 2 passes run one after the other
+    // (inner_ways).
     u32 ways;
 };
 
@@ -1010,7 +1011,9 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
                                               u32 inst) {
     typedef typename AR::T T;
     const u32 ways = HOISTED ? 1 : a.ways, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r = ways == 1 ? tile * 16 + ch : tile * 4 + (ch & 3);
+    // the `ways` wavefronts of a team share four rows
+    const u32 part = wave & (ways - 1), first = ways == 1 ? wave * 4 : ways == 2 ? (wave >> 1) * 4 : 0;  // row of the tile
+    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r0 = tile * (ways == 1 ? 16 : ways == 2 ? 8 : 4) + first, r = r0 + (ch & 3);
     const u32 L = tb.L, D = tb.D;
     const u32 pi = tb.phys(i), Dkey = tb.Lfull + tb.K;  // keys are laid out over the whole chain
     const PrimeConst pc = tb.pc[pi];
@@ -1031,7 +1034,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
 #pragma unroll
     for (int k = 0; k < 16; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
     u32 since = 0;
-    for (u32 jj = ways == 1 ? 0 : wave; jj < (SUM ? a.n_sum : 1) * tb.dnum; jj += ways) {
+    for (u32 jj = part; jj < (SUM ? a.n_sum : 1) * tb.dnum; jj += ways) {
         u32 j = jj, src = inst;
         if constexpr (SUM) {  // digits in rotated order: the cheap own digits spread over the wavefronts that share the row
             src = jj / tb.dnum, j = (jj + src) % tb.dnum;
@@ -1112,28 +1115,32 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
             for (int k = 0; k < 16; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
         }
     }
-    if (!HOISTED && ways != 1) {  // wavefront t of the four gets component t of the joined sums
+    if (!HOISTED && ways != 1) {  // wavefront t of a team gets component t of the joined sums
 #pragma unroll
         for (u32 t = 0; t < 2; t++) {
             __syncthreads();
-            if (wave != t) {
+            if (part != t) {
 #pragma unroll
                 for (int k = 0; k < 16; k++) lds[wave * 1024 + k * 64 + (tid & 63)] = AR::to_raw(AR::acc_fold(t ? acc1[k] : acc0[k], m));
             }
             __syncthreads();
-            if (wave == t) {
+            if (part == t) {
+                T s[16];
+                auto join = [&](u32 v) __attribute__((always_inline)) {
+                    const u64* p = lds + (wave - part + ((t + v) & (ways - 1))) * 1024 + (tid & 63);
 #pragma unroll
-                for (int k = 0; k < 16; k++) {
-                    T s = AR::acc_fold(t ? acc1[k] : acc0[k], m);
+                    for (int k = 0; k < 16; k++) s[k] = AR::wide_join(s[k], AR::from_raw(p[k * 64]), m);
+                };
 #pragma unroll
-                    for (u32 v = 1; v < 4; v++) s = AR::wide_join(s, AR::from_raw(lds[((t + v) & 3) * 1024 + k * 64 + (tid & 63)]), m);
-                    if (t) acc1[k] = s;
-                    else acc0[k] = s;
-                }
+                for (int k = 0; k < 16; k++) s[k] = AR::acc_fold(t ? acc1[k] : acc0[k], m);
+                join(1);
+                if (ways == 4) join(2), join(3);
+#pragma unroll
+                for (int k = 0; k < 16; k++) (t ? acc1[k] : acc0[k]) = s[k];
             }
         }
         __syncthreads();
-        if (wave > 1) return;
+        if (part > 1) return;
     }
     if (FUSED) {
         // c' stays in registers: out = (c' - second forward pass of the converted special part) * P^-1
@@ -1144,12 +1151,12 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         // it is computed before the accumulation loop, which has no registers to spare.
         u32 e0f = e0, chf = ch, gal_fin = gal;
         asm volatile("" : "+v"(e0f), "+v"(chf), "+s"(gal_fin));
-        const u32 rf = ways == 1 ? tile * 16 + chf : tile * 4 + (chf & 3), row_off_f = rf * 256;
+        const u32 rf = r0 + (chf & 3), row_off_f = rf * 256;
         u64* lrow_f = lds + chf * 272;
         const PinvConst pinv = a.fin_pinv[i];
 #pragma unroll
         for (int t = 0; t < 2; t++) {
-            if (ways != 1 && wave != (u32)t) continue;
+            if (ways != 1 && part != (u32)t) continue;
             T v[16];
             const u64* p = a.cv + (((size_t)inst * 2 + t) * a.split + i) * N + row_off_f;
 #pragma unroll
@@ -1194,7 +1201,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         u64 res[16];
 #pragma unroll
         for (int t = 0; t < 2; t++) {
-            if (ways != 1 && wave != (u32)t) continue;
+            if (ways != 1 && part != (u32)t) continue;
 #pragma unroll
             for (int k = 0; k < 16; k++) res[k] = AR::acc_canon(AR::acc_finish(t ? acc1[k] : acc0[k], m), m);
             store_row_cp(a.cq + (((size_t)inst * 2 + t) * a.split + i) * N + row_off, e0, res);
@@ -1202,7 +1209,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
     } else {
 #pragma unroll
         for (int t = 0; t < 2; t++) {
-            if (ways != 1 && wave != (u32)t) continue;
+            if (ways != 1 && part != (u32)t) continue;
             T x[16];
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = AR::acc_finish(t ? acc1[k] : acc0[k], m);
@@ -1218,7 +1225,6 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
 template <class AR, int A, int OWN, bool HOISTED, bool FUSED>
 __global__ __launch_bounds__(256, 2) void ks_inner_kernel(InnerArgs a, Tables tb, LimbRun run) {
     constexpr bool ANY = __is_same(AR, AnyAr), TWL = !HOISTED && !__is_same(AR, IntAr);
-    static_assert(HOISTED || !ANY, "the twiddle block in LDS belongs to one arithmetic");
     __shared__ u64 lds[NTT_LDS_WORDS + (TWL ? 16 * CKKS_ROW_TW_WORDS : 0)];
     const u32 TILES = (1u << A) / 16 * (HOISTED ? 1 : a.ways);
     u32 group, inst;
@@ -1584,7 +1590,8 @@ __global__ __launch_bounds__(256) void sum_instances_kernel(const u64* __restric
 
 // ======================================================================== final combine
 // ks_t[i] = (c'_t[i] - NTT(conv_t)[i]) * P^-1 mod q_i, the NTT's second pass done here, then
-//   FIN_KS     : out[inst][t][i] = ks
+//   FIN_KS     : out[inst / 2][t][i] = ks, t = inst % 2: a workgroup per component, the two adjacent on one XCD (with both in one
+//                workgroup, one after the other: rescale of one ciphertext at N = 2^16, 24 limbs 38.4 us, so 35.5; 8 of 35 limbs 240, 235)
 //   FIN_HOISTED: out[t][i] (+)= sum_r pt_r[i] * (ks_r + (t == 0 ? sigma_{g_r}(b) : 0)); work item (i, tile, t)
 //   FIN_SUMMED : the same words as (C_t - sum_r pt_r * NTT(conv_{r,t})) * P^-1 with C_t = sum_r pt_r * (c'_{r,t} + P * (t == 0 ?
 //                sigma_{g_r}(b) : 0)), which dh_accum_kernel has left in cq: on a q-limb everything after the conversions is linear,
@@ -1599,7 +1606,7 @@ struct FinalArgs {
     const u64* pt;   // HOISTED, SUMMED: plaintexts of this chunk [n_rot][L][N]
     u64* out;
     u32 galois[CKKS_ROT_CHUNK];  // HOISTED
-    u32 n_inst;      // batch (or 2 for HOISTED and SUMMED: the component t)
+    u32 n_inst;      // KS: 2 * batch; HOISTED, SUMMED: 2, the component t
     u32 n_rot;       // HOISTED, SUMMED
     u32 accumulate;  // HOISTED, SUMMED: add to what out already holds
     u32 cq_L;        // limbs per component of cq (L, or L + 1 when cq is a ciphertext about to lose its last limb)
@@ -1744,31 +1751,28 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
         store_row_cp(o, e0, res);
         return;
     }
+    T v[16];
+    const u64* p = a.cv + ((size_t)inst * L + i) * N + row_off;
 #pragma unroll
-    for (int t = 0; t < 2; t++) {
-        T v[16];
-        const u64* p = a.cv + (((size_t)inst * 2 + t) * L + i) * N + row_off;
+    for (int k = 0; k < 16; k++) v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
+    NttCore<AR, A>::fwd_contig(v, lrow, e0, r, ti, tf, N, m);
+    exchange_cb_to_cp<AR>(v, lrow, e0);
+    u64 c[16], res[16];
+    load_row_cp<true>(a.cq + ((size_t)inst * a.cq_L + i) * N + row_off, e0, c);
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
-        NttCore<AR, A>::fwd_contig(v, lrow, e0, r, ti, tf, N, m);
-        exchange_cb_to_cp<AR>(v, lrow, e0);
-        u64 c[16], res[16];
-        load_row_cp<true>(a.cq + (((size_t)inst * 2 + t) * a.cq_L + i) * N + row_off, e0, c);
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            if constexpr (AR::is_fp) {
-                const FpAr::Mod fm = FpAr::mod(pc);
-                res[k] = FpAr::canon(FpAr::mulmod_lazy(u64_to_f64(c[k]) - v[k], pinv.d, fm), fm);
-            } else {
-                res[k] = mul_shoup(submod(c[k], AR::canon_fwd(v[k], m), q), pinv.w, pinv.wp, q);
-            }
+    for (int k = 0; k < 16; k++) {
+        if constexpr (AR::is_fp) {
+            const FpAr::Mod fm = FpAr::mod(pc);
+            res[k] = FpAr::canon(FpAr::mulmod_lazy(u64_to_f64(c[k]) - v[k], pinv.d, fm), fm);
+        } else {
+            res[k] = mul_shoup(submod(c[k], AR::canon_fwd(v[k], m), q), pinv.w, pinv.wp, q);
         }
-        store_row_cp(a.out + (((size_t)inst * 2 + t) * L + i) * N + row_off, e0, res);
     }
+    store_row_cp(a.out + ((size_t)inst * L + i) * N + row_off, e0, res);
 }
 
 template <class AR, int A, int MODE>
-__global__ __launch_bounds__(256, MODE != FIN_KS ? (AR::is_fp ? 3 : 2) : 4) void ks_final_kernel(FinalArgs a, Tables tb, LimbRun run) {
+__global__ __launch_bounds__(256, MODE >= FIN_HOISTED ? (AR::is_fp ? 3 : 2) : 4) void ks_final_kernel(FinalArgs a, Tables tb, LimbRun run) {
     __shared__ u64 lds[NTT_LDS_WORDS];
     constexpr u32 TILES = (1u << A) / 16;
     u32 group, inst;
