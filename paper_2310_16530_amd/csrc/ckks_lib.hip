@@ -738,6 +738,7 @@ static int hip_check(const View* c, const char* what) {
 
 // grid of an XCD-aware launch: groups padded to a multiple of 8, times the instances per group
 static inline u32 xcd_grid(u32 groups, u32 inst) { return ((groups + 7) / 8) * 8 * inst; }
+static inline u32 cdiv(u32 a, u32 b) { return (a + b - 1) / b; }
 static inline u32 tiles_of(const View* c) { return (1u << (c->logN - 8)) / 16; }
 
 // Maximal runs of consecutive primes [lo, hi) that share an arithmetic (FpAr / IntAr).
@@ -764,6 +765,15 @@ static bool any_fp_prime(const View* c, u32 lo, u32 hi) {
 // A launcher type L provides
 //   template <class AR, int A> static void go(grid, stream, args, tables, run)   the launch
 //   static std::string name(const char* ar, int A)                               the profiler's kernel name
+// Words that one launch leaves for the next, `limbs` of them: written and read with ordinary accesses they may stay in the 256 MB
+// Infinity Cache, which nontemporal ones leave empty; small amounts reach the next launch sooner past the L2 (what is dirty there
+// is written back when the launch ends), and reads of more than the cache holds only evict it.  Rescale, N = 2^16, 24 limbs,
+// inputs cold, both / none, us: 8 ciphertexts (184 MiB) 153 / 174, 4 (92) 92 / 99, 1 (23) 41 / 37; 12 (276 MiB) written so, read
+// nontemporal 244 / 260.  Not the ModDown conversions on the matrix cores, whose launches share the cache with the digits (HMult,
+// batch 8: 699 / 704).  First forward pass of 16 x 24 limbs (192 MiB): the transform 160.6 / 162.7, of 4 (48 MiB) no difference.
+static bool stores_cached(const View* c, u64 limbs) { return (limbs * 8 << c->logN) >= (48ull << 20); }
+static bool loads_cached(const View* c, u64 limbs) { return stores_cached(c, limbs) && (limbs * 8 << c->logN) <= (224ull << 20); }
+
 template <class L, class ArgT>
 static void dispatch_kernel(const View* c, bool fp, dim3 grid, hipStream_t s, const ArgT& a, LimbRun run) {
 #define CKKS_CASE_A(AV)                                               \
@@ -1047,6 +1057,13 @@ static bool conv_up_both(const View* c, const ConvArgs& base, hipStream_t s, u32
     return true;
 }
 
+// workgroups of a ModUp onto every class of targets, four FpAr or two IntAr targets each
+static u32 conv_up_workgroups(const View* c, u32 batch) {
+    u32 blocks = 0, total;
+    for (const ClassRun& r : class_runs(c, 0, c->D)) blocks += cdiv(conv_up_targets(c, r, total), r.fp ? 4 : 2);
+    return batch * c->dnum * tiles_of(c) * blocks;
+}
+
 // word format in which the last inverse stage leaves the sources of a conversion
 static inline u32 conv_src_fmt(const ConvTab& t, int dir) { return t.ks ? SRC_DIGITS : dir == CONV_UP ? SRC_F64 : SRC_CANON; }
 
@@ -1097,7 +1114,7 @@ static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t
 static void launch_forward(const View* c, u64* d_x, const LimbSel& sel, hipStream_t s) {
     const FwdContigArgs a2 = {d_x, sel, 0, 0};
     if (!inv_one_kernel((int)c->logN - 8) || spread_limbs(c, sel, 80)) {
-        const FwdStridedArgs a1 = {d_x, d_x, sel};
+        const FwdStridedArgs a1 = {d_x, d_x, sel, stores_cached(c, (u64)sel.n_l * sel.n_inst)};
         launch_fwd_strided(c, a1, s);
         launch_fwd_contig(c, a2, s);
         return;
@@ -1553,14 +1570,14 @@ static void launch_decompose_inverse(const View* c, const InvContigArgs& a, hipS
 // integer limbs take the side stream from here on.
 enum ExtendMode { EXTEND_PLAIN, EXTEND_BESIDE, EXTEND_FORK };
 static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, ExtendMode mode) {
-    const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0};
+    const ConvArgs a3 = {w.x, w.dt, groups, 0, 0, nullptr, nullptr, 0};
     SideStream& sd = c->sh->side;
     const bool second = mode != EXTEND_PLAIN && sd.enabled && c->mixed_classes;
     if (conv_up_both(c, a3, s, !second ? 0xffffffffu : mode == EXTEND_BESIDE ? 1024 : 512)) {  // before a fork: what follows on either stream comes after it
         if (mode == EXTEND_FORK) fork_side(c, s);
         return;
     }
-    if (mode == EXTEND_BESIDE && sd.enabled && c->mixed_classes && !sd.active && side_stream_ready(sd)) {
+    if (mode == EXTEND_BESIDE && conv_up_workgroups(c, groups) >= 512 && sd.enabled && c->mixed_classes && !sd.active && side_stream_ready(sd)) {
         // the IntAr targets first, on s; the FpAr targets on the side stream from the moment those are done, beside
         // whatever s runs next (the caller joins before it reads the FpAr limbs of dt)
         launch_conv<CONV_UP>(c, a3, s, 0);
@@ -1598,7 +1615,7 @@ static void moddown_convert(const View* c, const Workspace& w, u32 cg, hipStream
         launch_inv_strided(c, a6, s);
     }
     join_side(c, s);  // the conversion reads every special limb
-    const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, nullptr, nullptr, 0};
+    const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, c->dn.ks == 0 && stores_cached(c, (u64)cg * 2 * c->L), nullptr, nullptr, 0};
     launch_conv<CONV_DN>(c, a7, s);
 }
 
@@ -1796,7 +1813,7 @@ static int rescale_impl(ckks_ctx* ctx, uint32_t level, const uint64_t* d_ct, uin
     moddown_convert(c, w, batch, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
-    fa.cq = d_ct, fa.cq_L = level, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 2 * batch;
+    fa.cq = d_ct, fa.cq_L = level, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 2 * batch, fa.cached = loads_cached(c, (u64)batch * 2 * c->L);
     launch_ks_final<FIN_KS>(c, fa, s);
     return hip_check(c, "ckks_rescale");
 }

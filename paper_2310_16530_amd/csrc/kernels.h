@@ -417,12 +417,13 @@ struct FwdStridedArgs {
     const u64* src;  // canonical coefficients addressed by sel
     u64* dst;        // raw forward-lazy words, same addressing (in place when dst == src)
     LimbSel sel;
+    u32 cached;      // ordinary stores (stores_cached)
 };
 
-// stages + store shared by the plain and the conversion-fused first pass; x in layout SA
+// stages + store; x in layout SA
 template <class AR, int A>
 __device__ __forceinline__ void fwd_strided_finish(typename AR::T (&x)[16], const Tables& tb, u64* lds, u32 vi,
-                                                   u64* dst, u32 tile) {
+                                                   u64* dst, u32 tile, bool cached) {
     typedef NttCore<AR, A> C;
     const u32 N = 1u << tb.logN, pi = tb.phys(vi);
     const u32 tid = threadIdx.x;
@@ -433,7 +434,14 @@ __device__ __forceinline__ void fwd_strided_finish(typename AR::T (&x)[16], cons
     C::fwd_strided(x, lds, tid, ti, tf, N, m);
     if constexpr (A > 4) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) __builtin_nontemporal_store(AR::to_raw(AR::round_reduce(x[k], m)), &dst[(size_t)(r0 * 16 + k) * 256 + col]);
+        for (int k = 0; k < 16; k++) x[k] = AR::round_reduce(x[k], m);
+        if (cached) {
+#pragma unroll
+            for (int k = 0; k < 16; k++) dst[(size_t)(r0 * 16 + k) * 256 + col] = AR::to_raw(x[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; k++) __builtin_nontemporal_store(AR::to_raw(x[k]), &dst[(size_t)(r0 * 16 + k) * 256 + col]);
+        }
     } else {
 #pragma unroll
         for (int k = 0; k < 16; k++)
@@ -451,7 +459,7 @@ __device__ __forceinline__ void fwd_strided_body(const FwdStridedArgs& a, const 
     typename AR::T x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = AR::from_canon(a.src[off + (size_t)(k * C::RB + r0) * 256 + col], m);
-    fwd_strided_finish<AR, A>(x, tb, lds, pi, a.dst + off, tile);
+    fwd_strided_finish<AR, A>(x, tb, lds, pi, a.dst + off, tile, a.cached);
 }
 template <class AR, int A>
 __global__ __launch_bounds__(256) void fwd_strided_kernel(FwdStridedArgs a, Tables tb, LimbRun run) {
@@ -474,6 +482,7 @@ struct ConvArgs {
     u64* dst;             // raw forward-lazy words after the first pass: CONV_UP dt [b][dnum][D][N], CONV_DN cv [g][L][N]
     u32 groups_outer;     // CONV_UP: batch; CONV_DN: number of g
     u32 blocks;           // workgroups per (group, tile): the run's targets in blocks
+    u32 cached;           // CONV_DN from a single source: ordinary stores (stores_cached)
     // matrix cores: constant operands [digit][prime of the chain][KS][2 lane halves][8 digit rows][2 words], and the same
     // of a shorter last digit, [limb of the level]; digits from n_full on use the latter
     const u64* aop;
@@ -627,7 +636,14 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
             for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lds[(r0 * 16 + k) * C::TC + c]);
             strided_stages_hi<AR, A>(x, tw, r0, m);
 #pragma unroll
-            for (int k = 0; k < 16; k++) dst.st_nt(AR::to_raw(AR::round_reduce(x[k], m)), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
+            for (int k = 0; k < 16; k++) x[k] = AR::round_reduce(x[k], m);
+            if (DIR == CONV_DN && a.cached) {
+#pragma unroll
+                for (int k = 0; k < 16; k++) dst.st(AR::to_raw(x[k]), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 16; k++) dst.st_nt(AR::to_raw(x[k]), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
+            }
         } else {
             u64* dst = dst0 + (size_t)vi * N;
 #pragma unroll
@@ -877,7 +893,7 @@ __device__ __forceinline__ void fwd_contig_body(const FwdContigArgs& a, const Ta
     T x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = AR::from_raw(p[k * 16 + e0]);
-    NttCore<AR, A>::fwd_contig(x, lrow, e0, r, ti, tf, N, m);
+    NttCore<AR, A>::template fwd_contig<true>(x, lrow, e0, r, ti, tf, N, m);
     row_sync();
 #pragma unroll
     for (int k = 0; k < 16; k++) lrow[pad16(e0 * 16 + k)] = AR::canon_fwd(x[k], m);
@@ -1609,6 +1625,7 @@ struct FinalArgs {
     u32 n_inst;      // KS: 2 * batch; HOISTED, SUMMED: 2, the component t
     u32 n_rot;       // HOISTED, SUMMED
     u32 accumulate;  // HOISTED, SUMMED: add to what out already holds
+    u32 cached;      // KS: ordinary loads of cv (loads_cached)
     u32 cq_L;        // limbs per component of cq (L, or L + 1 when cq is a ciphertext about to lose its last limb)
 };
 
@@ -1753,9 +1770,14 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
     }
     T v[16];
     const u64* p = a.cv + ((size_t)inst * L + i) * N + row_off;
+    if (a.cached) {
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
-    NttCore<AR, A>::fwd_contig(v, lrow, e0, r, ti, tf, N, m);
+        for (int k = 0; k < 16; k++) v[k] = AR::from_raw(p[k * 16 + e0]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
+    }
+    NttCore<AR, A>::template fwd_contig<true>(v, lrow, e0, r, ti, tf, N, m);
     exchange_cb_to_cp<AR>(v, lrow, e0);
     u64 c[16], res[16];
     load_row_cp<true>(a.cq + ((size_t)inst * a.cq_L + i) * N + row_off, e0, c);

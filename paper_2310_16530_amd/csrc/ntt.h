@@ -79,7 +79,9 @@ struct NttCore {
 
     // ---- forward contiguous pass: x in layout CA (row r of the limb) -> 8 stages -> layout CB.
     // TW supplies the twiddle of stage u for the pair whose first word has index w in the row: get(u, w).
-    template <class TW>
+    // AHEAD as in inv_contig (24 x 8 integer limbs at N = 2^16: the transform 97.2 -> 95.2 us); the inner product has no registers for
+    // it (spills, special limbs of one HMult 28 -> 33 us).
+    template <bool AHEAD = false, class TW>
     static __device__ __forceinline__ void fwd_contig_with(T (&x)[16], u64* l, u32 e0, const TW& tw, const Mod& m) {
 #pragma unroll
         for (int u = 0; u < 4; u++) {
@@ -94,17 +96,26 @@ struct NttCore {
         }
 #pragma unroll
         for (int k = 0; k < 16; k++) l[pad16(k * 16 + e0)] = AR::to_raw(AR::round_reduce(x[k], m));
+        typename AR::Tw t[AHEAD ? 15 : 1];  // stage u at 2^(u-4) - 1, one per 2^(8-u) words
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int u = 4; u < 8; u++)
+#pragma unroll
+                for (int g = 0; g < (1 << (u - 4)); g++) t[(1 << (u - 4)) - 1 + g] = tw.get(u, e0 * 16 + (u32)(g << (8 - u)));
+        }
         row_sync();
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = AR::from_raw(l[pad16(e0 * 16 + k)]);
+        if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 4; u < 8; u++) {
             const int d = 8 >> (u - 4);
 #pragma unroll
             for (int k = 0; k < 16; k++) {
                 if (k & d) continue;
-                if (u & 1) AR::template bfly_fwd<false>(x[k], x[k + d], tw.get(u, e0 * 16 + (u32)k), m);
-                else AR::template bfly_fwd<true>(x[k], x[k + d], tw.get(u, e0 * 16 + (u32)k), m);
+                const typename AR::Tw w = AHEAD ? t[AHEAD ? (1 << (u - 4)) - 1 + (k >> (8 - u)) : 0] : tw.get(u, e0 * 16 + (u32)k);
+                if (u & 1) AR::template bfly_fwd<false>(x[k], x[k + d], w, m);
+                else AR::template bfly_fwd<true>(x[k], x[k + d], w, m);
             }
         }
     }
@@ -117,9 +128,10 @@ struct NttCore {
             return AR::tw(ti, tf, (1u << (A + u)) + (r << u) + (w >> (8 - u)), N, false);
         }
     };
+    template <bool AHEAD = false>
     static __device__ __forceinline__ void fwd_contig(T (&x)[16], u64* l, u32 e0, u32 r, const u64* ti,
                                                       const double* tf, u32 N, const Mod& m) {
-        fwd_contig_with(x, l, e0, GlobalTw{ti, tf, r, N}, m);
+        fwd_contig_with<AHEAD>(x, l, e0, GlobalTw{ti, tf, r, N}, m);
     }
 
     // ---- inverse contiguous pass: x in layout CB (inverse-lazy range) -> 8 stages -> layout CA
