@@ -1141,18 +1141,19 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
             }
             __syncthreads();
             if (part == t) {
-                T s[16];
-                auto join = [&](u32 v) __attribute__((always_inline)) {
-                    const u64* p = lds + (wave - part + ((t + v) & (ways - 1))) * 1024 + (tid & 63);
+                if (ways == 4) {
 #pragma unroll
-                    for (int k = 0; k < 16; k++) s[k] = AR::wide_join(s[k], AR::from_raw(p[k * 64]), m);
-                };
+                    for (int k = 0; k < 16; k++) {
+                        T s = AR::acc_fold(t ? acc1[k] : acc0[k], m);
 #pragma unroll
-                for (int k = 0; k < 16; k++) s[k] = AR::acc_fold(t ? acc1[k] : acc0[k], m);
-                join(1);
-                if (ways == 4) join(2), join(3);
+                        for (u32 v = 1; v < 4; v++) s = AR::wide_join(s, AR::from_raw(lds[((t + v) & 3) * 1024 + k * 64 + (tid & 63)]), m);
+                        (t ? acc1[k] : acc0[k]) = s;
+                    }
+                } else {
+                    const u64* mate = lds + (wave ^ 1) * 1024 + (tid & 63);
 #pragma unroll
-                for (int k = 0; k < 16; k++) (t ? acc1[k] : acc0[k]) = s[k];
+                    for (int k = 0; k < 16; k++) (t ? acc1[k] : acc0[k]) = AR::wide_join(AR::acc_fold(t ? acc1[k] : acc0[k], m), AR::from_raw(mate[k * 64]), m);
+                }
             }
         }
         __syncthreads();
