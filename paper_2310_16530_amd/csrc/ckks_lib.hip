@@ -1014,8 +1014,9 @@ static void launch_conv_runs(const View* c, ConvArgs a, hipStream_t s, int only)
 
 // ModUp onto both arithmetics in one launch, where the chain is FpAr limbs followed by IntAr limbs (N >= 2^14; below, and with more
 // than eight sources, no such kernel is built).  Two launches / one, whole calls on one stream, us: one rotation at N = 2^16, 24 + 6
-// limbs 146.5 / 134, level 13 113 / 108; 2 of them 224 / 211, 8 683 / 681; N = 2^15, level 17, 3 135 (one) against 145, 8 262 / 251;
-// N = 2^14, 24 + 6, 12 296 / 284.  Where the targets would otherwise run beside each other on the second stream, up to `most`
+// limbs 146.5 / 134, level 13 113 / 108; 2 of them 224 / 211, at level 13 8 (2304 workgroups) 414 / 405; N = 2^15, level 17, 3 145 / 135, 8
+// 262 / 251; N = 2^14, 24 + 6, 12 296 / 284; from 4096 workgroups on no difference (8 of 24 + 6: 683 / 681; 8 of 35 + 7: 1086 / 1084), each
+// has its own launch.  Where the targets would otherwise run beside each other on the second stream, up to `most`
 // workgroups: with BESIDE 1024 (N = 2^16, 24 + 6, 2 rotations (1024) 218 / 212, 4 (2048) 361 / 374; level 13, 2 157 / 145), with
 // FORK 512 (dh, 35 + 7 limbs (880), one rotation 258 / 263).  Returns false where it does not apply.
 static bool conv_up_both(const View* c, const ConvArgs& base, hipStream_t s, u32 most) {
@@ -1573,7 +1574,7 @@ static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipS
     const ConvArgs a3 = {w.x, w.dt, groups, 0, 0, nullptr, nullptr, 0};
     SideStream& sd = c->sh->side;
     const bool second = mode != EXTEND_PLAIN && sd.enabled && c->mixed_classes;
-    if (conv_up_both(c, a3, s, !second ? 0xffffffffu : mode == EXTEND_BESIDE ? 1024 : 512)) {  // before a fork: what follows on either stream comes after it
+    if (conv_up_both(c, a3, s, !second ? 4095 : mode == EXTEND_BESIDE ? 1024 : 512)) {  // before a fork: what follows on either stream comes after it
         if (mode == EXTEND_FORK) fork_side(c, s);
         return;
     }
