@@ -1434,8 +1434,8 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
                 if constexpr (G > 1) {
 #pragma unroll
                     for (int k = 0; k < W; k++) {
-                        d0[k] = AR::wide_join(d0[k], AR::wide_reduce(w0[k], m), m);
-                        d1[k] = AR::wide_join(d1[k], AR::wide_reduce(w1[k], m), m);
+                        join_part<AR>(d0[k], AR::wide_reduce(w0[k], m), last, m);
+                        join_part<AR>(d1[k], AR::wide_reduce(w1[k], m), last, m);
                         w0[k] = w1[k] = AR::wide_zero();
                     }
                 } else {
@@ -1459,8 +1459,7 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
             }
         }
         if constexpr (G > 1) {
-            // FP64: the digit sum, joined from at most three parts of q/2, times a plaintext is at most 1.07 q
-            ++folds;
+            ++folds;  // FP64: at most 8 products (0.875 q each, join_part) between reductions
 #pragma unroll
             for (int k = 0; k < W; k++)
 #pragma unroll

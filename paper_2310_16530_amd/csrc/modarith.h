@@ -303,6 +303,15 @@ struct FpAr {
     static HD T acc_finish2(T acc, const Mod& m) { return reduce(acc, m); }
 };
 
+// A sum of more products than wide_terms, from its parts: `part` is a wide_reduce result, `last` the final one of the sum.  FpAr parts
+// are at most q/2 each and any number of them may come (128 terms are 22): what the next part joins is folded, so the sum that
+// leaves stays within q and its product with a residue within 0.875 q, eight of which on a folded q/2 are below 2^53.
+template <class AR>
+HD void join_part(typename AR::T& sum, typename AR::T part, bool last, const typename AR::Mod& m) {
+    sum = AR::wide_join(sum, part, m);
+    if (!last) sum = AR::acc_fold(sum, m);
+}
+
 // ------------------------------------------- recombination of a base conversion's digit sums (see conv_mfma_body)
 // s[o + g] = S_g, the sum over sources and source digits of (digit g of the folded constant) * (source digit);
 // |S_g| <= 17 * 2^17, V = sum_g 256^g S_g, |V| <= 2^14 m.

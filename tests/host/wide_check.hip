@@ -1,5 +1,6 @@
-// Host-side check of the unreduced sums of csrc/modarith.h (Wide: FpAr pairs of doubles, IntAr 128 bits) and of the
-// recombination of a base conversion's digit sums (conv_recombine), against 128-bit integer arithmetic.  x86-64 FMA and
+// Host-side check of the unreduced sums of csrc/modarith.h (Wide: FpAr pairs of doubles, IntAr 128 bits), of longer sums joined from
+// them that then meet plaintexts (join_part, acc_mac_wide), and of the recombination of a base conversion's digit sums
+// (conv_recombine), against 128-bit integer arithmetic.  x86-64 FMA and
 // CDNA4 FMA are both IEEE-754 binary64, so exactness shown here is exactness on the GPU.
 // Arguments: moduli.  Prints "OK <count>" or the first failure.
 #include <stdio.h>
@@ -26,8 +27,55 @@ static PrimeConst prime_const(u64 q) {
     u64 x = q;
     for (int i = 0; i < 6; i++) x *= 2 - q * x;
     p.qneg = (u64)0 - x;
-    p.r1 = (u64)(((u128)1 << 64) % q);
+    p.r1 = (u64)(((u128)1 << 64) % q), p.r1_p = (u64)(((u128)p.r1 << 64) / q);
     return p;
+}
+
+// up to 32 rotations, each a sum of 1 .. 128 digit products times a plaintext, as dh_accum_kernel adds them for several giant steps.
+// how = 0: operands at random; else every part of a sum ends at the same value near +q/2 (1, 2: the same for all
+// rotations) or -q/2 (3), the farthest from zero that many parts can take the sum
+template <class AR>
+static bool joined_sums(const PrimeConst& pc, u32 terms, u32 rotations, int how) {
+    const u64 q = pc.q;
+    const typename AR::Mod m = AR::mod(pc);
+    typename AR::T acc = AR::acc_zero();
+    u64 want = 0;
+    const u64 pt0 = rnd() % q;
+    for (u32 r = 0; r < rotations; r++) {
+        typename AR::T sum = AR::acc_zero();
+        typename AR::Wide w = AR::wide_zero();
+        u64 value = 0, part = 0;
+        for (u32 j = 0, in_sum = 0; j < terms; j++) {
+            const bool last = j + 1 == terms, ends = in_sum + 1 == AR::wide_terms || last;
+            u64 x = pick(q, how ? 3 : (int)(rnd() % 4)), y = pick(q, how ? 3 : (int)(rnd() % 4));
+            if (how && ends) {  // 1 * what is missing
+                const u64 goal = how == 3 ? q - (q - 1) / 2 + rnd() % 3 : (q - 1) / 2 - rnd() % 3;
+                x = 1, y = (goal + q - part) % q;
+            }
+            const u64 p = (u64)((u128)x * y % q);
+            value = (value + p) % q, part = (part + p) % q;
+            AR::wide_mac(w, x, y);
+            if (++in_sum == AR::wide_terms || last) {
+                join_part<AR>(sum, AR::wide_reduce(w, m), last, m);
+                w = AR::wide_zero(), in_sum = 0, part = 0;
+            }
+        }
+        if (AR::is_fp && fabs((double)sum) > (double)q + 2) return false;
+        u64 pt = rnd() % q;
+        if (how == 1) pt = pt0;
+        for (int d = 0; how > 1 && d < 64; d++) {  // of 64, the one whose lazily reduced product is the largest
+            const u64 other = rnd() % q;
+            typename AR::T x = AR::acc_zero(), y = AR::acc_zero();
+            AR::acc_mac_wide(x, sum, pt, m);
+            AR::acc_mac_wide(y, sum, other, m);
+            if (y > x) pt = other;
+        }
+        AR::acc_mac_wide(acc, sum, pt, m);
+        want = (want + (u64)((u128)value * pt % q)) % q;
+        if ((r & 7) == 7) acc = AR::acc_fold(acc, m);
+    }
+    // IntAr sums carry 2^-128 through the two reductions, acc_finish2 takes it off
+    return AR::acc_canon(AR::acc_finish2(acc, m), m) == want;
 }
 
 int main(int argc, char** argv) {
@@ -58,6 +106,12 @@ int main(int argc, char** argv) {
             }
             count++;
         }
+        for (u32 terms = 1; terms <= 128; terms++)
+            for (int it = 0; it < 60; it++, count++) {
+                const u32 rotations = it < 40 ? 8 : 1 + (u32)(rnd() % 32);
+                if (!(pc.fp ? joined_sums<FpAr>(pc, terms, rotations, it % 4) : joined_sums<IntAr>(pc, terms, rotations, it % 4))) {
+                    printf("joined sum q=%llu terms=%u rotations=%u kind %d\n", (unsigned long long)q, terms, rotations, it % 4); return 1; }
+            }
         for (int it = 0; it < 20000; it++) {
             // a conversion from 1 .. 17 sources below 2^61
             const int ns = 1 + (int)(rnd() % 17);

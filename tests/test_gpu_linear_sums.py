@@ -90,3 +90,28 @@ def test_baby_step_giant_step_sums(orc, logN, q, p, dnum, level, steps):
             assert np.array_equal(got, want), (a, b, overlap)
             assert any(k.startswith("inv_strided_sum_kernel") for k in names) == (ps.K > 1), names
             assert any(k.startswith("bsgs_mac_kernel") for k in names) == (a > 32 or b > 4), names
+
+
+def test_baby_steps_of_many_digits_leave_room_for_eight_products(orc):
+    """59 digits of one limb just below 3 * 2^48 (ten parts of an unreduced sum), every part near +q/2 on one component and -q/2 on
+    the other: joined without a reduction they reach 5 q, and eight of their products with a plaintext pass 2^53."""
+    L, limit = 59, 3 << 48
+    primes = _below(limit, 2 << 12, L) + _below(1 << 60, 2 << 12, 1)
+    ps = synth.ExplicitParamSet("many_digits", 12, L, primes[:L], primes[L:])
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(5959)
+    ct = np.zeros((2, L, ps.N), dtype=np.uint64)
+    ct[1] = 1  # every digit is the constant 1 on every limb
+    key = synth.uniform_residues(rng, ps.primes, ps.N, lead=(L, 2))
+    for i, q in enumerate(primes[:L]):
+        for first in range(0, L, 6):
+            last = min(first + 6, L) - 1
+            for t, goal in ((0, (q - 1) // 2), (1, (q + 1) // 2)):
+                rest = key[first:last, t, i].sum(axis=0, dtype=np.uint64) % np.uint64(q)
+                key[last, t, i] = (np.uint64(goal) + np.uint64(q) - rest) % np.uint64(q)
+    n1, n2 = 32, 2
+    gs = [synth.galois_element((-1) ** r * (r // 2 + 1), ps.logN) for r in range(n1 + n2)]
+    pt = synth.uniform_residues(rng, ps.primes, ps.N, lead=(n2, n1))
+    d_key = dev(key)
+    got = host(ctx.lintrans_bsgs_at(L, dev(ct), gs[:n1], [d_key] * n1, gs[n1:], [d_key] * n2, dev(pt)))
+    assert np.array_equal(got, orc.lintrans_bsgs_level(ct, gs[:n1], [key] * n1, gs[n1:], [key] * n2, pt, P))
