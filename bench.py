@@ -58,6 +58,9 @@ def load_counter_table(path=None):
 
 
 MEASURED = load_counter_table()
+# the step's two conversion kernels on FP64 limbs (digits of six limbs, six special limbs)
+MODUP_FP_KERNEL = "conv_fwd_strided_kernel<FpAr, 8, 1, 4, false, 3>"
+MODDOWN_FP_KERNEL = "conv_mfma_kernel<8, 2, 2, 2, 3>"
 
 
 def main():
@@ -170,9 +173,9 @@ def main():
     n_fp_q = sum(1 for q in ps.q_primes if q < 3 << 48)
     alg_lane_ops = {
         # ModUp: per ciphertext and coefficient, every digit writes the FP64 q-limbs it does not own
-        "conv_fwd_strided_kernel<FpAr, 8, 1, 4, false>": B * N * dnum * (n_fp_q - ps.L // dnum) * (15 + bfly),
+        MODUP_FP_KERNEL: B * N * dnum * (n_fp_q - ps.L // dnum) * (15 + bfly),
         # ModDown: both components, every FP64 q-limb
-        "conv_mfma_kernel<8, 2, 2, 2>": B * 2 * N * n_fp_q * (15 + bfly),
+        MODDOWN_FP_KERNEL: B * 2 * N * n_fp_q * (15 + bfly),
     }
     for kname_, ops in alg_lane_ops.items():
         if kname_ in kernels:

@@ -40,3 +40,8 @@ def test_kernel_stats_summary_lists_the_same_kernels():
             if m:
                 names.add(m.group(1))
     assert names == set(bench.MEASURED)
+
+
+def test_kernels_with_a_counted_algorithm_are_those_of_the_profile():
+    bench = _bench_module()
+    assert {bench.MODUP_FP_KERNEL, bench.MODDOWN_FP_KERNEL} <= set(bench.MEASURED)
