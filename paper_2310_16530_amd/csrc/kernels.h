@@ -1027,9 +1027,9 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
                                               u32 inst) {
     typedef typename AR::T T;
     const u32 ways = HOISTED ? 1 : a.ways, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // the `ways` wavefronts of a team share four rows
-    const u32 part = wave & (ways - 1), first = ways == 1 ? wave * 4 : ways == 2 ? (wave >> 1) * 4 : 0;  // row of the tile
-    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r0 = tile * (ways == 1 ? 16 : ways == 2 ? 8 : 4) + first, r = r0 + (ch & 3);
+    // the `ways` (1, 2 or 4) wavefronts of a team share four rows; by shifts: chosen by comparisons they cost branches
+    const u32 lg = ways >> 1, part = wave & (ways - 1);
+    const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r0 = (tile * (4 >> lg) + (wave >> lg)) * 4, r = r0 + (ch & 3);
     const u32 L = tb.L, D = tb.D;
     const u32 pi = tb.phys(i), Dkey = tb.Lfull + tb.K;  // keys are laid out over the whole chain
     const PrimeConst pc = tb.pc[pi];
@@ -1131,31 +1131,30 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
             for (int k = 0; k < 16; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
         }
     }
-    if (!HOISTED && ways != 1) {  // wavefront t of a team gets component t of the joined sums
+    if (!HOISTED && ways != 1) {
+        // The wavefronts of a team join their sums, the first two end with a component each: the other two of a team of four add
+        // theirs to those of the first, which then exchange a component with one another as a team of two does.
+        auto put = [&](u32 at, const T (&acc)[16]) __attribute__((always_inline)) {
 #pragma unroll
-        for (u32 t = 0; t < 2; t++) {
+            for (int k = 0; k < 16; k++) lds[at * 1024 + k * 64 + (tid & 63)] = AR::to_raw(acc[k]);
+        };
+        auto join = [&](u32 at, T (&acc)[16]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < 16; k++) acc[k] = AR::wide_join(acc[k], AR::from_raw(lds[at * 1024 + k * 64 + (tid & 63)]), m);
+        };
+#pragma unroll
+        for (int k = 0; k < 16; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
+        __syncthreads();  // the exchanges of the transforms have been read
+        if (ways == 4) {
+            if (wave > 1) put(wave - 2, acc0), put(wave, acc1);
             __syncthreads();
-            if (part != t) {
-#pragma unroll
-                for (int k = 0; k < 16; k++) lds[wave * 1024 + k * 64 + (tid & 63)] = AR::to_raw(AR::acc_fold(t ? acc1[k] : acc0[k], m));
-            }
-            __syncthreads();
-            if (part == t) {
-                if (ways == 4) {
-#pragma unroll
-                    for (int k = 0; k < 16; k++) {
-                        T s = AR::acc_fold(t ? acc1[k] : acc0[k], m);
-#pragma unroll
-                        for (u32 v = 1; v < 4; v++) s = AR::wide_join(s, AR::from_raw(lds[((t + v) & 3) * 1024 + k * 64 + (tid & 63)]), m);
-                        (t ? acc1[k] : acc0[k]) = s;
-                    }
-                } else {
-                    const u64* mate = lds + (wave ^ 1) * 1024 + (tid & 63);
-#pragma unroll
-                    for (int k = 0; k < 16; k++) (t ? acc1[k] : acc0[k]) = AR::wide_join(AR::acc_fold(t ? acc1[k] : acc0[k], m), AR::from_raw(mate[k * 64]), m);
-                }
-            }
+            if (wave < 2) join(wave, acc0), join(wave + 2, acc1);
         }
+        if (part == 0) put(wave, acc1);  // block `wave` has been read by this wavefront alone
+        else if (part == 1) put(wave, acc0);
+        __syncthreads();
+        if (part == 0) join(wave ^ 1, acc0);
+        else if (part == 1) join(wave ^ 1, acc1);
         __syncthreads();
         if (part > 1) return;
     }
