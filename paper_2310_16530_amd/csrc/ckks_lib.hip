@@ -1838,6 +1838,23 @@ extern "C" int ckks_rescale_static(ckks_ctx* ctx, uint32_t level, const uint64_t
     return rescale_impl(ctx, level, d_ct, d_out, batch, ctx->scratch_ptr, CKKS_STATIC_SCRATCH_BYTES, stream, true);
 }
 
+// Hoisted rotate-MAC: the plaintext products of c' summed before the ModDowns' converted parts join them (FIN_SUMMED), which takes the
+// round trip of every rotation's c' away, needs half the ModDown launches, and costs one launch and the joint launch of both
+// arithmetics.  Times of the other form / this one, 17 to 40 rotations unless said:
+//   chains of integer primes (9 + 1 to 20 + 5 limbs, 1 to 9 digits, N = 2^12 .. 2^16) 1.02 to 1.25, half of them integer 1.2 to 1.36
+//   N = 2^16, FP64 limbs: 1.02 to 1.17 for up to 10 digits (20 + 1 limbs, 20 digits 1.06; 30 + 1, 30 1.04); 12, 14, 16 rotations of 9 limbs and
+//   more 1.02 to 1.11, of fewer 0.98 to 1.01; N = 2^15, 12, 24 + 6 434 / 440 us
+//   smaller rings: the accumulation and the special limbs' launch follow one another where the other form has one launch, each as long as
+//   dnum digits take on a few workgroups.  Up to four digits 1.00 to 1.15 (3 + 1 limbs at N = 2^12, four workgroups a rotation:
+//   0.97 to 1.01); more: 0.75 to 1.0 below 16 dnum workgroups a rotation (20 + 1, 20 digits, N = 2^12 0.84; 9 + 1, 9, N = 2^14 0.92;
+//   20 + 2, 10, N = 2^14 0.95), 0.97 to 1.11 above (10 + 2, 5, N = 2^15 1.01; 24 + 4, 6, N = 2^14 1.02; 20 + 2, 10, N = 2^15 1.04)
+static bool hoisted_summed(const View* c, u32 n_rot) {
+    if (n_rot <= CKKS_ROT_CHUNK && !(c->logN == 16 && n_rot >= 12 && c->L >= 9)) return false;
+    u32 integer = 0;
+    for (u32 i = 0; i < c->L; i++) integer += c->primes[i] >= CKKS_FP_PRIME_LIMIT;
+    return 2 * integer >= c->L || c->dnum <= 4 || c->D * tiles_of(c) >= 16 * c->dnum;
+}
+
 extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uint64_t* d_ct, uint32_t n_rot,
                                         const uint32_t* h_galois, const uint64_t* const* h_rk_ptrs, const uint64_t* d_pt,
                                         uint64_t* d_out, void* d_ws, size_t ws_bytes, void* stream) {
@@ -1873,21 +1890,16 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
         decompose_extend(c, w, 1, s, mode);
         launch_extended_fwd_contig(c, w, s);
     };
-    // Many rotations: the plaintext products of c' are summed before the ModDowns' converted parts join them (FIN_SUMMED), which takes
-    // the round trip of every rotation's c' away and costs one launch and the joint launch of both arithmetics.  More rotations
-    // than one launch of the other form takes: always faster (us, N = 2^16, 17 rotations, 24 + 6 limbs 1162 / 1043, level 13 725 /
-    // 674; 20 rotations, 6 + 6 limbs 449 / 411; N = 2^15, level 7, 20 rotations 324 / 312).  Up to 16 rotations, N = 2^16: 12, 24 + 6
-    // 820 / 770, 9 + 3 373 / 362, 6 + 6 265 / 269; 8, 9 + 3 267 / 269; N = 2^15, 12, 24 + 6 434 / 440, level 7 196 / 207.
-    if (n_rot > CKKS_ROT_CHUNK || (c->logN == 16 && n_rot >= 12 && c->L >= 9)) {
-        // Evenly sized chunks of as many rotations as the workspace has room for: x and dt, then the sum on the q-limbs ([2][L])
-        // and, per rotation, the special limbs ([2][K]) and the converted part ([2][L]).
+    if (hoisted_summed(c, n_rot)) {
+        // Equal parts of at most CKKS_ROT_CHUNK rotations, a launch of the special limbs' inner product each, and as many of them to a chunk
+        // as the workspace has room for: x and dt, then the sum on the q-limbs ([2][L]) and, per rotation, the special limbs ([2][K])
+        // and the converted part ([2][L]).  The workspace of CKKS_ROT_CHUNK rotations of the other form holds one part at least.
         Workspace w = carve(c, d_ws, 1, 1, 1);
         u64 *const cq = w.cq, *const cp = cq + (size_t)2 * c->L * N;
         const size_t fit = (need / sizeof(u64) / N - 3 * (size_t)c->L - (size_t)c->dnum * c->D) / (2 * (size_t)c->D);
-        const u32 most = fit < CKKS_DH_CHUNK ? (u32)fit : CKKS_DH_CHUNK, n_chunks = (n_rot + most - 1) / most;
-        const u32 chunk = (n_rot + n_chunks - 1) / n_chunks;
+        const u32 part = cdiv(n_rot, cdiv(n_rot, CKKS_ROT_CHUNK)), chunk = part * (fit < CKKS_DH_CHUNK ? (u32)fit / part : CKKS_DH_CHUNK / part);
         // second stream: the integer special limbs' inner products and inverse transforms beside the sum on the q-limbs
-        const bool fork = sd.enabled && c->mixed_classes && chunk * c->D * tiles_of(c) >= 5 * 512;
+        const bool fork = sd.enabled && c->mixed_classes && (n_rot < chunk ? n_rot : chunk) * c->D * tiles_of(c) >= 5 * 512;
         decompose(w, fork ? EXTEND_FORK : EXTEND_PLAIN);
         for (u32 r0 = 0; r0 < n_rot; r0 += chunk) {
             const u32 nr = (n_rot - r0) < chunk ? (n_rot - r0) : chunk;
@@ -1898,10 +1910,10 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
             da.n_rot = nr, da.split = c->L;
             if (fork) fork_side(c, s);  // no-op in the first chunk (still forked); later chunks wait for the previous ModDown
             launch_dh_accum(c, da, s, c->L);
-            for (u32 f = 0; f < nr; f += CKKS_ROT_CHUNK) {
+            for (u32 f = 0; f < nr; f += part) {
                 InnerArgs ia;
                 memset(&ia, 0, sizeof(ia));
-                ia.n_inst = nr - f < CKKS_ROT_CHUNK ? nr - f : CKKS_ROT_CHUNK;
+                ia.n_inst = nr - f < part ? nr - f : part;
                 for (u32 r = 0; r < ia.n_inst; r++) ia.key[r] = da.key[f + r], ia.galois[r] = da.galois[f + r];
                 ia.dt = w.dt, ia.own = d_ct, ia.cp = cp + (size_t)f * 2 * c->K * N, ia.split = c->L;
                 launch_ks_inner<OWN_COPY, true>(c, ia, s, c->L, c->D);

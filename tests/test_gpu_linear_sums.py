@@ -115,3 +115,43 @@ def test_baby_steps_of_many_digits_leave_room_for_eight_products(orc):
     d_key = dev(key)
     got = host(ctx.lintrans_bsgs_at(L, dev(ct), gs[:n1], [d_key] * n1, gs[n1:], [d_key] * n2, dev(pt)))
     assert np.array_equal(got, orc.lintrans_bsgs_level(ct, gs[:n1], [key] * n1, gs[n1:], [key] * n2, pt, P))
+
+
+@pytest.mark.parametrize("logN,q,p,dnum,counts,summed", [
+    (12, (49,) * 9, (59,), 9, (17, 40), False),            # many digits on few workgroups: one launch of both arithmetics
+    (15, (49,) * 10, (59,) * 2, 5, (17,), True),           # as many as 16 workgroups a digit
+    (12, (49, 55) * 3, (59,), 6, (40,), True),             # half the limbs integer
+    (12, (49,) * 4, (59,), 4, (33, 40, 50), True)])        # parts of 11, 14 and 13 rotations, two to a chunk, the last one shorter
+def test_form_of_a_hoisted_sum_by_digits_and_workgroups(orc, logN, q, p, dnum, counts, summed):
+    ps = synth.mixed_params(logN, list(q), list(p), dnum, "form")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    n = max(counts)
+    gs, keys, ct, pt = _inputs(ps, n, 3, 1800 + logN + dnum, ps.q_primes, (n,))
+    d_ct, d_pt, d_keys = dev(ct), dev(pt), [dev(k) for k in keys]
+    for m in counts:
+        print(logN, dnum, "rotations", m, flush=True)
+        got, names = _kernels(ctx, lambda: ctx.hrot_hoisted_mac(d_ct, gs[:m], [d_keys[r % 3] for r in range(m)], d_pt[:m].contiguous()))
+        assert np.array_equal(got, orc.hrot_hoisted_mac(ct, gs[:m], [keys[r % 3] for r in range(m)], pt[:m], P)), m
+        assert any(k.startswith("ks_final_kernel") and k.endswith(", 4>") for k in names) == summed, names
+
+
+def test_hoisted_sums_on_integer_limbs_with_the_second_stream_at_work(orc):
+    """N = 2^16, FP64 and integer q-limbs, 32 rotations in two chunks: with the second stream on the sum on the integer q-limbs is
+    written there, and once more after the fork of the second chunk."""
+    ps = synth.mixed_params(16, [49, 49, 49, 55, 49, 55, 49, 55], [59, 59], 2, "two_streams")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    n = 32
+    gs, keys, ct, pt = _inputs(ps, n, 3, 3232, ps.q_primes, (n,))
+    d_ct, d_pt, d_keys = dev(ct), dev(pt), [dev(k) for k in keys]
+    call = lambda: ctx.hrot_hoisted_mac(d_ct, gs, [d_keys[r % 3] for r in range(n)], d_pt)
+    want = orc.hrot_hoisted_mac(ct, gs, [keys[r % 3] for r in range(n)], pt, P)
+    got, one = _kernels(ctx, call)
+    assert np.array_equal(got, want) and not any(k.startswith("dh_accum_kernel<IntAr") for k in one), one
+    ctx.set_overlap(True)
+    try:
+        got, two = _kernels(ctx, call)
+        assert np.array_equal(got, want) and any(k.startswith("dh_accum_kernel<IntAr") for k in two), two
+        for _ in range(3):
+            assert np.array_equal(host(call()), want)
+    finally:
+        ctx.set_overlap(False)
