@@ -762,18 +762,20 @@ static bool any_fp_prime(const View* c, u32 lo, u32 hi) {
     return false;
 }
 
+// Words that one launch leaves for the next, `limbs` of them: written and read with ordinary accesses they may stay in the 256 MB
+// Infinity Cache, which nontemporal ones leave empty; below 64 MiB there is no difference (46 MiB 53.6 / 53.6 us), more than it holds only
+// evicts it (322 MiB and more written so: 2 to 10 % slower).  Times without / with, N = 2^16, one call after the other, us.  Rescale, 24 limbs: 3
+// ciphertexts (69 MiB) 77.8 / 76.4, 4 (92) 94.3 / 88.3, 8 (184) 170 / 151, 12 (276, written so, read nontemporal) 253 / 233.  First
+// forward pass of 24 limbs (the transform): 6 instances (72 MiB) 54.9 / 53.8, 16 (192) 136 / 128, 20 (240) 178 / 173; of 24 + 6 limbs: 6 (90)
+// 76 / 78, 12 (180) 137 / 135.  On operands that were written just before, whose lines fill the cache, less: rescales behind the
+// multiplication that they follow 0 to 2 % of both (8 ciphertexts 895 / 884), behind a copy -9 (4) to +6 % (3).  Not the ModDown conversions on
+// the matrix cores, whose launches share the cache with the digits (HMult, batch 8: 699 / 704), nor conversions whose readers read nontemporal.
+static bool stores_cached(const View* c, u64 limbs) { return (limbs * 8 << c->logN) >= (64ull << 20) && (limbs * 8 << c->logN) <= (320ull << 20); }
+static bool loads_cached(const View* c, u64 limbs) { return stores_cached(c, limbs) && (limbs * 8 << c->logN) <= (224ull << 20); }
+
 // A launcher type L provides
 //   template <class AR, int A> static void go(grid, stream, args, tables, run)   the launch
 //   static std::string name(const char* ar, int A)                               the profiler's kernel name
-// Words that one launch leaves for the next, `limbs` of them: written and read with ordinary accesses they may stay in the 256 MB
-// Infinity Cache, which nontemporal ones leave empty; small amounts reach the next launch sooner past the L2 (what is dirty there
-// is written back when the launch ends), and reads of more than the cache holds only evict it.  Rescale, N = 2^16, 24 limbs,
-// inputs cold, both / none, us: 8 ciphertexts (184 MiB) 153 / 174, 4 (92) 92 / 99, 1 (23) 41 / 37; 12 (276 MiB) written so, read
-// nontemporal 244 / 260.  Not the ModDown conversions on the matrix cores, whose launches share the cache with the digits (HMult,
-// batch 8: 699 / 704).  First forward pass of 16 x 24 limbs (192 MiB): the transform 160.6 / 162.7, of 4 (48 MiB) no difference.
-static bool stores_cached(const View* c, u64 limbs) { return (limbs * 8 << c->logN) >= (48ull << 20); }
-static bool loads_cached(const View* c, u64 limbs) { return stores_cached(c, limbs) && (limbs * 8 << c->logN) <= (224ull << 20); }
-
 template <class L, class ArgT>
 static void dispatch_kernel(const View* c, bool fp, dim3 grid, hipStream_t s, const ArgT& a, LimbRun run) {
 #define CKKS_CASE_A(AV)                                               \
@@ -871,6 +873,26 @@ struct FwdStridedL {
     }
     static std::string name(const char* ar, int A) { return kname("fwd_strided_kernel", ar, A, ""); }
 };
+struct FwdStridedCachedL {
+    static constexpr bool any = true;
+    template <class AR, int A>
+    static void go(dim3 g, hipStream_t s, const FwdStridedArgs& a, const Tables& tb, LimbRun run) {
+        if constexpr (!inv_one_kernel(A)) hipLaunchKernelGGL((fwd_strided_cached_kernel<AR, A>), g, dim3(256), 0, s, a, tb, run);
+        else FwdStridedL::go<AR, A>(g, s, a, tb, run);  // two passes for a few limbs only: not reached
+    }
+    static std::string name(const char* ar, int A) { return kname("fwd_strided_cached_kernel", ar, A, ""); }
+};
+// ModDown from a single source with ordinary stores (enough targets for four FpAr ones per workgroup)
+struct ConvOneCachedL {
+    static constexpr bool packed = false;
+    template <class AR>
+    static constexpr int per_block() { return AR::is_fp ? 4 : 1; }
+    template <class AR, int A>
+    static void go(dim3 g, hipStream_t s, const ConvArgs& a, const Tables& tb, LimbRun run) {
+        hipLaunchKernelGGL((conv_one_cached_kernel<AR, A, per_block<AR>()>), g, dim3(256), 0, s, a, tb, run);
+    }
+    static std::string name(const char* ar, int A) { return kname("conv_one_cached_kernel", ar, A, ar[0] == 'F' ? ", 4" : ", 1"); }
+};
 // Conversions: KS products per coefficient group on the matrix cores, or (KS = 0) a single source and TB targets per
 // workgroup (one for IntAr).  KS > 0 and TB = 1: ModDown with two FpAr targets per workgroup instead of four
 template <int DIR, int KS, int TB = 0, int... NW>
@@ -929,6 +951,14 @@ struct KsFinalL {
         return kname("ks_final_kernel", ar, A, (std::string(", ") + std::to_string(MODE)).c_str());
     }
 };
+struct KsFinalCachedL {
+    static constexpr bool any = false;
+    template <class AR, int A>
+    static void go(dim3 g, hipStream_t s, const FinalArgs& a, const Tables& tb, LimbRun run) {
+        hipLaunchKernelGGL((ks_final_cached_kernel<AR, A>), g, dim3(256), 0, s, a, tb, run);
+    }
+    static std::string name(const char* ar, int A) { return kname("ks_final_cached_kernel", ar, A, ""); }
+};
 
 template <int LOAD>
 static void launch_inv_contig(const View* c, const InvContigArgs& a, hipStream_t s) {
@@ -971,11 +1001,12 @@ static void launch_inverse(const View* c, InvContigArgs a, u32 scale, u32 out_fm
     launch_inv_strided(c, a2, s);
 }
 
-static void launch_fwd_strided(const View* c, const FwdStridedArgs& a, hipStream_t s) {
+static void launch_fwd_strided(const View* c, const FwdStridedArgs& a, hipStream_t s, bool cached) {
     const u32 pb = a.sel.prime_base;
     const u64 per = (u64)a.sel.n_inst * 2;
-    launch_runs<FwdStridedL>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s,
-                             [per](u32, u32 n) { return per * n; });
+    const auto alg = [per](u32, u32 n) { return per * n; };
+    if (cached) launch_runs<FwdStridedCachedL>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s, alg);
+    else launch_runs<FwdStridedL>(c, pb, pb + a.sel.n_l, pb, tiles_of(c), a.sel.n_inst, a, s, alg);
 }
 
 // largest number of targets of the run over the digits, and their sum: a digit's own limbs are none of its targets
@@ -1115,8 +1146,8 @@ static void launch_fwd_contig(const View* c, const FwdContigArgs& a, hipStream_t
 static void launch_forward(const View* c, u64* d_x, const LimbSel& sel, hipStream_t s) {
     const FwdContigArgs a2 = {d_x, sel, 0, 0};
     if (!inv_one_kernel((int)c->logN - 8) || spread_limbs(c, sel, 80)) {
-        const FwdStridedArgs a1 = {d_x, d_x, sel, stores_cached(c, (u64)sel.n_l * sel.n_inst)};
-        launch_fwd_strided(c, a1, s);
+        const FwdStridedArgs a1 = {d_x, d_x, sel};
+        launch_fwd_strided(c, a1, s, stores_cached(c, (u64)sel.n_l * sel.n_inst));
         launch_fwd_contig(c, a2, s);
         return;
     }
@@ -1250,13 +1281,13 @@ static void launch_dh_accum(const View* c, const DhInnerArgs& a, hipStream_t s, 
     for (const ClassRun& r : class_runs(c, 0, hi)) launch_dh_accum_run(c, a, r.first, r.count, !r.fp, r.fp ? s : c->sh->side.stream);
 }
 
-template <int MODE>
+template <int MODE, bool CACHED = false>
 static void launch_ks_final(const View* c, const FinalArgs& a, hipStream_t s) {
     u64 per;  // algorithmic limbs per q-limb
     if (MODE == FIN_HOISTED) per = (u64)a.n_rot * (2 + 2 + 1 + 1) + (2 + (a.accumulate ? 2 : 0));
     else if (MODE == FIN_SUMMED) per = (u64)a.n_rot * (2 + 1) + (2 + 2 + (a.accumulate ? 2 : 0));
     else per = (u64)a.n_inst * 3;
-    launch_runs<KsFinalL<MODE>>(c, 0, c->L, 0, tiles_of(c), a.n_inst, a, s, [per](u32, u32 n) { return per * n; });
+    launch_runs<typename std::conditional<CACHED, KsFinalCachedL, KsFinalL<MODE>>::type>(c, 0, c->L, 0, tiles_of(c), a.n_inst, a, s, [per](u32, u32 n) { return per * n; });
 }
 
 template <int AL>
@@ -1571,7 +1602,7 @@ static void launch_decompose_inverse(const View* c, const InvContigArgs& a, hipS
 // integer limbs take the side stream from here on.
 enum ExtendMode { EXTEND_PLAIN, EXTEND_BESIDE, EXTEND_FORK };
 static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, ExtendMode mode) {
-    const ConvArgs a3 = {w.x, w.dt, groups, 0, 0, nullptr, nullptr, 0};
+    const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0};
     SideStream& sd = c->sh->side;
     const bool second = mode != EXTEND_PLAIN && sd.enabled && c->mixed_classes;
     if (conv_up_both(c, a3, s, !second ? 4095 : mode == EXTEND_BESIDE ? 1024 : 512)) {  // before a fork: what follows on either stream comes after it
@@ -1611,15 +1642,16 @@ static void join_fp_beside(const View* c, hipStream_t s) {
 }
 
 // ModDown side: w.cp holds c' on the special limbs after the first inverse pass (done = false) or as coefficients times the
-// conversion pre-factor.
-static void moddown_convert(const View* c, const Workspace& w, u32 cg, hipStream_t s, bool done = false) {
+// conversion pre-factor.  cached: the converted part, from a single source, is stored with ordinary accesses (stores_cached).
+static void moddown_convert(const View* c, const Workspace& w, u32 cg, hipStream_t s, bool done = false, bool cached = false) {
     if (!done) {
         const InvStridedArgs a6 = {w.cp, LimbSel{c->K, cg * 2, c->K, 0, c->L}, SC_DN, conv_src_fmt(c->dn, CONV_DN)};
         launch_inv_strided(c, a6, s);
     }
     join_side(c, s);  // the conversion reads every special limb
-    const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, c->dn.ks == 0 && stores_cached(c, (u64)cg * 2 * c->L), nullptr, nullptr, 0};
-    launch_conv<CONV_DN>(c, a7, s);
+    const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, nullptr, nullptr, 0};
+    if (cached) launch_conv_runs<ConvOneCachedL, CONV_DN>(c, a7, s, -1);
+    else launch_conv<CONV_DN>(c, a7, s);
 }
 
 // second forward pass of every extended digit of one decomposition
@@ -1813,11 +1845,12 @@ static int rescale_impl(ckks_ctx* ctx, uint32_t level, const uint64_t* d_ct, uin
     const LimbSel dst = {1, batch * 2, 1, 0, level - 1};
     InvContigArgs a1 = {d_ct, nullptr, w.cp, src, dst, {1}, 0};
     launch_inverse<INV_PLAIN>(c, a1, SC_DN, conv_src_fmt(c->dn, CONV_DN), s);
-    moddown_convert(c, w, batch, s, true);
+    moddown_convert(c, w, batch, s, true, stores_cached(c, (u64)batch * 2 * c->L));
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
-    fa.cq = d_ct, fa.cq_L = level, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 2 * batch, fa.cached = loads_cached(c, (u64)batch * 2 * c->L);
-    launch_ks_final<FIN_KS>(c, fa, s);
+    fa.cq = d_ct, fa.cq_L = level, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 2 * batch;
+    if (loads_cached(c, (u64)batch * 2 * c->L)) launch_ks_final<FIN_KS, true>(c, fa, s);
+    else launch_ks_final<FIN_KS>(c, fa, s);
     return hip_check(c, "ckks_rescale");
 }
 

@@ -417,13 +417,12 @@ struct FwdStridedArgs {
     const u64* src;  // canonical coefficients addressed by sel
     u64* dst;        // raw forward-lazy words, same addressing (in place when dst == src)
     LimbSel sel;
-    u32 cached;      // ordinary stores (stores_cached)
 };
 
-// stages + store; x in layout SA
-template <class AR, int A>
+// stages + store; x in layout SA.  CACHED: ordinary stores (stores_cached), in kernels of their own (see ks_final_cached_kernel)
+template <class AR, int A, bool CACHED>
 __device__ __forceinline__ void fwd_strided_finish(typename AR::T (&x)[16], const Tables& tb, u64* lds, u32 vi,
-                                                   u64* dst, u32 tile, bool cached) {
+                                                   u64* dst, u32 tile) {
     typedef NttCore<AR, A> C;
     const u32 N = 1u << tb.logN, pi = tb.phys(vi);
     const u32 tid = threadIdx.x;
@@ -434,13 +433,10 @@ __device__ __forceinline__ void fwd_strided_finish(typename AR::T (&x)[16], cons
     C::fwd_strided(x, lds, tid, ti, tf, N, m);
     if constexpr (A > 4) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = AR::round_reduce(x[k], m);
-        if (cached) {
-#pragma unroll
-            for (int k = 0; k < 16; k++) dst[(size_t)(r0 * 16 + k) * 256 + col] = AR::to_raw(x[k]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 16; k++) __builtin_nontemporal_store(AR::to_raw(x[k]), &dst[(size_t)(r0 * 16 + k) * 256 + col]);
+        for (int k = 0; k < 16; k++) {
+            u64* const o = &dst[(size_t)(r0 * 16 + k) * 256 + col];
+            if constexpr (CACHED) *o = AR::to_raw(AR::round_reduce(x[k], m));
+            else __builtin_nontemporal_store(AR::to_raw(AR::round_reduce(x[k], m)), o);
         }
     } else {
 #pragma unroll
@@ -449,7 +445,7 @@ __device__ __forceinline__ void fwd_strided_finish(typename AR::T (&x)[16], cons
     }
 }
 
-template <class AR, int A>
+template <class AR, int A, bool CACHED>
 __device__ __forceinline__ void fwd_strided_body(const FwdStridedArgs& a, const Tables& tb, u64* lds, u32 l, u32 tile, u32 inst) {
     typedef NttCore<AR, A> C;
     const u32 N = 1u << tb.logN, tid = threadIdx.x, pi = a.sel.prime_base + l;
@@ -459,16 +455,25 @@ __device__ __forceinline__ void fwd_strided_body(const FwdStridedArgs& a, const 
     typename AR::T x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = AR::from_canon(a.src[off + (size_t)(k * C::RB + r0) * 256 + col], m);
-    fwd_strided_finish<AR, A>(x, tb, lds, pi, a.dst + off, tile, a.cached);
+    fwd_strided_finish<AR, A, CACHED>(x, tb, lds, pi, a.dst + off, tile);
 }
-template <class AR, int A>
-__global__ __launch_bounds__(256) void fwd_strided_kernel(FwdStridedArgs a, Tables tb, LimbRun run) {
-    __shared__ u64 lds[4096];
+template <class AR, int A, bool CACHED>
+__device__ __forceinline__ void fwd_strided_workgroup(const FwdStridedArgs& a, const Tables& tb, const LimbRun run, u64* lds) {
     constexpr u32 TILES = (1u << A) / 16;
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.sel.n_inst, run.count * TILES, group, inst)) return;
     const u32 l = run.first + group / TILES;
-    CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (fwd_strided_body<AR_, A>(a, tb, lds, l, group % TILES, inst)))
+    CKKS_BY_ARITHMETIC(AR, a.sel.prime_base + l, (fwd_strided_body<AR_, A, CACHED>(a, tb, lds, l, group % TILES, inst)))
+}
+template <class AR, int A>
+__global__ __launch_bounds__(256) void fwd_strided_kernel(FwdStridedArgs a, Tables tb, LimbRun run) {
+    __shared__ u64 lds[4096];
+    fwd_strided_workgroup<AR, A, false>(a, tb, run, lds);
+}
+template <class AR, int A>
+__global__ __launch_bounds__(256) void fwd_strided_cached_kernel(FwdStridedArgs a, Tables tb, LimbRun run) {
+    __shared__ u64 lds[4096];
+    fwd_strided_workgroup<AR, A, true>(a, tb, run, lds);
 }
 
 // ============================== base conversion fused into the first forward pass of its targets
@@ -482,7 +487,6 @@ struct ConvArgs {
     u64* dst;             // raw forward-lazy words after the first pass: CONV_UP dt [b][dnum][D][N], CONV_DN cv [g][L][N]
     u32 groups_outer;     // CONV_UP: batch; CONV_DN: number of g
     u32 blocks;           // workgroups per (group, tile): the run's targets in blocks
-    u32 cached;           // CONV_DN from a single source: ordinary stores (stores_cached)
     // matrix cores: constant operands [digit][prime of the chain][KS][2 lane halves][8 digit rows][2 words], and the same
     // of a shorter last digit, [limb of the level]; digits from n_full on use the latter
     const u64* aop;
@@ -551,7 +555,8 @@ __device__ __forceinline__ void strided_stages_hi(typename AR::T (&x)[16], const
 // A workgroup keeps the words of one load and reduces them to TB targets in turn: 4 FP64 targets share a load where the
 // launch fills the chip (rescale of 8 ciphertexts at N = 2^16, 23 limbs: 63 -> 53 us against three targets converted before
 // the first is transformed), 1 where it does not and the time is that of one workgroup; integer targets always 1 (launch_conv).
-template <class AR, int A, int DIR, int TB>
+// CACHED: see fwd_strided_finish.
+template <class AR, int A, int DIR, int TB, bool CACHED = false>
 __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& tb, const LimbRun run) {
     typedef NttCore<AR, A> C;
     typedef StridedTw<AR, A> TW;
@@ -636,13 +641,9 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
             for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lds[(r0 * 16 + k) * C::TC + c]);
             strided_stages_hi<AR, A>(x, tw, r0, m);
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = AR::round_reduce(x[k], m);
-            if (DIR == CONV_DN && a.cached) {
-#pragma unroll
-                for (int k = 0; k < 16; k++) dst.st(AR::to_raw(x[k]), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 16; k++) dst.st_nt(AR::to_raw(x[k]), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
+            for (int k = 0; k < 16; k++) {
+                if constexpr (CACHED) dst.st(AR::to_raw(AR::round_reduce(x[k], m)), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
+                else dst.st_nt(AR::to_raw(AR::round_reduce(x[k], m)), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
             }
         } else {
             u64* dst = dst0 + (size_t)vi * N;
@@ -844,6 +845,11 @@ void conv_fwd_strided_kernel(ConvArgs a, Tables tb, LimbRun run) {
     if constexpr (ONE) conv_one_body<AR, A, DIR, P>(a, tb, run);
     else conv_mfma_workgroup<AR, A, P - conv_mfma_ntt<AR>(), DIR, conv_mfma_ntt<AR>(), conv_words(P - conv_mfma_ntt<AR>(), NW...)>(a, tb, run);
 }
+// ModDown from a single source with ordinary stores
+template <class AR, int A, int P>
+__global__ __launch_bounds__(256, AR::is_fp ? 4 : 3) void conv_one_cached_kernel(ConvArgs a, Tables tb, LimbRun run) {
+    conv_one_body<AR, A, CONV_DN, P, true>(a, tb, run);
+}
 // ModDown onto FpAr targets, KS products per coefficient group, NTT targets per lane: a name of its own, so that profiles tell
 // it from ModUp
 template <int A, int KS, int DIR, int NTT, int... NW>
@@ -893,7 +899,7 @@ __device__ __forceinline__ void fwd_contig_body(const FwdContigArgs& a, const Ta
     T x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = AR::from_raw(p[k * 16 + e0]);
-    NttCore<AR, A>::template fwd_contig<true>(x, lrow, e0, r, ti, tf, N, m);
+    NttCore<AR, A>::template fwd_contig<!AR::is_fp>(x, lrow, e0, r, ti, tf, N, m);
     row_sync();
 #pragma unroll
     for (int k = 0; k < 16; k++) lrow[pad16(e0 * 16 + k)] = AR::canon_fwd(x[k], m);
@@ -1624,11 +1630,11 @@ struct FinalArgs {
     u32 n_inst;      // KS: 2 * batch; HOISTED, SUMMED: 2, the component t
     u32 n_rot;       // HOISTED, SUMMED
     u32 accumulate;  // HOISTED, SUMMED: add to what out already holds
-    u32 cached;      // KS: ordinary loads of cv (loads_cached)
     u32 cq_L;        // limbs per component of cq (L, or L + 1 when cq is a ciphertext about to lose its last limb)
 };
 
-template <class AR, int A, int MODE>
+// CACHED (KS): ordinary loads of cv (loads_cached)
+template <class AR, int A, int MODE, bool CACHED = false>
 __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& tb, u64* lds, u32 i, u32 tile, u32 inst) {
     typedef typename AR::T T;
     const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, ch = tid / 16, r = tile * 16 + ch;
@@ -1769,12 +1775,10 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
     }
     T v[16];
     const u64* p = a.cv + ((size_t)inst * L + i) * N + row_off;
-    if (a.cached) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = AR::from_raw(p[k * 16 + e0]);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
+    for (int k = 0; k < 16; k++) {
+        if constexpr (CACHED) v[k] = AR::from_raw(p[k * 16 + e0]);
+        else v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
     }
     NttCore<AR, A>::template fwd_contig<true>(v, lrow, e0, r, ti, tf, N, m);
     exchange_cb_to_cp<AR>(v, lrow, e0);
@@ -1799,6 +1803,17 @@ __global__ __launch_bounds__(256, MODE >= FIN_HOISTED ? (AR::is_fp ? 3 : 2) : 4)
     u32 group, inst;
     if (!xcd_decode(blockIdx.x, a.n_inst, run.count * TILES, group, inst)) return;
     ks_final_body<AR, A, MODE>(a, tb, lds, run.first + group / TILES, group % TILES, inst);
+}
+// MODE 0 with ordinary loads of the converted part.  A kernel of its own: of two loads behind a condition, one of them nontemporal, the compiler
+// makes a single ordinary one, and the conversion of the next call writes more slowly over lines that such loads have left in the
+// caches (rescale of ten ciphertexts, 13 limbs, N = 2^14: conversion 10.9 -> 14.0 us)
+template <class AR, int A>
+__global__ __launch_bounds__(256, 4) void ks_final_cached_kernel(FinalArgs a, Tables tb, LimbRun run) {
+    __shared__ u64 lds[NTT_LDS_WORDS];
+    constexpr u32 TILES = (1u << A) / 16;
+    u32 group, inst;
+    if (!xcd_decode(blockIdx.x, a.n_inst, run.count * TILES, group, inst)) return;
+    ks_final_body<AR, A, FIN_KS, true>(a, tb, lds, run.first + group / TILES, group % TILES, inst);
 }
 
 // ================================================== stand-alone coefficient-form base conversions

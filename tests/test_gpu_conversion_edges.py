@@ -124,3 +124,42 @@ def test_source_words_and_joint_conversions(orc, logN, L, K, dnum, batch, order)
         assert np.array_equal(got[-1], want[1]) and all(np.array_equal(x, want[0]) for x in got[:-1])
         joint = any(k.startswith("conv_up_both_kernel") for k in names)
         assert joint == (order == "fp first" and logN >= 14 and not (overlap and batch == 30)), names
+
+
+@pytest.mark.parametrize("batch", [23, 24, 82, 117])
+def test_converted_part_through_the_cache_by_its_size(orc, batch):
+    """Rescale of 12 limbs at N = 2^14, both arithmetics: the converted part is stored with ordinary accesses from 64 to 320 MiB and read
+    so up to 224 MiB; 63, 66, 226 and 322 MiB."""
+    ps = synth.mixed_params(14, [49, 55, 49] * 4, [59], 12, "cached")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(64 + batch)
+    ct = _extreme(rng, ps.q_primes, ps.N, (3, 2))
+    which = np.arange(batch) % 3
+    d_ct, want = dev(ct)[dev(which)].contiguous(), dev(orc.rescale(ct, P))
+    print("batch", batch, flush=True)
+    ctx.profile_enable(True)
+    try:
+        got, names = ctx.rescale(ps.L, d_ct), set(ctx.profile_read())
+    finally:
+        ctx.profile_enable(False)
+    assert bool((got == want[dev(which)]).all())
+    assert any(n.startswith("conv_one_cached_kernel") for n in names) == (24 <= batch <= 82), names
+    assert any(n.startswith("ks_final_cached_kernel") for n in names) == (batch == 24), names
+
+
+@pytest.mark.parametrize("first,n,batch,ar", [(0, 8, 63, "FpAr"), (0, 8, 64, "FpAr"), (8, 4, 128, "IntAr"), (3, 9, 57, "AnyAr"), (3, 9, 56, "AnyAr")])
+def test_transform_through_the_cache_by_its_size(orc, first, n, batch, ar):
+    """The first forward pass stores with ordinary accesses from 64 MiB on: N = 2^14, ranges of either arithmetic and of both."""
+    ps = synth.mixed_params(14, [49] * 8 + [55] * 4, [59], 12, "cached")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    x = _extreme(np.random.default_rng(64 + n), ps.primes[first:first + n], ps.N, (3,))
+    which = np.arange(batch) % 3
+    d_x, want = dev(x)[dev(which)].contiguous(), dev(orc.ntt_batch(x, P, first))
+    print(ar, "batch", batch, flush=True)
+    ctx.profile_enable(True)
+    try:
+        got, names = ctx.ntt(d_x, first), set(ctx.profile_read())
+    finally:
+        ctx.profile_enable(False)
+    assert bool((got == want[dev(which)]).all())
+    assert ("fwd_strided_cached_kernel<%s, 6>" % ar in names) == (n * batch >= 512), names
