@@ -1660,15 +1660,26 @@ static void launch_extended_fwd_contig(const View* c, const Workspace& w, hipStr
     launch_fwd_contig(c, a, s);
 }
 
-// cm: the view whose ModDown ends the pipeline: c itself, or the merged view of c's level (the ModDown then
-// also divides by the last q-limb: limb c->L - 1 joins the special limbs and the output has c->L - 1 limbs)
-// multi_galois / multi_keys (rotations only, batch <= CKKS_ROT_CHUNK): one Galois element and key per instance.
 // most rotations whose special parts may be added as integers: the eight digits of a conversion's source word hold the sum
 static u32 summed_rotations_max(const View* c) {
     u64 most = 0;
     for (u32 i = c->L; i < c->D; i++) most = c->primes[i] > most ? c->primes[i] : most;
     const u64 fit = CKKS_DIGIT_MAX / most;
     return fit < CKKS_ROT_CHUNK ? (u32)fit : CKKS_ROT_CHUNK;
+}
+
+// Giant rotations with one ModDown (summed_rotations) instead of as a batch: conversions, inverse pass, q-limb product and sum of 8 x 4 at
+// N = 2^16, 24 + 6 limbs 300 -> 241 us.  But a workgroup of the q-limb product then runs over the digits of all of them, and what does not
+// fit one sum (3 rotations near 2^61, 7 just above 2^60, 15 at 2^59) starts over.  Batch / sum, whole transforms of 2 to 21 giant steps, by
+// the workgroups of the smallest q-limb launch, N = 2^12 .. 2^16: up to 64 0.60 to 1.01 (runs of one limb, the arithmetics alternating, 0.42 to 0.92), 72 and
+// 80 0.97 to 1.05, 96 and more 0.98 to 1.20, one giant step 0.94 to 1.0; where the sums are more than the launches of a batch: 96 0.89 to 0.99, 144 and
+// 160 0.92 to 1.0, 192 0.97 to 1.05, 256 and more 1.0 to 1.12, but three a sum 0.78 to 1.02 up to 560
+static bool giants_summed(const View* c, u32 n) {
+    if (n < 2 || !c->dn.ks) return false;  // one special prime is reduced directly: there are no digits to add
+    const u32 at_once = summed_rotations_max(c);
+    u32 least = ~0u;
+    for (const ClassRun& r : class_runs(c, 0, c->L)) least = r.count * tiles_of(c) < least ? r.count * tiles_of(c) : least;
+    return cdiv(n, at_once) == cdiv(n, CKKS_ROT_CHUNK) ? least >= 96 : least >= 192 && at_once >= 6;
 }
 
 // out = the sum of n (at most CKKS_ROT_CHUNK) rotated ciphertexts, each with its own element and key
@@ -1694,6 +1705,9 @@ static void summed_rotations(const View* c, const u64* in, u32 n, const u32* gal
     launch_ks_inner<OWN_ROT_SUM, false, true>(c, ia, s, 0, c->L);
 }
 
+// cm: the view whose ModDown ends the pipeline: c itself, or the merged view of c's level (the ModDown then
+// also divides by the last q-limb: limb c->L - 1 joins the special limbs and the output has c->L - 1 limbs)
+// multi_galois / multi_keys (rotations only, batch <= CKKS_ROT_CHUNK): one Galois element and key per instance.
 template <int LOAD, int OWN>
 static void keyswitch_pipeline(const View* c, const View* cm, const u64* in1, const u64* in2, const u64* key, u64* out,
                                u32 batch, u32 galois, void* ws, hipStream_t s, const u32* multi_galois = nullptr,
@@ -2193,20 +2207,20 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
     memset(&fa, 0, sizeof(fa));
     fa.cq = w.cq, fa.cq_L = c->L, fa.cv = w.cv, fa.out = inner, fa.n_inst = 2 * n2;
     launch_ks_final<FIN_KS>(c, fa, s);
-    // Giant rotations, each inner sum with its own key, and their sum.  Their ModDowns are one (summed_rotations; 8 x 4 at N = 2^16,
-    // 24 + 6 limbs: conversions, inverse pass, q-limb product and
-    // sum 300 -> 241 us, the call 1080 -> 1008; 8 x 8 1783 -> 1627) for as many at a time as the digits of its sources allow; with
-    // one special prime there are no digits and every rotation ends by itself.
-    const u32 at_once = c->dn.ks ? summed_rotations_max(c) : CKKS_ROT_CHUNK, n_chunks = (n2 + at_once - 1) / at_once;
-    const u32 chunk = (n2 + n_chunks - 1) / n_chunks, n_sums = c->dn.ks ? n_chunks : n2;
+    // Giant rotations, each inner sum with its own key, and their sum: with one ModDown for as many at a time as the digits of its
+    // sources allow where that is the faster way, else as a batch
+    const bool summed = giants_summed(c, n2);
+    const u32 n_chunks = cdiv(n2, summed ? summed_rotations_max(c) : CKKS_ROT_CHUNK);
+    const u32 chunk = summed ? cdiv(n2, n_chunks) : CKKS_ROT_CHUNK;  // a batch: full launches first (20 rotations as 10 + 10 4 % slower)
+    const u32 n_sums = summed ? n_chunks : n2;
     for (u32 g0 = 0, k = 0; g0 < n2; g0 += chunk, k++) {
         const u32 ng = (n2 - g0) < chunk ? (n2 - g0) : chunk;
         const u64* in = inner + (size_t)g0 * 2 * LN;
-        if (c->dn.ks) summed_rotations(c, in, ng, h_giant_galois + g0, h_giant_rk_ptrs + g0, n_sums == 1 ? d_out : rot + (size_t)k * 2 * LN, ks_ws, s);
-        else keyswitch_pipeline<INV_ROT, OWN_ROT>(c, c, in, nullptr, nullptr, rot + (size_t)g0 * 2 * LN, ng, 1, ks_ws, s, h_giant_galois + g0,
-                                                  h_giant_rk_ptrs + g0);
+        u64* to = n_sums == 1 ? d_out : rot + (size_t)(summed ? k : g0) * 2 * LN;
+        if (summed && ng > 1) summed_rotations(c, in, ng, h_giant_galois + g0, h_giant_rk_ptrs + g0, to, ks_ws, s);
+        else keyswitch_pipeline<INV_ROT, OWN_ROT>(c, c, in, nullptr, nullptr, to, ng, 1, ks_ws, s, h_giant_galois + g0, h_giant_rk_ptrs + g0);
     }
-    if (!c->dn.ks || n_sums > 1) {
+    if (n_sums > 1) {
         ProfScope ps(c, std::string("sum_instances_kernel"), (u64)(n_sums + 1) * 2 * c->L, s);
         hipLaunchKernelGGL(sum_instances_kernel, dim3((1u << c->logN) / 256, 2 * c->L), dim3(256), 0, s, rot, d_out,
                            c->tb.pc, c->logN, c->L, 2 * c->L, n_sums);

@@ -55,6 +55,19 @@ def test_hoisted_sums_before_the_mod_down(orc, logN, q, p, dnum, counts):
             assert any(k.startswith("ks_final_kernel") and k.endswith(", 4>") for k in names) == summed, names
 
 
+def _one_mod_down(ps, level, n):
+    """Whether n giant rotations share a ModDown: enough workgroups in the q-limb product's smallest launch, a run of limbs of one
+    arithmetic, and sums that hold as many rotations as a batch does or nearly so."""
+    if n < 2 or ps.K < 2:
+        return False
+    fp = [q < 3 << 48 for q in ps.primes[:level]]
+    runs = [1]
+    for a, b in zip(fp, fp[1:]):
+        runs[-1:] = [runs[-1] + 1] if a == b else [runs[-1], 1]
+    least, a_sum = min(runs) * (ps.N >> 12), min(16, 0x7f7f7f7f7f7f7f7f // max(ps.primes[ps.L:]))
+    return least >= 96 if -(-n // a_sum) == -(-n // 16) else least >= 192 and a_sum >= 6
+
+
 @pytest.mark.parametrize("logN,q,p,dnum,level,steps", [
     (12, (49,) * 6, (59, 59), 3, 6, ((1, 1), (3, 2), (2, 3), (5, 4), (2, 5), (3, 16), (33, 2))),
     (12, (49, 60, 50, 58, 49), (48, 60), 3, 4, ((2, 1), (3, 4), (2, 6))),   # both arithmetics, a partial last digit
@@ -62,6 +75,14 @@ def test_hoisted_sums_before_the_mod_down(orc, logN, q, p, dnum, counts):
     (12, None, 2, 2, 6, ((2, 3), (2, 4), (3, 7))),                          # primes just below 2^61: three sums fit the digits
     (14, (49,) * 16, (59,) * 2, 8, 15, ((2, 2), (1, 4))),                   # more digits than one unreduced sum takes
     (16, (49,) * 8, (59,) * 4, 2, 8, ((8, 4), (3, 3))),
+    (12, (49,) * 96, (59,) * 12, 12, 96, ((2, 3), (1, 5))),                 # as few workgroups as the joint ModDown takes
+    (13, (49,) * 50, (59,) * 8, 7, 48, ((2, 2),)),
+    (14, (49,) * 24, (49,) * 6, 4, 23, ((2, 3),)),                          # one workgroup less
+    (15, (49,) * 12 + (55,) * 12, (48, 60, 59), 8, 24, ((2, 4),)),          # 96 of either arithmetic, special limbs of both
+    (14, (49,) * 23 + (55,), (59, 60, 59), 8, 24, ((2, 3),)),               # a short run of integer limbs
+    (16, (60,) * 12, (60,) * 2, 6, 12, ((1, 7), (1, 8))),                   # seven a sum: one sum, two sums of four
+    (16, (60,) * 11, (60,) * 2, 6, 11, ((1, 8),)),                          # ... on fewer workgroups
+    (16, None, 2, 2, 6, ((1, 3), (1, 4))),                                  # three a sum
 ])
 def test_baby_step_giant_step_sums(orc, logN, q, p, dnum, level, steps):
     if q is None:
@@ -88,7 +109,7 @@ def test_baby_step_giant_step_sums(orc, logN, q, p, dnum, level, steps):
             finally:
                 ctx.set_overlap(False)
             assert np.array_equal(got, want), (a, b, overlap)
-            assert any(k.startswith("inv_strided_sum_kernel") for k in names) == (ps.K > 1), names
+            assert any(k.startswith("inv_strided_sum_kernel") for k in names) == _one_mod_down(ps, level, b), names
             assert any(k.startswith("bsgs_mac_kernel") for k in names) == (a > 32 or b > 4), names
 
 
