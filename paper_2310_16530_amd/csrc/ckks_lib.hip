@@ -2173,8 +2173,12 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         launch_extended_fwd_contig(c, w, s);
     }
     // Baby steps and combinations in one kernel where its registers hold the sums (8 x 4, N = 2^16, 24 + 6 limbs: 468 -> 390 us; 8 x 3
-    // the call 1032 -> 880)
-    if (n2 <= CKKS_DH_SUMS && n1 <= CKKS_DH_CHUNK) {
+    // the call 1032 -> 880).  On chains of integer primes alone four sums spill and pay only while all rows of 128 words are in flight at
+    // once (apart / in one, 12 + 4 limbs, 4 x 4 and 16 x 4: N = 2^12 (512 rows) 1.01 and 1.07, 2^13 0.99 and 1.01, 2^14 to 2^16
+    // 0.95 to 0.98; two or three sums 0.99 to 1.04)
+    const bool all_int = !any_fp_prime(c, 0, c->D);
+    const u32 sums_max = all_int && (c->D << (c->logN - 7)) > 768 ? CKKS_DH_SUMS - 1 : CKKS_DH_SUMS;
+    if (n2 <= sums_max && n1 <= CKKS_DH_CHUNK) {
         DhInnerArgs ia;
         memset(&ia, 0, sizeof(ia));
         for (u32 b = 0; b < n1; b++) ia.key[b] = h_baby_rk_ptrs[b], ia.galois[b] = h_baby_galois[b];
