@@ -915,7 +915,7 @@ struct ConvL {
     static std::string name(const char* ar, int A) {
         const bool fp = ar[0] == 'F';
         const int t = fp ? ntt<FpAr>() : ntt<IntAr>();
-        const std::string dir = std::to_string(DIR), words = sizeof...(NW) ? ", " + std::to_string(conv_words(KS, NW...)) : std::string();
+        const std::string dir = std::to_string(DIR), words = sizeof...(NW) ? ", " + std::to_string((0 + ... + NW)) : std::string();
         if (KS && fp && DIR == CONV_DN) return "conv_mfma_kernel<" + std::to_string(A) + ", " + std::to_string(KS) + ", " + dir + ", " + std::to_string(t) + words + ">";
         return kname("conv_fwd_strided_kernel", ar, A, (", " + dir + ", " + std::to_string(KS ? KS + t : fp ? TB : 1) + (KS ? ", false" : ", true") + words).c_str());
     }
@@ -1262,16 +1262,16 @@ static void launch_dh_accum_run(const View* c, DhInnerArgs a, u32 first, u32 cou
     const std::string form = std::string(all_int ? "IntAr, " : "AnyAr, ") + (narrow ? "2" : "4") + (sums > 1 ? ", " + std::to_string(sums) : std::string());
     ProfScope ps(c, c->sh->prof.on ? "dh_accum_kernel<" + form + ">" : std::string(), limbs, s);
     const dim3 grid((rows * a.waves / 4 + 7) / 8 * 8);
-#define CKKS_DH(W, G)                                                                                          \
-    if (all_int) hipLaunchKernelGGL((dh_accum_kernel<IntAr, W, G>), grid, dim3(256), 0, s, a, c->tb);          \
-    else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, W, G>), grid, dim3(256), 0, s, a, c->tb)
+#define CKKS_DH(...)                                                                                                 \
+    if (all_int) hipLaunchKernelGGL((dh_accum_kernel<IntAr, __VA_ARGS__>), grid, dim3(256), 0, s, a, c->tb);         \
+    else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, __VA_ARGS__>), grid, dim3(256), 0, s, a, c->tb)
     switch (sums) {
         case 2: CKKS_DH(2, 2); break;
         case 3: CKKS_DH(2, 3); break;
         case 4: CKKS_DH(2, 4); break;
         default:
-            if (narrow) { CKKS_DH(2, 1); }
-            else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 4, 1>), grid, dim3(256), 0, s, a, c->tb);
+            if (narrow) { CKKS_DH(2); }
+            else hipLaunchKernelGGL((dh_accum_kernel<AnyAr, 4>), grid, dim3(256), 0, s, a, c->tb);
     }
 #undef CKKS_DH
 }

@@ -833,17 +833,21 @@ __device__ __forceinline__ void conv_mfma_workgroup(const ConvArgs& a, const Tab
 // K = 12, dnum 3, batch 2: 396 -> 358; a rotation, L = 27, K = 9, dnum 3: 205 -> 168)
 template <class AR>
 constexpr int conv_mfma_ntt() { return AR::is_fp ? 2 : 1; }
-// source words a lane half loads per coefficient: half of what KS products take, unless the sources need fewer (a last template
-// argument of the kernels: six sources three words instead of four, two sources one instead of two)
-constexpr int conv_words(int KS) { return 2 * KS; }
-constexpr int conv_words(int, int NW) { return NW; }
 // ONE: a single source, P targets per workgroup.  Else the matrix-core form, P = products per coefficient group + targets
-// per lane.
-template <class AR, int A, int DIR, int P, bool ONE, int... NW>
+// per lane.  NW: source words a lane half loads per coefficient where that is one fewer than the products take (six sources three words
+// instead of four, two sources one instead of two), overloads so that the argument is in their names and only there.
+template <class AR, int A, int DIR, int P, bool ONE>
 __global__ __launch_bounds__(ONE ? 256 : 512, ONE ? (AR::is_fp ? 4 : 3) : !AR::is_fp ? 4 : P <= 4 ? 4 : 2)
 void conv_fwd_strided_kernel(ConvArgs a, Tables tb, LimbRun run) {
+    constexpr int NTT = conv_mfma_ntt<AR>();
     if constexpr (ONE) conv_one_body<AR, A, DIR, P>(a, tb, run);
-    else conv_mfma_workgroup<AR, A, P - conv_mfma_ntt<AR>(), DIR, conv_mfma_ntt<AR>(), conv_words(P - conv_mfma_ntt<AR>(), NW...)>(a, tb, run);
+    else conv_mfma_workgroup<AR, A, P - NTT, DIR, NTT, 2 * (P - NTT)>(a, tb, run);
+}
+template <class AR, int A, int DIR, int P, bool ONE, int NW>
+__global__ __launch_bounds__(512, !AR::is_fp || P <= 4 ? 4 : 2) void conv_fwd_strided_kernel(ConvArgs a, Tables tb, LimbRun run) {
+    static_assert(!ONE, "a single source is one word");
+    constexpr int NTT = conv_mfma_ntt<AR>();
+    conv_mfma_workgroup<AR, A, P - NTT, DIR, NTT, NW>(a, tb, run);
 }
 // ModDown from a single source with ordinary stores
 template <class AR, int A, int P>
@@ -852,10 +856,15 @@ __global__ __launch_bounds__(256, AR::is_fp ? 4 : 3) void conv_one_cached_kernel
 }
 // ModDown onto FpAr targets, KS products per coefficient group, NTT targets per lane: a name of its own, so that profiles tell
 // it from ModUp
-template <int A, int KS, int DIR, int NTT, int... NW>
+template <int A, int KS, int DIR, int NTT>
 __global__ __launch_bounds__(512, KS <= 2 ? 4 : 2) void conv_mfma_kernel(ConvArgs a, Tables tb, LimbRun run) {
     static_assert(DIR == CONV_DN, "the other conversions are conv_fwd_strided_kernel");
-    conv_mfma_workgroup<FpAr, A, KS, DIR, NTT, conv_words(KS, NW...)>(a, tb, run);
+    conv_mfma_workgroup<FpAr, A, KS, DIR, NTT, 2 * KS>(a, tb, run);
+}
+template <int A, int KS, int DIR, int NTT, int NW>
+__global__ __launch_bounds__(512, KS <= 2 ? 4 : 2) void conv_mfma_kernel(ConvArgs a, Tables tb, LimbRun run) {
+    static_assert(DIR == CONV_DN, "the other conversions are conv_fwd_strided_kernel");
+    conv_mfma_workgroup<FpAr, A, KS, DIR, NTT, NW>(a, tb, run);
 }
 // ModUp onto both classes of targets in one launch: the first workgroups convert to the IntAr run, the longer ones, the others to
 // the FpAr run; bound by instructions and by source words from L2, they share the compute units (conv_up_both has the figures).
@@ -864,19 +873,23 @@ struct ConvBothArgs {
     LimbRun run_fp, run_in;
     u32 grid_in;  // workgroups of the IntAr part, a multiple of 8
 };
-template <int A, int KS, int... NW>
-__global__ __launch_bounds__(512, 4) void conv_up_both_kernel(ConvBothArgs a, Tables tb) {
+template <int A, int KS, int NW>
+__device__ __forceinline__ void conv_up_both_workgroup(const ConvBothArgs& a, const Tables& tb) {
     constexpr u32 EXCH = ConvLds<FpAr, A, 2>::exch, TWF = ConvLds<FpAr, A, 2>::tw, TWI = ConvLds<IntAr, A, 1>::tw, TILES = (1u << A) / 16;
     __shared__ __align__(16) u64 lds[EXCH + (TWF > TWI ? TWF : TWI)];
     u32 group, inst;
     if (blockIdx.x >= a.grid_in) {
         if (!xcd_decode(blockIdx.x - a.grid_in, a.fp.blocks, a.fp.groups_outer * tb.dnum * TILES, group, inst)) return;
-        conv_mfma_body<FpAr, A, KS, CONV_UP, 2, conv_words(KS, NW...), 1>(a.fp, tb, a.run_fp, lds, lds + EXCH, threadIdx.x, group, inst);
+        conv_mfma_body<FpAr, A, KS, CONV_UP, 2, NW, 1>(a.fp, tb, a.run_fp, lds, lds + EXCH, threadIdx.x, group, inst);
     } else {
         if (!xcd_decode(blockIdx.x, a.in.blocks, a.in.groups_outer * tb.dnum * TILES, group, inst)) return;
-        conv_mfma_body<IntAr, A, KS, CONV_UP, 1, conv_words(KS, NW...), 1>(a.in, tb, a.run_in, lds, lds + EXCH, threadIdx.x, group, inst);
+        conv_mfma_body<IntAr, A, KS, CONV_UP, 1, NW, 1>(a.in, tb, a.run_in, lds, lds + EXCH, threadIdx.x, group, inst);
     }
 }
+template <int A, int KS>
+__global__ __launch_bounds__(512, 4) void conv_up_both_kernel(ConvBothArgs a, Tables tb) { conv_up_both_workgroup<A, KS, 2 * KS>(a, tb); }
+template <int A, int KS, int NW>
+__global__ __launch_bounds__(512, 4) void conv_up_both_kernel(ConvBothArgs a, Tables tb) { conv_up_both_workgroup<A, KS, NW>(a, tb); }
 
 // =========================================================== forward transform, second pass
 struct FwdContigArgs {
@@ -1521,8 +1534,8 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
 // W words per lane; a row, a wavefront's share, is 64 times that (sigma_g maps every aligned block of 2^m slots onto one).
 // AnyAr, FP64 and integer limbs in one launch: rows of 256 words, 12 KiB in flight per wavefront and three waves per SIMD, or
 // of 128 and five.  IntAr, for chains of integer primes alone: rows of 128 words.  launch_dh_accum has the rule.
-template <class AR, int W, int G = 1>
-__global__ __launch_bounds__(256, G > 1 || W == 4 ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) {
+template <class AR, int W, int G>
+__device__ __forceinline__ void dh_accum_workgroup(const DhInnerArgs& a, const Tables& tb) {
     __shared__ __align__(16) u64 lds[512 * W];  // a row per wavefront to permute it in; eight to join four pairs of sums
     const u32 rows_wg = 4 / a.waves, per_limb = ((1u << tb.logN) / (64 * W)) / rows_wg, total = a.count * per_limb, per = (total + 7) / 8;
     const u32 pos = blockIdx.x >> 3, q = (blockIdx.x & 7) * per + pos;  // workgroups go to the XCDs round-robin
@@ -1532,6 +1545,11 @@ __global__ __launch_bounds__(256, G > 1 || W == 4 ? 3 : 5) void dh_accum_kernel(
     const PrimeConst pc = tb.pc[tb.phys(i)];
     CKKS_BY_ARITHMETIC(AR, i, (dh_accum_body<AR_, W, G>(a, tb, pc, lds, i, row, wave)))
 }
+// one sum, or G of them
+template <class AR, int W>
+__global__ __launch_bounds__(256, W == 4 ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) { dh_accum_workgroup<AR, W, 1>(a, tb); }
+template <class AR, int W, int G>
+__global__ __launch_bounds__(256, 3) void dh_accum_kernel(DhInnerArgs a, Tables tb) { dh_accum_workgroup<AR, W, G>(a, tb); }
 
 // ==================================================== baby-step giant-step accumulation and sums
 // C[g][t][i] = sum_b pt[g][b][i] * R[b][t][i] on every limb i of the extended basis: the giant-step
