@@ -919,6 +919,16 @@ struct ConvL {
         if (KS && fp && DIR == CONV_DN) return "conv_mfma_kernel<" + std::to_string(A) + ", " + std::to_string(KS) + ", " + dir + ", " + std::to_string(t) + words + ">";
         return kname("conv_fwd_strided_kernel", ar, A, (", " + dir + ", " + std::to_string(KS ? KS + t : fp ? TB : 1) + (KS ? ", false" : ", true") + words).c_str());
     }
+    struct Halves {  // IntAr targets in workgroups of 256 lanes
+        static constexpr int words = sizeof...(NW) ? (0 + ... + NW) : 2 * KS;
+        template <class AR, int A>
+        static void go(dim3 g, hipStream_t s, const ConvArgs& a, const Tables& tb, LimbRun run) {
+            if constexpr (!AR::is_fp && KS) hipLaunchKernelGGL((conv_int_kernel<A, KS, DIR, words>), g, dim3(256), 0, s, a, tb, run);
+        }
+        static std::string name(int A) {
+            return "conv_int_kernel<" + std::to_string(A) + ", " + std::to_string(KS) + ", " + std::to_string(DIR) + ", " + std::to_string(words) + ">";
+        }
+    };
 };
 struct FwdContigL {
     static constexpr bool any = true;
@@ -1023,6 +1033,12 @@ static u32 conv_up_targets(const View* c, const ClassRun& cr, u32& total) {
     return most;
 }
 
+// Conversions onto IntAr targets of a launch of that many workgroups and more: 256 lanes a workgroup with two positions each instead of
+// 512 with one.  The short workgroups are the faster ones while the launch is a few rounds (whole rotations, 256 / 512 lanes: below
+// 600 workgroups 1.02 to 1.08), the long ones, three to a compute unit instead of two, on many (integer chains of 12 + 4 to 96 + 8 limbs,
+// N = 2^12 .. 2^16, 512 / 256 lanes: 1200 to 3000 workgroups 0.99 to 1.02, from there on 1.00 to 1.04, two sources at N = 2^12 0.97 to 0.99;
+// special limbs alone 0.99 to 1.02).  The conversion of 42 + 12 limbs, 10 sources, batch 4, N = 2^16: 339 -> 300 us
+#define CKKS_CONV_INT_FROM 3072u
 // one launch per arithmetic run of the targets
 // only: -1 = every run, 0 = IntAr runs only, 1 = FpAr runs only
 template <class L, int DIR>
@@ -1037,8 +1053,14 @@ static void launch_conv_runs(const View* c, ConvArgs a, hipStream_t s, int only)
         const dim3 grid(xcd_grid(a.groups_outer * (DIR == CONV_UP ? c->dnum : 1) * tiles_of(c), a.blocks));
         hipStream_t rs = (!cr.fp && c->sh->side.active) ? c->sh->side.stream : s;
         // every target written, plus the source coefficients, read once
-        ProfScope ps(c, c->sh->prof.on ? L::name(cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(),
-                     (u64)a.groups_outer * (written + (DIR == CONV_UP ? c->L : c->K)), rs);
+        const u64 alg = (u64)a.groups_outer * (written + (DIR == CONV_UP ? c->L : c->K));
+        if constexpr (L::packed)
+            if (!cr.fp && grid.x >= CKKS_CONV_INT_FROM) {
+                ProfScope ps(c, c->sh->prof.on ? L::Halves::name((int)c->logN - 8) : std::string(), alg, rs);
+                dispatch_kernel<typename L::Halves>(c, false, grid, rs, a, LimbRun{cr.first, cr.count});
+                continue;
+            }
+        ProfScope ps(c, c->sh->prof.on ? L::name(cr.fp ? "FpAr" : "IntAr", (int)c->logN - 8) : std::string(), alg, rs);
         dispatch_kernel<L>(c, cr.fp, grid, rs, a, LimbRun{cr.first, cr.count});
     }
 }

@@ -5,7 +5,7 @@
 //   inv_contig_kernel   load (copy | a1*a2 | sigma_g gather) -> first inverse pass (N <= 2^13: both)
 //   inv_contig_rows_kernel  first inverse pass alone at N = 2^13 (few integer limbs)
 //   inv_strided_kernel  second inverse pass -> scale by N^-1 (* base-conversion pre-factor)
-//   conv_fwd_strided_kernel, conv_mfma_kernel, conv_up_both_kernel
+//   conv_fwd_strided_kernel, conv_mfma_kernel, conv_int_kernel, conv_up_both_kernel
 //                       base conversion from the digit / special limbs -> first forward pass of the targets
 //   fwd_strided_kernel  load -> first forward pass
 //   fwd_contig_kernel   second forward pass -> canonical store
@@ -668,7 +668,7 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
 //
 // A lane keeps NTT x 16 converted words, x[u][k], k the coefficient's row block: rows k*RB + r0 of column c, the inputs of the
 // first four forward stages, which therefore run in the lane that converted them; (r0, c) from a position pp = wave*32 + lane%32
-// of the tile as tid maps to (r0, c) in layout SA.  A workgroup has 512 lanes and 2*NTT targets, u = target slot 2*u + h.
+// of the tile as tid maps to (r0, c) in layout SA.  A workgroup has 512 lanes (SETS = 1) and 2*NTT targets, u = target slot 2*u + h.
 // What bounds it: the source words come from L2, and that traffic (7.3 TB/s with two targets at batch 8, N = 2^16, six sources;
 // all loads from one cached row: 121 -> 78 us per launch) is the limit rather than the arithmetic, so four targets share a
 // load where the registers allow it: FpAr targets need 128 (four waves per SIMD): 121 -> 111 us ModUp, 84 -> 71 us
@@ -678,12 +678,15 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
 // Source i travels in word (i / 2) % 2 of lane half i % 2, so that six sources take three loads a lane half and not four (NW; both
 // conversions of a batch of 8 108 -> 105 and 71 -> 68 us with the second batch of loads in flight, AHEAD).
 typedef int v4i __attribute__((ext_vector_type(4)));
-template <class AR, int A, int KS, int DIR, int NTT, int NW, int AHEAD>
+// SETS = 2: workgroups of 256 lanes that keep two positions each, pp = wave*64 + 32*set + lane%32, 32 words (IntAr targets of large
+// launches).
+template <class AR, int A, int KS, int DIR, int NTT, int NW, int AHEAD, int SETS = 1>
 __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& tb, const LimbRun run, u64* lds, u64* tws, const u32 tid,
                                                const u32 group, const u32 inst) {
     typedef NttCore<AR, A> C;
     typedef StridedTw<AR, A> TW;
     typedef typename AR::T T;
+    static_assert(SETS == 1 || NTT == 1, "two targets or two positions a lane");
     constexpr u32 TILES = (1u << A) / 16, TPW = 2 * NTT;  // targets per workgroup
     const u32 N = 1u << tb.logN, lane = tid & 63, wave = tid >> 6, n = lane & 31, h = lane >> 5;
     const u32 tile = group % TILES;
@@ -724,11 +727,11 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
         for (int ks = 0; ks < KS; ks++) aop[ks] = *reinterpret_cast<const v4i*>(base + ks * 32 + h * 16 + dg * 2);
     }
 #pragma unroll
-    for (u32 tt = 0; tt < NTT; tt++) {
-        const u32 sl = 2 * tt + (tid >> 8);  // 256 lanes fill one slot's twiddles
+    for (u32 tt = 0; tt < NTT * SETS; tt++) {
+        const u32 sl = SETS == 2 ? tt : 2 * tt + (tid >> 8);  // 256 lanes fill one slot's twiddles
         if (sl < nt) TW::fill(tws + sl * TW::WORDS, tid & 255, tb, tb.phys(limb_of(sl)));
     }
-    T x[NTT][16];
+    T x[NTT * SETS][16];
     {
         const PrimeConst pc0 = tb.pc[tb.phys(limb_of(h))], pc1 = tb.pc[tb.phys(limb_of(NTT == 2 ? 2 + h : h))];
         const typename AR::Mod m0 = AR::mod(pc0), m1 = AR::mod(pc1);
@@ -736,13 +739,15 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
         // constant rows of those sources are zero)
         const Buf sb(src);
         u32 so[NW];
-        const u32 pp0 = wave * 32 + n;
+        const u32 pp0 = wave * (32 * SETS) + n;
 #pragma unroll
         for (int q = 0; q < NW; q++) {
             const u32 i = 4 * (q >> 1) + 2 * (q & 1) + h;
             so[q] = 8 * ((i < ns ? i : ns - 1) * N + tile * C::TC + (pp0 / C::TC) * 256 + pp0 % C::TC);
         }
-        auto src_off = [&](int k) { return 8 * (u32)(k * C::RB * 256); };
+        // the second set is 32 positions on: 32 / TC rows down, or 32 columns on where a row holds more
+        constexpr u32 SET = C::TC >= 64 ? 32 : (32 / C::TC) * 256;
+        auto src_off = [&](int g) { return 8 * (u32)((g & 15) * C::RB * 256 + (g >> 4) * SET); };
         // one row block (32 coefficients a wave) at a time; the source words of the next AHEAD ones are requested before its products
         // are issued; scheduling barriers keep the compiler from hoisting every load of the unrolled loop (which would spill)
         u64 bw[AHEAD + 1][NW];
@@ -751,12 +756,13 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
 #pragma unroll
             for (int q = 0; q < NW; q++) bw[f][q] = sb.ld(so[q], src_off(f));
 #pragma unroll
-        for (int k = 0; k < 16; k++) {
-            if (k + AHEAD < 16) {
+        for (int g = 0; g < 16 * SETS; g++) {
+            const int k = g & 15;
+            if (g + AHEAD < 16 * SETS) {
 #pragma unroll
-                for (int q = 0; q < NW; q++) bw[(k + AHEAD) % (AHEAD + 1)][q] = sb.ld(so[q], src_off(k + AHEAD));
+                for (int q = 0; q < NW; q++) bw[(g + AHEAD) % (AHEAD + 1)][q] = sb.ld(so[q], src_off(g + AHEAD));
             }
-            const u64* w = bw[k % (AHEAD + 1)];
+            const u64* w = bw[g % (AHEAD + 1)];
             v16i acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
             for (int ks = 0; ks < KS; ks++) {
@@ -765,8 +771,8 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
                 acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(aop[ks], bop, acc, 0, 0, 0);
             }
             // the empty statements keep a recombination here: sunk to a conditional use it would keep the sums alive
-            x[0][k] = conv_recombine(acc, 0, m0, pc0);
-            asm volatile("" : "+v"(x[0][k]));
+            x[g >> 4][k] = conv_recombine(acc, 0, m0, pc0);
+            asm volatile("" : "+v"(x[g >> 4][k]));
             if constexpr (NTT == 2) {
                 x[1][k] = conv_recombine(acc, 8, m1, pc1);
                 asm volatile("" : "+v"(x[1][k]));
@@ -778,6 +784,39 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
         strided_stages_lo<AR, A>(x[0], tws + h * TW::WORDS, m0);
         if constexpr (NTT == 2)
             if (nt > 2) strided_stages_lo<AR, A>(x[1], tws + (2 + h) * TW::WORDS, m1);
+        if constexpr (SETS == 2) strided_stages_lo<AR, A>(x[1], tws + h * TW::WORDS, m0);
+    }
+    if constexpr (SETS == 2) {  // one target after the other through half the memory
+#pragma unroll
+        for (u32 u = 0; u < 2; u++) {
+            if constexpr (A > 4) {
+                if (u >= nt) break;
+                if (u) __syncthreads();  // the first exchange has been read
+                const u32 t = limb_of(u), c = tid % C::TC, r1 = tid / C::TC;
+                const typename AR::Mod m = AR::mod(tb.pc[tb.phys(t)]);
+                if (h == u) {
+#pragma unroll
+                    for (u32 v = 0; v < 2; v++)
+#pragma unroll
+                        for (int k = 0; k < 16; k++) lds[k * 256 + wave * 64 + v * 32 + n] = AR::to_raw(AR::round_reduce(x[v][k], m));
+                }
+                __syncthreads();
+                T y[16];
+#pragma unroll
+                for (int k = 0; k < 16; k++) y[k] = AR::from_raw(lds[(r1 * 16 + k) * C::TC + c]);
+                strided_stages_hi<AR, A>(y, tws + u * TW::WORDS, r1, m);
+                u64* dst = dst0 + (size_t)t * N + (size_t)r1 * 16 * 256 + tile * C::TC + c;
+#pragma unroll
+                for (int k = 0; k < 16; k++) __builtin_nontemporal_store(AR::to_raw(AR::round_reduce(y[k], m)), &dst[k * 256]);
+            } else if (h < nt) {
+                const u32 t = limb_of(h), pp = wave * 64 + u * 32 + n;
+                const typename AR::Mod m = AR::mod(tb.pc[tb.phys(t)]);
+                u64* dst = dst0 + (size_t)t * N + (pp / C::TC) * 256 + tile * C::TC + pp % C::TC;
+#pragma unroll
+                for (int k = 0; k < 16; k++) dst[k * C::RB * 256] = AR::to_raw(AR::round_reduce(x[u][k], m));
+            }
+        }
+        return;
     }
 #pragma unroll
     for (u32 u = 0; u < NTT; u++) {  // slots 2u and 2u + 1
@@ -812,6 +851,18 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
         }
     }
 }
+
+// IntAr targets in workgroups of 256 lanes
+template <int A, int KS, int DIR, int NW>
+__device__ __forceinline__ void conv_int_workgroup(const ConvArgs& a, const Tables& tb, const LimbRun run) {
+    constexpr u32 EXCH = A > 4 ? 4096 : 2, TW = 2 * StridedTw<IntAr, A>::WORDS;
+    __shared__ __align__(16) u64 lds[EXCH + TW];
+    u32 group, inst;
+    if (!xcd_decode(blockIdx.x, a.blocks, a.groups_outer * (DIR == CONV_UP ? tb.dnum : 1) * ((1u << A) / 16), group, inst)) return;
+    conv_mfma_body<IntAr, A, KS, DIR, 1, NW, KS <= 2 ? 2 : 1, 2>(a, tb, run, lds, lds + EXCH, threadIdx.x, group, inst);
+}
+template <int A, int KS, int DIR, int NW>
+__global__ __launch_bounds__(256, 3) void conv_int_kernel(ConvArgs a, Tables tb, LimbRun run) { conv_int_workgroup<A, KS, DIR, NW>(a, tb, run); }
 
 // row blocks whose source words are requested ahead: two where the registers allow it
 constexpr int conv_ahead(int KS, int NW) { return KS <= 2 && NW <= 3 ? 2 : 1; }

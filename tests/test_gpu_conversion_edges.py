@@ -163,3 +163,45 @@ def test_transform_through_the_cache_by_its_size(orc, first, n, batch, ar):
         ctx.profile_enable(False)
     assert bool((got == want[dev(which)]).all())
     assert ("fwd_strided_cached_kernel<%s, 6>" % ar in names) == (n * batch >= 512), names
+
+
+@pytest.mark.parametrize("logN,L,K,dnum,batch,up,dn", [
+    (12, 24, 2, 12, 22, True, False), (12, 24, 2, 12, 20, False, False), (12, 48, 5, 6, 64, True, True),   # two, five and eight sources; no exchange at N = 2^12
+    (13, 20, 10, 2, 77, True, True), (13, 20, 10, 2, 76, False, False),                                    # ten sources, 3080 and 3040 workgroups
+    (14, 13, 3, 3, 64, True, True),                                                                        # a last workgroup of one target, a short last digit
+    (15, 30, 6, 5, 13, True, True)])                                                                       # six sources, three words a lane half
+def test_integer_targets_of_many_workgroups(orc, logN, L, K, dnum, batch, up, dn):
+    """Conversions onto integer limbs from 3072 workgroups on: 256 lanes with two positions each."""
+    ps = synth.mixed_params(logN, [55] * L, [59] * K, dnum, "halves")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(256 + logN + L)
+    ct, key = _extreme(rng, ps.q_primes, ps.N, (3, 2)), _extreme(rng, ps.primes, ps.N, (dnum, 2))
+    which, g = np.arange(batch) % 3, synth.galois_element(-3, logN)
+    d_ct, want = dev(ct)[dev(which)].contiguous(), dev(np.stack([orc.hrot(c, g, key, P) for c in ct]))
+    print(logN, L, K, "batch", batch, flush=True)
+    ctx.profile_enable(True)
+    try:
+        got, names = ctx.hrot(d_ct, g, dev(key)), set(ctx.profile_read())
+    finally:
+        ctx.profile_enable(False)
+    assert bool((got == want[dev(which)]).all())
+    halves = {int(n.split(", ")[2]) for n in names if n.startswith("conv_int_kernel<%d, " % (logN - 8))}
+    assert halves == {d for d, is_on in ((1, up), (2, dn)) if is_on}, names
+
+
+def test_integer_targets_of_many_workgroups_from_seventeen_sources(orc):
+    """The ModDown merged with a rescale: sixteen special primes and the last limb."""
+    ps = synth.mixed_params(13, [55] * 24, [59] * 16, 2, "halves")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    rng = np.random.default_rng(1717)
+    a, b, key = _extreme(rng, ps.q_primes, ps.N, (2, 2)), _extreme(rng, ps.q_primes, ps.N, (2, 2)), _extreme(rng, ps.primes, ps.N, (2, 2))
+    which = np.arange(64) % 2
+    want = dev(np.stack([orc.hmult_relin_rescale_level(x, y, key, P) for x, y in zip(a, b)]))
+    print("seventeen sources", flush=True)
+    ctx.profile_enable(True)
+    try:
+        got, names = ctx.hmult_relin_rescale_at(ps.L, dev(a)[dev(which)].contiguous(), dev(b)[dev(which)].contiguous(), dev(key)), set(ctx.profile_read())
+    finally:
+        ctx.profile_enable(False)
+    assert bool((got == want[dev(which)]).all())
+    assert "conv_int_kernel<5, 5, 2, 10>" in names, names
