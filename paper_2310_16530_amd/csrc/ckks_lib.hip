@@ -1632,8 +1632,10 @@ static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipS
         return;
     }
     // below 512 workgroups the events cost more than the second stream gives (N = 2^13, 24 + 6 limbs, overlap on, HMult of 4 (256) 110 us
-    // forked, 99 on one stream; 8 (512) 128 / 131; N = 2^12, 3 + 1 limbs, one 72 / 53)
-    if (mode == EXTEND_BESIDE && second && !sd.active && conv_up_workgroups(c, groups) >= 512 && side_stream_ready(sd)) {
+    // forked, 99 on one stream; 8 (512) 128 / 131; N = 2^12, 3 + 1 limbs, one 72 / 53), unless a workgroup takes long: more than eight
+    // sources (N = 2^13, 92 + 5 limbs, 9 digits, one rotation (432) 0.87 of the time on one stream; N = 2^12, 57 + 5, 5 digits, 4 (300) 0.88)
+    const bool worth = c->up.ks >= 4 || conv_up_workgroups(c, groups) >= 512;
+    if (mode == EXTEND_BESIDE && second && !sd.active && worth && side_stream_ready(sd)) {
         // the IntAr targets first, on s; the FpAr targets on the side stream from the moment those are done, beside
         // whatever s runs next (the caller joins before it reads the FpAr limbs of dt)
         launch_conv<CONV_UP>(c, a3, s, 0);

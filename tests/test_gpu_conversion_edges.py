@@ -96,7 +96,8 @@ def test_single_source_conversions_share_a_load_for_fp64_targets_only(orc, logN,
 @pytest.mark.parametrize("logN,L,K,dnum,batch,order", [
     (14, 10, 2, 5, 1, "fp first"), (14, 12, 5, 3, 1, "fp first"), (15, 11, 6, 2, 2, "fp first"), (14, 14, 7, 2, 3, "fp first"),
     (14, 16, 8, 2, 1, "fp first"), (14, 9, 3, 3, 30, "fp first"), (15, 13, 6, 3, 5, "alternating"), (16, 6, 2, 3, 1, "fp first"),
-    (16, 13, 6, 3, 1, "fp first"), (12, 12, 6, 2, 1, "fp first"), (13, 7, 5, 2, 40, "fp first")])
+    (16, 13, 6, 3, 1, "fp first"), (12, 12, 6, 2, 1, "fp first"), (13, 7, 5, 2, 40, "fp first"),
+    (13, 39, 5, 3, 1, "fp first")])  # thirteen sources: on two streams whatever the number of workgroups
 def test_source_words_and_joint_conversions(orc, logN, L, K, dnum, batch, order):
     """Two, three and five to eight sources (a lane half loads half of them, rounded up), both classes of targets in one launch where
     the FP64 limbs come first and N >= 2^14, ModDowns with two FP64 targets per workgroup and with four, target counts that
