@@ -1188,13 +1188,18 @@ static void launch_forward(const View* c, u64* d_x, const LimbSel& sel, hipStrea
 // at N = 2^12, dnum = 3: special limb 14 -> 9 us, q-limbs 16 -> 10 us (four); HMult at N = 2^15, level 17, batch 3, special limbs, 144
 // workgroups: the call 141 -> 133 us (two); N = 2^16, 12 + 2 limbs, dnum = 6, q-limbs, 192 workgroups: 123 -> 113 (two).  On more
 // than one round of workgroups two are no gain whatever the rounds say: 768 workgroups, N = 2^16, dnum = 6, 235 -> 242 us.
-static u32 inner_ways(u32 wgs, u32 dnum) {
-    u32 best = 1, least = (wgs + 511) / 512 * (2 * dnum + 4);
+static u32 inner_ways(u32 wgs, u32 dnum, u32& least) {
+    u32 best = 1;
+    least = (wgs + 511) / 512 * (2 * dnum + 4);
     for (u32 ways = 2; ways <= 4 && dnum > 1; ways *= 2) {
         const u32 t = (ways * wgs + 511) / 512 * (2 * ((dnum + ways - 1) / ways) + 3);
         if (t < least && (ways == 4 || wgs <= 512)) best = ways, least = t;
     }
     return best;
+}
+static u32 inner_ways(u32 wgs, u32 dnum) {
+    u32 time;
+    return inner_ways(wgs, dnum, time);
 }
 
 // limbs [lo, hi) of the extended basis.  FUSED: the launch also ends the ModDown on its limbs (all below
@@ -1697,13 +1702,21 @@ static u32 summed_rotations_max(const View* c) {
 // fit one sum (3 rotations near 2^61, 7 just above 2^60, 15 at 2^59) starts over.  Batch / sum, whole transforms of 2 to 21 giant steps, by
 // the workgroups of the smallest q-limb launch, N = 2^12 .. 2^16: up to 64 0.60 to 1.01 (runs of one limb, the arithmetics alternating, 0.42 to 0.92), 72 and
 // 80 0.97 to 1.05, 96 and more 0.98 to 1.20, one giant step 0.94 to 1.0; where the sums are more than the launches of a batch: 96 0.89 to 0.99, 144 and
-// 160 0.92 to 1.0, 192 0.97 to 1.05, 256 and more 1.0 to 1.12, but three a sum 0.78 to 1.02 up to 560
+// 160 0.92 to 1.0, 192 0.97 to 1.05, 256 and more 1.0 to 1.12, but three a sum 0.78 to 1.02 up to 560.  And never where the q-limb
+// product by itself, in the units of inner_ways, would take more than 5/4 of the batch's (3 steps, 70 + 14 integer limbs in 24 digits,
+// N = 2^13, 140 workgroups: 75 against 52 units, 544 against 386 us; 20 + 4 limbs in 5 digits, N = 2^15, 19 / 14, the call 0.98)
 static bool giants_summed(const View* c, u32 n) {
     if (n < 2 || !c->dn.ks) return false;  // one special prime is reduced directly: there are no digits to add
-    const u32 at_once = summed_rotations_max(c);
-    u32 least = ~0u;
-    for (const ClassRun& r : class_runs(c, 0, c->L)) least = r.count * tiles_of(c) < least ? r.count * tiles_of(c) : least;
-    return cdiv(n, at_once) == cdiv(n, CKKS_ROT_CHUNK) ? least >= 96 : least >= 192 && at_once >= 6;
+    const u32 at_once = summed_rotations_max(c), sums = cdiv(n, at_once);
+    u32 least = ~0u, one = 0, batch = 0, t;
+    for (const ClassRun& r : class_runs(c, 0, c->L)) {
+        const u32 wgs = r.count * tiles_of(c);
+        if (wgs < least) least = wgs;
+        inner_ways(wgs, cdiv(n, sums) * c->dnum, t), one += t;
+        inner_ways(wgs * n, c->dnum, t), batch += t;
+    }
+    if (4 * sums * one > 5 * batch) return false;
+    return sums == cdiv(n, CKKS_ROT_CHUNK) ? least >= 96 : least >= 192 && at_once >= 6;
 }
 
 // out = the sum of n (at most CKKS_ROT_CHUNK) rotated ciphertexts, each with its own element and key

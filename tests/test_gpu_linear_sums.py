@@ -55,17 +55,29 @@ def test_hoisted_sums_before_the_mod_down(orc, logN, q, p, dnum, counts):
             assert any(k.startswith("ks_final_kernel") and k.endswith(", 4>") for k in names) == summed, names
 
 
+def _inner_time(wgs, terms):
+    """Rounds of workgroups times passes per wavefront of an inner product, the best of one, two and four wavefronts a row."""
+    times = [-(-wgs // 512) * (2 * terms + 4)]
+    for ways in (2, 4) if terms > 1 else ():
+        if ways == 4 or wgs <= 512:
+            times.append(-(-ways * wgs // 512) * (2 * -(-terms // ways) + 3))
+    return min(times)
+
+
 def _one_mod_down(ps, level, n):
     """Whether n giant rotations share a ModDown: enough workgroups in the q-limb product's smallest launch, a run of limbs of one
-    arithmetic, and sums that hold as many rotations as a batch does or nearly so."""
+    arithmetic; a product not much longer than that of a batch; and sums that hold as many rotations as a batch does or nearly so."""
     if n < 2 or ps.K < 2:
         return False
     fp = [q < 3 << 48 for q in ps.primes[:level]]
     runs = [1]
     for a, b in zip(fp, fp[1:]):
         runs[-1:] = [runs[-1] + 1] if a == b else [runs[-1], 1]
-    least, a_sum = min(runs) * (ps.N >> 12), min(16, 0x7f7f7f7f7f7f7f7f // max(ps.primes[ps.L:]))
-    return least >= 96 if -(-n // a_sum) == -(-n // 16) else least >= 192 and a_sum >= 6
+    wgs, a_sum = [r * (ps.N >> 12) for r in runs], min(16, 0x7f7f7f7f7f7f7f7f // max(ps.primes[ps.L:]))
+    sums, digits = -(-n // a_sum), -(-level // -(-ps.L // ps.dnum))
+    if 4 * sums * sum(_inner_time(w, -(-n // sums) * digits) for w in wgs) > 5 * sum(_inner_time(w * n, digits) for w in wgs):
+        return False
+    return min(wgs) >= 96 if sums == -(-n // 16) else min(wgs) >= 192 and a_sum >= 6
 
 
 @pytest.mark.parametrize("logN,q,p,dnum,level,steps", [
@@ -82,6 +94,7 @@ def _one_mod_down(ps, level, n):
     (14, (49,) * 23 + (55,), (59, 60, 59), 8, 24, ((2, 3),)),               # a short run of integer limbs
     (16, (60,) * 12, (60,) * 2, 6, 12, ((1, 7), (1, 8))),                   # seven a sum: one sum, two sums of four
     (16, (60,) * 11, (60,) * 2, 6, 11, ((1, 8),)),                          # ... on fewer workgroups
+    (13, (55,) * 70, (59,) * 3, 24, 70, ((2, 3),)),                         # many digits: the product would take longer than a batch's
     (16, None, 2, 2, 6, ((1, 3), (1, 4))),                                  # three a sum; four sums of baby steps on many integer rows
 ])
 def test_baby_step_giant_step_sums(orc, logN, q, p, dnum, level, steps):
