@@ -20,6 +20,8 @@
 //                       words on integer chains and for few rotations, of 256 otherwise)
 //   bsgs_mac_kernel     giant-step combinations of baby-step rotations kept in the extended basis (more than four giant steps;
 //                       up to four are sums of dh_accum_kernel)
+//   fwd_strided_cached_kernel, conv_one_cached_kernel, ks_final_cached_kernel
+//                       the same with ordinary accesses to the words between two launches, where they fit the Infinity Cache
 //   inv_strided_sum_kernel  second inverse pass of several instances, their words added as integers: one ModDown for a sum
 //   modup_kernel / moddown_kernel / automorph kernels: the stand-alone coefficient-form entry points.
 //
