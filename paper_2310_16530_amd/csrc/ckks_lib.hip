@@ -1982,8 +1982,12 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
         u64 *const cq = w.cq, *const cp = cq + (size_t)2 * c->L * N;
         const size_t fit = (need / sizeof(u64) / N - 3 * (size_t)c->L - (size_t)c->dnum * c->D) / (2 * (size_t)c->D);
         const u32 part = cdiv(n_rot, cdiv(n_rot, CKKS_ROT_CHUNK)), chunk = part * (fit < CKKS_DH_CHUNK ? (u32)fit / part : CKKS_DH_CHUNK / part);
-        // second stream: the integer special limbs' inner products and inverse transforms beside the sum on the q-limbs
-        const bool fork = sd.enabled && c->mixed_classes && (n_rot < chunk ? n_rot : chunk) * c->D * tiles_of(c) >= 5 * 512;
+        // Second stream: the integer special limbs' inner products and inverse transforms beside the sum on the q-limbs.  Not where the
+        // special limbs mix the arithmetics, whose joint launches it would split (one stream / two, us: 40 + 9 limbs, 49, 59 and 60 bits in
+        // turn, N = 2^14, 17 rotations 598 / 889, 32 960 / 1281; 24 + 6, N = 2^15, 17 588 / 754, 32 1013 / 1173; all of 59 bits 551 / 546,
+        // 954 / 937; 560 / 580, 992 / 1005)
+        const bool fork = sd.enabled && c->mixed_classes && class_runs(c, c->L, c->D).size() == 1 &&
+                          (n_rot < chunk ? n_rot : chunk) * c->D * tiles_of(c) >= 5 * 512;
         decompose(w, fork ? EXTEND_FORK : EXTEND_PLAIN);
         for (u32 r0 = 0; r0 < n_rot; r0 += chunk) {
             const u32 nr = (n_rot - r0) < chunk ? (n_rot - r0) : chunk;

@@ -190,3 +190,22 @@ def test_hoisted_sums_on_integer_limbs_with_the_second_stream_at_work(orc):
             assert np.array_equal(host(call()), want)
     finally:
         ctx.set_overlap(False)
+
+
+def test_hoisted_sums_on_special_limbs_of_both_arithmetics_stay_on_one_stream(orc):
+    """The sizes of the test above: the launches that the special limbs' arithmetics share are not split for the second stream."""
+    ps = synth.mixed_params(16, [49] * 8, [49, 59], 2, "one_stream")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    n = 32
+    gs, keys, ct, pt = _inputs(ps, n, 3, 3233, ps.q_primes, (n,))
+    d_ct, d_pt, d_keys = dev(ct), dev(pt), [dev(k) for k in keys]
+    call = lambda: ctx.hrot_hoisted_mac(d_ct, gs, [d_keys[r % 3] for r in range(n)], d_pt)
+    want = orc.hrot_hoisted_mac(ct, gs, [keys[r % 3] for r in range(n)], pt, P)
+    got, one = _kernels(ctx, call)
+    assert np.array_equal(got, want)
+    ctx.set_overlap(True)
+    try:
+        got, two = _kernels(ctx, call)
+    finally:
+        ctx.set_overlap(False)
+    assert np.array_equal(got, want) and two == one, two ^ one
