@@ -1275,14 +1275,18 @@ static void launch_dh_accum_run(const View* c, DhInnerArgs a, u32 first, u32 cou
     // With few rotations the accumulation is a chain of a few waits on the keys, which more wavefronts in flight shorten
     // (N = 2^16, 26 + 6 limbs, dnum 5: 3 rotations 317 us wide, 310 narrow, 6 rotations 441 / 425, 8 rotations 507 / 497); from
     // about ten on the wide rows of a mixed chain are even or up to 3 % faster.  Several sums: narrow rows, for the registers (four
-    // sums with the products inside the digit loop spilled: 577 us, after it 390).
+    // sums of 8 rotations, 24 + 6 limbs, in rows of 256 words at two waves per SIMD: the call 956 us with four rows a workgroup and
+    // 1005 with one shared, against 955).
     const bool narrow = all_int || n_rot <= 8 || sums > 1;
     const u32 rows = count * ((1u << c->logN) / (64 * (narrow ? 2 : 4)));
-    // Four rows per workgroup, or one whose rotations the four wavefronts share.  Narrow: fewer rounds of the 1280 resident
-    // workgroups (768 with several sums) times rotations per wavefront.  Wide: with fewer than eight rotations the wavefronts
-    // would end up with unequal shares, which only a grid below two workgroups per compute unit makes up for.
-    const u32 resident = sums > 1 ? 768 : 1280;
-    if (narrow) a.waves = (rows + resident - 1) / resident * ((a.n_rot + 3) / 4) < (rows / 4 + resident - 1) / resident * a.n_rot ? 4 : 1;
+    // Four rows per workgroup, or one whose rotations the four wavefronts share.  Narrow, one sum: fewer rounds of the 1280 resident
+    // workgroups times rotations per wavefront.  Several sums: shared where four rows a workgroup leave the chip half empty (whole
+    // transforms of 3 to 16 baby steps, shared / not: 480 to 1024 rows 1.02 to 1.16, 1536 1.01 to 1.03; 1920 and 2048 0.98 to 1.0,
+    // more 0.95 to 1.0).  Wide: with fewer than eight rotations the wavefronts would end up with unequal shares, which only a grid
+    // below two workgroups per compute unit makes up for.
+    const u32 resident = 1280;
+    if (sums > 1) a.waves = rows < 1792 ? 4 : 1;
+    else if (narrow) a.waves = (rows + resident - 1) / resident * ((a.n_rot + 3) / 4) < (rows / 4 + resident - 1) / resident * a.n_rot ? 4 : 1;
     else a.waves = n_rot >= 8 || (rows / 4 < 512 && n_rot > 1) ? 4 : 1;
     u64 limbs = 0;  // per limb and rotation: the digits, the plaintexts, both key components (and b on q-limbs); C_t written
     for (u32 i = first; i < first + count; i++) limbs += n_rot * (3 * dnum + (a.pt ? sums : 0) + (i < c->L ? 1 : 0)) + (a.each ? 2 * n_rot : 2 * sums) + acc;
@@ -2213,12 +2217,11 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         decompose_extend(c, w, 1, s, EXTEND_PLAIN);
         launch_extended_fwd_contig(c, w, s);
     }
-    // Baby steps and combinations in one kernel where its registers hold the sums (8 x 4, N = 2^16, 24 + 6 limbs: 468 -> 390 us; 8 x 3
-    // the call 1032 -> 880).  On chains of integer primes alone four sums spill and pay only while all rows of 128 words are in flight at
-    // once (apart / in one, 12 + 4 limbs, 4 x 4 and 16 x 4: N = 2^12 (512 rows) 1.01 and 1.07, 2^13 0.99 and 1.01, 2^14 to 2^16
-    // 0.95 to 0.98; two or three sums 0.99 to 1.04)
+    // Baby steps and combinations in one kernel where its registers hold the sums (8 x 4, N = 2^16, 24 + 6 limbs: 468 -> 354 us; on
+    // integer chains of 4 + 2 and 12 + 4 limbs the call gains 2 to 4 % at N = 2^12 and 2^13, 6 to 9 % from 2^14 on).  One baby step
+    // of such a chain, which leaves little to combine, is within 1 to 3 % either way and stays apart from 768 rows on.
     const bool all_int = !any_fp_prime(c, 0, c->D);
-    const u32 sums_max = all_int && (c->D << (c->logN - 7)) > 768 ? CKKS_DH_SUMS - 1 : CKKS_DH_SUMS;
+    const u32 sums_max = all_int && n1 == 1 && (c->D << (c->logN - 7)) > 768 ? CKKS_DH_SUMS - 1 : CKKS_DH_SUMS;
     if (n2 <= sums_max && n1 <= CKKS_DH_CHUNK) {
         DhInnerArgs ia;
         memset(&ia, 0, sizeof(ia));

@@ -1379,9 +1379,15 @@ struct DhSum<IntAr, 2> {
     __device__ __forceinline__ u64 get(const IntAr::Mod& m) const { return redc_lazy(u128w{s.lo, csub(csub(s.hi, m.q2), m.q)}, m.q, m.qneg); }
 };
 
+// an address that is the same in every lane, in scalar registers
+template <class P>
+__device__ __forceinline__ P uniform_ptr(P p) {
+    const u64 v = (u64)p;
+    return (P)((u64)(u32)__builtin_amdgcn_readfirstlane((int)(u32)v) | (u64)(u32)__builtin_amdgcn_readfirstlane((int)(u32)(v >> 32)) << 32);
+}
+
 // G > 1: up to G sums of the same rotations, each with plaintexts of its own (the giant steps of a transform): the rotations, kept
-// in the extended basis, meet all of them in registers instead of making a round trip through memory.  The plaintexts of a
-// rotation are requested when it begins and used when its digits are done.
+// in the extended basis, meet all of them in registers instead of making a round trip through memory.
 template <class AR, int W, int G>
 __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables& tb, const PrimeConst& pc, u64* lds, u32 i, u32 row, u32 wave) {
     typedef typename AR::T T;
@@ -1422,97 +1428,174 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
     };
     typedef DhSum<AR, G == 1 ? W : 0> Sum;  // G > 1: no registers for 128-bit sums
     Sum acc0[G][W], acc1[G][W];
-    // terms of a rotation: digits 0 .. dnum - 1, then (q-limbs) b times P.  The words of the next term, also across
-    // rotations, are requested before this one is worked on: a wavefront of the wide form has 12 KiB in flight.
-    const u32 n_terms = tb.dnum + (is_q ? 1 : 0);
-    u64 sv[W], kv0[W], kv1[W], ptv[G][W];
+    typedef const u64 __attribute__((address_space(1))) * Global;  // known to be global behind an opaque selection
     const u64 *ct = a.ct, *dt = a.dt;
-#pragma unroll
-    for (int k = 0; k < W; k++) ptv[0][k] = 1;
     const size_t pt_step = (size_t)a.pt_limbs * N;
-    // EVEN: every request is the same number of loads, and what a term does not need is the source row once more (L2): behind
-    // a branch that may skip some, the compiler waits for all of them before the previous term's words are used.  The narrow
-    // form gains (18 rotations, L + K = 12 + 4, dnum = 3: 360 -> 354 us), the wide one loses by the extra loads (24 + 6: 672 -> 684).
-    constexpr bool EVEN = W == 2 && G == 1;
-    auto request = [&](u32 r, u32 j, u64 (&s)[W], u64 (&k0)[W], u64 (&k1)[W], u64 (&p)[W]) __attribute__((always_inline)) {
-        const u32 src_off = eval_perm(row_off, a.galois[r], logN) & ~(ROW - 1);
-        const bool is_b = j == tb.dnum;
-        const u64* src = (is_b ? ct + (size_t)i * N : j == own_digit ? ct + ((size_t)L + i) * N : dt + ((size_t)j * D + i) * N) + src_off;
-        const u64* key = a.key[r] + ((size_t)j * 2 * Dkey + pi) * N + row_off;
-        const u64* pt = a.pt + r * pt_step + (size_t)i * N + row_off;
-        if constexpr (EVEN) {
-            typedef const u64 __attribute__((address_space(1))) * Global;  // known to be global behind the opaque selection
-            Global kp = (Global)(is_b ? src : key), kp1 = (Global)(is_b ? src : key + (size_t)Dkey * N), pp = (Global)(j == 0 && a.pt ? pt : src);
-            asm volatile("" : "+s"(kp), "+s"(kp1), "+s"(pp));  // addresses selected, not loads skipped
-            load(src, s, false);
-            load((const u64*)kp, k0, true);
-            load((const u64*)kp1, k1, true);
-            load((const u64*)pp, p, true);
-        } else {
-            load(src, s, false);
-            if (!is_b) {
-                load(key, k0, true);
-                load(key + (size_t)Dkey * N, k1, true);
-            }
-            if (G == 1 && j == 0 && a.pt) load(pt, p, true);
-        }
-    };
+    u64 sv[W], kv0[W], kv1[W];  // the term worked on: row of the digit or of b, both components of the key
     Wide w0[W], w1[W];
 #pragma unroll
     for (int k = 0; k < W; k++) w0[k] = w1[k] = AR::wide_zero();
-    u32 folds = 0, in_sum = 0, rr = a.waves == 1 ? 0 : wave, j = 0;
-    if (rr < a.n_rot) request(rr, 0, sv, kv0, kv1, ptv[0]);
-    while (rr < a.n_rot) {
-        if constexpr (G > 1) {
-#pragma unroll
-            for (int g = 0; g < G; g++)
-                load(a.pt + ((size_t)g * a.n_rot + rr) * pt_step + (size_t)i * N + row_off, ptv[g], true);
-        }
-        u32 idx[W];
+    u32 folds = 0, in_sum = 0, rr = a.waves == 1 ? 0 : wave, idx[W];
+    auto permutation = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < W; k++) idx[k] = eval_perm(row_off + (k >> 1) * 128 + lane * 2 + (k & 1), a.galois[rr], logN) & (ROW - 1);
-        T d0[W], d1[W];  // G > 1: the rotation's digit sums
-        if constexpr (G > 1) {
+    };
+    auto permute = [&]() __attribute__((always_inline)) {
+        row_sync();  // the previous term's words have been read
+#pragma unroll
+        for (int h = 0; h < W / 2; h++) {
+            u64x2 t;
+            t.x = sv[2 * h], t.y = sv[2 * h + 1];
+            *reinterpret_cast<u64x2*>(stage + h * 128 + lane * 2) = t;
+        }
+        row_sync();
+#pragma unroll
+        for (int k = 0; k < W; k++) sv[k] = stage[idx[k]];
+    };
+    if constexpr (G > 1) {
+        // Terms of a rotation: digits 0 .. dnum - 1, then one for every two plaintexts, the first of which also brings b (times P, on
+        // q-limbs).  The words of the next term, also across rotations, are requested before this one is worked on, and no request
+        // depends on a branch: behind one that may skip a load, the compiler waits for all of them before the previous term's words
+        // are used.  The digits end before the plaintexts come, so that no register holds a plaintext meanwhile: 104 registers and
+        // four waves per SIMD with four sums where a loop over all terms took 168 and three (8 x 4 transform at N = 2^16, 24 + 6
+        // limbs: 387 -> 354 us, 1.6 GB).
+        constexpr u32 PT = (G + 1) / 2;
+        u64 sn[W], kn0[W], kn1[W];
+        auto source = [&](u32 r) { return eval_perm(row_off, a.galois[r], logN) & ~(ROW - 1); };
+        auto request_digit = [&](u32 r, u32 j, u64 (&s)[W], u64 (&k0)[W], u64 (&k1)[W]) __attribute__((always_inline)) {
+            const u64* key = a.key[r] + ((size_t)j * 2 * Dkey + pi) * N + row_off;
+            Global row = uniform_ptr((Global)((j == own_digit ? ct + ((size_t)L + i) * N : dt + ((size_t)j * D + i) * N) + source(r)));
+            asm volatile("" : "+s"(row));  // the address is selected, not the load skipped
+            load((const u64*)row, s, false);
+            load(key, k0, true);
+            load(key + (size_t)Dkey * N, k1, true);
+        };
+        // plaintexts 2u and 2u + 1; u = 0: and b, or, on special limbs, a row that is not used
+        auto request_pt = [&](u32 r, u32 u, u64 (&s)[W], u64 (&k0)[W], u64 (&k1)[W]) __attribute__((always_inline)) {
+            const u64* pt = a.pt + ((size_t)(2 * u) * a.n_rot + r) * pt_step + (size_t)i * N + row_off;
+            Global row = uniform_ptr((Global)((is_q ? ct : dt) + (size_t)i * N + source(r)));
+            asm volatile("" : "+s"(row));
+            if (u == 0) load((const u64*)row, s, false);
+            load(pt, k0, true);
+            if (2 * u + 1 < G) load(pt + (size_t)a.n_rot * pt_step, k1, true);
+        };
+        if (rr < a.n_rot) request_digit(rr, 0, sv, kv0, kv1);
+        while (rr < a.n_rot) {
+            permutation();
+            T d0[W], d1[W];  // the rotation's digit sums
 #pragma unroll
             for (int k = 0; k < W; k++) d0[k] = d1[k] = AR::acc_zero();
-        }
-        for (; j < n_terms; j++) {
-            const bool last = j + 1 == n_terms;
-            const bool more = !last || rr + a.waves < a.n_rot;  // else (EVEN) this term once more, unused
-            u64 sn[W], kn0[W], kn1[W], pn[W];
+            auto join = [&](bool last) __attribute__((always_inline)) {
 #pragma unroll
-            for (int k = 0; k < W; k++) pn[k] = 1;
-            if (EVEN || more) request(more && last ? rr + a.waves : rr, !more ? j : last ? 0 : j + 1, sn, kn0, kn1, pn);
-            row_sync();  // the previous term's words have been read
+                for (int k = 0; k < W; k++) {
+                    join_part<AR>(d0[k], AR::wide_reduce(w0[k], m), last, m);
+                    join_part<AR>(d1[k], AR::wide_reduce(w1[k], m), last, m);
+                    w0[k] = w1[k] = AR::wide_zero();
+                }
+                in_sum = 0;
+            };
+            auto advance = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int h = 0; h < W / 2; h++) {
-                u64x2 t;
-                t.x = sv[2 * h], t.y = sv[2 * h + 1];
-                *reinterpret_cast<u64x2*>(stage + h * 128 + lane * 2) = t;
-            }
-            row_sync();
-#pragma unroll
-            for (int k = 0; k < W; k++) sv[k] = stage[idx[k]];
-            if (j == tb.dnum) {
-#pragma unroll
-                for (int k = 0; k < W; k++) AR::wide_mac(w0[k], sv[k], pmod);
-            } else {
+                for (int k = 0; k < W; k++) sv[k] = sn[k], kv0[k] = kn0[k], kv1[k] = kn1[k];
+            };
+            auto digit = [&]() __attribute__((always_inline)) {
+                permute();
 #pragma unroll
                 for (int k = 0; k < W; k++) AR::wide_mac(w0[k], sv[k], kv0[k]), AR::wide_mac(w1[k], sv[k], kv1[k]);
+                if (++in_sum == AR::wide_terms) join(false);
+                advance();
+            };
+            for (u32 j = 1; j < tb.dnum; j++) {
+                request_digit(rr, j, sn, kn0, kn1);
+                digit();
             }
-            if (++in_sum == AR::wide_terms || last) {
-                in_sum = 0;
-                if constexpr (G > 1) {
+            request_pt(rr, 0, sn, kn0, kn1);
+            digit();
+            ++folds;  // FP64: at most 8 products (0.875 q each, join_part) between reductions
+            const u32 next = rr + a.waves < a.n_rot ? rr + a.waves : rr;  // at the end a term once more, unused
+#pragma unroll
+            for (u32 u = 0; u < PT; u++) {
+                if (u + 1 < PT) request_pt(rr, u + 1, sn, kn0, kn1);
+                else request_digit(next, 0, sn, kn0, kn1);
+                if (u == 0) {
+                    if (is_q) {
+                        permute();
+#pragma unroll
+                        for (int k = 0; k < W; k++) AR::wide_mac(w0[k], sv[k], pmod);
+                    }
+                    join(true);
+                }
+#pragma unroll
+                for (u32 g = 2 * u; g < (u32)G && g < 2 * u + 2; g++) {
 #pragma unroll
                     for (int k = 0; k < W; k++) {
-                        join_part<AR>(d0[k], AR::wide_reduce(w0[k], m), last, m);
-                        join_part<AR>(d1[k], AR::wide_reduce(w1[k], m), last, m);
-                        w0[k] = w1[k] = AR::wide_zero();
+                        acc0[g][k].add(d0[k], g & 1 ? kv1[k] : kv0[k], m);
+                        acc1[g][k].add(d1[k], g & 1 ? kv1[k] : kv0[k], m);
+                        if ((folds & 7) == 0) acc0[g][k].fold(m), acc1[g][k].fold(m);
+                        __builtin_amdgcn_sched_barrier(0);  // one product's temporaries at a time
                     }
+                }
+                advance();
+            }
+            rr += a.waves;
+        }
+    } else {
+        // terms of a rotation: digits 0 .. dnum - 1, then (q-limbs) b times P.  The words of the next term, also across
+        // rotations, are requested before this one is worked on: a wavefront of the wide form has 12 KiB in flight.
+        const u32 n_terms = tb.dnum + (is_q ? 1 : 0);
+        u64 ptv[W];
+#pragma unroll
+        for (int k = 0; k < W; k++) ptv[k] = 1;
+        // EVEN: every request is the same number of loads, and what a term does not need is the source row once more (L2): behind
+        // a branch that may skip some, the compiler waits for all of them before the previous term's words are used.  The narrow
+        // form gains (18 rotations, L + K = 12 + 4, dnum = 3: 360 -> 354 us), the wide one loses by the extra loads (24 + 6: 672 -> 684).
+        constexpr bool EVEN = W == 2;
+        auto request = [&](u32 r, u32 j, u64 (&s)[W], u64 (&k0)[W], u64 (&k1)[W], u64 (&p)[W]) __attribute__((always_inline)) {
+            const u32 src_off = eval_perm(row_off, a.galois[r], logN) & ~(ROW - 1);
+            const bool is_b = j == tb.dnum;
+            const u64* src = (is_b ? ct + (size_t)i * N : j == own_digit ? ct + ((size_t)L + i) * N : dt + ((size_t)j * D + i) * N) + src_off;
+            const u64* key = a.key[r] + ((size_t)j * 2 * Dkey + pi) * N + row_off;
+            const u64* pt = a.pt + r * pt_step + (size_t)i * N + row_off;
+            if constexpr (EVEN) {
+                Global kp = (Global)(is_b ? src : key), kp1 = (Global)(is_b ? src : key + (size_t)Dkey * N), pp = (Global)(j == 0 && a.pt ? pt : src);
+                asm volatile("" : "+s"(kp), "+s"(kp1), "+s"(pp));  // addresses selected, not loads skipped
+                load(src, s, false);
+                load((const u64*)kp, k0, true);
+                load((const u64*)kp1, k1, true);
+                load((const u64*)pp, p, true);
+            } else {
+                load(src, s, false);
+                if (!is_b) {
+                    load(key, k0, true);
+                    load(key + (size_t)Dkey * N, k1, true);
+                }
+                if (j == 0 && a.pt) load(pt, p, true);
+            }
+        };
+        u32 j = 0;
+        if (rr < a.n_rot) request(rr, 0, sv, kv0, kv1, ptv);
+        while (rr < a.n_rot) {
+            permutation();
+            for (; j < n_terms; j++) {
+                const bool last = j + 1 == n_terms;
+                const bool more = !last || rr + a.waves < a.n_rot;  // else (EVEN) this term once more, unused
+                u64 sn[W], kn0[W], kn1[W], pn[W];
+#pragma unroll
+                for (int k = 0; k < W; k++) pn[k] = 1;
+                if (EVEN || more) request(more && last ? rr + a.waves : rr, !more ? j : last ? 0 : j + 1, sn, kn0, kn1, pn);
+                permute();
+                if (j == tb.dnum) {
+#pragma unroll
+                    for (int k = 0; k < W; k++) AR::wide_mac(w0[k], sv[k], pmod);
                 } else {
 #pragma unroll
+                    for (int k = 0; k < W; k++) AR::wide_mac(w0[k], sv[k], kv0[k]), AR::wide_mac(w1[k], sv[k], kv1[k]);
+                }
+                if (++in_sum == AR::wide_terms || last) {
+                    in_sum = 0;
+#pragma unroll
                     for (int k = 0; k < W; k++) {
-                        const u64 ptk = EVEN && !a.pt ? 1 : ptv[0][k];
+                        const u64 ptk = EVEN && !a.pt ? 1 : ptv[k];
                         acc0[0][k].add(AR::wide_reduce(w0[k], m), ptk, m);
                         acc1[0][k].add(AR::wide_reduce(w1[k], m), ptk, m);
                         w0[k] = w1[k] = AR::wide_zero();
@@ -1522,34 +1605,22 @@ __device__ __forceinline__ void dh_accum_body(const DhInnerArgs& a, const Tables
                         for (int k = 0; k < W; k++) acc0[0][k].fold(m), acc1[0][k].fold(m);
                     }
                 }
-            }
 #pragma unroll
-            for (int k = 0; k < W; k++) {
-                sv[k] = sn[k], kv0[k] = kn0[k], kv1[k] = kn1[k];
-                if (G == 1 && last) ptv[0][k] = pn[k];
-            }
-        }
-        if constexpr (G > 1) {
-            ++folds;  // FP64: at most 8 products (0.875 q each, join_part) between reductions
-#pragma unroll
-            for (int k = 0; k < W; k++)
-#pragma unroll
-                for (int g = 0; g < G; g++) {
-                    acc0[g][k].add(d0[k], ptv[g][k], m);
-                    acc1[g][k].add(d1[k], ptv[g][k], m);
-                    if ((folds & 7) == 0) acc0[g][k].fold(m), acc1[g][k].fold(m);
-                    __builtin_amdgcn_sched_barrier(0);  // one product's temporaries at a time
+                for (int k = 0; k < W; k++) {
+                    sv[k] = sn[k], kv0[k] = kn0[k], kv1[k] = kn1[k];
+                    if (last) ptv[k] = pn[k];
                 }
-        }
-        if (G == 1 && a.each) {
-            T t0[W], t1[W];
+            }
+            if (a.each) {
+                T t0[W], t1[W];
 #pragma unroll
-            for (int k = 0; k < W; k++) t0[k] = acc0[0][k].get(m), t1[k] = acc1[0][k].get(m), acc0[0][k] = acc1[0][k] = Sum();
-            store(t0, out(rr, 0));
-            store(t1, out(rr, 1));
-            folds = 0;
+                for (int k = 0; k < W; k++) t0[k] = acc0[0][k].get(m), t1[k] = acc1[0][k].get(m), acc0[0][k] = acc1[0][k] = Sum();
+                store(t0, out(rr, 0));
+                store(t1, out(rr, 1));
+                folds = 0;
+            }
+            j = 0, rr += a.waves;
         }
-        j = 0, rr += a.waves;
     }
     if (G == 1 && a.each) return;
 #pragma unroll
@@ -1602,7 +1673,7 @@ __device__ __forceinline__ void dh_accum_workgroup(const DhInnerArgs& a, const T
 template <class AR, int W>
 __global__ __launch_bounds__(256, W == 4 ? 3 : 5) void dh_accum_kernel(DhInnerArgs a, Tables tb) { dh_accum_workgroup<AR, W, 1>(a, tb); }
 template <class AR, int W, int G>
-__global__ __launch_bounds__(256, 3) void dh_accum_kernel(DhInnerArgs a, Tables tb) { dh_accum_workgroup<AR, W, G>(a, tb); }
+__global__ __launch_bounds__(256, 4) void dh_accum_kernel(DhInnerArgs a, Tables tb) { dh_accum_workgroup<AR, W, G>(a, tb); }
 
 // ==================================================== baby-step giant-step accumulation and sums
 // C[g][t][i] = sum_b pt[g][b][i] * R[b][t][i] on every limb i of the extended basis: the giant-step
