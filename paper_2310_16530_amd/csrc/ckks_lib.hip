@@ -499,7 +499,7 @@ extern "C" int ckks_ctx_create(ckks_ctx** out, uint32_t logN, uint32_t L, uint32
         p.qd = (double)m;  // exact for FpAr primes
         p.qinv = 1.0 / (double)m;
         p.fp = fp ? 1 : 0;
-        p.pad = 0;
+        p.narrow = fp && m <= CKKS_FP_NARROW_MAX ? 1 : 0;
         ninv[i] = h_invmod(N % m, m);
         wlast[i] = fw[2 * N + 1];
         sc_plain[i] = make_scale(1, ninv[i], wlast[i], m, fp);

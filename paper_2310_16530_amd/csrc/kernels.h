@@ -636,8 +636,9 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
             const Buf dst(dst0 + (size_t)vi * N);
             if (again) __syncthreads();  // the previous target's exchange has been read
             again = true;
+            AR::mid_reduce(x, m);
 #pragma unroll
-            for (int k = 0; k < 16; k++) lds[k * 256 + tid] = AR::to_raw(AR::round_reduce(x[k], m));
+            for (int k = 0; k < 16; k++) lds[k * 256 + tid] = AR::to_raw(x[k]);
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lds[(r0 * 16 + k) * C::TC + c]);
@@ -689,6 +690,7 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
     typedef StridedTw<AR, A> TW;
     typedef typename AR::T T;
     static_assert(SETS == 1 || NTT == 1, "two targets or two positions a lane");
+    static_assert(SETS == 1 || !AR::is_fp, "FP64 sums are reduced before their exchange");
     constexpr u32 TILES = (1u << A) / 16, TPW = 2 * NTT;  // targets per workgroup
     const u32 N = 1u << tb.logN, lane = tid & 63, wave = tid >> 6, n = lane & 31, h = lane >> 5;
     const u32 tile = group % TILES;
@@ -721,6 +723,11 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
         const u32 t = run.first + inst * TPW + (sl < nt ? sl : 0);
         return skip_n && t >= skip_lo ? t + skip_n : t;
     };
+    bool narrow = true;  // of every target of the workgroup, so that the lane halves agree
+    if constexpr (AR::is_fp) {
+#pragma unroll
+        for (u32 sl = 0; sl < TPW; sl++) narrow &= tb.pc[tb.phys(limb_of(sl))].narrow != 0;
+    }
     v4i aop[KS];
     {
         const u32 sl = (NTT == 2 ? (n >> 4) * 2 : 0) + ((n >> 2) & 1), dg = ((n >> 3) & 1) * 4 + (n & 3), t = limb_of(sl);
@@ -800,7 +807,7 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
 #pragma unroll
                     for (u32 v = 0; v < 2; v++)
 #pragma unroll
-                        for (int k = 0; k < 16; k++) lds[k * 256 + wave * 64 + v * 32 + n] = AR::to_raw(AR::round_reduce(x[v][k], m));
+                        for (int k = 0; k < 16; k++) lds[k * 256 + wave * 64 + v * 32 + n] = AR::to_raw(x[v][k]);  // integers: no reduction
                 }
                 __syncthreads();
                 T y[16];
@@ -825,9 +832,13 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
         if (2 * u >= nt) break;
         if constexpr (A > 4) {
             if (u) __syncthreads();  // the first exchange has been read
-            const typename AR::Mod mx = AR::mod(tb.pc[tb.phys(limb_of(2 * u + h))]);
+            if (AR::is_fp && !narrow) {
+                const typename AR::Mod mx = AR::mod(tb.pc[tb.phys(limb_of(2 * u + h))]);
 #pragma unroll
-            for (int k = 0; k < 16; k++) lds[h * 4096 + k * 256 + wave * 32 + n] = AR::to_raw(AR::round_reduce(x[u][k], mx));
+                for (int k = 0; k < 16; k++) x[u][k] = AR::round_reduce(x[u][k], mx);
+            }
+#pragma unroll
+            for (int k = 0; k < 16; k++) lds[h * 4096 + k * 256 + wave * 32 + n] = AR::to_raw(x[u][k]);
             __syncthreads();
             const u32 half = tid >> 8, sl = 2 * u + half, st = tid & 255, c = st % C::TC, r1 = st / C::TC;
             if (sl < nt) {  // uniform per wave
@@ -1121,7 +1132,10 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
     T acc0[16], acc1[16];  // layout CP
 #pragma unroll
     for (int k = 0; k < 16; k++) acc0[k] = AR::acc_zero(), acc1[k] = AR::acc_zero();
+    // FpAr sums at most 8 lazily reduced products (0.69 q each) between reductions; narrow primes five of digits that were not reduced
+    // (2.6 q each: 13.5 q with what is left of the sum before)
     u32 since = 0;
+    const u32 fold_at = AR::is_fp && AR::narrow(m) ? 5 : 8;
     for (u32 jj = part; jj < (SUM ? a.n_sum : 1) * tb.dnum; jj += ways) {
         u32 j = jj, src = inst;
         if constexpr (SUM) {  // digits in rotated order: the cheap own digits spread over the wavefronts that share the row
@@ -1188,8 +1202,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
             for (int k = 0; k < 16; k++) v[k] = AR::from_raw(__builtin_nontemporal_load(&p[k * 16 + e0]));
             if constexpr (TWL) NttCore<AR, A>::fwd_contig_with(v, lrow, e0, RowTwLds{twblk, e0}, m);
             else NttCore<AR, A>::fwd_contig(v, lrow, e0, r, ti, tf, N, m);
-#pragma unroll
-            for (int k = 0; k < 16; k++) v[k] = AR::round_reduce(v[k], m);
+            AR::mid_reduce(v, m);
             exchange_cb_to_cp<AR>(v, lrow, e0);
         }
         if constexpr (!EARLY0) load_row_cp<false>(k0, e0, kv0);
@@ -1198,7 +1211,8 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         if constexpr (!EARLY1) load_row_cp<false>(k1, e0, kv1);
 #pragma unroll
         for (int k = 0; k < 16; k++) AR::acc_mac(acc1[k], v[k], kv1[k], m);
-        if ((++since & 7) == 0) {  // FpAr sums at most 8 lazily reduced products (0.69 q each) between reductions
+        if (++since == fold_at) {
+            since = 0;
 #pragma unroll
             for (int k = 0; k < 16; k++) acc0[k] = AR::acc_fold(acc0[k], m), acc1[k] = AR::acc_fold(acc1[k], m);
         }
@@ -1234,7 +1248,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         // c' stays in registers: out = (c' - second forward pass of the converted special part) * P^-1
         // (+ sigma_g(b) on the first component of a rotation; adding it as P * sigma_g(b) where sigma_g(a) is
         // gathered measured slower: the accumulation loop has no registers for it).  FP64 magnitudes in units
-        // of q: c' <= 0.5, v <= 5.2, the product with P^-1 <= 2.9; canonicalised before the store.
+        // of q: c' <= 0.5, v <= 5.2 (narrow primes 10.5), the product with P^-1 <= 2.9; canonicalised before the store.
         // Opaque copies of the lane coordinates: every address of this part is derived from them, so none of
         // it is computed before the accumulation loop, which has no registers to spare.
         u32 e0f = e0, chf = ch, gal_fin = gal;
@@ -1791,7 +1805,7 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
     const u64 q = pc.q;
     // The converted part leaves its second forward pass in layout CP: c', plaintexts and results move with 16-byte
     // accesses, and sigma_g(b) comes as a whole source row permuted in LDS (gather_row_cp).
-    // FP64 pipe (magnitudes in units of q): v <= 5.2, c' - v <= 6.2, ks = (c' - v) * P^-1 <= 2.9,
+    // FP64 pipe (magnitudes in units of q): v <= 5.2, c' - v <= 6.2, ks = (c' - v) * P^-1 <= 2.9 (narrow primes 10.5, 11.5, 2.8),
     // every added product of canonical operands <= 0.875; everything is canonicalised before the store.
     if (MODE == FIN_HOISTED) {
         const u32 t = inst;
@@ -1832,10 +1846,12 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
             {
                 u64 ptw[16];
                 load_row_cp<true>(a.pt + ((size_t)rr * L + i) * N + row_off, e0, ptw);
+                AR::mid_reduce(ks, m);
 #pragma unroll
                 for (int k = 0; k < 16; k++) {
-                    // FP64: reduced to <= q/2 so that the at most 8 products accumulated between folds stay below 6 q
-                    if constexpr (AR::is_fp) facc[k] += FpAr::mulmod_lazy(FpAr::reduce(ks[k], FpAr::mod(pc)), u64_to_f64(ptw[k]), FpAr::mod(pc));
+                    // FP64: ks reduced to <= q/2, so that the at most 8 products accumulated between folds stay below 6 q; narrow primes:
+                    // ks <= 3.8 q, 1.3 q a product
+                    if constexpr (AR::is_fp) facc[k] += FpAr::mulmod_lazy(ks[k], u64_to_f64(ptw[k]), FpAr::mod(pc));
                     else mac128(iacc[k], ks[k], ptw[k]);
                 }
             }
@@ -1864,7 +1880,8 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
         return;
     }
     if (MODE == FIN_SUMMED) {
-        const u32 t = inst;
+        const u32 t = inst, fold_at = AR::is_fp && AR::narrow(m) ? 5 : 8;
+        u32 since = 0;
         double facc[AR::is_fp ? 16 : 1];
         u128w iacc[AR::is_fp ? 1 : 16];
 #pragma unroll
@@ -1881,14 +1898,16 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
             load_row_cp<true>(a.pt + ((size_t)rr * L + i) * N + row_off, e0, ptw);
             NttCore<AR, A>::fwd_contig(v, lrow, e0, r, ti, tf, N, m);
             exchange_cb_to_cp<AR>(v, lrow, e0);
+            AR::mid_reduce(v, m);
 #pragma unroll
             for (int k = 0; k < 16; k++) {
-                // FP64: reduced to <= q/2 so that the at most 8 products accumulated between folds stay below 6 q.  Integers: a
-                // term below 2q * q < q * 2^62, eight of them on hi < q below 3q * 2^64; hi alone takes multiples of q * 2^64 off
-                if constexpr (AR::is_fp) facc[k] += FpAr::mulmod_lazy(FpAr::reduce(v[k], FpAr::mod(pc)), u64_to_f64(ptw[k]), FpAr::mod(pc));
+                // FP64: reduced to <= q/2 so that the at most 8 products accumulated between folds stay below 6 q; narrow primes: not
+                // reduced, 2.6 q a product, five between folds.  Integers: a term below 2q * q < q * 2^62, eight of them on hi < q below 3q * 2^64; hi alone takes multiples of q * 2^64 off
+                if constexpr (AR::is_fp) facc[k] += FpAr::mulmod_lazy(v[k], u64_to_f64(ptw[k]), FpAr::mod(pc));
                 else mac128(iacc[k], csub(csub(v[k], 4 * q), 2 * q), ptw[k]);
             }
-            if ((rr & 7) == 7) {
+            if (++since == fold_at) {
+                since = 0;
 #pragma unroll
                 for (int k = 0; k < 16; k++) {
                     if constexpr (AR::is_fp) facc[k] = FpAr::reduce(facc[k], FpAr::mod(pc));

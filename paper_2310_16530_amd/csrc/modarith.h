@@ -17,6 +17,9 @@
 //   gives r = a*w (mod q) with |r| <= (0.5 + 3A/8) q.  Four forward stages started from |x| <= q
 //   stay below 7q, four inverse stages started from |x| <= q/2 stay at or below 8q < 2^53; a
 //   3-instruction reduction x - rint(x/q)*q brings values back to |x| <= q/2 between rounds.
+//   Narrow primes, q <= 17*2^45: the quotient is off by 0.5 + 3A q/2^53 <= 0.5 + 0.2A, so a stage takes A to at most 1.2A + 0.5: eight
+//   forward stages from |x| <= 0.51q end below 10.5q (1.12, 1.84, 2.71, 3.75, 5.0, 6.5, 8.3, 10.5), from canonical words below 12.6q,
+//   and 2^53 is 15q.  What leaves such a pass unreduced makes products with residues of at most 2.6q.
 //
 // All functions are __host__ __device__ so that the same source is unit-tested on the CPU.
 #pragma once
@@ -31,6 +34,8 @@ typedef unsigned __int128 u128_t;
 
 // primes strictly below this bound use FpAr
 #define CKKS_FP_PRIME_LIMIT (3ull << 48)
+// FpAr primes up to this bound (49 bits and a little) are narrow: a forward pass of eight stages reduces nothing on its way, see FpAr
+#define CKKS_FP_NARROW_MAX (17ull << 45)
 
 struct u128w {
     u64 lo, hi;
@@ -95,7 +100,7 @@ struct PrimeConst {
     double qd;    // q as a double (exact for FpAr primes)
     double qinv;  // fl(1/q)
     u32 fp;       // 1 if the prime uses FpAr
-    u32 pad;
+    u32 narrow;   // 1 if it is at most CKKS_FP_NARROW_MAX
 };
 
 // scaling constants of the last inverse-NTT stage: sx multiplies the sums, sy the differences
@@ -149,6 +154,9 @@ struct IntAr {
         Y = mul_shoup_lazy(d, t.w, t.wp, m.q);
     }
     static HD T round_reduce(T v, const Mod&) { return v; }  // lazy ranges are invariants: nothing to do
+    static HD bool narrow(const Mod&) { return true; }
+    template <int W>
+    static HD void mid_reduce(T (&)[W], const Mod&) {}
     static HD u64 canon_fwd(T v, const Mod& m) { return csub(csub(csub(v, m.q2 + m.q2), m.q2), m.q); }  // from [0, 8q)
     // last inverse stage with scaling, canonical results (fmt: SRC_CANON or SRC_DIGITS; SRC_F64 does not apply)
     static HD void bfly_inv_last(T& X, T& Y, const InvScale& s, const Mod& m, u32 fmt, u64& ox, u64& oy) {
@@ -205,11 +213,12 @@ struct FpAr {
     static constexpr bool is_fp = true;
     struct Mod {
         double q, qinv;
+        u32 narrow_;
     };
     struct Tw {
         double w;
     };
-    static HD Mod mod(const PrimeConst& p) { return Mod{p.qd, p.qinv}; }
+    static HD Mod mod(const PrimeConst& p) { return Mod{p.qd, p.qinv, p.narrow}; }
     // tables: tw_fp [prime][2][N] = fwd w, inv w (as doubles)
     static HD Tw tw(const u64*, const double* tf, u32 idx, u32 N, bool inverse) {
         return Tw{tf[(inverse ? (size_t)N : 0) + idx]};
@@ -252,6 +261,18 @@ struct FpAr {
         Y = mulmod_lazy(d, t.w, m);
     }
     static HD T round_reduce(T v, const Mod& m) { return reduce(v, m); }
+    static HD bool narrow(const Mod& m) { return m.narrow_ != 0; }
+    // between the two halves of a forward pass, and where its results meet canonical factors: nothing for narrow primes.  Three of the
+    // four reductions a word meets between a conversion and a key product, bound by issue (N = 2^16, 24 + 6 limbs, batch 8, just
+    // above 2^49: conversion 116 -> 110 us, inner product 258 -> 248, ModDown conversion 74 -> 71; the whole HMult 707 -> 692, 17
+    // hoisted rotations 1011 -> 998; wider primes as before)
+    template <int W>
+    static HD void mid_reduce(T (&x)[W], const Mod& m) {
+        if (!narrow(m)) {
+#pragma unroll
+            for (int k = 0; k < W; k++) x[k] = reduce(x[k], m);
+        }
+    }
     static HD u64 canon(T v, const Mod& m) {
         double r = reduce(v, m);
         r = r < 0.0 ? r + m.q : r;

@@ -58,8 +58,9 @@ struct NttCore {
         }
         if constexpr (A > 4) {
             const u32 c = tid % TC, r1 = tid / TC;
+            AR::mid_reduce(x, m);
 #pragma unroll
-            for (int k = 0; k < 16; k++) lds[k * 256 + tid] = AR::to_raw(AR::round_reduce(x[k], m));
+            for (int k = 0; k < 16; k++) lds[k * 256 + tid] = AR::to_raw(x[k]);
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lds[(r1 * 16 + k) * TC + c]);
@@ -94,8 +95,9 @@ struct NttCore {
                 else AR::template bfly_fwd<true>(x[k], x[k + d], tw.get(u, (u32)k * 16 + e0), m);
             }
         }
+        AR::mid_reduce(x, m);
 #pragma unroll
-        for (int k = 0; k < 16; k++) l[pad16(k * 16 + e0)] = AR::to_raw(AR::round_reduce(x[k], m));
+        for (int k = 0; k < 16; k++) l[pad16(k * 16 + e0)] = AR::to_raw(x[k]);
         typename AR::Tw t[AHEAD ? 15 : 1];  // stage u at 2^(u-4) - 1, one per 2^(8-u) words
         if constexpr (AHEAD) {
 #pragma unroll
