@@ -1979,13 +1979,14 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
         launch_extended_fwd_contig(c, w, s);
     };
     if (hoisted_summed(c, n_rot)) {
-        // Equal parts of at most CKKS_ROT_CHUNK rotations, a launch of the special limbs' inner product each, and as many of them to a chunk
-        // as the workspace has room for: x and dt, then the sum on the q-limbs ([2][L]) and, per rotation, the special limbs ([2][K])
-        // and the converted part ([2][L]).  The workspace of CKKS_ROT_CHUNK rotations of the other form holds one part at least.
+        // Equal chunks of as many rotations as the workspace has room for: x and dt, then the sum on the q-limbs ([2][L]) and, per
+        // rotation, the special limbs ([2][K]) and the converted part ([2][L]).  That of CKKS_ROT_CHUNK rotations of the other form
+        // holds as many at least.  One launch of the special limbs for a chunk: in two, of equal parts, each ends in a round of
+        // workgroups that is half empty (N = 2^16, 24 + 6 limbs: 17 rotations 990 -> 979 us, 18 1043 -> 1020, 24 1331 -> 1303; 16 and 32 even).
         Workspace w = carve(c, d_ws, 1, 1, 1);
         u64 *const cq = w.cq, *const cp = cq + (size_t)2 * c->L * N;
         const size_t fit = (need / sizeof(u64) / N - 3 * (size_t)c->L - (size_t)c->dnum * c->D) / (2 * (size_t)c->D);
-        const u32 part = cdiv(n_rot, cdiv(n_rot, CKKS_ROT_CHUNK)), chunk = part * (fit < CKKS_DH_CHUNK ? (u32)fit / part : CKKS_DH_CHUNK / part);
+        const u32 chunk = cdiv(n_rot, cdiv(n_rot, fit < CKKS_DH_CHUNK ? (u32)fit : CKKS_DH_CHUNK));
         // Second stream: the integer special limbs' inner products and inverse transforms beside the sum on the q-limbs.  Not where the
         // special limbs mix the arithmetics, whose joint launches it would split (one stream / two, us: 40 + 9 limbs, 49, 59 and 60 bits in
         // turn, N = 2^14, 17 rotations 598 / 889, 32 960 / 1281; 24 + 6, N = 2^15, 17 588 / 754, 32 1013 / 1173; all of 59 bits 551 / 546,
@@ -2002,14 +2003,11 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
             da.n_rot = nr, da.split = c->L;
             if (fork) fork_side(c, s);  // no-op in the first chunk (still forked); later chunks wait for the previous ModDown
             launch_dh_accum(c, da, s, c->L);
-            for (u32 f = 0; f < nr; f += part) {
-                InnerArgs ia;
-                memset(&ia, 0, sizeof(ia));
-                ia.n_inst = nr - f < part ? nr - f : part;
-                for (u32 r = 0; r < ia.n_inst; r++) ia.key[r] = da.key[f + r], ia.galois[r] = da.galois[f + r];
-                ia.dt = w.dt, ia.own = d_ct, ia.cp = cp + (size_t)f * 2 * c->K * N, ia.split = c->L;
-                launch_ks_inner<OWN_COPY, true>(c, ia, s, c->L, c->D);
-            }
+            InnerArgs ia;
+            memset(&ia, 0, sizeof(ia));
+            for (u32 r = 0; r < nr; r++) ia.key[r] = da.key[r], ia.galois[r] = da.galois[r];
+            ia.dt = w.dt, ia.own = d_ct, ia.cp = cp, ia.n_inst = nr, ia.split = c->L;
+            launch_ks_inner<OWN_COPY, true>(c, ia, s, c->L, c->D);
             w.cp = cp, w.cv = cp + (size_t)nr * 2 * c->K * N;
             moddown_convert(c, w, nr, s);
             FinalArgs fa;

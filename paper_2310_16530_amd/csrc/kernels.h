@@ -162,6 +162,8 @@ struct Buf {
 
 // most rotations (each with its own key and Galois element) one launch can be given
 #define CKKS_ROT_CHUNK 16
+// ... and where it leaves one sum, or the special limbs of each alone
+#define CKKS_DH_CHUNK 32
 
 // ============================================================ inverse transform, first pass
 enum InvLoad { INV_PLAIN = 0, INV_TENSOR = 1, INV_ROT = 2 };
@@ -1054,8 +1056,8 @@ struct InnerArgs {
     const u64* dt;    // [inst or 1][dnum][D][N]: raw forward-lazy (NTT_INSIDE) or canonical eval (hoisted)
     const u64* own;   // COPY: d [inst][L][N]; TENSOR: ct1; ROT: ct ([inst][2][L][N]); hoisted: ct [2][L][N]
     const u64* own2;  // TENSOR: ct2
-    const u64* key[CKKS_ROT_CHUNK];  // one shared key (index 0) or one per instance (hoisted)
-    u32 galois[CKKS_ROT_CHUNK];      // ROT: [0]; hoisted: per instance
+    const u64* key[CKKS_DH_CHUNK];  // one shared key (index 0) or one per instance (hoisted: at most CKKS_DH_CHUNK)
+    u32 galois[CKKS_DH_CHUNK];      // ROT: [0]; hoisted: per instance
     u64* cq;                         // [inst][2][L][N] canonical
     u64* cp;                         // [inst][2][D - split][N] raw inverse-lazy after the first inverse pass
     u32 n_inst;
@@ -1353,7 +1355,6 @@ __global__ __launch_bounds__(256, 2) void ks_inner_kernel(InnerArgs a, Tables tb
 // per XCD and its digits stay in the L2; and both arithmetics share one launch.  32 rotations at N = 2^16, L + K = 42,
 // dnum = 5 (7.8 GB of keys and plaintexts): 1673 us in two launches -> 1414 us, 5.5 TB/s; without the shared rows 1623 us,
 // without the early requests 1730 us, with the digit reads removed 1386 us.
-#define CKKS_DH_CHUNK 32
 #define CKKS_DH_SUMS 4
 struct DhInnerArgs {
     const u64* dt;   // [dnum][D][N] canonical evaluation form
