@@ -1623,6 +1623,35 @@ static int check_ks_args(const View* c, const void* a, const void* b, const void
     return CKKS_OK;
 }
 
+// Conversions from a single limb on small grids: the inverse pass that leaves the source's words is repeated by the workgroup of every
+// target, a launch and a round trip less.  Counted in workgroups of a tile and a target.  Calls before / with it, us:
+// ModUp (digits of one limb; both arithmetics' targets share the launch too), HMult with K = 1 as a whole: N = 2^12, 3 + 1 limbs (12
+// workgroups) 52.8 / 43.2, 35-bit primes 36.8 / 32.1, 12 + 1, 2 ciphertexts (312) 78.7 / 70.6; N = 2^13, 3 + 1 (24) 61.6 / 52.2, 12 + 1, 2
+// (624) 92.2 / 87.6 (1000 and more: worse); N = 2^14, 3 + 1 (48) 63.0 / 52.2, 5 + 1, 4 (480) 82.5 / 71; N = 2^16, 3 + 1 (192) 71.5 / 59.8;
+// all of 55 bits 3 to 7 % of the call.
+static bool up_with_inverse(const View* c, u32 batch) {
+    return !c->up.ks && !c->sh->side.active && batch * c->dnum * c->D * tiles_of(c) <= (c->logN <= 13 ? 640u : 448u);
+}
+// ModDown by one prime.  After an inner product, which has run the first inverse pass: HMult with digits of two limbs, N = 2^12, 6 + 1 limbs (12)
+// 59.0 / 57.2, N = 2^16, 6 + 1 (192) 79.6 / 75.7, 8 + 1, 3 ciphertexts (768) 124.3 / 124.9 (an integer special prime).  Rescale: N = 2^14, 24 -> 23
+// limbs (192) 22.7 / 19.4, N = 2^16, 7 limbs (192) 24.3 / 20.7, 25 (768) 36.4 / 35.1, 17, 2 ciphertexts (1024) 42.0 / 41.6, 3 (1536) 55 / 57.
+// whole: both passes in one workgroup: N = 2^12, 17 limbs, 2 (64) 18.6 / 15.5, 23, 9 (396) 26.7 / 26.0 (528: 30.6 / 31.1); N = 2^13, 23, 3
+// (264) 26.0 / 23.3 (400: 28.0 / 31.7), few integer limbs 31.3 / 32.8 (spread_limbs: two passes are the faster ones there).
+static bool dn_with_inverse(const View* c, u32 sources, bool whole) {
+    const u32 tiles = sources * tiles_of(c), most = whole ? c->logN == 12 ? 448 : 288 : c->primes[c->L] >= CKKS_FP_PRIME_LIMIT ? 512 : 768;
+    return c->K == 1 && !c->sh->side.active && tiles * c->L <= most && tiles * cdiv(c->L, 4) < 512;  // fewer than 512: launch_conv takes single targets
+}
+template <int LOAD, int DIR>
+static void launch_inv_whole_conv_one(const View* c, InvContigArgs a, u64* dst, hipStream_t s) {
+    const u32 sources = a.sel.n_inst * a.sel.n_l, targets = DIR == CONV_UP ? c->D : c->L;
+    a.scale = DIR == CONV_UP ? SC_UP : SC_DN, a.out_fmt = SRC_CANON;
+    ProfScope ps(c, c->sh->prof.on ? "inv_whole_conv_one_kernel<" + std::to_string((int)c->logN - 8) + ", " + std::to_string(LOAD) + ", " + std::to_string(DIR) + ">" : std::string(),
+                 (u64)sources * (targets + (LOAD == INV_TENSOR ? 2 : 1)), s);
+    const dim3 grid(xcd_grid(sources, targets));
+    if (c->logN == 12) hipLaunchKernelGGL((inv_whole_conv_one_kernel<4, LOAD, DIR>), grid, dim3(256), 0, s, a, dst, c->tb);
+    else hipLaunchKernelGGL((inv_whole_conv_one_kernel<5, LOAD, DIR>), grid, dim3(512), 0, s, a, dst, c->tb);
+}
+
 // ModUp side shared by every key switch: w.x holds the coefficients of the polynomial(s) times the conversion pre-factor
 // (launch_decompose_inverse); conversion fused into the first forward pass of every extended limb.
 template <int LOAD>
@@ -1633,7 +1662,7 @@ static void launch_decompose_inverse(const View* c, const InvContigArgs& a, hipS
 // integer limbs take the side stream from here on.
 enum ExtendMode { EXTEND_PLAIN, EXTEND_BESIDE, EXTEND_FORK };
 static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipStream_t s, ExtendMode mode) {
-    const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0};
+    const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0, 0};
     SideStream& sd = c->sh->side;
     const bool second = mode != EXTEND_PLAIN && sd.enabled && c->mixed_classes;
     if (conv_up_both(c, a3, s, !second ? 4095 : mode == EXTEND_BESIDE ? 1024 : 512)) {  // before a fork: what follows on either stream comes after it
@@ -1662,6 +1691,31 @@ static void decompose_extend(const View* c, const Workspace& w, u32 groups, hipS
     launch_conv<CONV_UP>(c, a3, s);
 }
 
+// Both: a's limbs into their extended digits
+template <int LOAD>
+static void decompose(const View* c, const InvContigArgs& a, const Workspace& w, hipStream_t s, ExtendMode mode) {
+    const u32 groups = a.sel.n_inst;
+    if (!up_with_inverse(c, groups) || (LOAD == INV_PLAIN && spread_limbs(c, a.sel, 24))) {
+        launch_decompose_inverse<LOAD>(c, a, s);
+        decompose_extend(c, w, groups, s, mode);
+        return;
+    }
+    if (inv_one_kernel((int)c->logN - 8)) {
+        launch_inv_whole_conv_one<LOAD, CONV_UP>(c, a, w.dt, s);
+    } else {
+        launch_inv_contig<LOAD>(c, a, s);
+        ProfScope ps(c, c->sh->prof.on ? "inv_conv_one_kernel<" + std::to_string((int)c->logN - 8) + ">" : std::string(), (u64)groups * c->L * (c->D + 1), s);
+        const dim3 grid(xcd_grid(groups * c->dnum * tiles_of(c), c->D));
+        const ConvArgs a3 = {w.x, w.dt, groups, 0, nullptr, nullptr, 0, 0};
+        switch (c->logN) {
+            case 14: hipLaunchKernelGGL(inv_conv_one_kernel<6>, grid, dim3(256), 0, s, a3, c->tb); break;
+            case 15: hipLaunchKernelGGL(inv_conv_one_kernel<7>, grid, dim3(256), 0, s, a3, c->tb); break;
+            case 16: hipLaunchKernelGGL(inv_conv_one_kernel<8>, grid, dim3(256), 0, s, a3, c->tb); break;
+        }
+    }
+    if (mode == EXTEND_FORK) fork_side(c, s);
+}
+
 // s waits for the FpAr conversion that decompose_extend put on the side stream
 static void join_fp_beside(const View* c, hipStream_t s) {
     SideStream& sd = c->sh->side;
@@ -1677,14 +1731,29 @@ static void join_fp_beside(const View* c, hipStream_t s) {
 // ModDown side: w.cp holds c' on the special limbs after the first inverse pass (done = false) or as coefficients times the
 // conversion pre-factor.  cached: the converted part, from a single source, is stored with ordinary accesses (stores_cached).
 static void moddown_convert(const View* c, const Workspace& w, u32 cg, hipStream_t s, bool done = false, bool cached = false) {
-    if (!done) {
+    const bool inverse = !done && dn_with_inverse(c, cg * 2, false);
+    if (!done && !inverse) {
         const InvStridedArgs a6 = {w.cp, LimbSel{c->K, cg * 2, c->K, 0, c->L}, SC_DN, conv_src_fmt(c->dn, CONV_DN)};
         launch_inv_strided(c, a6, s);
     }
     join_side(c, s);  // the conversion reads every special limb
-    const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, nullptr, nullptr, 0};
+    const ConvArgs a7 = {w.cp, w.cv, cg * 2, 0, nullptr, nullptr, 0, inverse};
     if (cached) launch_conv_runs<ConvOneCachedL, CONV_DN>(c, a7, s, -1);
     else launch_conv<CONV_DN>(c, a7, s);
+}
+
+// the same from the special limbs in evaluation form, a's source: their inverse transform into w.cp and the conversion
+static void moddown_from_eval(const View* c, const InvContigArgs& a, const Workspace& w, u32 cg, hipStream_t s, bool cached = false) {
+    const bool whole = inv_one_kernel((int)c->logN - 8);
+    if (!dn_with_inverse(c, cg * 2, whole) || spread_limbs(c, a.sel, 24)) {
+        launch_inverse<INV_PLAIN>(c, a, SC_DN, conv_src_fmt(c->dn, CONV_DN), s);
+        moddown_convert(c, w, cg, s, true, cached);
+    } else if (whole) {
+        launch_inv_whole_conv_one<INV_PLAIN, CONV_DN>(c, a, w.cv, s);
+    } else {
+        launch_inv_contig<INV_PLAIN>(c, a, s);
+        moddown_convert(c, w, cg, s);
+    }
 }
 
 // second forward pass of every extended digit of one decomposition
@@ -1734,8 +1803,7 @@ static void summed_rotations(const View* c, const u64* in, u32 n, const u32* gal
     memset(&ia, 0, sizeof(ia));
     ia.dt = w.dt, ia.own = in, ia.cp = w.cp, ia.n_inst = n, ia.split = c->L, ia.per_inst = 1;
     for (u32 g = 0; g < n; g++) a1.galois[g] = ia.galois[g] = galois[g], ia.key[g] = keys[g];
-    launch_decompose_inverse<INV_ROT>(c, a1, s);
-    decompose_extend(c, w, n, s, EXTEND_BESIDE);
+    decompose<INV_ROT>(c, a1, w, s, EXTEND_BESIDE);
     if (any_fp_prime(c, c->L, c->D)) join_fp_beside(c, s);  // as in keyswitch_pipeline
     launch_ks_inner<OWN_COPY, false, false>(c, ia, s, c->L, c->D);
     const InvStridedSumArgs a2 = {w.cp, LimbSel{c->K, 2, c->K, 0, c->L}, SC_DN, n};
@@ -1768,8 +1836,7 @@ static void keyswitch_pipeline(const View* c, const View* cm, const u64* in1, co
         for (u32 b = 0; b < batch; b++)
             a1.galois[b] = ia.galois[b] = multi_galois[b], ia.key[b] = multi_keys[b];
     }
-    launch_decompose_inverse<LOAD>(c, a1, s);
-    decompose_extend(c, w, batch, s, EXTEND_BESIDE);
+    decompose<LOAD>(c, a1, w, s, EXTEND_BESIDE);
     ia.dt = w.dt, ia.own = in1, ia.own2 = in2;
     ia.cp = w.cp, ia.n_inst = batch, ia.split = cm->L;
     // the limbs that feed the ModDown conversion first; the q-limbs then finish in one kernel, c' in registers.
@@ -1899,8 +1966,7 @@ static int rescale_impl(ckks_ctx* ctx, uint32_t level, const uint64_t* d_ct, uin
     const LimbSel src = {1, batch * 2, level, level - 1, level - 1};  // limb level-1 of every component
     const LimbSel dst = {1, batch * 2, 1, 0, level - 1};
     InvContigArgs a1 = {d_ct, nullptr, w.cp, src, dst, {1}, 0};
-    launch_inverse<INV_PLAIN>(c, a1, SC_DN, conv_src_fmt(c->dn, CONV_DN), s);
-    moddown_convert(c, w, batch, s, true, stores_cached(c, (u64)batch * 2 * c->L));
+    moddown_from_eval(c, a1, w, batch, s, stores_cached(c, (u64)batch * 2 * c->L));
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
     fa.cq = d_ct, fa.cq_L = level, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 2 * batch;
@@ -1970,12 +2036,11 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
     const size_t N = (size_t)1 << c->logN;
     const SideStream& sd = c->sh->side;
     // decompose a = ct[1] once and finish the transform of every extended limb
-    auto decompose = [&](const Workspace& w, ExtendMode mode) {
+    auto decompose_input = [&](const Workspace& w, ExtendMode mode) {
         const LimbSel src = {c->L, 1, c->L, c->L, 0};  // limbs L .. 2L-1 of ct, primes 0 .. L-1
         const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
-        launch_decompose_inverse<INV_PLAIN>(c, a1, s);
-        decompose_extend(c, w, 1, s, mode);
+        decompose<INV_PLAIN>(c, a1, w, s, mode);
         launch_extended_fwd_contig(c, w, s);
     };
     if (hoisted_summed(c, n_rot)) {
@@ -1993,7 +2058,7 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
         // 954 / 937; 560 / 580, 992 / 1005)
         const bool fork = sd.enabled && c->mixed_classes && class_runs(c, c->L, c->D).size() == 1 &&
                           (n_rot < chunk ? n_rot : chunk) * c->D * tiles_of(c) >= 5 * 512;
-        decompose(w, fork ? EXTEND_FORK : EXTEND_PLAIN);
+        decompose_input(w, fork ? EXTEND_FORK : EXTEND_PLAIN);
         for (u32 r0 = 0; r0 < n_rot; r0 += chunk) {
             const u32 nr = (n_rot - r0) < chunk ? (n_rot - r0) : chunk;
             DhInnerArgs da;
@@ -2028,7 +2093,7 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
     // N = 2^16, one stream / two: L + K = 30, 7 rotations (3360 workgroups) 550 / 526 us, 3 (1440) 303 / 314, 1 182 / 198;
     // 13 + 6, chunks of 9 (2736) 730 / 710; 10 + 5, chunks of 9 (2160) 546 / 567.
     const bool fork = chunk * c->D * tiles_of(c) >= 5 * 512;
-    decompose(w, fork ? EXTEND_FORK : EXTEND_PLAIN);
+    decompose_input(w, fork ? EXTEND_FORK : EXTEND_PLAIN);
     for (u32 r0 = 0; r0 < n_rot; r0 += chunk) {
         const u32 nr = (n_rot - r0) < chunk ? (n_rot - r0) : chunk;
         InnerArgs ia;
@@ -2097,12 +2162,11 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
         const LimbSel src = {c->L, 1, c->L, c->L, 0};
         const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
-        launch_decompose_inverse<INV_PLAIN>(c, a1, s);
         // From five rounds of extended workgroups on the integer limbs take the second stream up to the ModDown conversion (rotations:
         // one stream / two, us; N = 2^16: 40 + 10 limbs, dnum 4 (3200 workgroups) 1: 317 / 281, 6: 566 / 533, 24: 1325 / 1305; 26 + 6,
         // dnum 5 (2560) 1: 221 / 216, 6: 426 / 411).  Below, splitting the joint launches costs more (24 + 6, dnum 4 (1920) 1: 186 /
         // 196, 12: 514 / 512; level 13 (912) 1: 129 / 146, 6: 218 / 228, 12: 313 / 300).
-        decompose_extend(c, w, 1, s, c->dnum * c->D * tiles_of(c) >= 5 * 512 ? EXTEND_FORK : EXTEND_PLAIN);
+        decompose<INV_PLAIN>(c, a1, w, s, c->dnum * c->D * tiles_of(c) >= 5 * 512 ? EXTEND_FORK : EXTEND_PLAIN);
         launch_extended_fwd_contig(c, w, s);
     }
     for (u32 r0 = 0; r0 < n_rot; r0 += CKKS_DH_CHUNK) {
@@ -2117,9 +2181,8 @@ static int dh_mac_impl(ckks_ctx* ctx, uint32_t level, bool rescale, const uint64
     {  // ModDown of the sum: first inverse pass of its source limbs, then the shared tail
         const LimbSel sel = {cm->K, 2, cm->K, 0, cm->L};
         InvContigArgs ic = {w.cp, nullptr, w.cp, sel, sel, {1}, 0};
-        launch_inverse<INV_PLAIN>(cm, ic, SC_DN, conv_src_fmt(cm->dn, CONV_DN), s);
+        moddown_from_eval(cm, ic, w, 1, s);
     }
-    moddown_convert(cm, w, 1, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
     fa.cq = w.cq, fa.cq_L = cm->L, fa.cv = w.cv, fa.out = d_out, fa.n_inst = 2;
@@ -2211,8 +2274,7 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         const LimbSel src = {c->L, 1, c->L, c->L, 0};
         const LimbSel dst = {c->L, 1, c->L, 0, 0};
         InvContigArgs a1 = {d_ct, nullptr, w.x, src, dst, {1}, 0};
-        launch_decompose_inverse<INV_PLAIN>(c, a1, s);
-        decompose_extend(c, w, 1, s, EXTEND_PLAIN);
+        decompose<INV_PLAIN>(c, a1, w, s, EXTEND_PLAIN);
         launch_extended_fwd_contig(c, w, s);
     }
     // Baby steps and combinations in one kernel where its registers hold the sums (8 x 4, N = 2^16, 24 + 6 limbs: 468 -> 354 us; on
@@ -2246,9 +2308,8 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
     {
         const LimbSel sel = {c->K, n2 * 2, c->K, 0, c->L};
         InvContigArgs ic = {w.cp, nullptr, w.cp, sel, sel, {1}, 0};
-        launch_inverse<INV_PLAIN>(c, ic, SC_DN, conv_src_fmt(c->dn, CONV_DN), s);
+        moddown_from_eval(c, ic, w, n2, s);
     }
-    moddown_convert(c, w, n2, s, true);
     FinalArgs fa;
     memset(&fa, 0, sizeof(fa));
     fa.cq = w.cq, fa.cq_L = c->L, fa.cv = w.cv, fa.out = inner, fa.n_inst = 2 * n2;

@@ -7,6 +7,8 @@
 //   inv_strided_kernel  second inverse pass -> scale by N^-1 (* base-conversion pre-factor)
 //   conv_fwd_strided_kernel, conv_mfma_kernel, conv_int_kernel, conv_up_both_kernel
 //                       base conversion from the digit / special limbs -> first forward pass of the targets
+//   inv_conv_one_kernel, inv_whole_conv_one_kernel
+//                       second, or both, inverse passes of a limb -> conversion from it -> first forward pass (small grids)
 //   fwd_strided_kernel  load -> first forward pass
 //   fwd_contig_kernel   second forward pass -> canonical store
 //   fwd_whole_kernel    both forward passes, N <= 2^13
@@ -252,8 +254,9 @@ struct AnyAr {};
     else if (tb.pc[tb.phys(prime)].fp) { typedef FpAr AR_; CALL; }                       \
     else { typedef IntAr AR_; CALL; }
 
+// both passes of limb l of instance inst: the lane's sixteen words, in layout SA of its tile
 template <class AR, int A, int LOAD>
-__device__ __forceinline__ void inv_whole_body(const InvContigArgs& a, const Tables& tb, u64* lds, u32 l, u32 inst) {
+__device__ __forceinline__ void inv_whole_words(u64 (&o)[16], const InvContigArgs& a, const Tables& tb, u64* lds, u32 l, u32 inst) {
     typedef NttCore<AR, A> C;
     const u32 N = 1u << tb.logN, tid = threadIdx.x, e0 = tid % 16, r = tid / 16;
     const u32 vi = a.sel.prime_base + l, pi = tb.phys(vi);
@@ -275,14 +278,18 @@ __device__ __forceinline__ void inv_whole_body(const InvContigArgs& a, const Tab
     if (A > 4) __syncthreads();  // the pass exchanges through the same memory
     C::inv_strided_but_last(x, lds + g * 4096, t, ti, tf, N, m);
     const InvScale sc = a.scale == SC_PLAIN ? tb.sc_plain[pi] : a.scale == SC_UP ? tb.sc_up[vi] : tb.sc_dn[vi - tb.L];
-    u64* base = a.dst + limb_offset(a.dsel, inst, l) * N + (size_t)r0 * 256 + col;
 #pragma unroll
-    for (int k = 0; k < 8; k++) {
-        u64 ox, oy;
-        AR::bfly_inv_last(x[k], x[k + 8], sc, m, a.out_fmt, ox, oy);
-        base[(size_t)k * C::RB * 256] = ox;
-        base[(size_t)(k + 8) * C::RB * 256] = oy;
-    }
+    for (int k = 0; k < 8; k++) AR::bfly_inv_last(x[k], x[k + 8], sc, m, a.out_fmt, o[k], o[k + 8]);
+}
+template <class AR, int A, int LOAD>
+__device__ __forceinline__ void inv_whole_body(const InvContigArgs& a, const Tables& tb, u64* lds, u32 l, u32 inst) {
+    typedef NttCore<AR, A> C;
+    u64 o[16];
+    inv_whole_words<AR, A, LOAD>(o, a, tb, lds, l, inst);
+    const u32 t = threadIdx.x & 255, r0 = t / C::TC, col = (threadIdx.x >> 8) * C::TC + t % C::TC;
+    u64* base = a.dst + (limb_offset(a.dsel, inst, l) << tb.logN) + (size_t)r0 * 256 + col;
+#pragma unroll
+    for (int k = 0; k < 16; k++) base[(size_t)k * C::RB * 256] = o[k];
 }
 template <class AR, int A, int LOAD>
 __global__ __launch_bounds__(inv_one_kernel(A) ? 16 << A : 256) void inv_contig_kernel(InvContigArgs a, Tables tb, LimbRun run) {
@@ -314,19 +321,17 @@ struct InvStridedArgs {
     u32 out_fmt;  // SrcFormat of the stored words: SRC_F64 applies to limbs of FpAr primes only (others stay canonical)
 };
 
+// the pass on a tile of limb vi at `base`, nothing stored
 template <class AR, int A>
-__device__ __forceinline__ void inv_strided_body(const InvStridedArgs& a, const Tables& tb, u64* lds, u32 l, u32 tile,
-                                                 u32 inst) {
+__device__ __forceinline__ void inv_strided_words(u64 (&o)[16], const u64* base, const Tables& tb, u64* lds, u32 vi, u32 tile, u32 scale, u32 out_fmt) {
     typedef typename AR::T T;
     typedef NttCore<AR, A> C;
-    const u32 N = 1u << tb.logN, tid = threadIdx.x;
-    const u32 vi = a.sel.prime_base + l, pi = tb.phys(vi);
+    const u32 N = 1u << tb.logN, tid = threadIdx.x, pi = tb.phys(vi);
     const typename AR::Mod m = AR::mod(tb.pc[pi]);
     const u64* ti = tb.tw_int + (size_t)pi * 4 * N;
     const double* tf = tb.tw_fp + (size_t)pi * 2 * N;
-    const InvScale sc = a.scale == SC_PLAIN ? tb.sc_plain[pi] : a.scale == SC_UP ? tb.sc_up[vi] : tb.sc_dn[vi - tb.L];
+    const InvScale sc = scale == SC_PLAIN ? tb.sc_plain[pi] : scale == SC_UP ? tb.sc_up[vi] : tb.sc_dn[vi - tb.L];
     const u32 c = tid % C::TC, r0 = tid / C::TC, col = tile * C::TC + c;
-    u64* base = a.data + limb_offset(a.sel, inst, l) * N;
     T x[16];
     if constexpr (A > 4) {
 #pragma unroll
@@ -337,12 +342,18 @@ __device__ __forceinline__ void inv_strided_body(const InvStridedArgs& a, const 
     }
     C::inv_strided_but_last(x, lds, tid, ti, tf, N, m);
 #pragma unroll
-    for (int k = 0; k < 8; k++) {
-        u64 ox, oy;
-        AR::bfly_inv_last(x[k], x[k + 8], sc, m, a.out_fmt, ox, oy);
-        base[(size_t)(k * C::RB + r0) * 256 + col] = ox;
-        base[(size_t)((k + 8) * C::RB + r0) * 256 + col] = oy;
-    }
+    for (int k = 0; k < 8; k++) AR::bfly_inv_last(x[k], x[k + 8], sc, m, out_fmt, o[k], o[k + 8]);
+}
+template <class AR, int A>
+__device__ __forceinline__ void inv_strided_body(const InvStridedArgs& a, const Tables& tb, u64* lds, u32 l, u32 tile,
+                                                 u32 inst) {
+    typedef NttCore<AR, A> C;
+    u64* base = a.data + (limb_offset(a.sel, inst, l) << tb.logN);
+    u64 o[16];
+    inv_strided_words<AR, A>(o, base, tb, lds, a.sel.prime_base + l, tile, a.scale, a.out_fmt);
+    const u32 c = threadIdx.x % C::TC, r0 = threadIdx.x / C::TC, col = tile * C::TC + c;
+#pragma unroll
+    for (int k = 0; k < 16; k++) base[(size_t)(k * C::RB + r0) * 256 + col] = o[k];
 }
 
 #ifndef CKKS_INV_STRIDED_WAVES
@@ -496,6 +507,8 @@ struct ConvArgs {
     const u64* aop;
     const u64* aop_part;
     u32 n_full;
+    u32 inverse;  // CONV_DN from a single source, one target per workgroup: src holds the words of the first inverse pass, the second is
+                  // done here
 };
 
 // Twiddles of the strided pass of one target, W[0 .. R1) of its table, staged in LDS before the pass: a global load
@@ -560,6 +573,59 @@ __device__ __forceinline__ void strided_stages_hi(typename AR::T (&x)[16], const
 // launch fills the chip (rescale of 8 ciphertexts at N = 2^16, 23 limbs: 63 -> 53 us against three targets converted before
 // the first is transformed), 1 where it does not and the time is that of one workgroup; integer targets always 1 (launch_conv).
 // CACHED: see fwd_strided_finish.
+// One target of a source whose words y are in layout SA: reduced, first forward pass, stored to `limb`.  src_fp: the words of an FpAr
+// source, doubles for FpAr targets, integers for IntAr ones.  tid: lane of the 256 that share the tile; again: lds still holds words.
+template <class AR, int A, bool MANY, bool CACHED>
+__device__ __forceinline__ void conv_one_target(u64 (&y)[16], bool src_fp, const PrimeConst& pc, const u64* tw, u64* lds, u64* limb, u32 tid, u32 tile, bool again) {
+    typedef NttCore<AR, A> C;
+    const typename AR::Mod m = AR::mod(pc);
+    const u32 c = tid % C::TC, r0 = tid / C::TC, col = tile * C::TC + c;
+    typename AR::T x[16];
+    if constexpr (AR::is_fp) {
+        if (src_fp) {
+#pragma unroll
+            for (int k = 0; k < 16; k++) x[k] = FpAr::reduce(FpAr::from_raw(y[k]), m);
+        } else {
+            // a 61-bit word is first brought below the target, which leaves it at most 0.6 q + 2^30
+#pragma unroll
+            for (int k = 0; k < 16; k++) {
+                if (MANY) asm volatile("" : "+v"(y[k]));  // split here, not once for all targets (64 registers)
+                x[k] = FpAr::reduce(FpAr::reduce_split((double)(u32)(y[k] >> 30) * 1073741824.0, (double)(u32)(y[k] & 0x3fffffffu), m), m);
+            }
+        }
+    } else if (src_fp) {  // every FpAr prime is below every IntAr prime: the source is canonical already
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = y[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            u128w p = {0, 0};
+            mac128(p, y[k], pc.r1);
+            x[k] = redc(p, pc.q, pc.qneg);
+        }
+    }
+    strided_stages_lo<AR, A>(x, tw, m);
+    if constexpr (A > 4) {
+        const Buf dst(limb);
+        if (again) __syncthreads();  // the previous exchange has been read
+        AR::mid_reduce(x, m);
+#pragma unroll
+        for (int k = 0; k < 16; k++) lds[k * 256 + tid] = AR::to_raw(x[k]);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lds[(r0 * 16 + k) * C::TC + c]);
+        strided_stages_hi<AR, A>(x, tw, r0, m);
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            if constexpr (CACHED) dst.st(AR::to_raw(AR::round_reduce(x[k], m)), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
+            else dst.st_nt(AR::to_raw(AR::round_reduce(x[k], m)), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
+        }
+    } else {
+        u64* dst = limb;
+#pragma unroll
+        for (int k = 0; k < 16; k++) dst[(size_t)(k * C::RB + r0) * 256 + col] = AR::to_raw(AR::round_reduce(x[k], m));
+    }
+}
 template <class AR, int A, int DIR, int TB, bool CACHED = false>
 __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& tb, const LimbRun run) {
     typedef NttCore<AR, A> C;
@@ -590,8 +656,13 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
     const bool src_fp = tb.pc[tb.phys(src_prime)].fp;
     const Buf sb(src);
     u64 y[16];
+    if (DIR == CONV_DN && TB == 1 && a.inverse) {
+        if (src_fp) inv_strided_words<FpAr, A>(y, src, tb, lds, src_prime, tile, SC_DN, SRC_CANON);
+        else inv_strided_words<IntAr, A>(y, src, tb, lds, src_prime, tile, SC_DN, SRC_CANON);
+    } else {
 #pragma unroll
-    for (int k = 0; k < 16; k++) y[k] = sb.ld(8 * (r0 * 256 + col), 8 * 256 * C::RB * k);
+        for (int k = 0; k < 16; k++) y[k] = sb.ld(8 * (r0 * 256 + col), 8 * 256 * C::RB * k);
+    }
 #pragma unroll
     for (int t = 0; t < TB; t++)
         if (first + t < end) TW::fill(tws + t * TW::WORDS, tid, tb, tb.phys(first + t));
@@ -606,56 +677,62 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
         const u32 vi = first + t;
         if (vi >= end) break;
         if (vi == own) continue;
-        const PrimeConst pc = tb.pc[tb.phys(vi)];
-        const typename AR::Mod m = AR::mod(pc);
-        const u64* tw = tws + t * TW::WORDS;
-        typename AR::T x[16];
-        if constexpr (AR::is_fp) {
-            if (src_fp) {
-#pragma unroll
-                for (int k = 0; k < 16; k++) x[k] = FpAr::reduce(FpAr::from_raw(y[k]), m);
-            } else {
-                // a 61-bit word is first brought below the target, which leaves it at most 0.6 q + 2^30
-#pragma unroll
-                for (int k = 0; k < 16; k++) {
-                    if (TB > 1) asm volatile("" : "+v"(y[k]));  // split here, not once for all targets (64 registers)
-                    x[k] = FpAr::reduce(FpAr::reduce_split((double)(u32)(y[k] >> 30) * 1073741824.0, (double)(u32)(y[k] & 0x3fffffffu), m), m);
-                }
-            }
-        } else if (src_fp) {  // every FpAr prime is below every IntAr prime: the source is canonical already
-#pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = y[k];
-        } else {
-#pragma unroll
-            for (int k = 0; k < 16; k++) {
-                u128w p = {0, 0};
-                mac128(p, y[k], pc.r1);
-                x[k] = redc(p, pc.q, pc.qneg);
-            }
-        }
-        strided_stages_lo<AR, A>(x, tw, m);
-        if constexpr (A > 4) {
-            const Buf dst(dst0 + (size_t)vi * N);
-            if (again) __syncthreads();  // the previous target's exchange has been read
-            again = true;
-            AR::mid_reduce(x, m);
-#pragma unroll
-            for (int k = 0; k < 16; k++) lds[k * 256 + tid] = AR::to_raw(x[k]);
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = AR::from_raw(lds[(r0 * 16 + k) * C::TC + c]);
-            strided_stages_hi<AR, A>(x, tw, r0, m);
-#pragma unroll
-            for (int k = 0; k < 16; k++) {
-                if constexpr (CACHED) dst.st(AR::to_raw(AR::round_reduce(x[k], m)), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
-                else dst.st_nt(AR::to_raw(AR::round_reduce(x[k], m)), 8 * (r0 * 16 * 256 + col), 8 * 256 * k);
-            }
-        } else {
-            u64* dst = dst0 + (size_t)vi * N;
-#pragma unroll
-            for (int k = 0; k < 16; k++) dst[(size_t)(k * C::RB + r0) * 256 + col] = AR::to_raw(AR::round_reduce(x[k], m));
-        }
+        conv_one_target<AR, A, (TB > 1), CACHED>(y, src_fp, tb.pc[tb.phys(vi)], tws + t * TW::WORDS, lds, dst0 + (size_t)vi * N, tid, tile, again);
+        again = true;
     }
+}
+
+// ---- the same with the inverse transform of the source, repeated by the workgroup of every target (up_with_inverse and dn_with_inverse
+// on the host): targets of either arithmetic in one launch.
+// words of an FpAr source as conv_one_target takes them
+__device__ __forceinline__ void conv_one_words(u64 (&y)[16], bool src_fp, bool dst_fp) {
+    if (src_fp && dst_fp) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) y[k] = FpAr::to_raw(u64_to_f64(y[k]));
+    }
+}
+// ModUp, N >= 2^14: the second inverse pass; a.src holds the words of the first
+template <int A>
+__global__ __launch_bounds__(256) void inv_conv_one_kernel(ConvArgs a, Tables tb) {
+    constexpr u32 TILES = (1u << A) / 16;
+    __shared__ u64 lds[4096];
+    __shared__ __align__(16) u64 tws[2u << A];
+    u32 group, vi;
+    if (!xcd_decode(blockIdx.x, tb.D, a.groups_outer * tb.dnum * TILES, group, vi)) return;
+    const u32 of = group / TILES, tile = group % TILES, src = of % tb.dnum;
+    if (vi == src) return;  // a digit's own limb
+    const PrimeConst &ps = tb.pc[tb.phys(src)], &pt = tb.pc[tb.phys(vi)];
+    const u64* limb = a.src + ((size_t)of << tb.logN);
+    u64 y[16];
+    if (ps.fp) inv_strided_words<FpAr, A>(y, limb, tb, lds, src, tile, SC_UP, SRC_CANON);
+    else inv_strided_words<IntAr, A>(y, limb, tb, lds, src, tile, SC_UP, SRC_CANON);
+    conv_one_words(y, ps.fp, pt.fp);
+    CKKS_BY_ARITHMETIC(AnyAr, vi, (StridedTw<AR_, A>::fill(tws, threadIdx.x, tb, tb.phys(vi))))
+    __syncthreads();
+    u64* to = a.dst + (((size_t)of * tb.D + vi) << tb.logN);
+    CKKS_BY_ARITHMETIC(AnyAr, vi, (conv_one_target<AR_, A, false, false>(y, ps.fp, pt, tws, lds, to, threadIdx.x, tile, false)))
+}
+// both inverse passes, N <= 2^13: of limb l of instance inst onto the level's limbs but itself (ModUp), or of the one
+// limb after the targets (rescale)
+template <int A, int LOAD, int DIR>
+__global__ __launch_bounds__(16 << A) void inv_whole_conv_one_kernel(InvContigArgs a, u64* dst, Tables tb) {
+    __shared__ u64 lds[(1 << A) * 272];
+    __shared__ __align__(16) u64 tws[2u << A];
+    u32 group, vi;
+    const u32 targets = DIR == CONV_UP ? tb.D : tb.L;
+    if (!xcd_decode(blockIdx.x, targets, a.sel.n_inst * a.sel.n_l, group, vi)) return;
+    const u32 inst = group / a.sel.n_l, l = group % a.sel.n_l, src = a.sel.prime_base + l;
+    if (vi == src) return;  // a digit's own limb
+    const PrimeConst &ps = tb.pc[tb.phys(src)], &pt = tb.pc[tb.phys(vi)];
+    u64 y[16];
+    if (ps.fp) inv_whole_words<FpAr, A, LOAD>(y, a, tb, lds, l, inst);
+    else inv_whole_words<IntAr, A, LOAD>(y, a, tb, lds, l, inst);
+    conv_one_words(y, ps.fp, pt.fp);
+    const u32 tid = threadIdx.x & 255, tile = threadIdx.x >> 8;
+    CKKS_BY_ARITHMETIC(AnyAr, vi, (StridedTw<AR_, A>::fill(tws, threadIdx.x, tb, tb.phys(vi))))
+    __syncthreads();
+    u64* to = dst + (((size_t)group * targets + vi) << tb.logN);
+    CKKS_BY_ARITHMETIC(AnyAr, vi, (conv_one_target<AR_, A, false, false>(y, ps.fp, pt, tws, lds + tile * 4096, to, tid, tile, false)))
 }
 
 // ---- several sources, on the matrix cores.
