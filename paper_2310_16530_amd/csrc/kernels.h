@@ -1073,8 +1073,10 @@ __device__ __forceinline__ void fwd_contig_body(const FwdContigArgs& a, const Ta
     store_row_cp<false>(p, e0, res);
 }
 
+// AnyAr: four waves per SIMD, as LDS allows; two registers above 128 made it three (transforms of mixed limbs, N = 2^14 .. 2^16: 31.3 -> 28.9 us,
+// 41.9 -> 40.6, 55.4 -> 54.1; those of one round of workgroups within 0.5 %)
 template <class AR, int A>
-__global__ __launch_bounds__(256) void fwd_contig_kernel(FwdContigArgs a, Tables tb, LimbRun run) {
+__global__ __launch_bounds__(256, __is_same(AR, AnyAr) ? 4 : 1) void fwd_contig_kernel(FwdContigArgs a, Tables tb, LimbRun run) {
     __shared__ u64 lds[NTT_LDS_WORDS];
     constexpr u32 TILES = (1u << A) / 16;
     u32 group, inst;
