@@ -660,7 +660,7 @@ __device__ __forceinline__ void conv_one_body(const ConvArgs& a, const Tables& t
     const bool src_fp = tb.pc[tb.phys(src_prime)].fp;
     const Buf sb(src);
     u64 y[16];
-    if (DIR == CONV_DN && TB == 1 && a.inverse) {
+    if (DIR == CONV_DN && TB == 1 && !CACHED && a.inverse) {  // CACHED: sources that are coefficients already
         auto keep = [&y](int k, u64 w) __attribute__((always_inline)) { y[k] = w; };
         if (src_fp) inv_strided_words<FpAr, A>(src, tb, lds, src_prime, tile, SC_DN, SRC_CANON, keep);
         else inv_strided_words<IntAr, A>(src, tb, lds, src_prime, tile, SC_DN, SRC_CANON, keep);
