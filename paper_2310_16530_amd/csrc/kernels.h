@@ -1332,13 +1332,16 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         __syncthreads();
         if (part > 1) return;
     }
+    // An opaque copy of the lane's row, and of its other coordinates below: every address of what follows is derived from them, so none
+    // of it is computed before the accumulation loop, which has no registers to spare (both arithmetics, HMult with the merged rescale: 12 bytes of scratch without).
+    u32 chl = ch;
+    if (!FUSED) asm volatile("" : "+v"(chl));
+    const u32 rl = r0 + (chl & 3);
     if (FUSED) {
         // c' stays in registers: out = (c' - second forward pass of the converted special part) * P^-1
         // (+ sigma_g(b) on the first component of a rotation; adding it as P * sigma_g(b) where sigma_g(a) is
         // gathered measured slower: the accumulation loop has no registers for it).  FP64 magnitudes in units
         // of q: c' <= 0.5, v <= 5.2 (narrow primes 10.5), the product with P^-1 <= 2.9; canonicalised before the store.
-        // Opaque copies of the lane coordinates: every address of this part is derived from them, so none of
-        // it is computed before the accumulation loop, which has no registers to spare.
         u32 e0f = e0, chf = ch, gal_fin = gal;
         asm volatile("" : "+v"(e0f), "+v"(chf), "+s"(gal_fin));
         const u32 rf = r0 + (chf & 3), row_off_f = rf * 256;
@@ -1394,7 +1397,7 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
             if (ways != 1 && part != (u32)t) continue;
 #pragma unroll
             for (int k = 0; k < 16; k++) res[k] = AR::acc_canon(AR::acc_finish(t ? acc1[k] : acc0[k], m), m);
-            store_row_cp(a.cq + (((size_t)inst * 2 + t) * a.split + i) * N + row_off, e0, res);
+            store_row_cp(a.cq + (((size_t)inst * 2 + t) * a.split + i) * N + rl * 256, e0, res);
         }
     } else {
 #pragma unroll
@@ -1404,8 +1407,8 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = AR::acc_finish(t ? acc1[k] : acc0[k], m);
             exchange_cp_to_cb<AR>(x, lrow, e0);
-            NttCore<AR, A>::inv_contig(x, lrow, e0, r, ti, tf, N, m);
-            u64* o = a.cp + (((size_t)inst * 2 + t) * (D - a.split) + (i - a.split)) * N + row_off;
+            NttCore<AR, A>::inv_contig(x, lrow, e0, rl, ti, tf, N, m);
+            u64* o = a.cp + (((size_t)inst * 2 + t) * (D - a.split) + (i - a.split)) * N + rl * 256;
 #pragma unroll
             for (int k = 0; k < 16; k++) o[k * 16 + e0] = AR::to_raw(AR::round_reduce(x[k], m));
         }

@@ -29,3 +29,10 @@ def test_conversions_with_ordinary_stores_hold_no_inverse_pass(tmp_path, arith, 
     code, _ = _assembly(tmp_path, "conv_one_cached_kernel<%s, %d, %d>" % (arith, logN - 8, targets), "ConvArgs, Tables, LimbRun", "_Z22conv_one_cached_kernel")
     barriers = sum(1 for l in code if re.match(r"\s+s_barrier\b", l))
     assert barriers <= (2 if targets == 1 else 3), barriers
+
+
+@pytest.mark.parametrize("logN", [12, 16])
+def test_joint_inner_product_of_a_merged_rescale_spills_nothing(tmp_path, logN):
+    """256 registers, all taken: an address computed before the accumulation loop and used after it goes to scratch memory."""
+    _, summary = _assembly(tmp_path, "ks_inner_kernel<AnyAr, %d, OWN_TENSOR, false, false>" % (logN - 8), "InnerArgs, Tables, LimbRun", "_Z15ks_inner_kernel")
+    assert int(re.search(r"; ScratchSize: (\d+)", "\n".join(summary)).group(1)) == 0
