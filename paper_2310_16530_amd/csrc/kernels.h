@@ -1344,12 +1344,15 @@ __device__ __forceinline__ void ks_inner_body(const InnerArgs& a, const Tables& 
         // of q: c' <= 0.5, v <= 5.2 (narrow primes 10.5), the product with P^-1 <= 2.9; canonicalised before the store.
         u32 e0f = e0, chf = ch, gal_fin = gal;
         asm volatile("" : "+v"(e0f), "+v"(chf), "+s"(gal_fin));
-        const u32 rf = r0 + (chf & 3), row_off_f = rf * 256;
-        u64* lrow_f = lds + chf * 272;
         const PinvConst pinv = a.fin_pinv[i];
 #pragma unroll
         for (int t = 0; t < 2; t++) {
             if (ways != 1 && part != (u32)t) continue;
+            // IntAr, whose twiddles come from memory: opaque for each component again, or the addresses of all of them are computed once for
+            // both and wait in scratch memory (348 to 480 bytes), a reload before every twiddle.
+            if constexpr (!TWL) asm volatile("" : "+v"(e0f), "+v"(chf));
+            const u32 rf = r0 + (chf & 3), row_off_f = rf * 256;
+            u64* lrow_f = lds + chf * 272;
             T v[16];
             const u64* p = a.cv + (((size_t)inst * 2 + t) * a.split + i) * N + row_off_f;
 #pragma unroll

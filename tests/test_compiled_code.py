@@ -36,3 +36,10 @@ def test_joint_inner_product_of_a_merged_rescale_spills_nothing(tmp_path, logN):
     """256 registers, all taken: an address computed before the accumulation loop and used after it goes to scratch memory."""
     _, summary = _assembly(tmp_path, "ks_inner_kernel<AnyAr, %d, OWN_TENSOR, false, false>" % (logN - 8), "InnerArgs, Tables, LimbRun", "_Z15ks_inner_kernel")
     assert int(re.search(r"; ScratchSize: (\d+)", "\n".join(summary)).group(1)) == 0
+
+
+@pytest.mark.parametrize("own", ["OWN_COPY", "OWN_TENSOR", "OWN_ROT", "OWN_ROT_SUM"])
+def test_integer_inner_product_keeps_its_twiddle_addresses_out_of_scratch_memory(tmp_path, own):
+    """The transforms that end the two components read the same twiddles: their addresses, computed once for both, filled 348 to 480 bytes."""
+    _, summary = _assembly(tmp_path, "ks_inner_kernel<IntAr, 8, %s, false, true>" % own, "InnerArgs, Tables, LimbRun", "_Z15ks_inner_kernel")
+    assert int(re.search(r"; ScratchSize: (\d+)", "\n".join(summary)).group(1)) <= 32
