@@ -1635,11 +1635,22 @@ static bool up_with_inverse(const View* c, u32 batch) {
 // ModDown by one prime.  After an inner product, which has run the first inverse pass: HMult with digits of two limbs, N = 2^12, 6 + 1 limbs (12)
 // 59.0 / 57.2, N = 2^16, 6 + 1 (192) 79.6 / 75.7, 8 + 1, 3 ciphertexts (768) 124.3 / 124.9 (an integer special prime).  Rescale: N = 2^14, 24 -> 23
 // limbs (192) 22.7 / 19.4, N = 2^16, 7 limbs (192) 24.3 / 20.7, 25 (768) 36.4 / 35.1, 17, 2 ciphertexts (1024) 42.0 / 41.6, 3 (1536) 55 / 57.
-// whole: both passes in one workgroup: N = 2^12, 17 limbs, 2 (64) 18.6 / 15.5, 23, 9 (396) 26.7 / 26.0 (528: 30.6 / 31.1); N = 2^13, 23, 3
-// (264) 26.0 / 23.3 (400: 28.0 / 31.7), few integer limbs 31.3 / 32.8 (spread_limbs: two passes are the faster ones there).
+// Those are targets of one arithmetic.  Targets of both take a launch for every run of one, and each repeats the pass: two runs from an FpAr source,
+// rescales of 4 to 20 targets, N = 2^14 .. 2^16, up to 512 workgroups 1.05 to 1.09 of the time with it, 576 to 768 0.99 to 1.04; from an
+// integer source 0.97 to 1.02 and 0.91 to 0.97 (behind an inner product at N = 2^12 and 2^13 1.00 to 1.02); three runs 0.98 to 1.03 and 0.90 to
+// 0.97; four 0.97 to 1.00 and 0.88 to 0.93; primes in turn 0.79 to 1.0 (N = 2^14, 12 limbs, 49 and 55 bits, 4 ciphertexts 225 / 247 us).
+// whole: both passes in one workgroup, whose launch serves every target: N = 2^12, 17 limbs, 2 (64) 18.6 / 15.5, 23, 9 (396) 26.7 / 26.0 (528: 30.6 / 31.1);
+// N = 2^13, 23, 3 (264) 26.0 / 23.3 (400: 28.0 / 31.7), few integer limbs 31.3 / 32.8 (spread_limbs: two passes are the faster ones there).
 static bool dn_with_inverse(const View* c, u32 sources, bool whole) {
-    const u32 tiles = sources * tiles_of(c), most = whole ? c->logN == 12 ? 448 : 288 : c->primes[c->L] >= CKKS_FP_PRIME_LIMIT ? 512 : 768;
-    return c->K == 1 && !c->sh->side.active && tiles * c->L <= most && tiles * cdiv(c->L, 4) < 512;  // fewer than 512: launch_conv takes single targets
+    if (c->K != 1 || c->sh->side.active) return false;
+    const u32 tiles = sources * tiles_of(c);
+    const bool integer = c->primes[c->L] >= CKKS_FP_PRIME_LIMIT;
+    u32 most = c->logN == 12 ? 448 : 288;
+    if (!whole) {
+        const size_t runs = class_runs(c, 0, c->L).size();
+        most = runs == 1 ? (integer ? 512 : 768) : runs == 2 && (!integer || c->logN <= 13) ? 512 : 0;
+    }
+    return tiles * c->L <= most && tiles * cdiv(c->L, 4) < 512;  // fewer than 512: launch_conv takes single targets
 }
 template <int LOAD, int DIR>
 static void launch_inv_whole_conv_one(const View* c, InvContigArgs a, u64* dst, hipStream_t s) {

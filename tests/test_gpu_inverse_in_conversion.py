@@ -19,8 +19,11 @@ def _up(logN, L, batch):
 
 
 def _dn(logN, sources, targets, int_source, whole):
-    tiles = sources << (logN - 12)
-    return tiles * targets <= ((448 if logN == 12 else 288) if whole else 512 if int_source else 768) and tiles * -(-targets // 4) < 512
+    """targets: their sizes in bits, integer arithmetic from 50 on; a launch for every run of one arithmetic, but one for all where whole"""
+    tiles, n = sources << (logN - 12), len(targets)
+    runs = 1 + sum((a >= 50) != (b >= 50) for a, b in zip(targets, targets[1:]))
+    most = (448 if logN == 12 else 288) if whole else (512 if int_source else 768) if runs == 1 else 512 if runs == 2 and (not int_source or logN <= 13) else 0
+    return tiles * n <= most and tiles * -(-n // 4) < 512
 
 
 # (logN, q, p, batch): digits of one limb, one special prime; floors from 50 bits on are integer arithmetic
@@ -38,7 +41,7 @@ def test_key_switches(orc, logN, q, p, batch):
     ct1, ct2 = (_extreme(rng, ps.q_primes, ps.N, (batch, 2)) for _ in range(2))
     d_key, d1, d2 = dev(key), dev(ct1), dev(ct2)
     g, L, whole = synth.galois_element(5, logN), ps.L, logN <= 13
-    up, dn = _up(logN, L, batch), _dn(logN, 2 * batch, L, p >= 50, False)
+    up, dn = _up(logN, L, batch), _dn(logN, 2 * batch, q, p >= 50, False)
     for overlap in (False, True):
         ctx.set_overlap(overlap)
         try:
@@ -61,7 +64,7 @@ def test_key_switches(orc, logN, q, p, batch):
 
 
 RESCALE = [(12, (49,) * 8, 32), (12, (49,) * 8, 33), (12, (55, 49, 58), 4), (13, (49,) * 7, 12), (13, (49,) * 7, 13), (13, (55,) * 5, 12), (13, (55,) * 5, 13),
-           (14, (49, 49), 63), (14, (49, 49), 64), (14, (49, 55, 58), 9), (15, (49,) * 7, 8), (15, (49,) * 7, 9), (16, (49,) * 3, 12), (16, (49,) * 3, 13), (16, (49, 50, 55), 8)]
+           (14, (49, 49), 63), (14, (49, 49), 64), (14, (49, 55, 58), 9), (14, (49, 55, 49), 9), (14, (49, 55, 49), 33), (15, (55, 49, 58, 49), 2), (14, (49, 55) * 4, 3), (15, (49,) * 7, 8), (15, (49,) * 7, 9), (16, (49,) * 3, 12), (16, (49,) * 3, 13), (16, (49, 50, 55), 8)]
 
 
 @pytest.mark.parametrize("logN,q,batch", RESCALE)
@@ -77,7 +80,7 @@ def test_rescales(orc, logN, q, batch):
         assert np.array_equal(got[::5], orc.rescale(np.ascontiguousarray(ct[::5]), P)), ell
         int_source = q[ell - 1] >= 50
         few_integer = logN == 13 and int_source and 2 * batch <= 24
-        want = _dn(logN, 2 * batch, ell - 1, int_source, whole) and not few_integer
+        want = _dn(logN, 2 * batch, q[:ell - 1], int_source, whole) and not few_integer
         if whole:
             assert any(n.startswith("inv_whole_conv_one_kernel") for n in names) == want, names
         else:
