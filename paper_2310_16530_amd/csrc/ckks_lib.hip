@@ -1280,12 +1280,10 @@ static void launch_dh_accum_run(const View* c, DhInnerArgs a, u32 first, u32 cou
     const bool narrow = all_int || n_rot <= 8 || sums > 1;
     const u32 rows = count * ((1u << c->logN) / (64 * (narrow ? 2 : 4)));
     // Four rows per workgroup, or one whose rotations the four wavefronts share.  Narrow, one sum: fewer rounds of the 1280 resident
-    // workgroups times rotations per wavefront.  Several sums: shared where four rows a workgroup leave the chip half empty (whole
-    // transforms of 3 to 16 baby steps, shared / not: 480 to 1024 rows 1.02 to 1.16, 1536 1.01 to 1.03; 1920 and 2048 0.98 to 1.0,
-    // more 0.95 to 1.0).  Wide: with fewer than eight rotations the wavefronts would end up with unequal shares, which only a grid
-    // below two workgroups per compute unit makes up for.
+    // workgroups times rotations per wavefront.  Several sums: sums_waves has the rule and both sides.  Wide: with fewer than eight
+    // rotations the wavefronts would end up with unequal shares, which only a grid below two workgroups per compute unit makes up for.
     const u32 resident = 1280;
-    if (sums > 1) a.waves = rows < 1792 ? 4 : 1;
+    if (sums > 1) a.waves = sums_waves(rows, a.n_rot);
     else if (narrow) a.waves = (rows + resident - 1) / resident * ((a.n_rot + 3) / 4) < (rows / 4 + resident - 1) / resident * a.n_rot ? 4 : 1;
     else a.waves = n_rot >= 8 || (rows / 4 < 512 && n_rot > 1) ? 4 : 1;
     u64 limbs = 0;  // per limb and rotation: the digits, the plaintexts, both key components (and b on q-limbs); C_t written

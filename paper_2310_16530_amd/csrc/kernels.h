@@ -1465,6 +1465,13 @@ struct DhInnerArgs {
     u32 each;        // rotations are not summed: rotation r's result goes to cq + r*2*split*N, cp + r*2*(D - split)*N
     u32 sums;        // G > 1: G; sum g takes the plaintexts pt[g][n_rot][pt_limbs][N] and goes to cq + g*2*split*N, cp likewise
 };
+// Wavefronts that share a row of 128 words where several sums are formed (DhInnerArgs::waves): four where four rows a workgroup leave
+// the chip half empty, counted by the wavefronts that have a rotation; one rotation is nothing to share.  Whole transforms (the
+// kernel), not shared / shared, both arithmetics and integers alone, two and four sums, N = 2^12 .. 2^16: 1 baby step 0.96 to 1.00 (0.68 to 0.98) at
+// every size; 2: 256 to 768 rows 1.00 to 1.01 (0.99 to 1.17), 960 and 1024 1.00 (0.94 to 1.02), 1536 0.97 to 0.99 (0.76 to 0.84); 3: 256 to
+// 1024 1.00 to 1.03 (0.97 to 1.41), 1536 0.98 to 1.00 (0.87 to 1.01); 4 to 6: 768 to 1344 0.99 to 1.03 (0.94 to 1.34), 1536 to 1792 0.98 to 1.02 (0.88 to
+// 1.11); 7 to 13: 768 to 1600 1.00 to 1.08 (0.99 to 1.52), 1728 and 1792 0.99 to 1.02 (0.96 to 1.09).
+HD u32 sums_waves(u32 rows, u32 n_rot) { return n_rot > 1 && rows * 4 < 1792 * (n_rot < 4 ? n_rot : 4) ? 4 : 1; }
 
 // Sum over the rotations of (unreduced digit sum, reduced) * plaintext, at most 8 terms between folds
 template <class AR, int W>

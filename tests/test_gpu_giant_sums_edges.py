@@ -19,6 +19,8 @@ pytestmark = pytest.mark.gpu
     (12, (49, 60, 50, 58, 49, 49, 49), (48, 60), 7, ((5, 4),)),  # seven digits, both arithmetics
     (13, (49,) * 23, (59,) * 4, 6, ((5, 2),)),  # 1728 rows: four wavefronts share each
     (13, (49,) * 24, (59,) * 4, 6, ((3, 3),)),  # 1792: one wavefront each
+    (12, (49,) * 24, (59,) * 3, 6, ((2, 2), (1, 3))),  # 864 rows: two rotations shared by four wavefronts, one by none
+    (12, (49,) * 24, (59,) * 4, 6, ((2, 2), (1, 3))),  # 896: neither
     (13, (55,) * 12, (59,) * 4, 3, ((2, 4), (1, 4))),  # integer primes alone; a single baby step stays apart
 ])
 def test_several_sums_in_one_kernel(orc, logN, q, p, dnum, steps):
