@@ -2287,11 +2287,9 @@ extern "C" int ckks_lintrans_bsgs_at(ckks_ctx* ctx, uint32_t level, const uint64
         launch_extended_fwd_contig(c, w, s);
     }
     // Baby steps and combinations in one kernel where its registers hold the sums (8 x 4, N = 2^16, 24 + 6 limbs: 468 -> 354 us; on
-    // integer chains of 4 + 2 and 12 + 4 limbs the call gains 2 to 4 % at N = 2^12 and 2^13, 6 to 9 % from 2^14 on).  One baby step
-    // of such a chain, which leaves little to combine, is within 1 to 3 % either way and stays apart from 768 rows on.
-    const bool all_int = !any_fp_prime(c, 0, c->D);
-    const u32 sums_max = all_int && n1 == 1 && (c->D << (c->logN - 7)) > 768 ? CKKS_DH_SUMS - 1 : CKKS_DH_SUMS;
-    if (n2 <= sums_max && n1 <= CKKS_DH_CHUNK) {
+    // integer chains of 4 + 2 and 12 + 4 limbs the call gains 2 to 4 % at N = 2^12 and 2^13, 6 to 9 % from 2^14 on; with a single baby step and
+    // four giant ones, which leaves least to combine, 0 to 2.6 % at 768 to 15360 rows, N = 2^12 .. 2^16)
+    if (n2 <= CKKS_DH_SUMS && n1 <= CKKS_DH_CHUNK) {
         DhInnerArgs ia;
         memset(&ia, 0, sizeof(ia));
         for (u32 b = 0; b < n1; b++) ia.key[b] = h_baby_rk_ptrs[b], ia.galois[b] = h_baby_galois[b];

@@ -95,7 +95,7 @@ def _one_mod_down(ps, level, n):
     (16, (60,) * 12, (60,) * 2, 6, 12, ((1, 7), (1, 8))),                   # seven a sum: one sum, two sums of four
     (16, (60,) * 11, (60,) * 2, 6, 11, ((1, 8),)),                          # ... on fewer workgroups
     (13, (55,) * 70, (59,) * 3, 24, 70, ((2, 3),)),                         # many digits: the product would take longer than a batch's
-    (16, None, 2, 2, 6, ((1, 3), (1, 4))),                                  # three a sum; four sums of baby steps on many integer rows
+    (16, None, 2, 2, 6, ((1, 3), (1, 4))),                                  # three a sum; four sums of one baby step on many integer rows
 ])
 def test_baby_step_giant_step_sums(orc, logN, q, p, dnum, level, steps):
     if q is None:
@@ -123,8 +123,7 @@ def test_baby_step_giant_step_sums(orc, logN, q, p, dnum, level, steps):
                 ctx.set_overlap(False)
             assert np.array_equal(got, want), (a, b, overlap)
             assert any(k.startswith("inv_strided_sum_kernel") for k in names) == _one_mod_down(ps, level, b), names
-            four = min(ps.primes) < 3 << 48 or (level + ps.K) * (ps.N >> 7) <= 768
-            assert any(k.startswith("bsgs_mac_kernel") for k in names) == (a > 32 or b > (4 if four else 3)), names
+            assert any(k.startswith("bsgs_mac_kernel") for k in names) == (a > 32 or b > 4), names
 
 
 def test_baby_steps_of_many_digits_leave_room_for_eight_products(orc):
