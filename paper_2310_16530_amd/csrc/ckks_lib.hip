@@ -1625,10 +1625,13 @@ static int check_ks_args(const View* c, const void* a, const void* b, const void
 // target, a launch and a round trip less.  Counted in workgroups of a tile and a target.  Calls before / with it, us:
 // ModUp (digits of one limb; both arithmetics' targets share the launch too), HMult with K = 1 as a whole: N = 2^12, 3 + 1 limbs (12
 // workgroups) 52.8 / 43.2, 35-bit primes 36.8 / 32.1, 12 + 1, 2 ciphertexts (312) 78.7 / 70.6; N = 2^13, 3 + 1 (24) 61.6 / 52.2, 12 + 1, 2
-// (624) 92.2 / 87.6 (1000 and more: worse); N = 2^14, 3 + 1 (48) 63.0 / 52.2, 5 + 1, 4 (480) 82.5 / 71; N = 2^16, 3 + 1 (192) 71.5 / 59.8;
-// all of 55 bits 3 to 7 % of the call.
+// (624) 92.2 / 87.6 (1000 and more: worse); N = 2^14, 3 + 1 (48) 63.0 / 52.2, 5 + 1, 4 (480) 75.4 / 68.8; N = 2^16, 3 + 1 (192) 71.5 / 59.8;
+// all of 55 bits 3 to 7 % of the call.  N = 2^14 .. 2^16, 2 to 15 limbs, HMult and HRot, before / with it as a quotient: 320 to 480 workgroups 1.08 to
+// 1.13 (50-bit limbs, 60-bit special limb), 1.03 to 1.06 (36 bits), 1.00 to 1.03 (all of 55 bits and more); 528 to 600 1.03 to 1.08, 1.00 to 1.03 and 0.98
+// to 1.00; 720 and 768 1.05 to 1.09, 1.00 to 1.04, 0.98 to 1.00; 960 1.02 to 1.07, 0.99 to 1.02, 0.96 to 0.99.  One line for all of them, two workgroups
+// to a compute unit, where the first of them begin to lose.
 static bool up_with_inverse(const View* c, u32 batch) {
-    return !c->up.ks && !c->sh->side.active && batch * c->dnum * c->D * tiles_of(c) <= (c->logN <= 13 ? 640u : 448u);
+    return !c->up.ks && !c->sh->side.active && batch * c->dnum * c->D * tiles_of(c) <= (c->logN <= 13 ? 640u : 512u);
 }
 // ModDown by one prime.  After an inner product, which has run the first inverse pass: HMult with digits of two limbs, N = 2^12, 6 + 1 limbs (12)
 // 59.0 / 57.2, N = 2^16, 6 + 1 (192) 79.6 / 75.7, 8 + 1, 3 ciphertexts (768) 124.3 / 124.9 (an integer special prime).  Rescale: N = 2^14, 24 -> 23

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _up(logN, L, batch):
-    return batch * L * (L + 1) << (logN - 12) <= (640 if logN <= 13 else 448)
+    return batch * L * (L + 1) << (logN - 12) <= (640 if logN <= 13 else 512)
 
 
 def _dn(logN, sources, targets, int_source, whole):
@@ -28,8 +28,8 @@ def _dn(logN, sources, targets, int_source, whole):
 
 # (logN, q, p, batch): digits of one limb, one special prime; floors from 50 bits on are integer arithmetic
 KEY_SWITCH = [(12, (35,) * 3, 36, 1), (12, (49,) * 8, 59, 8), (12, (49,) * 8, 59, 9), (12, (49, 55, 58, 49), 49, 2), (12, (55,) * 8, 59, 32), (12, (49,) * 8, 59, 33),
-              (13, (49,) * 5, 59, 10), (13, (49,) * 5, 59, 11), (13, (55, 49, 60), 60, 2), (14, (49,) * 4, 59, 5), (14, (49,) * 4, 59, 6), (14, (55, 49, 58), 48, 3),
-              (15, (49, 49), 59, 9), (15, (55, 56), 59, 10), (16, (49, 49), 48, 4), (16, (58, 49), 59, 5), (16, (49,) * 2, 59, 9)]
+              (13, (49,) * 5, 59, 10), (13, (49,) * 5, 59, 11), (13, (55, 49, 60), 60, 2), (14, (49,) * 4, 59, 5), (14, (49,) * 4, 59, 6), (14, (49,) * 4, 59, 7), (14, (55, 49, 58), 48, 3),
+              (15, (49, 49), 59, 9), (15, (55, 56), 59, 10), (15, (55, 56), 59, 11), (16, (49, 49), 48, 4), (16, (58, 49), 59, 5), (16, (49,) * 2, 59, 9)]
 
 
 @pytest.mark.parametrize("logN,q,p,batch", KEY_SWITCH)
