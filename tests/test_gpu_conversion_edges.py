@@ -50,7 +50,7 @@ def test_conversions_at_the_edges_of_their_forms(orc, shape):
 
 # (logN, q floors, p floors, batch): digits of one limb and one special prime, grids on both sides of 512 workgroups of four
 # targets; floors from 50 bits on are integer arithmetic
-SINGLE = [(15, (49, 49, 49, 49), 59, 3), (15, (49, 49, 49, 49), 59, 14), (15, (49, 49, 49, 49), 59, 32),
+SINGLE = [(15, (49, 49, 49, 49), 59, 4), (15, (49, 49, 49, 49), 59, 14), (15, (49, 49, 49, 49), 59, 32),
           (14, (49, 50, 58, 55, 55, 58, 60), 48, 32), (13, (55, 56, 57, 58, 59, 60), 60, 8), (13, (55, 56, 57, 58, 59, 60), 60, 40)]
 
 
