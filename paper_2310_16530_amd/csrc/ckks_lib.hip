@@ -2057,13 +2057,15 @@ extern "C" int ckks_hrot_hoisted_mac_at(ckks_ctx* ctx, uint32_t level, const uin
     };
     if (hoisted_summed(c, n_rot)) {
         // Equal chunks of as many rotations as the workspace has room for: x and dt, then the sum on the q-limbs ([2][L]) and, per
-        // rotation, the special limbs ([2][K]) and the converted part ([2][L]).  That of CKKS_ROT_CHUNK rotations of the other form
-        // holds as many at least.  One launch of the special limbs for a chunk: in two, of equal parts, each ends in a round of
-        // workgroups that is half empty (N = 2^16, 24 + 6 limbs: 17 rotations 990 -> 979 us, 18 1043 -> 1020, 24 1331 -> 1303; 16 and 32 even).
+        // rotation, the special limbs ([2][K]) and the converted part ([2][L]).  That of m = min(n_rot, CKKS_ROT_CHUNK) rotations of the other
+        // form, L + dnum D + 2 m (2 L + K) limbs, holds (m (2 L + K) - L) / (L + K): m at least, 28 at 24 + 6 limbs, never 2 CKKS_ROT_CHUNK - 1.
+        // One launch of the special limbs for a chunk: in two, of equal parts, each ends in a round of workgroups that is half empty
+        // (N = 2^16, 24 + 6 limbs: 17 rotations 990 -> 979 us, 18 1043 -> 1020, 24 1331 -> 1303; 16 even).
         Workspace w = carve(c, d_ws, 1, 1, 1);
         u64 *const cq = w.cq, *const cp = cq + (size_t)2 * c->L * N;
         const size_t fit = (need / sizeof(u64) / N - 3 * (size_t)c->L - (size_t)c->dnum * c->D) / (2 * (size_t)c->D);
-        const u32 chunk = cdiv(n_rot, cdiv(n_rot, fit < CKKS_DH_CHUNK ? (u32)fit : CKKS_DH_CHUNK));
+        static_assert(2 * CKKS_ROT_CHUNK - 2 <= CKKS_DH_CHUNK, "a chunk is one launch");
+        const u32 chunk = cdiv(n_rot, cdiv(n_rot, (u32)fit));
         // Second stream: the integer special limbs' inner products and inverse transforms beside the sum on the q-limbs.  Not where the
         // special limbs mix the arithmetics, whose joint launches it would split (one stream / two, us: 40 + 9 limbs, 49, 59 and 60 bits in
         // turn, N = 2^14, 17 rotations 598 / 889, 32 960 / 1281; 24 + 6, N = 2^15, 17 588 / 754, 32 1013 / 1173; all of 59 bits 551 / 546,
