@@ -155,7 +155,7 @@ def test_baby_steps_of_many_digits_leave_room_for_eight_products(orc):
     (12, (49,) * 9, (59,), 9, (17, 40), False),            # many digits on few workgroups: one launch of both arithmetics
     (15, (49,) * 10, (59,) * 2, 5, (17,), True),           # as many as 16 workgroups a digit
     (12, (49, 55) * 3, (59,), 6, (40,), True),             # half the limbs integer
-    (12, (49,) * 4, (59,), 4, (33, 40, 50), True)])        # parts of 11, 14 and 13 rotations, two to a chunk, the last one shorter
+    (12, (49,) * 4, (59,), 4, (33, 40, 50), True)])        # two chunks: 17 and 16 rotations, 20 and 20, 25 and 25
 def test_form_of_a_hoisted_sum_by_digits_and_workgroups(orc, logN, q, p, dnum, counts, summed):
     ps = synth.mixed_params(logN, list(q), list(p), dnum, "form")
     ctx, P = gpu_ctx(ps), orc_params(orc, ps)
@@ -167,6 +167,26 @@ def test_form_of_a_hoisted_sum_by_digits_and_workgroups(orc, logN, q, p, dnum, c
         got, names = _kernels(ctx, lambda: ctx.hrot_hoisted_mac(d_ct, gs[:m], [d_keys[r % 3] for r in range(m)], d_pt[:m].contiguous()))
         assert np.array_equal(got, orc.hrot_hoisted_mac(ct, gs[:m], [keys[r % 3] for r in range(m)], pt[:m], P)), m
         assert any(k.startswith("ks_final_kernel") and k.endswith(", 4>") for k in names) == summed, names
+
+
+@pytest.mark.parametrize("m,chunks", [(17, 1), (28, 1), (29, 2), (56, 2), (57, 3), (59, 3)])
+def test_chunks_of_a_hoisted_sum_are_as_large_as_the_workspace(orc, m, chunks):
+    """4 + 1 limbs: the workspace holds 28 rotations of this form (31 * 4 + 16 limbs over 5).  The special limbs of a chunk are one launch; 59
+    rotations are chunks of 20, 20 and 19."""
+    ps = synth.mixed_params(12, [49] * 4, [59], 4, "chunks")
+    ctx, P = gpu_ctx(ps), orc_params(orc, ps)
+    gs, keys, ct, pt = _inputs(ps, m, 3, 5700 + m, ps.q_primes, (m,))
+    d_ct, d_pt, d_keys = dev(ct), dev(pt), [dev(k) for k in keys]
+    print("rotations", m, flush=True)
+    ctx.profile_enable(True)
+    try:
+        got = host(ctx.hrot_hoisted_mac(d_ct, gs, [d_keys[r % 3] for r in range(m)], d_pt))
+        launches = {k: v[0] for k, v in ctx.profile_read().items()}
+    finally:
+        ctx.profile_enable(False)
+    assert np.array_equal(got, orc.hrot_hoisted_mac(ct, gs, [keys[r % 3] for r in range(m)], pt, P))
+    for start in ("ks_inner_kernel<IntAr, 4, 0, true", "dh_accum_kernel", "ks_final_kernel<FpAr, 4, 4>"):
+        assert sum(n for k, n in launches.items() if k.startswith(start)) == chunks, launches
 
 
 def test_hoisted_sums_on_integer_limbs_with_the_second_stream_at_work(orc):
