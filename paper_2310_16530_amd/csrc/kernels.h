@@ -776,7 +776,7 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
     typedef StridedTw<AR, A> TW;
     typedef typename AR::T T;
     static_assert(SETS == 1 || NTT == 1, "two targets or two positions a lane");
-    static_assert(SETS == 1 || !AR::is_fp, "FP64 sums are reduced before their exchange");
+    static_assert(SETS == 1 || !AR::is_fp, "two positions a lane are for integers, whose sums go to the exchange unreduced");
     constexpr u32 TILES = (1u << A) / 16, TPW = 2 * NTT;  // targets per workgroup
     const u32 N = 1u << tb.logN, lane = tid & 63, wave = tid >> 6, n = lane & 31, h = lane >> 5;
     const u32 tile = group % TILES;
@@ -875,7 +875,7 @@ __device__ __forceinline__ void conv_mfma_body(const ConvArgs& a, const Tables& 
             __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();  // the twiddles are in LDS
-        // first four forward stages, in place (FP64: |x| <= 0.51 q on entry, below 7 q after)
+        // first four forward stages, in place (FP64: |x| <= 0.51 q on entry, below 7 q after, narrow primes 3.75 q)
         strided_stages_lo<AR, A>(x[0], tws + h * TW::WORDS, m0);
         if constexpr (NTT == 2)
             if (nt > 2) strided_stages_lo<AR, A>(x[1], tws + (2 + h) * TW::WORDS, m1);
@@ -2002,7 +2002,8 @@ __device__ __forceinline__ void ks_final_body(const FinalArgs& a, const Tables& 
 #pragma unroll
             for (int k = 0; k < 16; k++) {
                 // FP64: reduced to <= q/2 so that the at most 8 products accumulated between folds stay below 6 q; narrow primes: not
-                // reduced, 2.6 q a product, five between folds.  Integers: a term below 2q * q < q * 2^62, eight of them on hi < q below 3q * 2^64; hi alone takes multiples of q * 2^64 off
+                // reduced, 2.6 q a product, five between folds.  Integers: a term below 2q * q < q * 2^62, eight of them on hi < q below
+                // 3q * 2^64; hi alone takes multiples of q * 2^64 off
                 if constexpr (AR::is_fp) facc[k] += FpAr::mulmod_lazy(v[k], u64_to_f64(ptw[k]), FpAr::mod(pc));
                 else mac128(iacc[k], csub(csub(v[k], 4 * q), 2 * q), ptw[k]);
             }

@@ -16,7 +16,7 @@
 //       r = fma(-c, q, h) + l                   (both steps exact: integers below 2^53)
 //   gives r = a*w (mod q) with |r| <= (0.5 + 3A/8) q.  Four forward stages started from |x| <= q
 //   stay below 7q, four inverse stages started from |x| <= q/2 stay at or below 8q < 2^53; a
-//   3-instruction reduction x - rint(x/q)*q brings values back to |x| <= q/2 between rounds.
+//   3-instruction reduction x - rint(x/q)*q brings values back to |x| <= q/2 between rounds of four stages.
 //   Narrow primes, q <= 17*2^45: the quotient is off by 0.5 + 3A q/2^53 <= 0.5 + 0.2A, so a stage takes A to at most 1.2A + 0.5: eight
 //   forward stages from |x| <= 0.51q end below 10.5q (1.12, 1.84, 2.71, 3.75, 5.0, 6.5, 8.3, 10.5), from canonical words below 12.6q,
 //   and 2^53 is 15q.  What leaves such a pass unreduced makes products with residues of at most 2.6q.
@@ -266,7 +266,8 @@ struct FpAr {
     static HD T mul_canon(u64 a, u64 b, const PrimeConst&, const Mod& m) {
         return mulmod_lazy(u64_to_f64(a), u64_to_f64(b), m);  // |result| <= 0.875 q
     }
-    template <bool RED>  // the reduction schedule of the integer arithmetic does not apply: ranges are restored per round
+    template <bool RED>  // the reduction schedule of the integer arithmetic does not apply: ranges are restored per round of four stages, for
+                         // narrow primes per pass
     static HD void bfly_fwd(T& X, T& Y, const Tw& t, const Mod& m) {
         double r = mulmod_lazy(Y, t.w, m);
         double x = X;
@@ -283,7 +284,9 @@ struct FpAr {
     // between the two halves of a forward pass, and where its results meet canonical factors: nothing for narrow primes.  Three of the
     // four reductions a word meets between a conversion and a key product, bound by issue (N = 2^16, 24 + 6 limbs, batch 8, just
     // above 2^49: conversion 116 -> 110 us, inner product 258 -> 248, ModDown conversion 74 -> 71; the whole HMult 707 -> 692, 17
-    // hoisted rotations 1011 -> 998; wider primes as before)
+    // hoisted rotations 1011 -> 998).  Wider primes pay a branch a half pass (18.75 * 2^45, the same shapes, before narrow primes were told apart /
+    // now: HMult 708.0 / 707.0, HRot 673.6 / 671.7, one HMult 144.9 / 143.8, rescale of 8 151.0 / 151.5, 32 double-hoisted rotations of 35 + 7
+    // limbs 1601 / 1597)
     template <int W>
     static HD void mid_reduce(T (&x)[W], const Mod& m) {
         if (!narrow(m)) {
