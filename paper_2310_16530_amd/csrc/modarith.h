@@ -285,8 +285,8 @@ struct FpAr {
     // four reductions a word meets between a conversion and a key product, bound by issue (N = 2^16, 24 + 6 limbs, batch 8, just
     // above 2^49: conversion 116 -> 110 us, inner product 258 -> 248, ModDown conversion 74 -> 71; the whole HMult 707 -> 692, 17
     // hoisted rotations 1011 -> 998).  Wider primes pay a branch a half pass (18.75 * 2^45, the same shapes, before narrow primes were told apart /
-    // now: HMult 708.0 / 707.0, HRot 673.6 / 671.7, one HMult 144.9 / 143.8, rescale of 8 151.0 / 151.5, 32 double-hoisted rotations of 35 + 7
-    // limbs 1601 / 1597)
+    // now: HMult 708.0 / 707.0, HRot 673.6 / 671.7, one HMult 144.9 / 143.8, 32 double-hoisted rotations of 35 + 7 limbs 1601 / 1597;
+    // rescales show it: 8 of 24 limbs 151.0 / 151.5, 12 of 6 limbs 80.8 / 81.6)
     template <int W>
     static HD void mid_reduce(T (&x)[W], const Mod& m) {
         if (!narrow(m)) {
