@@ -1789,7 +1789,7 @@ static u32 summed_rotations_max(const View* c) {
 // 80 0.97 to 1.05, 96 and more 0.98 to 1.20, one giant step 0.94 to 1.0; where the sums are more than the launches of a batch: 96 0.89 to 0.99, 144 and
 // 160 0.92 to 1.0, 192 0.97 to 1.05, 256 and more 1.0 to 1.12, but three a sum 0.78 to 1.02 up to 560.  And never where the q-limb
 // product by itself, in the units of inner_ways, would take more than 5/4 of the batch's (3 steps, 70 + 14 integer limbs in 24 digits,
-// N = 2^13, 140 workgroups: 75 against 52 units, 544 against 386 us; 20 + 4 limbs in 5 digits, N = 2^15, 19 / 14, the call 0.98)
+// N = 2^13, 140 workgroups: 75 against 52 units, the transform with 2 baby steps 1127 against 993 us; 20 + 4 limbs in 5 digits, N = 2^15, 19 / 14, the call 0.98)
 static bool giants_summed(const View* c, u32 n) {
     if (n < 2 || !c->dn.ks) return false;  // one special prime is reduced directly: there are no digits to add
     const u32 at_once = summed_rotations_max(c), sums = cdiv(n, at_once);
