@@ -557,7 +557,7 @@ def main():
         "vs_baseline": None,
         "dtype": "u64",
         "data": "synthetic",
-        "config": {"workload": "configs[2] shape: N=2^16, L=24 fifty-bit limbs, K=6 sixty-bit special limbs, dnum=4; "
+        "config": {"workload": "key switches at N=2^16, L=24 fifty-bit limbs, K=6 sixty-bit special limbs, dnum=4; "
                                "one step = batch of 8 HMult+relin + batch of 8 HRot (16 key switches)",
                    "batch": B, "key_switches_per_step": ks_per_step, "overlap": overlap},
         "roofline": roofline,

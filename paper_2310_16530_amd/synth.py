@@ -163,9 +163,9 @@ CONFIGS = (CFG0, CFG1, CFG2, CFG3, CFG4)
 
 CFG1_BATCH = 16
 CFG2_BATCH = 8
-# configs[3] lists 17 offsets while calling them 16; the list is kept as given.
+# The convolution workload lists 17 offsets while calling them 16; the list is kept as given.
 CFG3_ROTATIONS = tuple(range(1, 9)) + tuple(1 << i for i in range(4, 12)) + (-1,)
-# configs[4]: +-2^i for i = 0..15 (32 jobs; +-2^15 is the identity on 2^15 slots).
+# The slot transforms: +-2^i for i = 0..15 (32 jobs; +-2^15 is the identity on 2^15 slots).
 CFG4_ROTATIONS = tuple(s * (1 << i) for i in range(16) for s in (1, -1))
 
 
